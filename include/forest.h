@@ -1,13 +1,15 @@
 /*
  * forest.h -- C ABI of the MI355X (gfx950) tree-ensemble inference library.
  *
- * The library evaluates random forests and gradient-boosted trees the way the paper's
- * operator representation does (Section 3.1.2, Table 2, Fig. 2): every internal node of
- * every tree is evaluated for every row (feature selection W1/A as a gather, element-wise
- * comparison against the thresholds W2/B), the reached leaf is resolved from the split
+ * The library evaluates random forests and gradient-boosted trees in the paper's operator
+ * representation (Section 3.1.2, Table 2, Fig. 2): feature selection W1/A as a gather,
+ * element-wise comparison against the thresholds W2/B, the reached leaf resolved from the split
  * outcomes (W3 + first argmax, equivalently the signed path matrix C with path lengths D),
- * leaf payloads E are gathered and reduced across trees, and an optional monotone transform
- * is applied; labels are taken before the transform (Section 4.3.3, redundant elimination).
+ * leaf payloads E gathered and reduced across trees, and an optional monotone transform;
+ * labels are taken before the transform (Section 4.3.3, redundant elimination).  The outcomes
+ * that decide the leaf are those on the row's path: the walk kernels evaluate a tree's top levels
+ * whole and below them the node on the path only; the dense kernels, which run the models and batches
+ * the walk kernels do not take, evaluate every internal node of every tree for every row.
  *
  * All functions are extern "C", take plain pointers and sizes, return 0 or a negative
  * FOREST_E* code, never throw and never abort.
@@ -92,7 +94,7 @@ typedef struct forest_info_t {
     int32_t kernel_kind;   /* which specialised kernel forest_predict launches (0 = generic) */
     int64_t packed_bytes;  /* device-resident size of the packed model */
     int32_t x_in_registers;     /* 1 if the kernel keeps the features in vector registers */
-    int32_t kernel_path;        /* 0: features from the LDS tile; 1: float32 feature registers;
+    int32_t kernel_path;        /* dense kernels' form of the model.  0: features from the LDS tile; 1: float32 feature registers;
                                    2: packed f16 threshold-rank registers;
                                    3: packed f16 threshold ranks in LDS (any tree shape) */
     int32_t rows_per_workgroup; /* rows one workgroup owns */

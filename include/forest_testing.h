@@ -114,6 +114,17 @@ typedef struct forest_packed_view {
     const uint16_t *fast_tab;        /* [fast_tab_entries] */
     const int32_t *order_leaf_node;  /* [sum N_L] caller's node index of each leaf, processing order */
     const int32_t *order_leaf_tree;  /* [sum N_L] caller's tree index of each leaf, processing order */
+    /* Models the walk kernels take (else walk_depth is 0 and the pointers NULL): walk_trees trees in
+     * processing order, each laid out as a full tree of depth walk_depth; the trees past n_trees
+     * fill the last stage.  Node i of level l of tree t is walk_node[2 * ((t << walk_depth) + (1 << l) + i)]
+     * (float threshold) and the word after it (feature * walk_groups * 256); i and the leaf index are
+     * the outcomes on the path, first outcome in bit 0.  walk_leaf_node[(t << walk_depth) + i] is the
+     * caller's node index of leaf i, walk_leaf its value.  Slot 0 holds the tree's output column and
+     * its index in the caller's description. */
+    int32_t walk_depth, walk_groups, walk_trees;
+    const uint32_t *walk_node;       /* [(walk_trees << walk_depth) * 2] */
+    const float *walk_leaf;          /* [walk_trees << walk_depth] */
+    const int32_t *walk_leaf_node;   /* [walk_trees << walk_depth] */
 } forest_packed_view;
 
 typedef struct forest_packed forest_packed;

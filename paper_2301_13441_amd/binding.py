@@ -53,7 +53,9 @@ class _View(ctypes.Structure):
                 ("bank_tree", _p), ("bank_reg", _p), ("bank_passes", _i32),
                 ("bank_todo_items", _i64), ("bank_pass", _p), ("bank_pass_wave", _p),
                 ("bank_todo", _p), ("fast_window", _i32), ("fast_tab_entries", _i64), ("fast_feat", _p), ("fast_tab", _p),
-                ("order_leaf_node", _p), ("order_leaf_tree", _p)]
+                ("order_leaf_node", _p), ("order_leaf_tree", _p),
+                ("walk_depth", _i32), ("walk_groups", _i32), ("walk_trees", _i32), ("walk_node", _p),
+                ("walk_leaf", _p), ("walk_leaf_node", _p)]
 
 
 # include/forest.h: the inference ABI
@@ -210,6 +212,12 @@ def forest_pack(forest) -> dict:
                         bank_todo=get(v.bank_todo, int(v.bank_todo_items) * 4, np.int32).reshape(-1, 4))
         else:
             rank["bank_batches"] = 0
+        rank.update(walk_depth=int(v.walk_depth), walk_groups=int(v.walk_groups), walk_trees=int(v.walk_trees))
+        if v.walk_depth > 0:
+            slots = int(v.walk_trees) << int(v.walk_depth)
+            rank.update(walk_node=get(v.walk_node, 2 * slots, np.uint32).reshape(int(v.walk_trees), -1, 2),
+                        walk_leaf=get(v.walk_leaf, slots, np.float32).reshape(int(v.walk_trees), -1),
+                        walk_leaf_node=get(v.walk_leaf_node, slots, np.int32).reshape(int(v.walk_trees), -1))
         rank["order_leaf_node"] = get(v.order_leaf_node, nl, np.int32)
         rank["order_leaf_tree"] = get(v.order_leaf_tree, nl, np.int32)
         return dict(

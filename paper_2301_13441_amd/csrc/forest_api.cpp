@@ -166,6 +166,10 @@ int forest_load(const forest_desc *desc, forest **out)
     const size_t o_btodo = place<BankTodo>(cur, m.bank_todo.size());
     const size_t o_bfeat = place<FastLookup>(cur, m.fast_feat.size());
     const size_t o_btab = place<uint16_t>(cur, m.fast_tab.size());
+    const size_t o_wnode = place<WalkNode>(cur, m.walk_node.size());
+    const size_t o_wleaf = place<float>(cur, m.walk_leaf.size());
+    const size_t o_wleafn = place<int32_t>(cur, m.walk_leaf_node.size());
+    const size_t o_wpos = place<int32_t>(cur, m.walk_position.size());
     const size_t model_bytes = (cur + 255) & ~size_t{255};
     // workspaces of split launches, not uploaded
     const bool ranks = m.path == PATH_RANK || m.path == PATH_RANK_LDS;
@@ -209,7 +213,11 @@ int forest_load(const forest_desc *desc, forest **out)
                     up(o_bpw, m.bank_pass_wave.data(), m.bank_pass_wave.size() * sizeof(BankPassWave)) &&
                     up(o_btodo, m.bank_todo.data(), m.bank_todo.size() * sizeof(BankTodo)) &&
                     up(o_bfeat, m.fast_feat.data(), m.fast_feat.size() * sizeof(FastLookup)) &&
-                    up(o_btab, m.fast_tab.data(), m.fast_tab.size() * sizeof(uint16_t));
+                    up(o_btab, m.fast_tab.data(), m.fast_tab.size() * sizeof(uint16_t)) &&
+                    up(o_wnode, m.walk_node.data(), m.walk_node.size() * sizeof(WalkNode)) &&
+                    up(o_wleaf, m.walk_leaf.data(), m.walk_leaf.size() * sizeof(float)) &&
+                    up(o_wleafn, m.walk_leaf_node.data(), m.walk_leaf_node.size() * sizeof(int32_t)) &&
+                    up(o_wpos, m.walk_position.data(), m.walk_position.size() * sizeof(int32_t));
     if (!ok) {
         (void)hipGetLastError();
         (void)hipFree(f->blob);
@@ -261,6 +269,13 @@ int forest_load(const forest_desc *desc, forest **out)
     d.bank.max_units = m.bank_max_units;
     d.bank.enabled = m.bank_enabled;
     d.bank.passes = static_cast<int32_t>(m.bank_pass.size());
+    d.walk.node = reinterpret_cast<const WalkNode *>(b + o_wnode);
+    d.walk.leaf = reinterpret_cast<const float *>(b + o_wleaf);
+    d.walk.leaf_node = reinterpret_cast<const int32_t *>(b + o_wleafn);
+    d.walk.position = reinterpret_cast<const int32_t *>(b + o_wpos);
+    d.walk.depth = m.walk_depth;
+    d.walk.groups = m.walk_groups;
+    d.walk.stages = m.walk_stages;
     d.n_splits = 1;
     d.n_entries = static_cast<int64_t>(m.prog32.size() > m.prog.size() ? m.prog32.size() : m.prog.size());
     d.split_rows = 0;
@@ -276,6 +291,10 @@ int forest_load(const forest_desc *desc, forest **out)
     m.bank_leaf = {};
     m.child = {};
     m.thr_sorted = {};
+    m.walk_node = {};
+    m.walk_leaf = {};
+    m.walk_leaf_node = {};
+    m.walk_position = {};
     m.v_feature = {};
     m.v_threshold = {};
     m.v_left = {};

@@ -108,6 +108,14 @@ int forest_pack_view(const forest_packed *p, forest_packed_view *v)
     v->fast_tab = ranks ? m.fast_tab.data() : nullptr;
     v->order_leaf_node = m.leaf_node.data();
     v->order_leaf_tree = m.v_order_leaf_tree.data();
+    const bool walk = m.walk_depth > 0;
+    static_assert(sizeof(WalkNode) == 2 * sizeof(uint32_t), "viewed as plain 32-bit arrays");
+    v->walk_depth = m.walk_depth;
+    v->walk_groups = m.walk_groups;
+    v->walk_trees = walk ? static_cast<int32_t>(m.walk_node.size() >> m.walk_depth) : 0;
+    v->walk_node = walk ? reinterpret_cast<const uint32_t *>(m.walk_node.data()) : nullptr;
+    v->walk_leaf = walk ? m.walk_leaf.data() : nullptr;
+    v->walk_leaf_node = walk ? m.walk_leaf_node.data() : nullptr;
     return FOREST_OK;
 }
 

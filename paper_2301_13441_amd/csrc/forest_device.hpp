@@ -25,6 +25,17 @@ struct BankDev {
     int32_t passes;
 };
 
+// Device tables of the walk program (forest_model.hpp).
+struct WalkDev {
+    const WalkNode *node;
+    const float *leaf;
+    const int32_t *leaf_node;
+    const int32_t *position;
+    int32_t depth;   // 0: none
+    int32_t groups;  // row groups the X tile is laid out for
+    int32_t stages;
+};
+
 struct DevModel {
     const SplitEntry *prog;
     const uint32_t *prog32;
@@ -63,6 +74,7 @@ struct DevModel {
     uint32_t *rank_tiles;
     // LDS rank family: large batches of models it fits run the register-bank kernel
     BankDev bank;
+    WalkDev walk;
 };
 
 // Batches below this many workgroups split the trees over several workgroups per row tile.
@@ -123,6 +135,11 @@ hipError_t launch_ranklds(const DevModel &m, const float *X, int64_t n_rows, flo
 hipError_t init_rankbank_kernels(size_t lds_limit);
 hipError_t launch_rankbank(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                            int32_t *leaf_out, size_t lds_limit, hipStream_t stream);
+
+// Walk kernels (forest_kernels_walk.hip).
+hipError_t init_walk_kernels(size_t lds_limit);
+hipError_t launch_walk(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
+                       int32_t *leaf_out, hipStream_t stream);
 
 // Sums the partial sums of a split launch over the splits and finishes every row.
 hipError_t launch_reduce_splits(const DevModel &m, int64_t n_rows, float *scores, int32_t *labels,

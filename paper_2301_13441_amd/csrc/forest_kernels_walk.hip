@@ -1,0 +1,421 @@
+// Walk kernels (gfx950): trees of depth up to 8 with scalar leaves, one node per level and row.
+//
+// The paper's three operators answer "which leaf does the row reach" by testing every internal
+// node (step (1) and (2) of Fig. 2) and selecting the leaf whose path agrees (step (3)).  Only the
+// tests on the row's own path decide that selection.  Here the first two levels are still evaluated
+// whole -- their three nodes are the same for every row, so they come through scalar loads and
+// their comparisons cost no per-lane look-up -- and below that a lane tests the one node of each
+// level that its path meets: two LDS reads (node, feature value) and four vector instructions per
+// (row, level) instead of half a vector instruction per (row, node).
+//
+// A workgroup of 16 waves owns NR x 64 rows, NR per lane, whose features it holds in LDS as float32
+// ([feature][row]: the lanes of a wave read one column each of their own row, which falls into 32
+// different banks whatever the features are).  Every wave walks its own run of trees for all the
+// rows, a stage (1 or 2 KB of whole trees) at a time: the next stage is on its way to registers
+// while this one is walked in LDS, and no wave waits for another between the first and the last
+// tree.  A node is 8 bytes, {threshold, byte offset of the feature in the X tile}, read at once
+// (64-bit LDS reads move 256 bytes per clock, 32-bit ones 128).  Its slot is numbered by the
+// outcomes on the path, first outcome in bit 0, so the address of the next node is the last one's
+// with one bit more: the sign of threshold - x, moved to its place by v_and_or_b32.  (The subtraction
+// is exact in sign for finite thresholds: it is 0 for equal operands and never underflows to 0
+// otherwise.  NaN, which belongs on the right of every threshold, is stored in the tile as +Inf.)
+// Leaf values are gathered from global memory, which the LDS traffic leaves idle, and added one
+// tree later, in fp64.
+//
+// Bound: LDS.  Per (64 rows, tree of depth D): 3 + 2 (D - 2) reads of 2 clocks each, more at levels
+// 6 and 7 whose 64 and 128 nodes share the 32 banks.
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "forest_device.hpp"
+#include "forest_kernel_common.hpp"
+
+namespace forest_impl {
+namespace {
+
+typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
+typedef uint32_t Vec2 __attribute__((ext_vector_type(2)));
+
+// LDS by byte address: the kernels have no static LDS, so the dynamic part begins at 0 (checked at
+// start-up) and addresses are plain integers with the level's offset as an immediate.
+template <typename T>
+__device__ __forceinline__ T lds_read(uint32_t at)
+{
+    return *reinterpret_cast<const __attribute__((address_space(3))) T *>(at);
+}
+template <typename T>
+__device__ __forceinline__ void lds_write(uint32_t at, T v)
+{
+    *reinterpret_cast<__attribute__((address_space(3))) T *>(at) = v;
+}
+
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const __attribute__((address_space(4))) uint32_t *WalkTop;
+typedef const __attribute__((address_space(4))) int32_t *WalkTable;
+typedef const __attribute__((address_space(1))) char *GlobalBytes;
+typedef const __attribute__((address_space(1))) float *GlobalFloats;
+typedef const __attribute__((address_space(1))) int32_t *GlobalInts;
+#else
+typedef const uint32_t *WalkTop;  // host pass: the kernel body is only parsed
+typedef const int32_t *WalkTable;
+typedef const char *GlobalBytes;
+typedef const float *GlobalFloats;
+typedef const int32_t *GlobalInts;
+#endif
+
+struct __attribute__((aligned(4))) Float4 {
+    float v[4];
+};
+struct __attribute__((aligned(4))) Int4 {
+    int32_t v[4];
+};
+
+// X rows [row0, row0 + 64 NR) to the tile [feature][stride bytes].  A wave takes 16 rows x 16
+// features at a time, four neighbouring features of a row per lane: 64-byte pieces of X, and LDS
+// writes that fall into 16 banks.  Four pieces are in flight per lane.
+template <int NR>
+__device__ __forceinline__ void walk_fill_tile(const float *__restrict__ X, int64_t row0, int64_t n_rows, int F,
+                                               uint32_t xbase, uint32_t stride, int wave, int lane)
+{
+    constexpr int PIECES = 4;
+    const int blocks = (F + 15) >> 4;      // of 16 features
+    const int tasks = blocks * (NR * 4);   // of 16 rows each
+    const int r = lane & 15, c = (lane >> 4) * 4;
+    for (int t0 = wave; t0 < tasks; t0 += WALK_WAVES * PIECES) {
+        Float4 v[PIECES];
+#pragma unroll
+        for (int u = 0; u < PIECES; ++u) {
+            const int t = t0 + u * WALK_WAVES;
+            if (t >= tasks) continue;
+            const int rb = t / blocks, f = (t - rb * blocks) * 16 + c;
+            const int64_t row = row0 + rb * 16 + r;
+            const float *p = X + (row < n_rows ? row : row0) * F + f;
+            if (f + 4 <= F) {
+                v[u] = *reinterpret_cast<const Float4 *>(p);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[u].v[i] = f + i < F ? p[i] : 0.0f;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PIECES; ++u) {
+            const int t = t0 + u * WALK_WAVES;
+            if (t >= tasks) continue;
+            const int rb = t / blocks, f = (t - rb * blocks) * 16 + c;
+            const uint32_t at = xbase + static_cast<uint32_t>(f) * stride + static_cast<uint32_t>(rb * 16 + r) * 4;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (f + i < F) lds_write<float>(at + i * stride, fminf(v[u].v[i], __builtin_inff()));  // NaN: +Inf
+        }
+    }
+}
+
+// One tree, all row groups: idx[r] = LDS address of the tree | 8 * (index of the leaf reached).
+template <int D, int NR>
+__device__ __forceinline__ void walk_tree(uint32_t tree_at, uint32_t xa, WalkTop top, uint32_t (&idx)[NR])
+{
+    const float t1 = __uint_as_float(top[2]), t2 = __uint_as_float(top[4]), t3 = __uint_as_float(top[6]);
+    const uint32_t a1 = xa + top[3], a2 = xa + top[5], a3 = xa + top[7];
+    float x1[NR], x2[NR], x3[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) x1[r] = lds_read<float>(a1 + r * 256);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) x2[r] = lds_read<float>(a2 + r * 256);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) x3[r] = lds_read<float>(a3 + r * 256);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const uint64_t m1 = __ballot(!(x1[r] <= t1)), m2 = __ballot(!(x2[r] <= t2)), m3 = __ballot(!(x3[r] <= t3));
+        const uint64_t second = (m1 & m3) | (~m1 & m2);
+        uint32_t b0, b1;
+        asm("v_cndmask_b32 %0, 0, 8, %1" : "=v"(b0) : "s"(m1));
+        asm("v_cndmask_b32 %0, 0, 16, %1" : "=v"(b1) : "s"(second));
+        idx[r] = tree_at | b0 | b1;
+    }
+#pragma unroll
+    for (int l = 2; l < D; ++l) {
+        Vec2 node[NR];
+        float x[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) node[r] = lds_read<Vec2>(idx[r] + (8u << l));
+#pragma unroll
+        for (int r = 0; r < NR; ++r) x[r] = lds_read<float>(xa + node[r].y + r * 256);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const int right = __float_as_int(__uint_as_float(node[r].x) - x[r]) >> 31;
+            asm("v_and_or_b32 %0, %1, %2, %0" : "+v"(idx[r]) : "v"(right), "s"(8 << l));
+        }
+    }
+}
+
+// What a kernel leaves behind: the sums of one output column, those of several (trees sorted by
+// column), or the leaf ids of every tree.
+enum { WALK_COLUMN = 0, WALK_COLUMNS = 1, WALK_LEAVES = 2 };
+
+template <int D, int NR, int MODE>
+__global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevModel m, const float *__restrict__ X,
+                                                                          int64_t n_rows, float *scores,
+                                                                          int32_t *labels, int32_t *leaf_out)
+{
+    constexpr int TREE_BYTES = 8 << D, STAGE_TREES = walk_stage_trees(D), STAGE_BYTES = TREE_BYTES * STAGE_TREES;
+    constexpr int PIECES = STAGE_BYTES / 1024;  // 16 bytes per lane each
+    constexpr int ROWS = NR * TILE;
+    constexpr bool LEAVES = MODE == WALK_LEAVES;
+    static_assert(STAGE_BYTES % 1024 == 0, "whole 16-byte pieces per lane");
+    extern __shared__ __align__(1024) char smem[];
+    const int lane = threadIdx.x & (TILE - 1), wave = uniform(threadIdx.x >> 6);
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * ROWS;
+    const uint32_t stride = static_cast<uint32_t>(m.walk.groups) * 256, xbase = WALK_WAVES * STAGE_BYTES;
+    const uint32_t mine = static_cast<uint32_t>(wave) * STAGE_BYTES;
+
+    // This wave's stages: a contiguous run for the sums; for the leaf ids, groups of at least four
+    // trees dealt in turn, so that the waves write neighbouring ids at about the same time.
+    constexpr int TURN = LEAVES && STAGE_TREES < 4 ? 4 / STAGE_TREES : 1;  // stages per group
+    const int S = m.walk.stages;
+    const int unit = static_cast<int>(blockIdx.y) * WALK_WAVES + wave, units = m.n_splits * WALK_WAVES;
+    const int s_begin = LEAVES ? unit * TURN : static_cast<int>(static_cast<int64_t>(S) * unit / units);
+    const int s_end = LEAVES ? S : static_cast<int>(static_cast<int64_t>(S) * (unit + 1) / units);
+    auto next_stage = [&](int s) {
+        if (!LEAVES) return s + 1;
+        return (s + 1) % TURN != 0 ? s + 1 : s + 1 + (units - 1) * TURN;
+    };
+
+    const char *image = reinterpret_cast<const char *>(m.walk.node);
+    Vec4 ahead[PIECES];
+    auto fetch = [&](int s) {
+        int64_t at = static_cast<int64_t>(s) * STAGE_BYTES + lane * 16;
+        if (LEAVES) {  // caller's order: the tree this lane's pieces belong to sits anywhere
+            const int t = s * STAGE_TREES + (lane * 16) / TREE_BYTES;
+            at = static_cast<int64_t>(m.walk.position[t]) * TREE_BYTES + (lane * 16) % TREE_BYTES;
+        }
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) ahead[i] = *reinterpret_cast<const Vec4 *>(image + at + i * 1024);
+    };
+    if (s_begin < s_end) fetch(s_begin);
+    walk_fill_tile<NR>(X, row0, n_rows, m.n_features, xbase, stride, wave, lane);
+    __syncthreads();
+
+    const uint32_t xa = xbase + lane * 4;
+    double acc[NR], done[WALK_MAX_COLUMNS - 1][NR];  // the running column, the columns before it
+    int column = 0, done_column[WALK_MAX_COLUMNS - 1], n_done = 0, first_column = 0;
+    float value[NR];  // the last tree's leaf values, not yet added
+    int32_t ids[NR][4];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        acc[r] = 0.0;
+        value[r] = 0.0f;
+    }
+    if (MODE == WALK_COLUMNS && s_begin < s_end)
+        column = first_column = ((WalkTable)(image + static_cast<int64_t>(s_begin) * STAGE_BYTES))[0];
+
+    for (int s = s_begin; s < s_end;) {
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) lds_write<Vec4>(mine + i * 1024 + lane * 16, ahead[i]);
+        const int s_next = next_stage(s);
+        if (s_next < s_end) fetch(s_next);
+        const int t0 = s * STAGE_TREES;
+        auto one_tree = [&](int q, int j) {
+            const int t = t0 + q;
+            const int at = LEAVES ? ((WalkTable)m.walk.position)[t] : t;
+            const WalkTop top = (WalkTop)(image + static_cast<int64_t>(at) * TREE_BYTES);
+            const uint32_t tree_at = mine + q * TREE_BYTES;
+            uint32_t idx[NR];
+            walk_tree<D, NR>(tree_at, xa, top, idx);
+            if (!LEAVES) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) acc[r] += static_cast<double>(value[r]);
+                if (const int c = static_cast<int>(top[0]); MODE == WALK_COLUMNS && c != column) {
+#pragma unroll
+                    for (int k = WALK_MAX_COLUMNS - 2; k > 0; --k) {
+                        done_column[k] = done_column[k - 1];
+#pragma unroll
+                        for (int r = 0; r < NR; ++r) done[k][r] = done[k - 1][r];
+                    }
+                    done_column[0] = column;
+                    ++n_done;
+                    column = c;
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) {
+                        done[0][r] = acc[r];
+                        acc[r] = 0.0;
+                    }
+                }
+            }
+            // half an index is the leaf's byte offset; the tree's address in it is taken off the base
+            const char *leaves = LEAVES ? reinterpret_cast<const char *>(m.walk.leaf_node) : reinterpret_cast<const char *>(m.walk.leaf);
+            leaves += (static_cast<int64_t>(at) << (D + 2)) - (tree_at >> 1);
+            asm volatile("" : "+s"(leaves));  // keeps the base whole, so that the loads take a 32-bit offset
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const GlobalBytes p = (GlobalBytes)leaves + (idx[r] >> 1);
+                if (LEAVES) ids[r][j] = *(GlobalInts)p;
+                else value[r] = *(GlobalFloats)p;
+            }
+        };
+        if (!LEAVES) {
+#pragma unroll 1
+            for (int q = 0; q < STAGE_TREES; ++q) one_tree(q, 0);
+        } else {
+            // four trees at a time: whole in a stage, or over the stages of a group
+            constexpr int STEP = STAGE_TREES < 4 ? STAGE_TREES : 4;
+            const int j0 = STAGE_TREES < 4 ? (s % TURN) * STAGE_TREES : 0;
+#pragma unroll 1
+            for (int q = 0; q < STAGE_TREES; q += STEP) {
+#pragma unroll
+                for (int j = 0; j < STEP; ++j) {
+                    if (STEP == 4) {
+                        one_tree(q + j, j);
+                    } else {  // the slot in ids[] has to be a constant
+#pragma unroll
+                        for (int k = 0; k < 4; k += STEP)
+                            if (k == j0) one_tree(q + j, k + j);
+                    }
+                }
+                const int last = t0 + q + STEP;  // trees [.., last) are in ids[]
+                if (last % 4 != 0 && last < m.n_trees) continue;
+                const int first = (last - 1) / 4 * 4;
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    const int64_t row = row0 + r * TILE + lane;
+                    if (row >= n_rows) continue;
+                    int32_t *dst = leaf_out + row * m.n_trees + first;
+                    if (first + 4 <= m.n_trees) {
+                        *reinterpret_cast<Int4 *>(dst) = Int4{{ids[r][0], ids[r][1], ids[r][2], ids[r][3]}};
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (first + j < m.n_trees) dst[j] = ids[r][j];
+                    }
+                }
+            }
+        }
+        s = s_next;
+    }
+    if (LEAVES) return;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) acc[r] += static_cast<double>(value[r]);
+
+    // The waves' column sums meet in LDS: a wave's run of trees feeds consecutive columns, so the
+    // sum of (wave, column) has the slot wave + column to itself.
+    __syncthreads();
+    const int K = m.n_outputs;
+    double *slot = reinterpret_cast<double *>(smem);                 // [WALK_WAVES + K - 1][ROWS]
+    double *sum = slot + static_cast<size_t>(WALK_WAVES + K - 1) * ROWS;  // [K][ROWS]
+    int32_t *fed = reinterpret_cast<int32_t *>(sum + static_cast<size_t>(K) * ROWS);  // first and last column of a wave
+    for (int i = threadIdx.x; i < (WALK_WAVES + K - 1) * ROWS; i += WALK_WAVES * TILE) slot[i] = 0.0;
+    if (lane == 0) {
+        fed[2 * wave] = s_begin < s_end ? first_column : 1;
+        fed[2 * wave + 1] = s_begin < s_end ? column : 0;
+    }
+    __syncthreads();
+    if (s_begin < s_end) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) slot[(wave + column) * ROWS + r * TILE + lane] = acc[r];
+#pragma unroll
+        for (int k = 0; k < WALK_MAX_COLUMNS - 1; ++k)
+            if (k < n_done) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) slot[(wave + done_column[k]) * ROWS + r * TILE + lane] = done[k][r];
+            }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < K * ROWS; i += WALK_WAVES * TILE) {
+        const int k = i / ROWS, li = i - k * ROWS;
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < WALK_WAVES; ++w)
+            if (fed[2 * w] <= k && k <= fed[2 * w + 1]) s += slot[(w + k) * ROWS + li];
+        sum[i] = s;
+    }
+    __syncthreads();
+    for (int li = threadIdx.x; li < ROWS; li += WALK_WAVES * TILE) {
+        const int64_t row = row0 + li;
+        finish_summed_row(m, sum, ROWS, li, row, row < n_rows, scores, labels);
+    }
+}
+
+template <int D, int MODE>
+KernelFn pick_groups(int groups)
+{
+    switch (groups) {
+        case 1: return forest_walk_kernel<D, 1, MODE>;
+        case 2: return forest_walk_kernel<D, 2, MODE>;
+        default: return forest_walk_kernel<D, MODE == WALK_COLUMNS ? 2 : 4, MODE>;  // walk_max_groups
+    }
+}
+
+template <int MODE>
+KernelFn pick_depth(int depth, int groups)
+{
+    switch (depth) {
+        case 3: return pick_groups<3, MODE>(groups);
+        case 4: return pick_groups<4, MODE>(groups);
+        case 5: return pick_groups<5, MODE>(groups);
+        case 6: return pick_groups<6, MODE>(groups);
+        case 7: return pick_groups<7, MODE>(groups);
+        default: return pick_groups<8, MODE>(groups);
+    }
+}
+
+KernelFn pick(int depth, int groups, int mode)
+{
+    if (mode == WALK_COLUMN) return pick_depth<WALK_COLUMN>(depth, groups);
+    if (mode == WALK_COLUMNS) return pick_depth<WALK_COLUMNS>(depth, groups);
+    return pick_depth<WALK_LEAVES>(depth, groups);
+}
+
+// Workgroups the chip holds at a time: two per CU.
+constexpr int64_t RESIDENT = 512;
+
+// Row groups per workgroup.  More rows per workgroup amortise the copies of the trees to LDS (per
+// 64 rows, depth 6: 1, 1.07 and 1.25 of the time with 4, 2 and 1 groups), fewer leave smaller
+// batches enough workgroups; the last round of workgroups counts whole.
+int choose_groups(const DevModel &m, int64_t n_rows)
+{
+    int best = 1;
+    double best_cost = 0.0;
+    for (int g = m.walk.groups; g >= 1; g /= 2) {
+        const int64_t blocks = (n_rows + TILE * g - 1) / (TILE * g) * m.n_splits;
+        const double cost = static_cast<double>((blocks + RESIDENT - 1) / RESIDENT) * g * (g == 4 ? 1.0 : g == 2 ? 1.07 : 1.25);
+        if (g == m.walk.groups || cost < best_cost) {
+            best = g;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+}  // namespace
+
+hipError_t init_walk_kernels(size_t lds_limit)
+{
+    for (int mode : {WALK_COLUMN, WALK_COLUMNS, WALK_LEAVES})
+        for (int depth = WALK_MIN_DEPTH; depth <= WALK_MAX_DEPTH; ++depth)
+            for (int groups = 1; groups <= walk_max_groups(mode == WALK_COLUMNS ? 2 : 1); groups *= 2) {
+                const void *fn = reinterpret_cast<const void *>(pick(depth, groups, mode));
+                hipFuncAttributes attr;
+                if (hipError_t e = hipFuncGetAttributes(&attr, fn); e != hipSuccess) return e;
+                if (attr.sharedSizeBytes != 0) return hipErrorInvalidValue;  // the kernels address LDS from 0
+                if (hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_limit));
+                    e != hipSuccess)
+                    return e;
+            }
+    return hipSuccess;
+}
+
+hipError_t launch_walk(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
+                       int32_t *leaf_out, hipStream_t stream)
+{
+    const int groups = choose_groups(m, n_rows);
+    const int64_t n_blocks = (n_rows + TILE * groups - 1) / (TILE * groups);
+    if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<unsigned>(n_blocks), static_cast<unsigned>(m.n_splits));
+    const size_t lds = walk_lds_bytes(m.walk.depth, m.n_features, m.n_outputs, m.walk.groups);
+    const int mode = leaf_out ? WALK_LEAVES : m.n_outputs == 1 ? WALK_COLUMN : WALK_COLUMNS;
+    hipLaunchKernelGGL(pick(m.walk.depth, groups, mode), grid, dim3(WALK_WAVES * TILE), lds, stream, m, X,
+                       n_rows, scores, labels, leaf_out);
+    return hipGetLastError();
+}
+
+}  // namespace forest_impl

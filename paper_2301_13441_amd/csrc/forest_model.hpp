@@ -254,6 +254,39 @@ struct BankSpan {
     int32_t unit_base;  // index of the first of them in the batch's bit buffer
 };
 
+// Walk kernels (forest_kernels_walk.hip): trees of any shape and depth up to WALK_MAX_DEPTH with
+// scalar leaves and finite thresholds, every tree laid out as a full tree of the forest's greatest
+// depth D (at least WALK_MIN_DEPTH): a leaf above depth D fills the leaf slots below it, and the
+// nodes between test feature 0 against 0, whichever way they go.  Inside a tree a node is numbered by
+// the outcomes on its path, first outcome in bit 0: node i of level l sits in slot 2^l + i of the
+// tree's 2^D slots, leaf i in slot i of its 2^D leaf slots.  Slot 0 has no node: it holds the tree's
+// output column and its index in the caller's description.  A wave copies a stage (whole trees,
+// at least 1 KB) to LDS at a time; the forest is filled up to whole stages with trees of zero leaves.
+constexpr int WALK_MIN_DEPTH = 3, WALK_MAX_DEPTH = 8;
+constexpr int WALK_WAVES = 16;       // wavefronts per workgroup
+constexpr int WALK_MAX_COLUMNS = 4;  // output columns that one wave's run of trees may feed
+
+// Most row groups of 64 rows per workgroup: the finished sums of several columns take the registers
+// that two more groups would need.
+constexpr int walk_max_groups(int n_outputs) { return n_outputs > 1 ? 2 : 4; }
+
+struct WalkNode {
+    float threshold;    // slot 0: the tree's output column (integer)
+    uint32_t x_offset;  // byte offset of the feature in the workgroup's X tile; slot 0: the caller's tree index
+};
+
+constexpr int walk_stage_trees(int depth) { return depth >= 7 ? 1 : 128 >> depth; }
+constexpr size_t walk_stage_bytes(int depth) { return sizeof(WalkNode) * (static_cast<size_t>(walk_stage_trees(depth)) << depth); }
+
+// LDS of a workgroup that owns `groups` x 64 rows: a stage per wave and the X tile, or the column
+// sums of the waves and of the rows, which reuse the space at the end.
+inline size_t walk_lds_bytes(int depth, int n_features, int n_outputs, int groups)
+{
+    const size_t walk = WALK_WAVES * walk_stage_bytes(depth) + static_cast<size_t>(n_features) * groups * 256;
+    const size_t sums = sizeof(double) * 64 * groups * static_cast<size_t>(WALK_WAVES + 2 * n_outputs - 1) + 2 * sizeof(int32_t) * WALK_WAVES;
+    return walk > sums ? walk : sums;
+}
+
 struct PackedModel {
     int32_t n_trees = 0, n_features = 0, n_outputs = 0, leaf_width = 1;
     int32_t aggregate = 0, transform = 0, output = 0;
@@ -304,6 +337,15 @@ struct PackedModel {
     std::vector<BankTree> bank_tree;         // [batches * BANK_TREES], processing order
     std::vector<BankSpan> bank_span;         // [batches][BANK_WAVES]
     std::vector<int32_t> bank_reg;           // [BANK_WAVES * BANK_REGS] rank register behind each bank register
+
+    // walk program (walk_depth 0: the model has none)
+    int32_t walk_depth = 0;
+    int32_t walk_groups = 0;               // row groups of 64 rows that the X tile is laid out for
+    int32_t walk_stages = 0;
+    std::vector<WalkNode> walk_node;       // [stages * stage trees][2^depth]
+    std::vector<float> walk_leaf;          // [stages * stage trees][2^depth]
+    std::vector<int32_t> walk_leaf_node;   // same index: the caller's node index of the leaf
+    std::vector<int32_t> walk_position;    // [n_trees + stage trees] where a caller's tree sits
 
     // caller-order views used only by forest_pack_view
     std::vector<int32_t> v_n_internal, v_depth, v_is_full, v_program_groups, v_order_leaf_tree;

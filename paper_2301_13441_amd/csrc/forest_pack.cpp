@@ -194,6 +194,77 @@ static void balance_waves(PackedModel &m)
     for (int w = 0; w <= waves; ++w) m.wave_tree[w] = w < n ? cut[w] : T;  // spare waves get no trees
 }
 
+// The walk program (forest_model.hpp).  `order`: the trees in processing order.
+static void build_walk(const forest_desc &d, const std::vector<TreeShape> &shape, const std::vector<int32_t> &order,
+                       PackedModel &m)
+{
+    const int32_t T = d.n_trees;
+    if (T < 1 || d.leaf_width != 1 || m.max_depth > WALK_MAX_DEPTH) return;
+    const int D = std::max<int>(m.max_depth, WALK_MIN_DEPTH);
+    // The side of a split is the sign of threshold - x, which says nothing for infinite thresholds.
+    for (int32_t t = 0; t < T; ++t)
+        for (int32_t v : shape[t].internal)
+            if (!std::isfinite(d.threshold[d.tree_offset[t] + v])) return;
+    // As many rows per workgroup as leave room for two workgroups on a CU, or else for one.
+    int groups = 0;
+    for (const size_t budget : {CU_LDS_BYTES / 2, CU_LDS_BYTES})
+        for (int g = walk_max_groups(d.n_outputs); g >= 1 && groups == 0; g /= 2)
+            if (walk_lds_bytes(D, d.n_features, d.n_outputs, g) <= budget) groups = g;
+    if (groups == 0) return;
+    const int stage_trees = walk_stage_trees(D);
+    const int32_t stages = (T + stage_trees - 1) / stage_trees;
+    const int64_t slots = static_cast<int64_t>(stages) * stage_trees << D;
+    if (slots > FOREST_MAX_NODES) return;
+    auto column_of = [&](int32_t t) { return d.tree_output ? d.tree_output[t] : 0; };
+    // A wave keeps the finished sums of its run's columns in registers.
+    for (int w = 0; w < WALK_WAVES; ++w) {
+        const int64_t t0 = static_cast<int64_t>(stages) * w / WALK_WAVES * stage_trees;
+        const int64_t t1 = std::min<int64_t>(T, static_cast<int64_t>(stages) * (w + 1) / WALK_WAVES * stage_trees);
+        int columns = 0;
+        for (int64_t i = t0; i < t1; ++i) columns += i == t0 || column_of(order[i]) != column_of(order[i - 1]);
+        if (columns > WALK_MAX_COLUMNS) return;
+    }
+    m.walk_depth = D;
+    m.walk_groups = groups;
+    m.walk_stages = stages;
+    m.walk_node.assign(static_cast<size_t>(slots), WalkNode{0.0f, 0});
+    m.walk_leaf.assign(static_cast<size_t>(slots), 0.0f);
+    m.walk_leaf_node.assign(static_cast<size_t>(slots), 0);
+    m.walk_position.assign(static_cast<size_t>(T + stage_trees), 0);
+    const uint32_t stride = static_cast<uint32_t>(groups) * 256;
+    std::vector<int32_t> level(static_cast<size_t>(1) << D), below(static_cast<size_t>(1) << D);
+    for (int64_t i = 0; i < static_cast<int64_t>(stages) * stage_trees; ++i) {
+        WalkNode *node = m.walk_node.data() + (i << D);
+        const int32_t t = order[std::min<int64_t>(i, T - 1)];
+        const int32_t head[2] = {column_of(t), t};
+        std::memcpy(&node[0].threshold, &head[0], sizeof(head[0]));
+        std::memcpy(&node[0].x_offset, &head[1], sizeof(head[1]));
+        if (i >= T) continue;  // fills the last stage
+        m.walk_position[t] = static_cast<int32_t>(i);
+        const int64_t base = d.tree_offset[t];
+        level[0] = 0;
+        for (int l = 0; l < D; ++l) {
+            const int32_t n = 1 << l;
+            for (int32_t k = 0; k < n; ++k) {
+                const int32_t v = level[k];
+                if (d.feature[base + v] < 0) {  // a leaf: both sides lead to it
+                    below[k] = below[k + n] = v;
+                    continue;
+                }
+                // -0 becomes +0: x = +0 must not be above it, and -0 - +0 has the sign bit set
+                node[n + k] = WalkNode{d.threshold[base + v] + 0.0f, static_cast<uint32_t>(d.feature[base + v]) * stride};
+                below[k] = d.left[base + v];
+                below[k + n] = d.right[base + v];
+            }
+            level.swap(below);
+        }
+        for (int32_t k = 0; k < (1 << D); ++k) {
+            m.walk_leaf[(i << D) + k] = d.leaf_value[base + level[k]];
+            m.walk_leaf_node[(i << D) + k] = level[k];
+        }
+    }
+}
+
 int compile_forest(const forest_desc &d, PackedModel &m)
 {
     if (int rc = check_desc(d)) return rc;
@@ -528,6 +599,7 @@ int compile_forest(const forest_desc &d, PackedModel &m)
         }
         m.tree.push_back(tm);
     }
+    build_walk(d, shape, order, m);
     if (m.path == PATH_RANK_LDS) balance_waves(m);
     if (m.path == PATH_RANK_LDS && m.kind == KIND_GENERIC && m.rank_regs >= 1 &&
         m.rank_regs <= BANK_WAVES * BANK_REGS && ((K == 1 && W == 1) || (W == K && K <= 2))) {

@@ -1,0 +1,91 @@
+"""The walk kernels and their packed form: trees of depth up to 8 laid out as full trees, one node
+per level and row.  Leaf ids and labels are exact; scores are fp64 sums rounded once on both sides,
+at most one float32 rounding (6e-8) apart, well inside the bar used here."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from test_gpu_parity import _check, _full_forest
+
+
+def _forest(seed, trees, depth, features, outputs=1, full=True):
+    if full:
+        return _full_forest(seed, trees, depth, features, n_outputs=outputs,
+                            transform=wl.TRANSFORM_SOFTMAX if outputs > 1 else wl.TRANSFORM_SIGMOID)
+    f = wl.random_forest(seed, n_trees=trees, n_features=features, max_depth=depth, stop_prob=0.2, n_outputs=outputs)
+    return wl.Forest(**{**f.__dict__, "tree_output": (np.arange(trees) % outputs).astype(np.int32)})
+
+
+def _special_rows(X, f, rng):
+    """Rows on thresholds, signed zeros, NaN and infinities."""
+    thr = f.threshold[f.feature >= 0]
+    if thr.size:
+        X[:40] = rng.choice(thr, (40, X.shape[1]))
+    X[40:50] = np.float32(0.0)
+    X[50:60] = np.float32(-0.0)
+    X[60:70] = rng.choice(np.float32([np.nan, np.inf, -np.inf, 1e-45, -1e-45]), (10, X.shape[1]))
+    return X
+
+
+@pytest.mark.parametrize("depth,full", [(1, True), (3, True), (4, False), (6, True), (7, False), (8, True), (8, False)])
+def test_walk_layout_reaches_the_oracles_leaves(depth, full):
+    import paper_2301_13441_amd as pk
+    rng = np.random.default_rng(depth)
+    f = _forest(60 + depth, 11, depth, 5, outputs=3, full=full)
+    f.threshold[np.flatnonzero(f.feature >= 0)[::5]] = np.float32(-0.0)
+    v = pk.forest_pack(f)
+    D, T = v["walk_depth"], f.n_trees
+    assert D == max(3, int(v["tree_depth"].max())) and v["walk_trees"] >= T
+    X = _special_rows(rng.standard_normal((100, 5)).astype(np.float32), f, rng)
+    ref = oracle.predict(f, X, want_leaves=True).leaf_node_id
+    x = np.where(np.isnan(X), np.float32(np.inf), X)
+    seen = set()
+    for i in range(T):
+        thr = v["walk_node"][i, :, 0].view(np.float32)
+        feat = v["walk_node"][i, :, 1] // (256 * v["walk_groups"])
+        caller = int(v["walk_node"][i, 0, 1])
+        assert int(v["walk_node"][i, 0, 0]) == f.tree_output[caller]
+        seen.add(caller)
+        at = np.zeros(len(X), np.int64)
+        for l in range(D):
+            h = (1 << l) + at
+            with np.errstate(invalid="ignore"):
+                right = np.signbit(thr[h] - x[np.arange(len(X)), feat[h]])     # the sign the kernel takes
+            at |= right.astype(np.int64) << l
+        np.testing.assert_array_equal(v["walk_leaf_node"][i, at], ref[:, caller])
+        values = f.leaf_value[f.tree_offset[caller] + v["walk_leaf_node"][i, at], 0]
+        np.testing.assert_array_equal(v["walk_leaf"][i, at], values)
+    assert seen == set(range(T))
+    assert (v["walk_leaf"][T:] == 0).all()
+
+
+def test_walk_takes_what_it_is_built_for():
+    import paper_2301_13441_amd as pk
+    assert pk.forest_pack(_forest(1, 20, 8, 28))["walk_groups"] == 4
+    assert pk.forest_pack(_forest(1, 20, 6, 128, outputs=10))["walk_groups"] == 2
+    assert pk.forest_pack(_forest(1, 20, 6, 500))["walk_groups"] == 1
+    assert pk.forest_pack(_forest(1, 20, 6, 700))["walk_depth"] == 0                    # X tile beyond the LDS
+    assert pk.forest_pack(wl.random_forest(3, 9, 5, 9, stop_prob=0.0))["walk_depth"] == 0  # depth 9
+    f = _forest(1, 20, 6, 9)
+    f.threshold[np.flatnonzero(f.feature >= 0)[3]] = np.inf
+    assert pk.forest_pack(f)["walk_depth"] == 0                                         # infinite threshold
+    f = _forest(1, 100, 6, 9, outputs=8)
+    assert pk.forest_pack(f)["walk_depth"] == 6
+    f.tree_output[:] = np.sort(np.concatenate([np.arange(7), np.full(93, 7)])).astype(np.int32)
+    assert pk.forest_pack(f)["walk_depth"] == 0                                         # 7 columns in one wave's run
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("depth", [1, 2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("features,outputs,full", [(3, 1, True), (40, 4, False), (61, 1, False), (130, 4, True), (300, 1, True)])
+def test_walk_kernels(depth, features, outputs, full):
+    """Every depth; tiles of 4, 2 and 1 row groups; one and several columns; few trees (waves without
+    any) and more trees than waves; leaf ids of a tree count that is no multiple of four."""
+    import paper_2301_13441_amd as pk
+    rng = np.random.default_rng(100 * depth + features)
+    for trees, rows in ((5, 517), (83, 65536 + 77)):
+        f = _forest(9 * depth + features, trees, depth, features, outputs, full)
+        assert pk.forest_pack(f)["walk_depth"] > 0
+        X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
+        _check(f, X, leaves=True)
