@@ -125,6 +125,20 @@ typedef struct forest_packed_view {
     const uint32_t *walk_node;       /* [(walk_trees << walk_depth) * 2] */
     const float *walk_leaf;          /* [walk_trees << walk_depth] */
     const int32_t *walk_leaf_node;   /* [walk_trees << walk_depth] */
+    /* Models the deep walk kernels take (else deep_groups is 0 and the pointers NULL), trees in processing
+     * order.  deep_top[t] holds the top's nodes and a copy of the first 1 << deep_top_levels units; deep_top[t][1 << l | i] is node i of level l of the top: {float threshold, 256 * feature};
+     * words 0 and 1 of deep_top[t] are the tree's first unit and its output column; path i of the top goes
+     * on at unit i from there;
+     * deep_unit[u] either a node, {float threshold, 0x7f800000 | feature << 14 | distance to the left
+     * child's unit} (the right child is the next unit), or a leaf, whose second word is no NaN: {value, 0},
+     * {value 0, value 1} or {row of deep_value, 0}.  deep_unit_node: the caller's node index. */
+    int32_t deep_groups, deep_top_levels, deep_value_width;
+    int64_t deep_units;
+    const uint32_t *deep_top;        /* [n_trees][2 << deep_top_levels][2] */
+    const uint32_t *deep_unit;       /* [deep_units][2] */
+    const int32_t *deep_unit_node;   /* [deep_units] */
+    const float *deep_value;         /* [][deep_value_width] of leaves wider than 2 */
+    const int32_t *deep_position;    /* [n_trees] where a caller's tree sits in processing order */
 } forest_packed_view;
 
 typedef struct forest_packed forest_packed;

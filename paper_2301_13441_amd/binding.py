@@ -55,7 +55,10 @@ class _View(ctypes.Structure):
                 ("bank_todo", _p), ("fast_window", _i32), ("fast_tab_entries", _i64), ("fast_feat", _p), ("fast_tab", _p),
                 ("order_leaf_node", _p), ("order_leaf_tree", _p),
                 ("walk_depth", _i32), ("walk_groups", _i32), ("walk_trees", _i32), ("walk_node", _p),
-                ("walk_leaf", _p), ("walk_leaf_node", _p)]
+                ("walk_leaf", _p), ("walk_leaf_node", _p),
+                ("deep_groups", _i32), ("deep_top_levels", _i32), ("deep_value_width", _i32), ("deep_units", _i64),
+                ("deep_top", _p), ("deep_unit", _p), ("deep_unit_node", _p), ("deep_value", _p),
+                ("deep_position", _p)]
 
 
 # include/forest.h: the inference ABI
@@ -218,6 +221,16 @@ def forest_pack(forest) -> dict:
             rank.update(walk_node=get(v.walk_node, 2 * slots, np.uint32).reshape(int(v.walk_trees), -1, 2),
                         walk_leaf=get(v.walk_leaf, slots, np.float32).reshape(int(v.walk_trees), -1),
                         walk_leaf_node=get(v.walk_leaf_node, slots, np.int32).reshape(int(v.walk_trees), -1))
+        rank.update(deep_groups=int(v.deep_groups))
+        if v.deep_groups > 0:
+            top, units = 2 << int(v.deep_top_levels), int(v.deep_units)
+            deep_unit = get(v.deep_unit, 2 * units, np.uint32).reshape(units, 2)
+            width = int(v.deep_value_width)
+            rows = int((~np.isnan(deep_unit[:, 1].copy().view(np.float32))).sum()) if width > 2 else 0
+            rank.update(deep_top=get(v.deep_top, 2 * top * forest.n_trees, np.uint32).reshape(forest.n_trees, top, 2),
+                        deep_unit=deep_unit, deep_unit_node=get(v.deep_unit_node, units, np.int32),
+                        deep_value=get(v.deep_value, rows * width, np.float32).reshape(rows, width) if rows else None,
+                        deep_position=get(v.deep_position, forest.n_trees, np.int32))
         rank["order_leaf_node"] = get(v.order_leaf_node, nl, np.int32)
         rank["order_leaf_tree"] = get(v.order_leaf_tree, nl, np.int32)
         return dict(

@@ -170,6 +170,11 @@ int forest_load(const forest_desc *desc, forest **out)
     const size_t o_wleaf = place<float>(cur, m.walk_leaf.size());
     const size_t o_wleafn = place<int32_t>(cur, m.walk_leaf_node.size());
     const size_t o_wpos = place<int32_t>(cur, m.walk_position.size());
+    const size_t o_dtop = place<WalkNode>(cur, m.deep_top.size());
+    const size_t o_dunit = place<WalkNode>(cur, m.deep_unit.size());
+    const size_t o_dnode = place<int32_t>(cur, m.deep_unit_node.size());
+    const size_t o_dvalue = place<float>(cur, m.deep_value.size());
+    const size_t o_dpos = place<int32_t>(cur, m.deep_position.size());
     const size_t model_bytes = (cur + 255) & ~size_t{255};
     // workspaces of split launches, not uploaded
     const bool ranks = m.path == PATH_RANK || m.path == PATH_RANK_LDS;
@@ -217,7 +222,12 @@ int forest_load(const forest_desc *desc, forest **out)
                     up(o_wnode, m.walk_node.data(), m.walk_node.size() * sizeof(WalkNode)) &&
                     up(o_wleaf, m.walk_leaf.data(), m.walk_leaf.size() * sizeof(float)) &&
                     up(o_wleafn, m.walk_leaf_node.data(), m.walk_leaf_node.size() * sizeof(int32_t)) &&
-                    up(o_wpos, m.walk_position.data(), m.walk_position.size() * sizeof(int32_t));
+                    up(o_wpos, m.walk_position.data(), m.walk_position.size() * sizeof(int32_t)) &&
+                    up(o_dtop, m.deep_top.data(), m.deep_top.size() * sizeof(WalkNode)) &&
+                    up(o_dunit, m.deep_unit.data(), m.deep_unit.size() * sizeof(WalkNode)) &&
+                    up(o_dnode, m.deep_unit_node.data(), m.deep_unit_node.size() * sizeof(int32_t)) &&
+                    up(o_dvalue, m.deep_value.data(), m.deep_value.size() * sizeof(float)) &&
+                    up(o_dpos, m.deep_position.data(), m.deep_position.size() * sizeof(int32_t));
     if (!ok) {
         (void)hipGetLastError();
         (void)hipFree(f->blob);
@@ -276,6 +286,12 @@ int forest_load(const forest_desc *desc, forest **out)
     d.walk.depth = m.walk_depth;
     d.walk.groups = m.walk_groups;
     d.walk.stages = m.walk_stages;
+    d.deep.top = reinterpret_cast<const WalkNode *>(b + o_dtop);
+    d.deep.unit = reinterpret_cast<const WalkNode *>(b + o_dunit);
+    d.deep.unit_node = reinterpret_cast<const int32_t *>(b + o_dnode);
+    d.deep.value = reinterpret_cast<const float *>(b + o_dvalue);
+    d.deep.position = reinterpret_cast<const int32_t *>(b + o_dpos);
+    d.deep.groups = m.deep_groups;
     d.n_splits = 1;
     d.n_entries = static_cast<int64_t>(m.prog32.size() > m.prog.size() ? m.prog32.size() : m.prog.size());
     d.split_rows = 0;
@@ -295,6 +311,11 @@ int forest_load(const forest_desc *desc, forest **out)
     m.walk_leaf = {};
     m.walk_leaf_node = {};
     m.walk_position = {};
+    m.deep_top = {};
+    m.deep_unit = {};
+    m.deep_unit_node = {};
+    m.deep_value = {};
+    m.deep_position = {};
     m.v_feature = {};
     m.v_threshold = {};
     m.v_left = {};

@@ -116,6 +116,16 @@ int forest_pack_view(const forest_packed *p, forest_packed_view *v)
     v->walk_node = walk ? reinterpret_cast<const uint32_t *>(m.walk_node.data()) : nullptr;
     v->walk_leaf = walk ? m.walk_leaf.data() : nullptr;
     v->walk_leaf_node = walk ? m.walk_leaf_node.data() : nullptr;
+    const bool deep = m.deep_groups > 0;
+    v->deep_groups = m.deep_groups;
+    v->deep_top_levels = DEEP_TOP;
+    v->deep_value_width = deep_width(m.leaf_width);
+    v->deep_units = static_cast<int64_t>(m.deep_unit.size());
+    v->deep_top = deep ? reinterpret_cast<const uint32_t *>(m.deep_top.data()) : nullptr;
+    v->deep_unit = deep ? reinterpret_cast<const uint32_t *>(m.deep_unit.data()) : nullptr;
+    v->deep_unit_node = deep ? m.deep_unit_node.data() : nullptr;
+    v->deep_value = deep ? m.deep_value.data() : nullptr;
+    v->deep_position = deep ? m.deep_position.data() : nullptr;
     return FOREST_OK;
 }
 

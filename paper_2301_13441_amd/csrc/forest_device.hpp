@@ -36,6 +36,16 @@ struct WalkDev {
     int32_t stages;
 };
 
+// Device tables of the deep walk program (forest_model.hpp).
+struct DeepDev {
+    const WalkNode *top;
+    const WalkNode *unit;
+    const int32_t *unit_node;
+    const float *value;
+    const int32_t *position;
+    int32_t groups;  // 0: none
+};
+
 struct DevModel {
     const SplitEntry *prog;
     const uint32_t *prog32;
@@ -75,6 +85,7 @@ struct DevModel {
     // LDS rank family: large batches of models it fits run the register-bank kernel
     BankDev bank;
     WalkDev walk;
+    DeepDev deep;
 };
 
 // Batches below this many workgroups split the trees over several workgroups per row tile.
@@ -139,6 +150,11 @@ hipError_t launch_rankbank(const DevModel &m, const float *X, int64_t n_rows, fl
 // Walk kernels (forest_kernels_walk.hip).
 hipError_t init_walk_kernels(size_t lds_limit);
 hipError_t launch_walk(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
+                       int32_t *leaf_out, hipStream_t stream);
+
+// Deep walk kernels (forest_kernels_deep.hip).
+hipError_t init_deep_kernels(size_t lds_limit);
+hipError_t launch_deep(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                        int32_t *leaf_out, hipStream_t stream);
 
 // Sums the partial sums of a split launch over the splits and finishes every row.

@@ -46,6 +46,16 @@ __device__ __forceinline__ void tree_range(const DevModel &m, int wave, int n_wa
     t_end = static_cast<int>((T * (unit + 1)) / units);
 }
 
+// Tables that are never written: read through the constant address space they are scalar loads where the
+// index is wave-uniform, whatever else the kernel writes.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const __attribute__((address_space(4))) double *ColumnTrees;
+typedef const __attribute__((address_space(4))) float *ColumnBase;
+#else
+typedef const double *ColumnTrees;  // host pass: the kernel body is only parsed
+typedef const float *ColumnBase;
+#endif
+
 // Aggregate, label, transform, store for one row whose K summed leaf values are raw[k * stride];
 // raw[] is overwritten with the aggregated values.
 __device__ __forceinline__ void finish_values(const DevModel &m, double *raw, int64_t stride, int64_t row,
@@ -57,8 +67,8 @@ __device__ __forceinline__ void finish_values(const DevModel &m, double *raw, in
     for (int k = 0; k < K; ++k) {
         double s = raw[k * stride];
         // a column no tree feeds: the mean over no trees adds nothing to the base score
-        if (m.aggregate == FOREST_AGG_MEAN && m.col_trees[k] > 0.0) s = s / m.col_trees[k];
-        s = static_cast<double>(m.base[k]) + s;
+        if (const double n = ((ColumnTrees)m.col_trees)[k]; m.aggregate == FOREST_AGG_MEAN && n > 0.0) s = s / n;
+        s = static_cast<double>(((ColumnBase)m.base)[k]) + s;
         raw[k * stride] = s;
         if (k == 0 || s > best) {
             best = s;

@@ -256,7 +256,8 @@ hipError_t init_kernels()
     if (hipError_t e = init_rank_kernels(g_lds_limit); e != hipSuccess) return e;
     if (hipError_t e = init_ranklds_kernels(g_lds_limit); e != hipSuccess) return e;
     if (hipError_t e = init_rankbank_kernels(g_lds_limit); e != hipSuccess) return e;
-    return init_walk_kernels(g_lds_limit);
+    if (hipError_t e = init_walk_kernels(g_lds_limit); e != hipSuccess) return e;
+    return init_deep_kernels(g_lds_limit);
 }
 
 int family_rows_per_block(const DevModel &m)
@@ -339,6 +340,9 @@ static hipError_t launch_family(const DevModel &m, const float *X, int64_t n_row
                                 int32_t *labels, int32_t *leaf_out, hipStream_t stream)
 {
     if (m.n_splits == 1 && m.walk.depth > 0) return launch_walk(m, X, n_rows, scores, labels, leaf_out, stream);
+    // trees deeper than 8, vector leaves, infinite thresholds: what a row does not meet is not tested
+    // (128 trees of depth 12: 2.9 ms against 14.5 with the register-bank kernel)
+    if (m.n_splits == 1 && m.deep.groups > 0) return launch_deep(m, X, n_rows, scores, labels, leaf_out, stream);
     if (m.path == PATH_RANK) return launch_rank(m, X, n_rows, scores, labels, leaf_out, stream);
     if (m.path == PATH_RANK_LDS) {
         // large batches of the models it fits: rank registers banked over the waves' vector registers

@@ -1,0 +1,432 @@
+// Deep walk kernels (gfx950): trees of any shape and depth, scalar or vector leaves, one node per
+// level and row.
+//
+// The top DEEP_TOP levels of a tree go as in the walk kernels (forest_kernels_walk.hip): laid out as
+// a full tree, the first two levels through scalar loads, below them one node per level out of the
+// wave's stage in LDS, and there the path ends on a unit (forest_model.hpp): for most rows of an
+// irregular tree their leaf.  The other rows go on through the units, which their lanes gather from
+// global memory, the lanes that have met their leaf masked off.  A subtree's units are contiguous,
+// so a lane finds most of its path in the line or two that its first unit came with, and the path
+// ends on the leaf's value itself.
+//
+// A workgroup of 16 waves owns NR x 64 rows, whose features it holds in LDS as float32
+// ([group][feature][row]); every wave walks its own run of trees for all the rows, two trees at a time
+// below their tops.
+//
+// 128 trees of depth 12, 256 features, 4,000,000 rows: 2.88 ms (14.5 with every node tested,
+// forest_kernels_rankbank.hip).  1.1 ms are the tile's (X once from memory, which one workgroup per
+// CU does not overlap with its walk, and 0.4 ms of launches and sums), 0.8 the tops (LDS round trips),
+// 1.0 the units (a gather costs the texture path about a cycle per active lane; with the first units
+// gathered too instead of held in LDS it was 1.1, at twice the path's load).  Keeping 64-row tiles, two
+// workgroups on a CU and the first units in global memory: 2.90 ms there, 94 us against 87 for
+// 300 trees of depth 9 over 90 features and 103,069 rows.  Workgroups that loop over tiles and request the
+// next rows before they finish the sums: 3.15 ms.
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+
+#include "forest_device.hpp"
+#include "forest_kernel_common.hpp"
+#include "forest_walk_common.hpp"
+
+namespace forest_impl {
+namespace {
+
+// What a kernel leaves behind: the sums of one output column, those of several (trees sorted by
+// column), those of vector leaves, or the leaf ids of every tree.
+enum { DEEP_COLUMN = 0, DEEP_COLUMNS = 1, DEEP_VECTOR = 2, DEEP_LEAVES = 3 };
+
+constexpr uint32_t TOP_BYTES = DEEP_TOP_WORDS * sizeof(WalkNode);     // of a tree
+constexpr uint32_t NODES_BYTES = TOP_BYTES / 2;                        // its nodes, and as much for its first units
+static_assert(NODES_BYTES == 64 * 16, "a lane copies 16 bytes of either");
+constexpr uint32_t XBASE = DEEP_WAVES * TOP_BYTES;  // LDS: the waves' nodes, their first units, the X tile
+
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef const __attribute__((address_space(1))) Vec2 *GlobalUnits;
+#else
+typedef const Vec2 *GlobalUnits;
+#endif
+
+// The first words of a tree's top, wave-uniform: its first unit, its column, the nodes of two levels.
+struct DeepHead {
+    uint32_t w[8];
+};
+
+__device__ __forceinline__ DeepHead deep_head(const char *tops, int at)
+{
+    const WalkTop p = (WalkTop)(tops + static_cast<int64_t>(at) * TOP_BYTES);
+    DeepHead h;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) h.w[i] = p[i];
+    return h;
+}
+
+// The top of one tree, all row groups: where the path goes on, as the byte offset from the tree's first
+// unit, and the unit there.
+template <int NR>
+__device__ __forceinline__ void deep_top(uint32_t stage, const uint32_t (&xa)[NR], const DeepHead &head, uint32_t (&at)[NR],
+                                         Vec2 (&what)[NR])
+{
+    const uint32_t (&top)[8] = head.w;
+    const float t1 = __uint_as_float(top[2]), t2 = __uint_as_float(top[4]), t3 = __uint_as_float(top[6]);
+    float x1[NR], x2[NR], x3[NR];
+    uint32_t idx[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) x1[r] = lds_read<float>(xa[r] + top[3]);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) x2[r] = lds_read<float>(xa[r] + top[5]);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) x3[r] = lds_read<float>(xa[r] + top[7]);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const uint64_t m1 = __ballot(!(x1[r] <= t1)), m2 = __ballot(!(x2[r] <= t2)), m3 = __ballot(!(x3[r] <= t3));
+        const uint64_t second = (m1 & m3) | (~m1 & m2);
+        uint32_t b0, b1;
+        asm("v_cndmask_b32 %0, 0, 8, %1" : "=v"(b0) : "s"(m1));
+        asm("v_cndmask_b32 %0, 0, 16, %1" : "=v"(b1) : "s"(second));
+        idx[r] = stage | b0 | b1;
+    }
+#pragma unroll
+    for (int l = 2; l < DEEP_TOP; ++l) {
+        Vec2 node[NR];
+        float x[NR];
+#pragma unroll
+        for (int r = 0; r < NR; ++r) node[r] = lds_read<Vec2>(idx[r] + (8u << l));
+#pragma unroll
+        for (int r = 0; r < NR; ++r) x[r] = lds_read<float>(xa[r] + node[r].y);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) idx[r] |= x[r] <= __uint_as_float(node[r].x) ? 0u : 8u << l;
+    }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) what[r] = lds_read<Vec2>(idx[r] + DEEP_WAVES * NODES_BYTES);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) at[r] = idx[r] - stage;
+}
+
+// SHARED: two workgroups on a CU (64 vector registers per lane), or one.
+template <int NR, int MODE, int WP, bool SHARED>
+__global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep_kernel(DevModel m, const float *__restrict__ X,
+                                                                                       int64_t n_rows, float *scores,
+                                                                                       int32_t *labels, int32_t *leaf_out)
+{
+    constexpr int ROWS = NR * TILE;
+    constexpr bool LEAVES = MODE == DEEP_LEAVES;
+    constexpr int W = LEAVES ? 1 : WP;
+    constexpr int NT = 2;  // trees whose units are walked together
+    static_assert(MODE == DEEP_VECTOR || WP == 1, "scalar leaves");
+    extern __shared__ __align__(1024) char smem[];
+    const int lane = threadIdx.x & (TILE - 1), wave = uniform(threadIdx.x >> 6);
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * ROWS;
+    const int F = m.n_features, T = m.n_trees;
+    const uint32_t group_stride = static_cast<uint32_t>(F) * 256;
+    const uint32_t stage = static_cast<uint32_t>(wave) * NODES_BYTES;
+
+    // This wave's trees: a contiguous run for the sums; for the leaf ids, fours dealt in turn, so
+    // that the waves write neighbouring ids at about the same time.
+    const int unit = static_cast<int>(blockIdx.y) * DEEP_WAVES + wave, units = m.n_splits * DEEP_WAVES;
+    const int t_begin = LEAVES ? unit * 4 : static_cast<int>(static_cast<int64_t>(T) * unit / units);
+    const int t_end = LEAVES ? T : static_cast<int>(static_cast<int64_t>(T) * (unit + 1) / units);
+    auto next_tree = [&](int t) { return !LEAVES || (t & 3) != 3 ? t + 1 : t + 1 + (units - 1) * 4; };
+    auto place = [&](int t) { return LEAVES ? ((WalkTable)m.deep.position)[t] : t; };  // leaf ids: caller's order
+
+    const char *tops = reinterpret_cast<const char *>(m.deep.top);
+    Vec4 ahead[2];
+    DeepHead head = {};  // of the tree whose top comes next
+    auto fetch = [&](int at) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            ahead[i] = *reinterpret_cast<const Vec4 *>(tops + static_cast<int64_t>(at) * TOP_BYTES + i * NODES_BYTES + lane * 16);
+    };
+    if (t_begin < t_end) {
+        fetch(place(t_begin));
+        head = deep_head(tops, place(t_begin));
+    }
+    tile_fill<NR, NR == 2 ? 8 : 4, false>(X, row0, n_rows, F, XBASE, group_stride, 256, wave, lane);
+    __syncthreads();
+
+    uint32_t xa[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) xa[r] = XBASE + static_cast<uint32_t>(r) * group_stride + lane * 4;
+
+    double acc[W][NR], done[MODE == DEEP_COLUMNS ? WALK_MAX_COLUMNS - 1 : 1][NR];
+    int column = 0, done_column[MODE == DEEP_COLUMNS ? WALK_MAX_COLUMNS - 1 : 1] = {}, n_done = 0, first_column = 0;
+#pragma unroll
+    for (int k = 0; k < W; ++k)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) acc[k][r] = 0.0;
+    if (MODE == DEEP_COLUMNS && t_begin < t_end) column = first_column = static_cast<int>(head.w[1]);
+    int32_t ids[NR][4];
+
+    // The lanes' places in the units of the trees at hand: byte offset from the tree's first unit, and
+    // what is there.
+    uint32_t at[NT][NR];
+    Vec2 what[NT][NR];
+    const char *units_of[NT];  // the trees' first units (wave-uniform)
+    uint32_t first_unit[NT];
+    int tree_column[NT];
+    auto go_on = [&]() {
+        for (;;) {
+            bool inside[NT][NR], any = false;
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    inside[j][r] = __builtin_isnan(__uint_as_float(what[j][r].y));
+                    any |= inside[j][r];
+                }
+            if (!__any(any)) break;
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if (inside[j][r]) {
+                        const uint32_t w = what[j][r].y;
+                        const float x = lds_read<float>(xa[r] + (__builtin_amdgcn_ubfe(w, 14, 9) << 8));
+                        const uint32_t step = (w & DEEP_MAX_DISTANCE) + (x <= __uint_as_float(what[j][r].x) ? 0u : 1u);
+                        at[j][r] += step << 3;
+                        what[j][r] = *(GlobalUnits)((GlobalBytes)units_of[j] + at[j][r]);
+                    }
+        }
+    };
+    auto add_values = [&](int j) {
+        if (WP <= 2) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                acc[0][r] += static_cast<double>(__uint_as_float(what[j][r].x));
+                if (W == 2) acc[W - 1][r] += static_cast<double>(__uint_as_float(what[j][r].y));
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const Vec4 *v = reinterpret_cast<const Vec4 *>(m.deep.value + static_cast<size_t>(what[j][r].x) * WP);
+#pragma unroll
+                for (int q = 0; q < WP / 4; ++q) {
+                    const Vec4 p = v[q];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[(4 * q + i) % W][r] += static_cast<double>(__uint_as_float(p[i]));
+                }
+            }
+        }
+    };
+    auto change_column = [&](int c) {  // the column of the values added next
+        if constexpr (MODE == DEEP_COLUMNS) {
+#pragma unroll
+            for (int k = WALK_MAX_COLUMNS - 2; k > 0; --k) {
+                done_column[k] = done_column[k - 1];
+#pragma unroll
+                for (int r = 0; r < NR; ++r) done[k][r] = done[k - 1][r];
+            }
+            done_column[0] = column;
+            ++n_done;
+            column = c;
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                done[0][r] = acc[0][r];
+                acc[0][r] = 0.0;
+            }
+        }
+    };
+
+    // The top of tree t (j: its place in the pair); the next tree's top is on its way from here on.
+    auto take = [&](int j, int t_after) {
+        lds_write<Vec4>(stage + lane * 16, ahead[0]);
+        lds_write<Vec4>(stage + DEEP_WAVES * NODES_BYTES + lane * 16, ahead[1]);
+        const DeepHead here = head;
+        first_unit[j] = here.w[0];
+        tree_column[j] = static_cast<int>(here.w[1]);
+        units_of[j] = reinterpret_cast<const char *>(m.deep.unit) + static_cast<int64_t>(here.w[0]) * 8;
+        asm volatile("" : "+s"(units_of[j]));  // keeps the base whole, so that the loads take a 32-bit offset
+        if (t_after < t_end) {
+            const int next = place(t_after);
+            fetch(next);
+            head = deep_head(tops, next);
+        }
+        deep_top<NR>(stage, xa, here, at[j], what[j]);
+    };
+    for (int t = t_begin; t < t_end;) {
+        const int second = next_tree(t), after = next_tree(second);
+        const bool two = second < t_end;  // a four begins with an even tree: its pairs stay together
+        take(0, second);
+        if (two) {
+            take(1, after);
+        } else {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) what[1][r] = Vec2{0, 0};
+        }
+        go_on();
+        if constexpr (!LEAVES) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                if (j > 0 && !two) break;
+                if (MODE == DEEP_COLUMNS && tree_column[j] != column) change_column(tree_column[j]);
+                add_values(j);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                if (j > 0 && !two) break;
+                const int32_t *node = m.deep.unit_node + first_unit[j];
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    const int32_t id = node[at[j][r] >> 3];
+                    ids[r][j] = (t & 2) == 0 ? id : ids[r][j];
+                    ids[r][2 + j] = (t & 2) != 0 ? id : ids[r][2 + j];
+                }
+            }
+            const int first = t & ~3;
+            if ((t & 2) != 0 || t + NT >= T) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    const int64_t row = row0 + r * TILE + lane;
+                    if (row >= n_rows) continue;
+                    int32_t *dst = leaf_out + row * T + first;
+                    if (first + 4 <= T) {
+                        *reinterpret_cast<Int4 *>(dst) = Int4{{ids[r][0], ids[r][1], ids[r][2], ids[r][3]}};
+                    } else {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            if (first + j < T) dst[j] = ids[r][j];
+                    }
+                }
+            }
+        }
+        t = two ? after : second;
+    }
+    if constexpr (!LEAVES) {
+        // The waves' sums meet in LDS, in the order of the waves.
+        __syncthreads();
+        const int K = m.n_outputs;
+        double *slot = reinterpret_cast<double *>(smem);
+        double *sum;  // [K][ROWS]
+        if constexpr (MODE == DEEP_VECTOR) {
+            sum = slot;  // [DEEP_WAVES][K][ROWS]
+#pragma unroll
+            for (int k = 0; k < W; ++k)
+                if (k < K) {
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) slot[(wave * K + k) * ROWS + r * TILE + lane] = acc[k][r];
+                }
+            __syncthreads();
+            for (int i = threadIdx.x; i < K * ROWS; i += DEEP_WAVES * TILE) {
+                double s = 0.0;
+#pragma unroll
+                for (int w = 0; w < DEEP_WAVES; ++w) s += slot[w * K * ROWS + i];
+                sum[i] = s;
+            }
+        } else {
+            // a wave's run of trees feeds consecutive columns, so the sum of (wave, column) has the
+            // slot wave + column to itself
+            sum = slot + static_cast<size_t>(DEEP_WAVES + K - 1) * ROWS;
+            int32_t *fed = reinterpret_cast<int32_t *>(sum + static_cast<size_t>(K) * ROWS);  // first and last column of a wave
+            for (int i = threadIdx.x; i < (DEEP_WAVES + K - 1) * ROWS; i += DEEP_WAVES * TILE) slot[i] = 0.0;
+            if (lane == 0) {
+                fed[2 * wave] = t_begin < t_end ? first_column : 1;
+                fed[2 * wave + 1] = t_begin < t_end ? column : 0;
+            }
+            __syncthreads();
+            if (t_begin < t_end) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) slot[(wave + column) * ROWS + r * TILE + lane] = acc[0][r];
+                if constexpr (MODE == DEEP_COLUMNS) {
+#pragma unroll
+                    for (int k = 0; k < WALK_MAX_COLUMNS - 1; ++k)
+                        if (k < n_done) {
+#pragma unroll
+                            for (int r = 0; r < NR; ++r) slot[(wave + done_column[k]) * ROWS + r * TILE + lane] = done[k][r];
+                        }
+                }
+            }
+            __syncthreads();
+            for (int i = threadIdx.x; i < K * ROWS; i += DEEP_WAVES * TILE) {
+                const int k = i / ROWS, li = i - k * ROWS;
+                double s = 0.0;
+#pragma unroll
+                for (int w = 0; w < DEEP_WAVES; ++w)
+                    if (fed[2 * w] <= k && k <= fed[2 * w + 1]) s += slot[(w + k) * ROWS + li];
+                sum[i] = s;
+            }
+        }
+        __syncthreads();
+        for (int li = threadIdx.x; li < ROWS; li += DEEP_WAVES * TILE) {
+            const int64_t row = row0 + li;
+            finish_summed_row(m, sum, ROWS, li, row, row < n_rows, scores, labels);
+        }
+    }
+}
+
+template <bool SHARED>
+KernelFn pick_mode(int groups, int mode, int width)
+{
+    const bool two = groups > 1;
+    if (mode == DEEP_LEAVES) return two ? forest_deep_kernel<2, DEEP_LEAVES, 1, SHARED> : forest_deep_kernel<1, DEEP_LEAVES, 1, SHARED>;
+    if (mode == DEEP_COLUMN) return two ? forest_deep_kernel<2, DEEP_COLUMN, 1, SHARED> : forest_deep_kernel<1, DEEP_COLUMN, 1, SHARED>;
+    if (mode == DEEP_COLUMNS) return two ? forest_deep_kernel<2, DEEP_COLUMNS, 1, SHARED> : forest_deep_kernel<1, DEEP_COLUMNS, 1, SHARED>;
+    switch (width) {
+        case 2: return two ? forest_deep_kernel<2, DEEP_VECTOR, 2, SHARED> : forest_deep_kernel<1, DEEP_VECTOR, 2, SHARED>;
+        case 4: return forest_deep_kernel<1, DEEP_VECTOR, 4, SHARED>;
+        case 8: return forest_deep_kernel<1, DEEP_VECTOR, 8, SHARED>;
+        default: return forest_deep_kernel<1, DEEP_VECTOR, 16, SHARED>;
+    }
+}
+
+KernelFn pick(int groups, int mode, int width, bool shared)
+{
+    return shared ? pick_mode<true>(groups, mode, width) : pick_mode<false>(groups, mode, width);
+}
+
+// Whether two workgroups fit a CU.
+bool shares_cu(const DevModel &m, int groups)
+{
+    return deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups) <= CU_LDS_BYTES / 2;
+}
+
+// Row groups per workgroup: two rows per lane share the copies of the trees' tops and keep twice as
+// many walks in flight (300 irregular trees, 90 features, 103,069 rows: 94 us with two, 108 with one);
+// one leaves a small batch more workgroups.  The last round of workgroups counts whole.
+int choose_groups(const DevModel &m, int64_t n_rows)
+{
+    if (m.deep.groups == 1) return 1;
+    double cost[2];
+    for (int g = 1; g <= 2; ++g) {
+        const int64_t per_cu = shares_cu(m, g) ? 2 : 1;
+        const int64_t blocks = (n_rows + TILE * g - 1) / (TILE * g) * m.n_splits, round = 256 * per_cu;
+        cost[g - 1] = static_cast<double>((blocks + round - 1) / round * per_cu * g) * (g == 1 ? 1.15 : 1.0);
+    }
+    return cost[0] < cost[1] ? 1 : 2;
+}
+
+}  // namespace
+
+hipError_t init_deep_kernels(size_t lds_limit)
+{
+    for (int mode : {DEEP_COLUMN, DEEP_COLUMNS, DEEP_VECTOR, DEEP_LEAVES})
+        for (int width : {2, 4, 8, 16})
+            for (int groups : {1, 2})
+                for (bool shared : {true, false}) {
+                    const void *fn = reinterpret_cast<const void *>(pick(groups, mode, width, shared));
+                    hipFuncAttributes attr;
+                    if (hipError_t e = hipFuncGetAttributes(&attr, fn); e != hipSuccess) return e;
+                    if (attr.sharedSizeBytes != 0) return hipErrorInvalidValue;  // the kernels address LDS from 0
+                    if (hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_limit));
+                        e != hipSuccess)
+                        return e;
+                }
+    return hipSuccess;
+}
+
+hipError_t launch_deep(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
+                       int32_t *leaf_out, hipStream_t stream)
+{
+    const int groups = choose_groups(m, n_rows);
+    const bool shared = shares_cu(m, groups);
+    const int64_t n_blocks = (n_rows + TILE * groups - 1) / (TILE * groups);
+    if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<unsigned>(n_blocks), static_cast<unsigned>(m.n_splits));
+    const size_t lds = deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups);
+    const int mode = leaf_out ? DEEP_LEAVES : m.leaf_width > 1 ? DEEP_VECTOR : m.n_outputs == 1 ? DEEP_COLUMN : DEEP_COLUMNS;
+    hipLaunchKernelGGL(pick(groups, mode, deep_width(m.leaf_width), shared), grid, dim3(DEEP_WAVES * TILE), lds, stream, m, X,
+                       n_rows, scores, labels, leaf_out);
+    return hipGetLastError();
+}
+
+}  // namespace forest_impl

@@ -30,86 +30,10 @@
 
 #include "forest_device.hpp"
 #include "forest_kernel_common.hpp"
+#include "forest_walk_common.hpp"
 
 namespace forest_impl {
 namespace {
-
-typedef uint32_t Vec4 __attribute__((ext_vector_type(4)));
-typedef uint32_t Vec2 __attribute__((ext_vector_type(2)));
-
-// LDS by byte address: the kernels have no static LDS, so the dynamic part begins at 0 (checked at
-// start-up) and addresses are plain integers with the level's offset as an immediate.
-template <typename T>
-__device__ __forceinline__ T lds_read(uint32_t at)
-{
-    return *reinterpret_cast<const __attribute__((address_space(3))) T *>(at);
-}
-template <typename T>
-__device__ __forceinline__ void lds_write(uint32_t at, T v)
-{
-    *reinterpret_cast<__attribute__((address_space(3))) T *>(at) = v;
-}
-
-#if defined(__HIP_DEVICE_COMPILE__)
-typedef const __attribute__((address_space(4))) uint32_t *WalkTop;
-typedef const __attribute__((address_space(4))) int32_t *WalkTable;
-typedef const __attribute__((address_space(1))) char *GlobalBytes;
-typedef const __attribute__((address_space(1))) float *GlobalFloats;
-typedef const __attribute__((address_space(1))) int32_t *GlobalInts;
-#else
-typedef const uint32_t *WalkTop;  // host pass: the kernel body is only parsed
-typedef const int32_t *WalkTable;
-typedef const char *GlobalBytes;
-typedef const float *GlobalFloats;
-typedef const int32_t *GlobalInts;
-#endif
-
-struct __attribute__((aligned(4))) Float4 {
-    float v[4];
-};
-struct __attribute__((aligned(4))) Int4 {
-    int32_t v[4];
-};
-
-// X rows [row0, row0 + 64 NR) to the tile [feature][stride bytes].  A wave takes 16 rows x 16
-// features at a time, four neighbouring features of a row per lane: 64-byte pieces of X, and LDS
-// writes that fall into 16 banks.  Four pieces are in flight per lane.
-template <int NR>
-__device__ __forceinline__ void walk_fill_tile(const float *__restrict__ X, int64_t row0, int64_t n_rows, int F,
-                                               uint32_t xbase, uint32_t stride, int wave, int lane)
-{
-    constexpr int PIECES = 4;
-    const int blocks = (F + 15) >> 4;      // of 16 features
-    const int tasks = blocks * (NR * 4);   // of 16 rows each
-    const int r = lane & 15, c = (lane >> 4) * 4;
-    for (int t0 = wave; t0 < tasks; t0 += WALK_WAVES * PIECES) {
-        Float4 v[PIECES];
-#pragma unroll
-        for (int u = 0; u < PIECES; ++u) {
-            const int t = t0 + u * WALK_WAVES;
-            if (t >= tasks) continue;
-            const int rb = t / blocks, f = (t - rb * blocks) * 16 + c;
-            const int64_t row = row0 + rb * 16 + r;
-            const float *p = X + (row < n_rows ? row : row0) * F + f;
-            if (f + 4 <= F) {
-                v[u] = *reinterpret_cast<const Float4 *>(p);
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[u].v[i] = f + i < F ? p[i] : 0.0f;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < PIECES; ++u) {
-            const int t = t0 + u * WALK_WAVES;
-            if (t >= tasks) continue;
-            const int rb = t / blocks, f = (t - rb * blocks) * 16 + c;
-            const uint32_t at = xbase + static_cast<uint32_t>(f) * stride + static_cast<uint32_t>(rb * 16 + r) * 4;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (f + i < F) lds_write<float>(at + i * stride, fminf(v[u].v[i], __builtin_inff()));  // NaN: +Inf
-        }
-    }
-}
 
 // One tree, all row groups: idx[r] = LDS address of the tree | 8 * (index of the leaf reached).
 template <int D, int NR>
@@ -193,7 +117,7 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
         for (int i = 0; i < PIECES; ++i) ahead[i] = *reinterpret_cast<const Vec4 *>(image + at + i * 1024);
     };
     if (s_begin < s_end) fetch(s_begin);
-    walk_fill_tile<NR>(X, row0, n_rows, m.n_features, xbase, stride, wave, lane);
+    tile_fill<NR, NR == 4 ? 8 : 4, true>(X, row0, n_rows, m.n_features, xbase, 256, stride, wave, lane);
     __syncthreads();
 
     const uint32_t xa = xbase + lane * 4;

@@ -287,6 +287,40 @@ inline size_t walk_lds_bytes(int depth, int n_features, int n_outputs, int group
     return walk > sums ? walk : sums;
 }
 
+// Deep walk kernels (forest_kernels_deep.hip): trees of any shape and depth, scalar or vector leaves,
+// that the walk program above does not take.  A tree's top DEEP_TOP levels are laid out as the walk
+// program's are (a full tree, 128 slots, x_offset being 256 * feature), and the path that leaves it at
+// leaf slot i goes on at the tree's unit i; the first 128 units stand behind the nodes a second time.  A unit is 8 bytes.  An internal node is {threshold, w} with w = DEEP_NODE | feature << 14 |
+// distance, the distance from the node to its left child in units; the right child follows the left one.
+// Read as a float w is a NaN, and that is what tells a node from a leaf.  A leaf is {value, 0}
+// (leaves of width 1), {value 0, value 1} (width 2), or {index of its row in deep_value, 0}.  A
+// subtree below the top is contiguous but for its root, in level order.  Slot 0 of the top has no node:
+// it holds the index of the tree's first unit and its output column.
+constexpr int DEEP_TOP = 7;
+constexpr int DEEP_WAVES = 16;             // wavefronts per workgroup
+constexpr int DEEP_MAX_FEATURES = 512;     // 9 bits of w
+constexpr int DEEP_MAX_DISTANCE = 0x3fff;  // 14 bits of w
+constexpr int DEEP_MAX_WIDTH = 16;         // leaf width
+constexpr uint32_t DEEP_NODE = 0x7f800000u;
+constexpr int DEEP_TOP_WORDS = 2 << DEEP_TOP;  // 8-byte words of a tree's top: nodes and first units
+constexpr size_t DEEP_STAGE_BYTES = sizeof(WalkNode) * DEEP_TOP_WORDS;  // per wave
+
+// Values a leaf holds in the kernels: the leaf width, rounded up.
+constexpr int deep_width(int leaf_width) { return leaf_width <= 2 ? leaf_width : leaf_width <= 4 ? 4 : leaf_width <= 8 ? 8 : 16; }
+
+// Row groups of 64 rows per workgroup: the sums of wide leaves take the registers of a second group.
+constexpr int deep_max_groups(int leaf_width) { return leaf_width > 2 ? 1 : 2; }
+
+// LDS of a workgroup that owns `groups` x 64 rows: the X tile and a stage per wave, or the sums,
+// which reuse the space at the end.
+inline size_t deep_lds_bytes(int n_features, int n_outputs, int leaf_width, int groups)
+{
+    const size_t walk = DEEP_WAVES * DEEP_STAGE_BYTES + static_cast<size_t>(n_features) * groups * 256;
+    const size_t slots = leaf_width > 1 ? static_cast<size_t>(DEEP_WAVES) * n_outputs : static_cast<size_t>(DEEP_WAVES) + 2 * n_outputs - 1;
+    const size_t sums = sizeof(double) * 64 * groups * slots + 2 * sizeof(int32_t) * DEEP_WAVES;
+    return walk > sums ? walk : sums;
+}
+
 struct PackedModel {
     int32_t n_trees = 0, n_features = 0, n_outputs = 0, leaf_width = 1;
     int32_t aggregate = 0, transform = 0, output = 0;
@@ -346,6 +380,14 @@ struct PackedModel {
     std::vector<float> walk_leaf;          // [stages * stage trees][2^depth]
     std::vector<int32_t> walk_leaf_node;   // same index: the caller's node index of the leaf
     std::vector<int32_t> walk_position;    // [n_trees + stage trees] where a caller's tree sits
+
+    // deep walk program (deep_groups 0: the model has none)
+    int32_t deep_groups = 0;               // row groups of 64 rows per workgroup, at most
+    std::vector<WalkNode> deep_top;        // [n_trees][DEEP_TOP_WORDS], processing order
+    std::vector<WalkNode> deep_unit;       // {threshold or value, w}
+    std::vector<int32_t> deep_unit_node;   // same index: the caller's node index
+    std::vector<float> deep_value;         // [leaves][deep_width] of leaves wider than 2
+    std::vector<int32_t> deep_position;    // [n_trees] where a caller's tree sits in processing order
 
     // caller-order views used only by forest_pack_view
     std::vector<int32_t> v_n_internal, v_depth, v_is_full, v_program_groups, v_order_leaf_tree;

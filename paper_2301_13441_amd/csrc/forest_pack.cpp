@@ -265,6 +265,115 @@ static void build_walk(const forest_desc &d, const std::vector<TreeShape> &shape
     }
 }
 
+// The deep walk program (forest_model.hpp).  `order`: the trees in processing order.
+static void build_deep(const forest_desc &d, const std::vector<TreeShape> &shape, const std::vector<int32_t> &order,
+                       PackedModel &m)
+{
+    const int32_t T = d.n_trees, W = d.leaf_width, K = d.n_outputs;
+    if (T < 1 || m.walk_depth > 0 || d.n_features > DEEP_MAX_FEATURES || W > DEEP_MAX_WIDTH) return;
+    // As many rows per workgroup as leave room for two workgroups on a CU, or else for one.
+    int groups = 0;
+    for (const size_t budget : {CU_LDS_BYTES / 2, CU_LDS_BYTES})
+        for (int g = deep_max_groups(W); g >= 1 && groups == 0; g /= 2)
+            if (deep_lds_bytes(d.n_features, K, W, g) <= budget) groups = g;
+    if (groups == 0) return;
+    auto column_of = [&](int32_t t) { return (W == 1 && d.tree_output) ? d.tree_output[t] : 0; };
+    // A wave keeps the finished sums of its run's columns in registers.
+    for (int w = 0; w < DEEP_WAVES; ++w) {
+        const int64_t t0 = static_cast<int64_t>(T) * w / DEEP_WAVES, t1 = static_cast<int64_t>(T) * (w + 1) / DEEP_WAVES;
+        int columns = 0;
+        for (int64_t i = t0; i < t1; ++i) columns += i == t0 || column_of(order[i]) != column_of(order[i - 1]);
+        if (columns > WALK_MAX_COLUMNS) return;
+    }
+    PackedModel p;  // only the deep program's members, moved to m at the end
+    const int WP = deep_width(W);
+    p.deep_position.assign(static_cast<size_t>(T), 0);
+    std::vector<int32_t> level(1 << DEEP_TOP), below(1 << DEEP_TOP), block;
+    for (int32_t i = 0; i < T; ++i) {
+        const int32_t t = order[i];
+        const int64_t base = d.tree_offset[t];
+        const size_t unit_base = p.deep_unit.size();
+        if (unit_base + 2 * shape[t].ordinal.size() + (1 << DEEP_TOP) > FOREST_MAX_NODES) return;
+        p.deep_position[t] = i;
+        const size_t top = p.deep_top.size();
+        p.deep_top.resize(top + DEEP_TOP_WORDS, WalkNode{0.0f, 0});
+        const int32_t head[2] = {static_cast<int32_t>(unit_base), column_of(t)};
+        std::memcpy(&p.deep_top[top].threshold, &head[0], sizeof(head[0]));
+        std::memcpy(&p.deep_top[top].x_offset, &head[1], sizeof(head[1]));
+        level[0] = 0;
+        for (int l = 0; l < DEEP_TOP; ++l) {
+            const int32_t n = 1 << l;
+            for (int32_t k = 0; k < n; ++k) {
+                const int32_t v = level[k];
+                if (d.feature[base + v] < 0) {  // a leaf: both sides lead to it
+                    below[k] = below[k + n] = v;
+                    continue;
+                }
+                p.deep_top[top + n + k] = WalkNode{d.threshold[base + v], static_cast<uint32_t>(d.feature[base + v]) * 256};
+                below[k] = d.left[base + v];
+                below[k + n] = d.right[base + v];
+            }
+            level.swap(below);
+        }
+        // The units: the 128 where the top's paths go on (a leaf above the top's end fills several),
+        // then one subtree after the other.
+        auto push_unit = [&](int32_t v, size_t children) {  // a node's left child will be unit `children`
+            WalkNode u{0.0f, 0};
+            const float *value = d.leaf_value + (base + v) * W;
+            if (d.feature[base + v] >= 0) {
+                const size_t distance = children - p.deep_unit.size();
+                if (distance > static_cast<size_t>(DEEP_MAX_DISTANCE)) return false;
+                u = WalkNode{d.threshold[base + v],
+                             DEEP_NODE | static_cast<uint32_t>(d.feature[base + v]) << 14 | static_cast<uint32_t>(distance)};
+            } else if (W <= 2) {
+                u.threshold = value[0];
+                if (W == 2) {
+                    std::memcpy(&u.x_offset, &value[1], sizeof(float));
+                    if (std::isnan(value[1])) return false;  // reads as a node
+                }
+            } else {
+                const int32_t row = static_cast<int32_t>(p.deep_value.size() / WP);
+                std::memcpy(&u.threshold, &row, sizeof(row));
+                p.deep_value.insert(p.deep_value.end(), value, value + W);
+                p.deep_value.resize(p.deep_value.size() + (WP - W), 0.0f);
+            }
+            p.deep_unit.push_back(u);
+            p.deep_unit_node.push_back(v);
+            return true;
+        };
+        size_t next = unit_base + (1 << DEEP_TOP);  // where the next subtree goes
+        for (int32_t k = 0; k < 1 << DEEP_TOP; ++k) {
+            if (!push_unit(level[k], next)) return;
+            if (d.feature[base + level[k]] < 0) continue;
+            block.assign(1, level[k]);
+            for (size_t b = 0; b < block.size(); ++b)
+                if (d.feature[base + block[b]] >= 0) {
+                    block.push_back(d.left[base + block[b]]);
+                    block.push_back(d.right[base + block[b]]);
+                }
+            next += block.size() - 1;
+        }
+        std::copy(p.deep_unit.begin() + unit_base, p.deep_unit.end(), p.deep_top.begin() + top + (1 << DEEP_TOP));
+        for (int32_t k = 0; k < 1 << DEEP_TOP; ++k) {
+            if (d.feature[base + level[k]] < 0) continue;
+            const size_t first = p.deep_unit.size();
+            block.assign({d.left[base + level[k]], d.right[base + level[k]]});
+            for (size_t b = 0; b < block.size(); ++b) {
+                if (!push_unit(block[b], first + block.size())) return;
+                if (d.feature[base + block[b]] < 0) continue;
+                block.push_back(d.left[base + block[b]]);
+                block.push_back(d.right[base + block[b]]);
+            }
+        }
+    }
+    m.deep_groups = groups;
+    m.deep_top = std::move(p.deep_top);
+    m.deep_unit = std::move(p.deep_unit);
+    m.deep_unit_node = std::move(p.deep_unit_node);
+    m.deep_value = std::move(p.deep_value);
+    m.deep_position = std::move(p.deep_position);
+}
+
 int compile_forest(const forest_desc &d, PackedModel &m)
 {
     if (int rc = check_desc(d)) return rc;
@@ -600,6 +709,7 @@ int compile_forest(const forest_desc &d, PackedModel &m)
         m.tree.push_back(tm);
     }
     build_walk(d, shape, order, m);
+    build_deep(d, shape, order, m);
     if (m.path == PATH_RANK_LDS) balance_waves(m);
     if (m.path == PATH_RANK_LDS && m.kind == KIND_GENERIC && m.rank_regs >= 1 &&
         m.rank_regs <= BANK_WAVES * BANK_REGS && ((K == 1 && W == 1) || (W == K && K <= 2))) {

@@ -1,0 +1,95 @@
+"""The deep walk kernels and their packed form: trees of any shape and depth, the top levels laid out
+as a full tree and the rest as units.  Leaf ids and labels are exact; scores are fp64 sums rounded once
+on both sides, at most one float32 rounding (6e-8) apart, well inside the bar used here."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from test_gpu_parity import _check
+from test_walk import _special_rows
+
+
+def _forest(seed, trees, depth, features, outputs=1, width=1, stop=0.2):
+    f = wl.random_forest(seed, n_trees=trees, n_features=features, max_depth=depth, stop_prob=stop, n_outputs=outputs,
+                         leaf_width=width, transform=wl.TRANSFORM_SOFTMAX if outputs > 1 else wl.TRANSFORM_SIGMOID)
+    if width == 1:
+        f = wl.Forest(**{**f.__dict__, "tree_output": (np.arange(trees) % outputs).astype(np.int32)})
+    inner = np.flatnonzero(f.feature >= 0)
+    f.threshold[inner[::7]] = np.float32(-0.0)
+    f.threshold[inner[3::29]] = np.float32(np.inf)
+    f.threshold[inner[5::31]] = np.float32(-np.inf)
+    return f
+
+
+@pytest.mark.parametrize("depth,outputs,width", [(9, 1, 1), (12, 3, 1), (13, 2, 2), (10, 5, 5), (3, 2, 2), (0, 3, 3)])
+def test_deep_layout_reaches_the_oracles_leaves(depth, outputs, width):
+    import paper_2301_13441_amd as pk
+    rng = np.random.default_rng(depth)
+    f = _forest(70 + depth, 9, depth, 6, outputs, width)
+    v = pk.forest_pack(f)
+    T = f.n_trees
+    assert v["deep_groups"] > 0
+    X = _special_rows(rng.standard_normal((120, 6)).astype(np.float32), f, rng)
+    ref = oracle.predict(f, X, want_leaves=True).leaf_node_id
+    lane = np.arange(len(X))
+    units = v["deep_unit"]
+    assert sorted(v["deep_position"]) == list(range(T))
+    for caller in range(T):
+        i = int(v["deep_position"][caller])
+        base, column = (int(a) for a in v["deep_top"][i, 0])
+        assert column == (f.tree_output[caller] if width == 1 else 0)
+        thr, feat = v["deep_top"][i, :, 0].copy().view(np.float32), v["deep_top"][i, :, 1] // 256
+        at = np.zeros(len(X), np.int64)
+        for l in range(7):
+            h = (1 << l) + at
+            at |= (~(X[lane, feat[h]] <= thr[h])).astype(np.int64) << l
+        np.testing.assert_array_equal(v["deep_top"][i, 128:], units[base:base + 128])
+        at = base + at
+        for _ in range(max(0, depth - 7)):
+            w = units[at, 1]
+            node = np.isnan(w.copy().view(np.float32))
+            right = ~(X[lane, np.where(node, (w >> 14) & 511, 0)] <= units[at, 0].copy().view(np.float32))
+            at = np.where(node, at + (w & 0x3fff) + right, at)
+        assert not np.isnan(units[at, 1].copy().view(np.float32)).any()
+        np.testing.assert_array_equal(v["deep_unit_node"][at], ref[:, caller])
+        value = f.leaf_value[f.tree_offset[caller] + ref[:, caller]]
+        if width <= 2:
+            got = units[at, :width].copy().view(np.float32)
+        else:
+            got = v["deep_value"][units[at, 0], :width]
+        np.testing.assert_array_equal(got, value)
+
+
+def test_deep_takes_what_it_is_built_for():
+    import paper_2301_13441_amd as pk
+    assert pk.forest_pack(_forest(1, 20, 9, 96))["deep_groups"] == 2                    # two workgroups on a CU
+    assert pk.forest_pack(_forest(1, 20, 9, 192))["deep_groups"] == 1                   # two workgroups on a CU
+    assert pk.forest_pack(_forest(1, 20, 9, 256))["deep_groups"] == 2                   # one
+    assert pk.forest_pack(_forest(1, 20, 9, 500))["deep_groups"] == 1
+    assert pk.forest_pack(_forest(1, 20, 9, 513))["deep_groups"] == 0                   # 9 bits of feature
+    assert pk.forest_pack(_forest(1, 20, 9, 9, 16, 16))["deep_groups"] == 1
+    assert pk.forest_pack(_forest(1, 20, 9, 9, 17, 17))["deep_groups"] == 0
+    f = wl.random_forest(3, 9, 5, 8, stop_prob=0.0)
+    assert pk.forest_pack(f)["deep_groups"] == 0 and pk.forest_pack(f)["walk_depth"] == 8
+    f = _forest(1, 20, 9, 9, 2, 2)
+    f.leaf_value[np.flatnonzero(f.feature < 0)[0], 1] = np.nan                          # would read as a node
+    assert pk.forest_pack(f)["deep_groups"] == 0
+    f = _forest(1, 100, 9, 9, 8)
+    f.tree_output[:] = np.sort(np.concatenate([np.arange(7), np.full(93, 7)])).astype(np.int32)
+    assert pk.forest_pack(f)["deep_groups"] == 0                                        # 7 columns in one wave's run
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("features", [3, 16, 61, 130, 256, 300])
+@pytest.mark.parametrize("depth,outputs,width", [(9, 1, 1), (11, 4, 1), (12, 2, 2), (10, 3, 3), (9, 8, 8), (5, 10, 10)])
+def test_deep_kernels(features, depth, outputs, width):
+    """One and two row groups; every kind of sum; few trees (waves without any) and more trees than
+    waves; leaf ids of a tree count that is no multiple of four."""
+    import paper_2301_13441_amd as pk
+    rng = np.random.default_rng(100 * depth + features)
+    for trees, rows in ((5, 517), (37, 65536 + 77)):
+        f = _forest(9 * depth + features, trees, depth, features, outputs, width, stop=0.3)
+        assert pk.forest_pack(f)["deep_groups"] > 0
+        X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
+        _check(f, X, leaves=True)
