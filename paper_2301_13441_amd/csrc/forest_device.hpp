@@ -94,6 +94,10 @@ constexpr int64_t SPLIT_BELOW_BLOCKS = 512;
 // at least this many program entries together.
 constexpr int64_t SPLIT_TARGET_BLOCKS = 1024;
 constexpr int64_t SPLIT_MIN_ENTRIES_PER_WAVE = 512;
+// Walk kernels: workgroups of 16 waves, two per CU, and the copies of trees to LDS that a split launch
+// leaves a wave at least.
+constexpr int64_t WALK_RESIDENT = 512;
+constexpr int64_t WALK_SPLIT_MIN_COPIES = 2;
 // Rows one workgroup of the model's kernel family owns, and its number of wavefronts.
 int family_rows_per_block(const DevModel &m);
 int family_waves_per_block(const DevModel &m);

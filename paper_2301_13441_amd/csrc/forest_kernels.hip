@@ -334,15 +334,35 @@ int choose_splits(const DevModel &m, const Workspace *ws, int64_t n_rows, bool n
     return static_cast<int>(s);
 }
 
+// The same for the models of the walk kernels, whose workgroups own 64 rows or more: as many shares
+// as fill the chip's workgroups once, each of its waves left two copies of trees to LDS or more.
+// (Against the dense kernels' shares with their rank tiles: 10,007 rows of 250 trees of depth 8, 64 features:
+// 63.6 -> 21.5 us a call; 1,021 rows of 2000 x depth 6, 128 features: 39.3 -> 22.4.  Half as many shares: 18.5
+// and 20.9 with a costly reduction, the same as now since it is cheap; at least 1 or 4 copies: no difference.)
+int choose_walk_splits(const DevModel &m, const Workspace *ws, int64_t n_rows, bool needs_sums)
+{
+    const int64_t n_blocks = (n_rows + TILE - 1) / TILE;
+    const int64_t copies = m.walk.depth > 0 ? m.walk.stages : m.n_trees;
+    // leaf ids are dealt four trees at a time
+    const int64_t waves = needs_sums ? copies / WALK_SPLIT_MIN_COPIES : (m.n_trees + 3) / 4;
+    int64_t s = WALK_RESIDENT / n_blocks;
+    if (waves / WALK_WAVES < s) s = waves / WALK_WAVES;
+    if (needs_sums && s > 1) {
+        const int64_t by_ws = (ws ? ws->partial_doubles : 0) / (n_rows * m.n_outputs);
+        if (by_ws < s) s = by_ws;
+    }
+    return s < 2 ? 1 : static_cast<int>(s);
+}
+
 }  // namespace
 
 static hipError_t launch_family(const DevModel &m, const float *X, int64_t n_rows, float *scores,
                                 int32_t *labels, int32_t *leaf_out, hipStream_t stream)
 {
-    if (m.n_splits == 1 && m.walk.depth > 0) return launch_walk(m, X, n_rows, scores, labels, leaf_out, stream);
+    if (m.walk.depth > 0) return launch_walk(m, X, n_rows, scores, labels, leaf_out, stream);
     // trees deeper than 8, vector leaves, infinite thresholds: what a row does not meet is not tested
     // (128 trees of depth 12: 2.9 ms against 14.5 with the register-bank kernel)
-    if (m.n_splits == 1 && m.deep.groups > 0) return launch_deep(m, X, n_rows, scores, labels, leaf_out, stream);
+    if (m.deep.groups > 0) return launch_deep(m, X, n_rows, scores, labels, leaf_out, stream);
     if (m.path == PATH_RANK) return launch_rank(m, X, n_rows, scores, labels, leaf_out, stream);
     if (m.path == PATH_RANK_LDS) {
         // large batches of the models it fits: rank registers banked over the waves' vector registers
@@ -374,11 +394,15 @@ hipError_t launch_predict(const DevModel &model, const Workspace *ws, bool must_
     bool fits = true;
     m.n_splits = choose_splits(m, ws, n_rows, sums, fits);
     if (!fits && must_fit) return hipErrorMemoryAllocation;
+    // A batch the dense kernels' workspace does not hold is refused above whichever kernel runs it: what
+    // forest_predict_static takes does not depend on the kernel.
+    const bool walk = m.walk.depth > 0 || m.deep.groups > 0;
+    if (walk) m.n_splits = choose_walk_splits(m, ws, n_rows, sums);
     m.split_rows = n_rows;
     m.partial = ws ? ws->partial : nullptr;
     m.partial_capacity = ws ? ws->partial_doubles : 0;
     m.rank_tiles = ws ? ws->rank_tiles : nullptr;
-    if (m.n_splits > 1 && (m.path == PATH_RANK || m.path == PATH_RANK_LDS)) {
+    if (m.n_splits > 1 && !walk && (m.path == PATH_RANK || m.path == PATH_RANK_LDS)) {
         const hipError_t e = launch_rank_tiles(m, X, n_rows, stream);
         if (e != hipSuccess) return e;
     }

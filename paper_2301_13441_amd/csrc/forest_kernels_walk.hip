@@ -289,9 +289,6 @@ KernelFn pick(int depth, int groups, int mode)
     return pick_depth<WALK_LEAVES>(depth, groups);
 }
 
-// Workgroups the chip holds at a time: two per CU.
-constexpr int64_t RESIDENT = 512;
-
 // Row groups per workgroup.  More rows per workgroup amortise the copies of the trees to LDS (per
 // 64 rows, depth 6: 1, 1.07 and 1.25 of the time with 4, 2 and 1 groups), fewer leave smaller
 // batches enough workgroups; the last round of workgroups counts whole.
@@ -301,7 +298,7 @@ int choose_groups(const DevModel &m, int64_t n_rows)
     double best_cost = 0.0;
     for (int g = m.walk.groups; g >= 1; g /= 2) {
         const int64_t blocks = (n_rows + TILE * g - 1) / (TILE * g) * m.n_splits;
-        const double cost = static_cast<double>((blocks + RESIDENT - 1) / RESIDENT) * g * (g == 4 ? 1.0 : g == 2 ? 1.07 : 1.25);
+        const double cost = static_cast<double>((blocks + WALK_RESIDENT - 1) / WALK_RESIDENT) * g * (g == 4 ? 1.0 : g == 2 ? 1.07 : 1.25);
         if (g == m.walk.groups || cost < best_cost) {
             best = g;
             best_cost = cost;
