@@ -30,32 +30,90 @@ __global__ __launch_bounds__(RROWS) void forest_rank_tiles_kernel(DevModel m, co
     store_rank(tile16, m, f, r, rank_of(m, f, x));
 }
 
-constexpr int RS_ROWS = 8;     // rows per workgroup of the reduction
-constexpr int RS_LANES = 16;   // lanes that share one (row, column) sum
-
-// 16 lanes per (row, column): lane g adds the shares g, g + 16, ... in ascending order, a
-// butterfly adds the 16 partial results, then one thread per row finishes the row exactly as
-// an unsplit launch does.  The order of the additions is fixed, so results are reproducible.
-__global__ __launch_bounds__(256) void forest_reduce_splits_kernel(DevModel m, int64_t n_rows, float *scores,
-                                                                   int32_t *labels)
+// finish_values for `rows` rows from row0 with all threads of the workgroup: thread by (row, column), and by row
+// where the columns meet (label, softmax).  raw[li * row_step + k * column_step] are the summed leaf values
+// of row row0 + li, overwritten; by_row: `rows` doubles of LDS.  Every thread of the workgroup calls it,
+// behind a barrier after the sums.  A reduction has few rows per workgroup: with a thread per row the
+// exponentials of a softmax over 10 columns come one after the other.  (1,021 rows, 10 columns, 31 shares:
+// 9.6 us with a thread per row, 16 threads per sum and 8 rows per workgroup, 4.8 so; 10,007 rows, 5 columns,
+// 3 shares: 7.8 and 4.4.  In the walk kernels, whose other waves have their own trees to walk, finishing
+// rows this way was 2 to 4 % slower than a thread per row.)
+__device__ __forceinline__ void finish_rows(const DevModel &m, double *raw, int row_step, int column_step, int rows, double *by_row,
+                                            int64_t row0, int64_t n_rows, float *scores, int32_t *labels)
 {
-    __shared__ double raw[RS_ROWS * FOREST_MAX_OUTPUTS];
-    const int K = m.n_outputs;
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * RS_ROWS;
-    const int g = threadIdx.x & (RS_LANES - 1);
-    for (int pair = threadIdx.x / RS_LANES; pair < RS_ROWS * K; pair += 256 / RS_LANES) {
-        const int rl = pair / K, k = pair - rl * K;
-        const int64_t row = row0 + rl;
-        double s = 0.0;
-        if (row < n_rows)
-            for (int sp = g; sp < m.n_splits; sp += RS_LANES) s += m.partial[(sp * m.split_rows + row) * K + k];
-#pragma unroll
-        for (int d = RS_LANES / 2; d >= 1; d >>= 1) s += __shfl_xor(s, d, RS_LANES);
-        if (g == 0) raw[rl * K + k] = s;
+    const int K = m.n_outputs, threads = static_cast<int>(blockDim.x), pairs = rows * K;
+    const bool softmax = scores && m.transform == FOREST_TRANSFORM_SOFTMAX;
+    for (int p = threadIdx.x; p < pairs; p += threads) {
+        const int li = p / K, k = p - li * K;
+        double *at = raw + li * row_step + k * column_step;
+        double s = *at;
+        // a column no tree feeds: the mean over no trees adds nothing to the base score
+        if (m.aggregate == FOREST_AGG_MEAN && m.col_trees[k] > 0.0) s = s / m.col_trees[k];
+        s = static_cast<double>(m.base[k]) + s;
+        if (softmax || labels) *at = s;
+        if (scores && !softmax && row0 + li < n_rows)
+            scores[row0 * K + p] = static_cast<float>(m.transform == FOREST_TRANSFORM_SIGMOID ? 1.0 / (1.0 + exp(-s)) : s);
+    }
+    if (!softmax && !labels) return;  // uniform
+    __syncthreads();
+    for (int li = threadIdx.x; li < rows; li += threads) {
+        const double *at = raw + li * row_step;
+        double best = at[0];
+        int lab = 0;
+        for (int k = 1; k < K; ++k)
+            if (const double s = at[k * column_step]; s > best) {
+                best = s;
+                lab = k;
+            }
+        by_row[li] = best;
+        if (K == 1) lab = (m.transform == FOREST_TRANSFORM_SIGMOID) ? (best > 0.0) : (best > 0.5);
+        if (labels && row0 + li < n_rows) labels[row0 + li] = lab;
+    }
+    if (!softmax) return;
+    __syncthreads();
+    for (int p = threadIdx.x; p < pairs; p += threads) {
+        const int li = p / K, k = p - li * K;
+        double *at = raw + li * row_step + k * column_step;
+        *at = exp(*at - by_row[li]);
     }
     __syncthreads();
-    const int64_t row = row0 + threadIdx.x;
-    if (threadIdx.x < RS_ROWS && row < n_rows) finish_values(m, raw + threadIdx.x * K, 1, row, scores, labels);
+    for (int li = threadIdx.x; li < rows; li += threads) {
+        double z = 0.0;
+        for (int k = 0; k < K; ++k) z += raw[li * row_step + k * column_step];
+        by_row[li] = z;
+    }
+    __syncthreads();
+    for (int p = threadIdx.x; p < pairs; p += threads) {
+        const int li = p / K, k = p - li * K;
+        if (row0 + li < n_rows) scores[row0 * K + p] = static_cast<float>(raw[li * row_step + k * column_step] / by_row[li]);
+    }
+}
+
+constexpr int RS_THREADS = 256;
+constexpr int RS_MAX_ROWS = 64;  // rows per workgroup of the reduction
+
+// `lanes` threads share the sum of a (row, column): thread g adds the shares g, g + lanes, ... in ascending
+// order, one thread adds the results of the lanes in theirs, and the workgroup finishes its rows exactly
+// as an unsplit launch does.  The order of the additions is fixed, so results are reproducible.  The sums
+// of a share lie in row order, so neighbouring threads read neighbouring sums.
+__global__ __launch_bounds__(RS_THREADS) void forest_reduce_splits_kernel(DevModel m, int64_t n_rows, float *scores,
+                                                                          int32_t *labels, int rows, int lanes)
+{
+    __shared__ double part[RS_THREADS], by_row[RS_MAX_ROWS];
+    const int K = m.n_outputs, pairs = rows * K;  // lanes * pairs <= RS_THREADS
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * rows;
+    const int g = static_cast<int>(threadIdx.x) / pairs, p = static_cast<int>(threadIdx.x) - g * pairs;
+    if (g < lanes) {
+        double s = 0.0;
+        if (row0 * K + p < n_rows * K)
+            for (int sp = g; sp < m.n_splits; sp += lanes) s += m.partial[(sp * m.split_rows + row0) * K + p];
+        part[threadIdx.x] = s;
+    }
+    __syncthreads();
+    if (g == 0)
+        for (int i = 1; i < lanes; ++i) part[p] += part[i * pairs + p];
+    __syncthreads();
+    finish_rows(m, part, K, 1, rows, by_row, row0, n_rows, scores, labels);
 }
 
 }  // namespace
@@ -73,9 +131,14 @@ hipError_t launch_rank_tiles(const DevModel &m, const float *X, int64_t n_rows, 
 hipError_t launch_reduce_splits(const DevModel &m, int64_t n_rows, float *scores, int32_t *labels,
                                 hipStream_t stream)
 {
-    const int64_t n_blocks = (n_rows + RS_ROWS - 1) / RS_ROWS;
-    hipLaunchKernelGGL(forest_reduce_splits_kernel, dim3(static_cast<unsigned>(n_blocks)), dim3(256), 0, stream, m,
-                       n_rows, scores, labels);
+    // a thread per sum and four shares, and as many rows as that leaves threads for
+    int lanes = 1;
+    while (lanes * 4 < m.n_splits && lanes < 16 && 2 * lanes * m.n_outputs <= RS_THREADS) lanes *= 2;
+    int rows = RS_THREADS / (lanes * m.n_outputs);
+    if (rows > RS_MAX_ROWS) rows = RS_MAX_ROWS;
+    const int64_t n_blocks = (n_rows + rows - 1) / rows;
+    hipLaunchKernelGGL(forest_reduce_splits_kernel, dim3(static_cast<unsigned>(n_blocks)), dim3(RS_THREADS), 0, stream, m,
+                       n_rows, scores, labels, rows, lanes);
     return hipGetLastError();
 }
 
