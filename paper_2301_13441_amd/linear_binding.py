@@ -6,7 +6,7 @@ import ctypes
 
 import numpy as np
 
-from .binding import load_library
+from .binding import _SHORT_ROWS, _short_predict, load_library
 
 _p = ctypes.c_void_p
 _i32, _i64 = ctypes.c_int32, ctypes.c_int64
@@ -87,6 +87,7 @@ class Linear:
         self._h = handle
         self.n_features = n_features
         self.n_outputs = n_outputs
+        self._parts = tuple(offset >= 0 for offset in self.out_layout(1))  # scores, labels
 
     def close(self):
         if self._h is not None:
@@ -123,6 +124,9 @@ class Linear:
         import torch
         _check_x(X, self.n_features)
         n = X.shape[0]
+        if out is None and stream is None and 0 < n < _SHORT_ROWS:
+            return _short_predict(self._h, _lib().linear_predict, LinearError, "linear_predict", X, self.n_outputs, n,
+                                  *self._parts)
         nbytes = self.out_bytes(n)
         if out is None:
             out = torch.empty(max(nbytes, 4), dtype=torch.uint8, device=X.device)

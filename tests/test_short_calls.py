@@ -1,0 +1,38 @@
+"""predict() with a buffer of its own against predict() into the caller's: same views, same bits."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from workloads.linear import LinearModel
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("outputs", [1, 3])
+@pytest.mark.parametrize("kind", [wl.OUT_SCORES, wl.OUT_LABELS, wl.OUT_BOTH])
+@pytest.mark.parametrize("family", ["forest", "linear"])
+def test_own_buffer_and_the_callers(family, kind, outputs):
+    import torch
+    import paper_2301_13441_amd as pk
+    rng = np.random.default_rng(5)
+    if family == "forest":
+        model = pk.forest_load(wl.random_forest(4, 30, 9, 6, n_outputs=outputs, output=kind))
+    else:
+        model = pk.linear_load(LinearModel(9, outputs, rng.standard_normal((9, outputs)).astype(np.float32),
+                                           np.zeros(outputs, np.float32), wl.TRANSFORM_NONE, kind))
+    for rows in (0, 1, 77):
+        X = torch.from_numpy(rng.standard_normal((rows, 9)).astype(np.float32)).cuda()
+        side = torch.cuda.Stream()
+        with torch.cuda.stream(side):
+            own = model.predict(X)
+            callers = model.predict(X, out=torch.empty(max(model.out_bytes(rows), 4), dtype=torch.uint8, device="cuda"))
+        side.synchronize()
+        for a, b, shape, dtype in zip(own, callers, ((rows, outputs), (rows,)), (torch.float32, torch.int32)):
+            assert (a is None) == (b is None)
+            if a is not None:
+                assert a.shape == b.shape == shape and a.dtype == b.dtype == dtype and a.is_contiguous()
+                assert torch.equal(a, b)
+    assert (own[0] is None) == (kind == wl.OUT_LABELS) and (own[1] is None) == (kind == wl.OUT_SCORES)
+    with pytest.raises(ValueError):
+        model.predict(X.double())
+    model.close()
