@@ -1,4 +1,5 @@
-"""predict() with a buffer of its own against predict() into the caller's: same views, same bits."""
+"""predict() with a buffer of its own against predict() into the caller's: same views, same bits; and linear
+models with several outputs, whose scores leave a wave as one piece."""
 import numpy as np
 import pytest
 
@@ -36,3 +37,24 @@ def test_own_buffer_and_the_callers(family, kind, outputs):
     with pytest.raises(ValueError):
         model.predict(X.double())
     model.close()
+
+
+@pytest.mark.parametrize("features,outputs", [(2, 12), (12, 12), (7, 3), (90, 2), (96, 32), (97, 5), (128, 10), (130, 24)])
+def test_linear_scores_of_whole_and_ragged_tiles(features, outputs):
+    import torch
+    import paper_2301_13441_amd as pk
+    from oracle.linear_oracle import predict_linear
+    rng = np.random.default_rng(features)
+    model = LinearModel(features, outputs, (rng.standard_normal((features, outputs)) / 9).astype(np.float32),
+                        rng.standard_normal(outputs).astype(np.float32), wl.TRANSFORM_SOFTMAX, wl.OUT_BOTH)
+    f = pk.linear_load(model)
+    for rows in (1, 63, 64, 65, 200, 1027):
+        X = rng.standard_normal((rows, features)).astype(np.float32)
+        out = torch.full((f.out_bytes(rows) + 64,), 0xAB, dtype=torch.uint8, device="cuda")
+        scores, labels = f.predict(torch.from_numpy(X).cuda(), out=out)
+        ref = predict_linear(model, X)
+        np.testing.assert_array_equal(labels.cpu().numpy(), ref.labels)
+        # fp64 sums rounded to fp32 once on both sides: one rounding apart at most (6e-8)
+        np.testing.assert_allclose(scores.cpu().numpy(), ref.scores, rtol=2e-7, atol=1e-30)
+        assert bool((out[f.out_bytes(rows):] == 0xAB).all())
+    f.close()
