@@ -161,6 +161,19 @@ hipError_t init_deep_kernels(size_t lds_limit);
 hipError_t launch_deep(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                        int32_t *leaf_out, hipStream_t stream);
 
+// One lane per (row, tree): the smallest batches of the walk kernels' models (forest_kernels_split.hip).
+// Up to a million tests the gathers take less than what a walk kernel's workgroups begin and end with.
+// Microseconds a call, this kernel / walk kernels with their reduction, 500 trees of depth 8: 1 row 5.2 / 10.4,
+// 64 rows 7.4 / 10.7, 256 rows 8.8 / 10.8, 1,024 rows 19.8 / 10.6; 2000 x depth 6, 10 columns: 64 rows 11.3 / 14.1,
+// 256 rows 17.7 / 14.4.  Ten trees of depth 4, which the walk kernels take in one launch: 1,000 rows 6.0 / 6.6,
+// 8,000 rows 6.2 / 6.6, 30,000 rows 10.0 / 6.9.
+constexpr int64_t POINT_MAX_TESTS = 1 << 20;  // rows x trees x depth
+constexpr int64_t POINT_MAX_ROWS = 8192;
+constexpr size_t POINT_MAX_LDS = 64 * 1024;
+bool takes_point(const DevModel &m, int64_t n_rows);
+hipError_t launch_point(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels, int32_t *leaf_out,
+                        hipStream_t stream);
+
 // Sums the partial sums of a split launch over the splits and finishes every row.
 hipError_t launch_reduce_splits(const DevModel &m, int64_t n_rows, float *scores, int32_t *labels,
                                 hipStream_t stream);

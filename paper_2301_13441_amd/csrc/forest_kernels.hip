@@ -396,6 +396,10 @@ hipError_t launch_predict(const DevModel &model, const Workspace *ws, bool must_
     if (!fits && must_fit) return hipErrorMemoryAllocation;
     // A batch the dense kernels' workspace does not hold is refused above whichever kernel runs it: what
     // forest_predict_static takes does not depend on the kernel.
+    if (takes_point(m, n_rows)) {
+        m.n_splits = 1;
+        return launch_point(m, X, n_rows, scores, labels, leaf_out, stream);
+    }
     const bool walk = m.walk.depth > 0 || m.deep.groups > 0;
     if (walk) m.n_splits = choose_walk_splits(m, ws, n_rows, sums);
     m.split_rows = n_rows;

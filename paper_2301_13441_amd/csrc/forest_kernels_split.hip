@@ -1,5 +1,5 @@
-// Kernels that only split launches (small batches) use: threshold ranks per row tile, and the
-// sum of the tree shares' partial sums.
+// Kernels that only small batches use: threshold ranks per row tile, the sum of the tree shares'
+// partial sums, and the walk with a lane per (row, tree) for the smallest.
 //
 // A batch of a few thousand rows has too few 128-row tiles to fill 256 compute units, so the
 // trees are cut into shares as well (grid y of the family kernels).  Two things are then done
@@ -116,7 +116,91 @@ __global__ __launch_bounds__(RS_THREADS) void forest_reduce_splits_kernel(DevMod
     finish_rows(m, part, K, 1, rows, by_row, row0, n_rows, scores, labels);
 }
 
+// The smallest batches of the walk kernels' models: a lane is a (row, tree) pair and walks the tree through
+// global memory, so that a few rows still fill wavefronts and a call is one launch.  A workgroup owns
+// `rows` rows, whose features it holds in LDS; the leaf values meet there, [row][tree], and a wave adds
+// those of a (row, column), whose trees are neighbours in processing order.  What bounds it is the chain of
+// dependent loads, one per level, and for more pairs the gathers: a cycle of the texture path per lane.
+constexpr int PT_THREADS = 1024, PT_MAX_ROWS = 16;
+
+template <bool LEAVES>
+__global__ __launch_bounds__(PT_THREADS) void forest_point_kernel(DevModel m, const float *__restrict__ X, int64_t n_rows,
+                                                                  float *scores, int32_t *labels, int32_t *leaf_out, int rows)
+{
+    extern __shared__ __align__(16) char smem[];
+    const int F = m.n_features, T = m.n_trees, K = m.n_outputs, D = m.walk.depth;
+    double *sum = reinterpret_cast<double *>(smem);                       // [rows][K]
+    double *by_row = sum + rows * K;                                      // [rows]
+    float *value = reinterpret_cast<float *>(by_row + rows);              // [rows][T]
+    float *xs = LEAVES ? reinterpret_cast<float *>(smem) : value + rows * T;  // [rows][F]
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * rows;
+    const int here = n_rows - row0 < rows ? static_cast<int>(n_rows - row0) : rows;
+    const int threads = static_cast<int>(blockDim.x);
+    for (int i = threadIdx.x; i < here * F; i += threads) xs[i] = X[row0 * F + i];
+    __syncthreads();
+    const int shift = 8 + (m.walk.groups >> 1);  // x_offset = feature * 256 * groups, groups 1, 2 or 4
+    for (int p = threadIdx.x; p < here * T; p += threads) {
+        const int r = p / T, t = p - r * T;
+        const WalkNode *__restrict__ node = m.walk.node + (static_cast<int64_t>(t) << D);
+        const float *x = xs + r * F;
+        uint32_t at = 0;
+        for (int l = 0; l < D; ++l) {
+            const WalkNode n = node[(1u << l) + at];
+            at |= (x[n.x_offset >> shift] <= n.threshold ? 0u : 1u) << l;
+        }
+        const int64_t leaf = (static_cast<int64_t>(t) << D) + at;
+        if (LEAVES) leaf_out[(row0 + r) * T + static_cast<int32_t>(node[0].x_offset)] = m.walk.leaf_node[leaf];
+        else value[p] = m.walk.leaf[leaf];
+    }
+    if (LEAVES) return;
+    __syncthreads();
+    const int lane = threadIdx.x & (TILE - 1);
+    for (int p = uniform(threadIdx.x >> 6); p < rows * K; p += threads / TILE) {
+        const int r = p / K, k = p - r * K;
+        double s = 0.0;
+        if (r < here) {
+            int first = 0;  // the columns' trees follow each other; counts are small integers
+            for (int c = 0; c < k; ++c) first += static_cast<int>(m.col_trees[c]);
+            const int n = static_cast<int>(m.col_trees[k]);
+            for (int t = lane; t < n; t += TILE) s += static_cast<double>(value[r * T + first + t]);
+        }
+#pragma unroll
+        for (int d = TILE / 2; d >= 1; d >>= 1) s += __shfl_xor(s, d, TILE);
+        if (lane == 0) sum[p] = s;
+    }
+    __syncthreads();
+    finish_rows(m, sum, K, 1, rows, by_row, row0, n_rows, scores, labels);
+}
+
+int point_rows(const DevModel &m)
+{
+    const int rows = PT_THREADS / (m.n_trees > 0 ? m.n_trees : 1);
+    return rows < 1 ? 1 : rows > PT_MAX_ROWS ? PT_MAX_ROWS : rows;
+}
+
+size_t point_lds_bytes(const DevModel &m)
+{
+    return static_cast<size_t>(point_rows(m)) * (sizeof(double) * (m.n_outputs + 1) + sizeof(float) * (static_cast<size_t>(m.n_trees) + m.n_features));
+}
+
 }  // namespace
+
+bool takes_point(const DevModel &m, int64_t n_rows)
+{
+    return m.walk.depth > 0 && n_rows <= POINT_MAX_ROWS && n_rows * m.n_trees * m.walk.depth <= POINT_MAX_TESTS && point_lds_bytes(m) <= POINT_MAX_LDS;
+}
+
+hipError_t launch_point(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels, int32_t *leaf_out,
+                        hipStream_t stream)
+{
+    const int rows = point_rows(m);
+    const int64_t pairs = static_cast<int64_t>(rows) * m.n_trees;
+    const int threads = pairs >= PT_THREADS ? PT_THREADS : static_cast<int>((pairs + TILE - 1) / TILE * TILE);
+    const dim3 grid(static_cast<unsigned>((n_rows + rows - 1) / rows));
+    if (leaf_out) hipLaunchKernelGGL(forest_point_kernel<true>, grid, dim3(threads), point_lds_bytes(m), stream, m, X, n_rows, scores, labels, leaf_out, rows);
+    else hipLaunchKernelGGL(forest_point_kernel<false>, grid, dim3(threads), point_lds_bytes(m), stream, m, X, n_rows, scores, labels, leaf_out, rows);
+    return hipGetLastError();
+}
 
 hipError_t launch_rank_tiles(const DevModel &m, const float *X, int64_t n_rows, hipStream_t stream)
 {

@@ -89,3 +89,18 @@ def test_walk_kernels(depth, features, outputs, full):
         assert pk.forest_pack(f)["walk_depth"] > 0
         X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
         _check(f, X, leaves=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("depth,trees,features,outputs", [(3, 1, 2, 1), (8, 500, 28, 1), (6, 2000, 128, 10), (7, 65, 300, 4), (4, 10, 9, 3)])
+def test_smallest_batches_with_a_lane_per_row_and_tree(depth, trees, features, outputs):
+    """One row, whole and ragged workgroups of rows, more pairs than threads, and the first batches beyond
+    the kernel's limit on rows and on tests."""
+    rng = np.random.default_rng(depth + trees)
+    f = _forest(trees + depth, trees, depth, features, outputs, full=True)
+    limit = min(8192, (1 << 20) // (trees * depth))
+    for rows in sorted({1, 2, 15, 17, 70, limit, limit + 1}):
+        X = rng.standard_normal((rows, features)).astype(np.float32)
+        if rows >= 70:
+            X = _special_rows(X, f, rng)
+        _check(f, X, leaves=rows <= 70)
