@@ -4,10 +4,8 @@ Prints ONE JSON line.  With no --workload it measures every configuration: the h
 (`value`, `config`, `roofline`, `cpu_baseline`, `parity`) are those of c5, the largest one, and
 `per_config` holds the same fields for c4, c3, c2 and, as a latency, c1.  `value` is rows/s with
 X already resident in HBM.  The `roofline` object prices the dominant (only) kernel against the
-vector-ALU peak: the method evaluates every internal node of every tree for every row, one
-comparison each, and the packed model stays on chip, so the rate of the compare instruction is
-what bounds it.  The rank kernels compare two rows per lane with one packed-f16 instruction, so
-their peak is two comparisons per lane and clock; the fp32 kernels' peak is one.
+LDS: the walk kernels, which run every configuration here, test the nodes on a row's path, and a
+test is two LDS reads, the node and the row's feature.
 `cpu_baseline` is the CPU oracle timed on this machine's host cores over all rows of the
 configuration (one warm-up pass, median of three timed passes), and `parity` compares every row
 of the timed output with it.  The configurations are set up first and timed back to back, so
@@ -25,11 +23,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
-# MI355X: 256 compute units x 4 SIMDs x 16 lanes x 2.4 GHz vector instructions per second and
-# lane.  The fp32 vector peak of 157.3 TFLOP/s is this number x 2 (FMA) x 2 (packed fp32).  A
-# float32 compare is neither fused nor packed: one comparison per lane-op.  A packed-f16
-# compare (v_pk_fma_f16 with clamp on exactly coded ranks) is two comparisons per lane-op.
-ALU_PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
+# MI355X: 256 compute units x 2.4 GHz; a wavefront's LDS read of 4 or 8 bytes per lane takes two
+# clocks without bank conflicts, so 64 tests take four.
+LDS_PEAK_TESTS = 256 * 2.4e9 * 64 / 4
 HBM_PEAK = 8.0e12
 ORACLE_THREADS_MAX = 16   # the share of host cores one GPU's job may use on the bench machine
 
@@ -38,10 +34,6 @@ ORACLE_THREADS_MAX = 16   # the share of host cores one GPU's job may use on the
 # entry names the summary under profiles/ it comes from and the commit whose kernels were
 # measured; a workload without an entry reports null.
 MEASURED_TRAFFIC = {
-    "c5": {"bytes": 4.284e9, "profile": "profiles/forest_rankbank_kernel_c5.md", "commit": "1e0bf79"},
-    "c4": {"bytes": 6.861e8, "profile": "profiles/forest_rank_kernel_c3_c4.md", "commit": "8101bd8"},
-    "c3": {"bytes": 2.130e8, "profile": "profiles/forest_rank_kernel_c3_c4.md", "commit": "8101bd8"},
-    "c2": {"bytes": 1.595e8, "profile": "profiles/forest_rank_kernel_c2.md", "commit": "8101bd8"},
     "l2": {"bytes": 1.456e9, "profile": "profiles/linear_kernels.md", "commit": "65bfc7c"},
     "l3": {"bytes": 1.120e9, "profile": "profiles/linear_kernels.md", "commit": "65bfc7c"},
     "l4": {"bytes": 9.600e8, "profile": "profiles/linear_kernels.md", "commit": "65bfc7c"},
@@ -211,6 +203,23 @@ def compare_issue_rate() -> float:
     return n / (start.elapsed_time(stop) * 1e-3)
 
 
+def _mean_path_tests(forest, leaves) -> float:
+    """Tests on a row's paths through all trees, averaged over the rows of `leaves` ([rows, trees])."""
+    import numpy as np
+    offset = np.asarray(forest.tree_offset)
+    depth = np.zeros(int(offset[-1]), np.int64)
+    tree_of = np.repeat(np.arange(len(offset) - 1), np.diff(offset))
+    at = offset[:-1].copy()
+    level = 0
+    while len(at):
+        depth[at] = level
+        at = at[np.asarray(forest.feature)[at] >= 0]
+        base = offset[tree_of[at]]
+        at = np.concatenate([base + forest.left[at], base + forest.right[at]])
+        level += 1
+    return float(depth[offset[:-1][None, :] + leaves].sum(axis=1).mean())
+
+
 class ForestRun:
     """One tree-ensemble configuration, measured in three steps so that the GPU timing of several
     configurations can run back to back: prepare (model and X to the device), time (W warm-up and
@@ -269,23 +278,20 @@ class ForestRun:
         scores, labels = f.predict(self.xd, out=self.out)
         torch.cuda.synchronize()
 
-        compares = float(info["n_internal"]) * n_rows          # one per (row, internal node)
-        achieved = compares / kernel_s
+        sample = f.predict_leaves(self.xd[:4096]).cpu().numpy()
+        tests = _mean_path_tests(self.w.forest, sample)
+        achieved = tests * n_rows / kernel_s
         algo_bytes = n_rows * (4.0 * F) + f.out_bytes(n_rows)
-        packed = info["kernel_path"] in (2, 3, 4)  # rank kernels: two comparisons per packed-f16 lane-op
-        peak = ALU_PEAK_LANE_OPS * (2 if packed else 1)
         traffic = MEASURED_TRAFFIC.get(name) if args.rows is None else None
         roofline = {
-            "bound": "alu",
-            "kernel": "forest_predict (fused compare + leaf resolution + reduction)",
+            "bound": "lds",
+            "kernel": "forest_predict (walk of the row's paths + reduction)",
             "achieved": achieved / 1e12,
-            "peak": peak / 1e12,
-            "unit": "Tcompare/s",
-            "frac": achieved / peak,
-            "peak_basis": "256 CU x 4 SIMD x 16 lanes x 2.4 GHz x "
-                          + ("2 comparisons per packed-f16 lane-op" if packed else "1 float32 comparison per lane-op"),
-            # against one float32 compare per (row, node) and lane-op, the floor a plain fp32 kernel has
-            "frac_vs_fp32_compare_peak": achieved / ALU_PEAK_LANE_OPS,
+            "peak": LDS_PEAK_TESTS / 1e12,
+            "unit": "Ttest/s",
+            "frac": achieved / LDS_PEAK_TESTS,
+            "peak_basis": "256 CU x 2.4 GHz x 64 rows per 4 clocks (two LDS reads of 2 clocks per test)",
+            "tests_per_row": tests,
             "kernel_ms_avg": kernel_s * 1e3,
             "kernel_ms_min": float(np.min(kernel_ms)),
             "kernel_ms_median": float(np.median(kernel_ms)),
@@ -320,8 +326,7 @@ class ForestRun:
         res = {
             "value": n_rows * args.steps / wall,
             "ms_per_step": wall / args.steps * 1e3,
-            "dtype": ("f16 threshold ranks (exact rewrite of the f32 compare), f64 accumulate"
-                      if packed else "f32 compare, f64 accumulate"),
+            "dtype": "f32 compare, f64 accumulate",
             "config": {"workload": name, "n_rows": n_rows, "n_features": F,
                        "n_trees": info["n_trees"], "max_depth": info["max_depth"],
                        "n_internal_nodes": info["n_internal"], "n_outputs": info["n_outputs"],

@@ -14,10 +14,12 @@
 //
 // This file holds the kernels that read features from the LDS tile for every comparison
 // (any number of features, any tree shape), the choice of how many shares the trees of a small
-// batch are cut into, and the launcher.  The other families: forest_kernels_rank.hip (packed
-// f16 threshold ranks in vector registers, the headline path), forest_kernels_ranklds.hip (the
-// same with the ranks in LDS, any tree shape), forest_kernels_reg.hip (float32 features in
-// vector registers), forest_kernels_split.hip (what only split launches need).
+// batch are cut into, and the launcher.  The walk kernels run nearly every model:
+// forest_kernels_walk.hip (depth up to 8, scalar leaves) and forest_kernels_deep.hip (the rest).  The
+// other dense families: forest_kernels_rank.hip (packed f16 threshold ranks in vector registers),
+// forest_kernels_ranklds.hip (the same with the ranks in LDS, any tree shape), forest_kernels_rankbank.hip
+// (large batches of those), forest_kernels_reg.hip (float32 features in vector registers).
+// forest_kernels_split.hip holds what only small batches need.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
