@@ -147,6 +147,33 @@ int forest_pack_view(const forest_packed *p, forest_packed_view *view);
 void forest_pack_free(forest_packed *p);
 
 /*
+ * What a call launches for n_rows rows (leaves: leaf ids, else scores and labels), so that a test can see that it
+ * reaches the kernel it is about.  forest_launch: of a loaded model; forest_packed_launch: of a packed one, no GPU
+ * needed, with the workspace that a handle gives its calls.  Returns FOREST_OK, FOREST_EINVAL (null pointer, n_rows
+ * < 1) or FOREST_ELIMIT.
+ */
+enum {
+    FOREST_KERNEL_LDS = 0,       /* dense kernels, by kernel_path */
+    FOREST_KERNEL_REG = 1,
+    FOREST_KERNEL_RANK = 2,
+    FOREST_KERNEL_RANK_LDS = 3,
+    FOREST_KERNEL_RANK_BANK = 4, /* kernel_path 3, batches that are not cut into shares */
+    FOREST_KERNEL_POINT = 5,     /* a lane per (row, tree) */
+    FOREST_KERNEL_WALK = 6,
+    FOREST_KERNEL_DEEP = 7
+};
+typedef struct forest_launch_t {
+    int32_t kernel;             /* FOREST_KERNEL_* */
+    int32_t shares;             /* shares the trees are cut into */
+    int32_t rows_per_workgroup;
+    int32_t threads;            /* per workgroup */
+    int32_t launches;           /* ranges of rows the batch goes in */
+    int64_t workgroups;         /* of the largest range, per share */
+} forest_launch_t;
+int forest_launch(const forest *f, int64_t n_rows, int32_t leaves, forest_launch_t *out);
+int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out);
+
+/*
  * Host-only view of the rank coding of kernel_path 2 and 3 (the input's dtype rewriting,
  * Section 4.3.1; no GPU needed): a rank register stores the local rank q of a row among the
  * thresholds of its segment as the f16 bit pattern *code, and a split on the segment's j-th

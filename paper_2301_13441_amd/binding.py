@@ -61,12 +61,20 @@ class _View(ctypes.Structure):
                 ("deep_position", _p)]
 
 
+class _Launch(ctypes.Structure):
+    _fields_ = [("kernel", _i32), ("shares", _i32), ("rows_per_workgroup", _i32), ("threads", _i32), ("launches", _i32),
+                ("workgroups", _i64)]
+
+
+_KERNELS = ("lds", "reg", "rank", "rank_lds", "rank_bank", "point", "walk", "deep")  # FOREST_KERNEL_*
+
+
 # include/forest.h: the inference ABI
 EXPORTS = ["forest_load", "forest_free", "forest_info", "forest_out_bytes", "forest_out_layout",
            "forest_predict", "forest_predict_static", "forest_predict_leaves", "forest_strerror"]
 # include/forest_testing.h: host-only views into the model compiler, for its tests
 TESTING_EXPORTS = ["forest_pack", "forest_pack_view", "forest_pack_free", "forest_rank_code",
-                   "forest_staged_position", "forest_probe_compare_rate"]
+                   "forest_staged_position", "forest_probe_compare_rate", "forest_launch", "forest_packed_launch"]
 
 
 def lib_path() -> str:
@@ -109,6 +117,9 @@ def load_library():
     lib.forest_rank_code.argtypes = [_i32, ctypes.POINTER(ctypes.c_uint16), ctypes.POINTER(ctypes.c_uint16)]
     lib.forest_staged_position.restype = ctypes.c_int
     lib.forest_staged_position.argtypes = [_i32, _i32, ctypes.POINTER(_i32)]
+    for fn in (lib.forest_launch, lib.forest_packed_launch):
+        fn.restype = ctypes.c_int
+        fn.argtypes = [_p, _i64, _i32, ctypes.POINTER(_Launch)]
     lib.forest_strerror.restype = ctypes.c_char_p
     lib.forest_strerror.argtypes = [ctypes.c_int]
     _lib = lib
@@ -268,6 +279,33 @@ def forest_staged_position(depth: int, pos: int) -> int:
     if rc != 0:
         raise ForestError(rc, _strerror(rc))
     return node.value
+
+
+def _launch(call, handle, what, n_rows, leaves) -> dict:
+    s = _Launch()
+    rc = call(handle, n_rows, int(leaves), ctypes.byref(s))
+    if rc != 0:
+        raise ForestError(rc, what)
+    return {**{name: int(getattr(s, name)) for name, _ in _Launch._fields_}, "kernel": _KERNELS[s.kernel]}
+
+
+def forest_launch(f, n_rows: int, leaves: bool = False) -> dict:
+    """What a call on the loaded model launches for n_rows rows (include/forest_testing.h)."""
+    return _launch(f._lib.forest_launch, f._h, "forest_launch", n_rows, leaves)
+
+
+def forest_packed_launch(forest, n_rows: int, leaves: bool = False) -> dict:
+    """The same for a model that is only packed: no GPU needed."""
+    lib = load_library()
+    d, keep = _desc_from(forest)
+    h = _p()
+    rc = lib.forest_pack(ctypes.byref(d), ctypes.byref(h))
+    if rc != 0:
+        raise ForestError(rc, "forest_pack")
+    try:
+        return _launch(lib.forest_packed_launch, h, "forest_packed_launch", n_rows, leaves)
+    finally:
+        lib.forest_pack_free(h)
 
 
 def forest_probe_compare_rate(iterations: int, device_word, stream=None) -> int:

@@ -234,7 +234,7 @@ int forest_load(const forest_desc *desc, forest **out)
         delete f;
         return FOREST_EHIP;
     }
-    DevModel &d = f->dev;
+    DevModel &d = f->dev = describe(m);
     d.prog = reinterpret_cast<const SplitEntry *>(b + o_prog);
     d.prog32 = reinterpret_cast<const uint32_t *>(b + o_prog32);
     d.child = reinterpret_cast<const ChildRef *>(b + o_child);
@@ -243,21 +243,6 @@ int forest_load(const forest_desc *desc, forest **out)
     d.tree = reinterpret_cast<const TreeMeta *>(b + o_tree);
     d.col_trees = reinterpret_cast<const double *>(b + o_colt);
     d.base = reinterpret_cast<const float *>(b + o_base);
-    d.n_trees = m.n_trees;
-    d.n_features = m.n_features;
-    d.n_outputs = m.n_outputs;
-    d.leaf_width = m.leaf_width;
-    d.aggregate = m.aggregate;
-    d.transform = m.transform;
-    d.output = m.output;
-    d.kind = m.kind;
-    d.max_words = m.max_words;
-    d.path = m.path;
-    d.reg_nv = m.reg_nv;
-    d.reg_r = m.reg_r;
-    d.rank_regs = m.rank_regs;
-    d.lds_waves = m.lds_waves;
-    for (int w = 0; w <= RANKLDS_WAVES_WIDE; ++w) d.wave_tree[w] = m.wave_tree[w];
     d.feat_bucket = reinterpret_cast<const FeatBucket *>(b + o_fbk);
     d.bucket_start = reinterpret_cast<const int32_t *>(b + o_bst);
     d.thr_sorted = reinterpret_cast<const float *>(b + o_thrs);
@@ -274,30 +259,15 @@ int forest_load(const forest_desc *desc, forest **out)
     d.bank.todo = reinterpret_cast<const BankTodo *>(b + o_btodo);
     d.fast_feat = reinterpret_cast<const FastLookup *>(b + o_bfeat);
     d.fast_tab = reinterpret_cast<const uint16_t *>(b + o_btab);
-    for (int w = 0; w < BANK_WAVES; ++w) d.bank.stream_base[w] = m.bank_stream_base[w];
-    d.bank.batches = m.bank_batches;
-    d.bank.max_units = m.bank_max_units;
-    d.bank.enabled = m.bank_enabled;
-    d.bank.passes = static_cast<int32_t>(m.bank_pass.size());
     d.walk.node = reinterpret_cast<const WalkNode *>(b + o_wnode);
     d.walk.leaf = reinterpret_cast<const float *>(b + o_wleaf);
     d.walk.leaf_node = reinterpret_cast<const int32_t *>(b + o_wleafn);
     d.walk.position = reinterpret_cast<const int32_t *>(b + o_wpos);
-    d.walk.depth = m.walk_depth;
-    d.walk.groups = m.walk_groups;
-    d.walk.stages = m.walk_stages;
     d.deep.top = reinterpret_cast<const WalkNode *>(b + o_dtop);
     d.deep.unit = reinterpret_cast<const WalkNode *>(b + o_dunit);
     d.deep.unit_node = reinterpret_cast<const int32_t *>(b + o_dnode);
     d.deep.value = reinterpret_cast<const float *>(b + o_dvalue);
     d.deep.position = reinterpret_cast<const int32_t *>(b + o_dpos);
-    d.deep.groups = m.deep_groups;
-    d.n_splits = 1;
-    d.n_entries = static_cast<int64_t>(m.prog32.size() > m.prog.size() ? m.prog32.size() : m.prog.size());
-    d.split_rows = 0;
-    d.partial = nullptr;  // set per launch from the workspace in use
-    d.partial_capacity = 0;
-    d.rank_tiles = nullptr;
     for (int i = 0; i < WS_SLOTS; ++i) f->slot[i] = carve_workspace(d, b + o_slot[i], slot_bytes, SPLIT_BELOW_BLOCKS);
     // the caller-order views are only for forest_pack_view; drop the bulk on the load path
     m.prog = {};
@@ -435,6 +405,15 @@ int forest_predict_leaves(const forest *f, const float *X, int64_t n_rows, int32
     const Workspace *ws = small_batch(f, n_rows) ? claim_slot(f, st) : nullptr;
     const hipError_t e = launch_predict(f->dev, ws, false, X, n_rows, nullptr, nullptr, leaf_node_id, st);
     return e == hipSuccess ? FOREST_OK : FOREST_EHIP;
+}
+
+int forest_launch(const forest *f, int64_t n_rows, int32_t leaves, forest_launch_t *out)
+{
+    if (!out || n_rows < 1) return FOREST_EINVAL;
+    if (int rc = check_out_args(f, n_rows)) return rc;
+    const Workspace *ws = small_batch(f, n_rows) ? &f->slot[0] : nullptr;
+    *out = launch_shape(f->dev, plan_launch(f->dev, ws, n_rows, !leaves), n_rows);
+    return FOREST_OK;
 }
 
 }  // extern "C"

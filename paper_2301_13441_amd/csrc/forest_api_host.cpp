@@ -4,6 +4,7 @@
 #include <new>
 
 #include "forest_model.hpp"
+#include "forest_plan.hpp"
 
 using namespace forest_impl;
 
@@ -29,6 +30,18 @@ int forest_pack(const forest_desc *desc, forest_packed **out)
         return rc;
     }
     *out = p;
+    return FOREST_OK;
+}
+
+int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out)
+{
+    if (!p || !out || n_rows < 1) return FOREST_EINVAL;
+    if (n_rows > FOREST_MAX_ROWS) return FOREST_ELIMIT;
+    const DevModel d = describe(p->m);
+    Workspace ws;
+    ws.rank_tile_words = static_cast<int64_t>(rank_tile_bytes(d.rank_regs, SPLIT_BELOW_BLOCKS) / sizeof(uint32_t));
+    ws.partial_doubles = split_workspace_doubles(d.n_outputs);
+    *out = launch_shape(d, plan_launch(d, &ws, n_rows, !leaves), n_rows);
     return FOREST_OK;
 }
 

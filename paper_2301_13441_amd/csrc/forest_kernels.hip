@@ -262,29 +262,6 @@ hipError_t init_kernels()
     return init_deep_kernels(g_lds_limit);
 }
 
-int family_rows_per_block(const DevModel &m)
-{
-    if (m.path == PATH_RANK || m.path == PATH_RANK_LDS) return 128;
-    if (m.path == PATH_REG) return TILE * m.reg_r;
-    return TILE;
-}
-
-int family_waves_per_block(const DevModel &m) { return m.path == PATH_RANK_LDS ? m.lds_waves : WAVES; }
-
-static int64_t split_workspace_doubles(int n_outputs)
-{
-    // splits x rows stays below (SPLIT_TARGET_BLOCKS + SPLIT_BELOW_BLOCKS) workgroups x 128 rows
-    const int64_t want = (SPLIT_TARGET_BLOCKS + SPLIT_BELOW_BLOCKS) * 128 * n_outputs;
-    const int64_t cap = int64_t{4} << 20;  // 32 MB
-    return want < cap ? want : cap;
-}
-
-static size_t rank_tile_bytes(int rank_regs, int64_t tiles)
-{
-    const size_t b = sizeof(uint32_t) * 64 * static_cast<size_t>(rank_regs > 0 ? rank_regs : 0) * static_cast<size_t>(tiles);
-    return (b + 255) & ~size_t{255};
-}
-
 size_t full_workspace_bytes(int rank_regs, int n_outputs)
 {
     return rank_tile_bytes(rank_regs, SPLIT_BELOW_BLOCKS) + sizeof(double) * static_cast<size_t>(split_workspace_doubles(n_outputs));
@@ -303,76 +280,19 @@ Workspace carve_workspace(const DevModel &m, void *base, size_t bytes, int64_t t
     return ws;
 }
 
-namespace {
-
-// How many shares the trees are cut into for a batch of n_rows rows (1 = no split); `fits`
-// tells whether the workspace allowed the split the batch asks for.
-int choose_splits(const DevModel &m, const Workspace *ws, int64_t n_rows, bool needs_sums, bool &fits)
-{
-    fits = true;
-    const int64_t rb = family_rows_per_block(m);
-    const int64_t n_blocks = (n_rows + rb - 1) / rb;
-    if (n_blocks >= SPLIT_BELOW_BLOCKS) return 1;
-    const int64_t per_tree = m.n_trees > 0 ? (m.n_entries + m.n_trees - 1) / m.n_trees : 1;
-    const int64_t trees_per_wave = (SPLIT_MIN_ENTRIES_PER_WAVE + per_tree - 1) / (per_tree > 0 ? per_tree : 1);
-    int64_t s = m.n_trees / (family_waves_per_block(m) * (trees_per_wave > 0 ? trees_per_wave : 1));
-    const int64_t by_grid = (SPLIT_TARGET_BLOCKS + n_blocks - 1) / n_blocks;
-    if (by_grid < s) s = by_grid;
-    if (s < 2) return 1;  // the model is too small to be worth cutting
-    const bool ranks = m.path == PATH_RANK || m.path == PATH_RANK_LDS;
-    const int64_t tile_words = ranks ? n_blocks * m.rank_regs * 64 : 0;
-    if (tile_words > (ws ? ws->rank_tile_words : 0)) {
-        fits = false;
-        return 1;
-    }
-    if (needs_sums) {
-        const int64_t by_ws = (ws ? ws->partial_doubles : 0) / (n_rows * m.n_outputs);
-        if (by_ws < s) s = by_ws;
-        if (s < 2) {
-            fits = false;
-            return 1;
-        }
-    }
-    return static_cast<int>(s);
-}
-
-// The same for the models of the walk kernels, whose workgroups own 64 rows or more: as many shares
-// as fill the chip's workgroups once, each of its waves left two copies of trees to LDS or more.
-// (Against the dense kernels' shares with their rank tiles: 10,007 rows of 250 trees of depth 8, 64 features:
-// 63.6 -> 21.5 us a call; 1,021 rows of 2000 x depth 6, 128 features: 39.3 -> 22.4.  Half as many shares: 18.5
-// and 20.9 with a costly reduction, the same as now since it is cheap; at least 1 or 4 copies: no difference.)
-int choose_walk_splits(const DevModel &m, const Workspace *ws, int64_t n_rows, bool needs_sums)
-{
-    const int64_t n_blocks = (n_rows + TILE - 1) / TILE;
-    const int64_t copies = m.walk.depth > 0 ? m.walk.stages : m.n_trees;
-    // leaf ids are dealt four trees at a time
-    const int64_t waves = needs_sums ? copies / WALK_SPLIT_MIN_COPIES : (m.n_trees + 3) / 4;
-    int64_t s = WALK_RESIDENT / n_blocks;
-    if (waves / WALK_WAVES < s) s = waves / WALK_WAVES;
-    if (needs_sums && s > 1) {
-        const int64_t by_ws = (ws ? ws->partial_doubles : 0) / (n_rows * m.n_outputs);
-        if (by_ws < s) s = by_ws;
-    }
-    return s < 2 ? 1 : static_cast<int>(s);
-}
-
-}  // namespace
-
-static hipError_t launch_family(const DevModel &m, const float *X, int64_t n_rows, float *scores,
+static hipError_t launch_family(const DevModel &m, const LaunchPlan &p, const float *X, int64_t n_rows, float *scores,
                                 int32_t *labels, int32_t *leaf_out, hipStream_t stream)
 {
-    if (m.walk.depth > 0) return launch_walk(m, X, n_rows, scores, labels, leaf_out, stream);
-    // trees deeper than 8, vector leaves, infinite thresholds: what a row does not meet is not tested
-    // (128 trees of depth 12: 2.9 ms against 14.5 with the register-bank kernel)
-    if (m.deep.groups > 0) return launch_deep(m, X, n_rows, scores, labels, leaf_out, stream);
-    if (m.path == PATH_RANK) return launch_rank(m, X, n_rows, scores, labels, leaf_out, stream);
-    if (m.path == PATH_RANK_LDS) {
-        // large batches of the models it fits: rank registers banked over the waves' vector registers
-        if (m.n_splits == 1 && m.bank.enabled)
-            return launch_rankbank(m, X, n_rows, scores, labels, leaf_out, g_lds_limit, stream);
-        return launch_ranklds(m, X, n_rows, scores, labels, leaf_out, g_lds_limit, stream);
+    switch (p.kernel) {
+        case FOREST_KERNEL_POINT: return launch_point(m, X, n_rows, scores, labels, leaf_out, stream);
+        case FOREST_KERNEL_WALK: return launch_walk(m, p.groups, X, n_rows, scores, labels, leaf_out, stream);
+        case FOREST_KERNEL_DEEP: return launch_deep(m, p.groups, X, n_rows, scores, labels, leaf_out, stream);
+        case FOREST_KERNEL_RANK: return launch_rank(m, X, n_rows, scores, labels, leaf_out, stream);
+        case FOREST_KERNEL_RANK_BANK: return launch_rankbank(m, X, n_rows, scores, labels, leaf_out, g_lds_limit, stream);
+        case FOREST_KERNEL_RANK_LDS: return launch_ranklds(m, X, n_rows, scores, labels, leaf_out, g_lds_limit, stream);
+        case FOREST_KERNEL_REG: return launch_reg(m, X, n_rows, scores, labels, leaf_out, stream);
+        default: break;
     }
-    if (m.path == PATH_REG) return launch_reg(m, X, n_rows, scores, labels, leaf_out, stream);
     bool staged = true;
     if (lds_bytes(m, true) > g_lds_limit) staged = false;
     const size_t lds = lds_bytes(m, staged);
@@ -393,27 +313,24 @@ hipError_t launch_predict(const DevModel &model, const Workspace *ws, bool must_
     // well (grid y) and a second kernel sums the shares.  The leaf-id output needs no sums.
     DevModel m = model;
     const bool sums = leaf_out == nullptr;
-    bool fits = true;
-    m.n_splits = choose_splits(m, ws, n_rows, sums, fits);
-    if (!fits && must_fit) return hipErrorMemoryAllocation;
-    // A batch the dense kernels' workspace does not hold is refused above whichever kernel runs it: what
-    // forest_predict_static takes does not depend on the kernel.
-    if (takes_point(m, n_rows)) {
-        m.n_splits = 1;
-        return launch_point(m, X, n_rows, scores, labels, leaf_out, stream);
-    }
-    const bool walk = m.walk.depth > 0 || m.deep.groups > 0;
-    if (walk) m.n_splits = choose_walk_splits(m, ws, n_rows, sums);
+    const LaunchPlan p = plan_launch(m, ws, n_rows, sums);
+    if (!p.fits && must_fit) return hipErrorMemoryAllocation;
+    m.n_splits = p.splits;
     m.split_rows = n_rows;
     m.partial = ws ? ws->partial : nullptr;
     m.partial_capacity = ws ? ws->partial_doubles : 0;
     m.rank_tiles = ws ? ws->rank_tiles : nullptr;
-    if (m.n_splits > 1 && !walk && (m.path == PATH_RANK || m.path == PATH_RANK_LDS)) {
+    if (m.n_splits > 1 && (p.kernel == FOREST_KERNEL_RANK || p.kernel == FOREST_KERNEL_RANK_LDS)) {
         const hipError_t e = launch_rank_tiles(m, X, n_rows, stream);
         if (e != hipSuccess) return e;
     }
-    const hipError_t e = launch_family(m, X, n_rows, scores, labels, leaf_out, stream);
-    if (e != hipSuccess || m.n_splits == 1 || !sums) return e;
+    for (int64_t r = 0; r < n_rows; r += MAX_LAUNCH_ROWS) {  // batches cut into shares are far smaller than a range
+        const int64_t here = n_rows - r < MAX_LAUNCH_ROWS ? n_rows - r : MAX_LAUNCH_ROWS;
+        const hipError_t e = launch_family(m, p, X + r * m.n_features, here, scores ? scores + r * m.n_outputs : nullptr,
+                                           labels ? labels + r : nullptr, leaf_out ? leaf_out + r * m.n_trees : nullptr, stream);
+        if (e != hipSuccess) return e;
+    }
+    if (m.n_splits == 1 || !sums) return hipSuccess;
     return launch_reduce_splits(m, n_rows, scores, labels, stream);
 }
 

@@ -374,27 +374,6 @@ KernelFn pick(int groups, int mode, int width, bool shared)
     return shared ? pick_mode<true>(groups, mode, width) : pick_mode<false>(groups, mode, width);
 }
 
-// Whether two workgroups fit a CU.
-bool shares_cu(const DevModel &m, int groups)
-{
-    return deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups) <= CU_LDS_BYTES / 2;
-}
-
-// Row groups per workgroup: two rows per lane share the copies of the trees' tops and keep twice as
-// many walks in flight (300 irregular trees, 90 features, 103,069 rows: 94 us with two, 108 with one);
-// one leaves a small batch more workgroups.  The last round of workgroups counts whole.
-int choose_groups(const DevModel &m, int64_t n_rows)
-{
-    if (m.deep.groups == 1) return 1;
-    double cost[2];
-    for (int g = 1; g <= 2; ++g) {
-        const int64_t per_cu = shares_cu(m, g) ? 2 : 1;
-        const int64_t blocks = (n_rows + TILE * g - 1) / (TILE * g) * m.n_splits, round = 256 * per_cu;
-        cost[g - 1] = static_cast<double>((blocks + round - 1) / round * per_cu * g) * (g == 1 ? 1.15 : 1.0);
-    }
-    return cost[0] < cost[1] ? 1 : 2;
-}
-
 }  // namespace
 
 hipError_t init_deep_kernels(size_t lds_limit)
@@ -414,11 +393,10 @@ hipError_t init_deep_kernels(size_t lds_limit)
     return hipSuccess;
 }
 
-hipError_t launch_deep(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
+hipError_t launch_deep(const DevModel &m, int groups, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                        int32_t *leaf_out, hipStream_t stream)
 {
-    const int groups = choose_groups(m, n_rows);
-    const bool shared = shares_cu(m, groups);
+    const bool shared = deep_shares_cu(m, groups);
     const int64_t n_blocks = (n_rows + TILE * groups - 1) / (TILE * groups);
     if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(n_blocks), static_cast<unsigned>(m.n_splits));

@@ -121,7 +121,7 @@ __global__ __launch_bounds__(RS_THREADS) void forest_reduce_splits_kernel(DevMod
 // `rows` rows, whose features it holds in LDS; the leaf values meet there, [row][tree], and a wave adds
 // those of a (row, column), whose trees are neighbours in processing order.  What bounds it is the chain of
 // dependent loads, one per level, and for more pairs the gathers: a cycle of the texture path per lane.
-constexpr int PT_THREADS = 1024, PT_MAX_ROWS = 16;
+
 
 template <bool LEAVES>
 __global__ __launch_bounds__(PT_THREADS) void forest_point_kernel(DevModel m, const float *__restrict__ X, int64_t n_rows,
@@ -172,30 +172,13 @@ __global__ __launch_bounds__(PT_THREADS) void forest_point_kernel(DevModel m, co
     finish_rows(m, sum, K, 1, rows, by_row, row0, n_rows, scores, labels);
 }
 
-int point_rows(const DevModel &m)
-{
-    const int rows = PT_THREADS / (m.n_trees > 0 ? m.n_trees : 1);
-    return rows < 1 ? 1 : rows > PT_MAX_ROWS ? PT_MAX_ROWS : rows;
-}
-
-size_t point_lds_bytes(const DevModel &m)
-{
-    return static_cast<size_t>(point_rows(m)) * (sizeof(double) * (m.n_outputs + 1) + sizeof(float) * (static_cast<size_t>(m.n_trees) + m.n_features));
-}
-
 }  // namespace
-
-bool takes_point(const DevModel &m, int64_t n_rows)
-{
-    return m.walk.depth > 0 && n_rows <= POINT_MAX_ROWS && n_rows * m.n_trees * m.walk.depth <= POINT_MAX_TESTS && point_lds_bytes(m) <= POINT_MAX_LDS;
-}
 
 hipError_t launch_point(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels, int32_t *leaf_out,
                         hipStream_t stream)
 {
     const int rows = point_rows(m);
-    const int64_t pairs = static_cast<int64_t>(rows) * m.n_trees;
-    const int threads = pairs >= PT_THREADS ? PT_THREADS : static_cast<int>((pairs + TILE - 1) / TILE * TILE);
+    const int threads = point_threads(m);
     const dim3 grid(static_cast<unsigned>((n_rows + rows - 1) / rows));
     if (leaf_out) hipLaunchKernelGGL(forest_point_kernel<true>, grid, dim3(threads), point_lds_bytes(m), stream, m, X, n_rows, scores, labels, leaf_out, rows);
     else hipLaunchKernelGGL(forest_point_kernel<false>, grid, dim3(threads), point_lds_bytes(m), stream, m, X, n_rows, scores, labels, leaf_out, rows);

@@ -289,24 +289,6 @@ KernelFn pick(int depth, int groups, int mode)
     return pick_depth<WALK_LEAVES>(depth, groups);
 }
 
-// Row groups per workgroup.  More rows per workgroup amortise the copies of the trees to LDS (per
-// 64 rows, depth 6: 1, 1.07 and 1.25 of the time with 4, 2 and 1 groups), fewer leave smaller
-// batches enough workgroups; the last round of workgroups counts whole.
-int choose_groups(const DevModel &m, int64_t n_rows)
-{
-    int best = 1;
-    double best_cost = 0.0;
-    for (int g = m.walk.groups; g >= 1; g /= 2) {
-        const int64_t blocks = (n_rows + TILE * g - 1) / (TILE * g) * m.n_splits;
-        const double cost = static_cast<double>((blocks + WALK_RESIDENT - 1) / WALK_RESIDENT) * g * (g == 4 ? 1.0 : g == 2 ? 1.07 : 1.25);
-        if (g == m.walk.groups || cost < best_cost) {
-            best = g;
-            best_cost = cost;
-        }
-    }
-    return best;
-}
-
 }  // namespace
 
 hipError_t init_walk_kernels(size_t lds_limit)
@@ -325,10 +307,9 @@ hipError_t init_walk_kernels(size_t lds_limit)
     return hipSuccess;
 }
 
-hipError_t launch_walk(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
+hipError_t launch_walk(const DevModel &m, int groups, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                        int32_t *leaf_out, hipStream_t stream)
 {
-    const int groups = choose_groups(m, n_rows);
     const int64_t n_blocks = (n_rows + TILE * groups - 1) / (TILE * groups);
     if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(n_blocks), static_cast<unsigned>(m.n_splits));

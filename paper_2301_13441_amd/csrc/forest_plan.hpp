@@ -1,0 +1,369 @@
+// The model as the kernels see it, and what one call launches for it: which kernel, how many rows a workgroup
+// owns and how many shares the trees are cut into.  Host only and free of HIP: the rules are checked without
+// a GPU (forest_testing.h).
+#pragma once
+
+#include <cstdint>
+
+#include "forest_model.hpp"
+
+namespace forest_impl {
+
+// Device tables of the register-bank program (forest_model.hpp, forest_pack.cpp).
+struct BankDev {
+    const uint32_t *prog;
+    const uint32_t *child;
+    const uint32_t *leaf;
+    const BankTree *tree;
+    const BankSpan *span;
+    const BankBatch *batch;
+    const BankPass *pass;           // [passes]
+    const BankPassWave *pass_wave;  // [passes][BANK_WAVES]
+    const BankTodo *todo;
+    int32_t stream_base[BANK_WAVES];
+    int32_t batches, max_units, enabled;
+    int32_t passes;
+};
+
+// Device tables of the walk program (forest_model.hpp).
+struct WalkDev {
+    const WalkNode *node;
+    const float *leaf;
+    const int32_t *leaf_node;
+    const int32_t *position;
+    int32_t depth;   // 0: none
+    int32_t groups;  // row groups the X tile is laid out for
+    int32_t stages;
+};
+
+// Device tables of the deep walk program (forest_model.hpp).
+struct DeepDev {
+    const WalkNode *top;
+    const WalkNode *unit;
+    const int32_t *unit_node;
+    const float *value;
+    const int32_t *position;
+    int32_t groups;  // 0: none
+};
+
+struct DevModel {
+    const SplitEntry *prog;
+    const uint32_t *prog32;
+    const ChildRef *child;
+    const float *leaf_value;
+    const int32_t *leaf_node;
+    const TreeMeta *tree;
+    const double *col_trees;
+    const float *base;
+    int32_t n_trees, n_features, n_outputs, leaf_width;
+    int32_t aggregate, transform, output, kind;
+    int32_t max_words;
+    int32_t path;            // PATH_LDS / PATH_REG / PATH_RANK
+    int32_t reg_nv, reg_r;   // REG family: 32 * reg_nv feature registers, reg_r rows per lane
+    // RANK family
+    int32_t rank_regs;
+    int32_t lds_waves;  // LDS rank family: wavefronts per workgroup
+    int32_t wave_tree[RANKLDS_WAVES_WIDE + 1];  // and the trees of each wave when the launch is not split
+    const FeatBucket *feat_bucket;
+    const int32_t *bucket_start;
+    const float *thr_sorted;
+    const int32_t *feat_thr_base;
+    const int32_t *feat_vfirst;
+    const FastLookup *fast_feat;  // [n_features] fast lookups (forest_rank_common.hpp)
+    const uint16_t *fast_tab;
+    // Tree splitting for small batches: with n_splits > 1 the grid's y index selects a share of
+    // the trees and the kernels store raw fp64 partial sums to partial[(split * split_rows + row)
+    // * n_outputs + k] instead of finishing the row; reduce_splits() finishes.  Set per launch.
+    int32_t n_splits;
+    int64_t split_rows;
+    double *partial;
+    int64_t partial_capacity;  // doubles available at `partial`
+    int64_t n_entries;         // entries of the split program, all trees (padding included)
+    // Rank families, split launches: the rank tiles ([tile][rank register][lane] packed f16 pairs)
+    // are computed once per row tile by forest_rank_tiles_kernel instead of by every workgroup.
+    uint32_t *rank_tiles;
+    // LDS rank family: large batches of models it fits run the register-bank kernel
+    BankDev bank;
+    WalkDev walk;
+    DeepDev deep;
+};
+
+// What a PackedModel says about its kernels; the device tables are left null.
+inline DevModel describe(const PackedModel &m)
+{
+    DevModel d{};
+    d.n_trees = m.n_trees;
+    d.n_features = m.n_features;
+    d.n_outputs = m.n_outputs;
+    d.leaf_width = m.leaf_width;
+    d.aggregate = m.aggregate;
+    d.transform = m.transform;
+    d.output = m.output;
+    d.kind = m.kind;
+    d.max_words = m.max_words;
+    d.path = m.path;
+    d.reg_nv = m.reg_nv;
+    d.reg_r = m.reg_r;
+    d.rank_regs = m.rank_regs;
+    d.lds_waves = m.lds_waves;
+    for (int w = 0; w <= RANKLDS_WAVES_WIDE; ++w) d.wave_tree[w] = m.wave_tree[w];
+    for (int w = 0; w < BANK_WAVES; ++w) d.bank.stream_base[w] = m.bank_stream_base[w];
+    d.bank.batches = m.bank_batches;
+    d.bank.max_units = m.bank_max_units;
+    d.bank.enabled = m.bank_enabled;
+    d.bank.passes = static_cast<int32_t>(m.bank_pass.size());
+    d.walk.depth = m.walk_depth;
+    d.walk.groups = m.walk_groups;
+    d.walk.stages = m.walk_stages;
+    d.deep.groups = m.deep_groups;
+    d.n_splits = 1;
+    d.n_entries = static_cast<int64_t>(m.prog32.size() > m.prog.size() ? m.prog32.size() : m.prog.size());
+    return d;
+}
+
+constexpr int PLAN_ROWS = 64;  // lanes per wavefront: rows go to workgroups in multiples of it
+
+// Batches below this many workgroups split the trees over several workgroups per row tile.
+constexpr int64_t SPLIT_BELOW_BLOCKS = 512;
+// A split launch aims at about this many workgroups in all and gives every wave whole trees of
+// at least this many program entries together.
+constexpr int64_t SPLIT_TARGET_BLOCKS = 1024;
+constexpr int64_t SPLIT_MIN_ENTRIES_PER_WAVE = 512;
+// Walk kernels: workgroups of 16 waves, two per CU, and the copies of trees to LDS that a split launch
+// leaves a wave at least.
+constexpr int64_t WALK_RESIDENT = 512;
+constexpr int64_t WALK_SPLIT_MIN_COPIES = 2;
+
+// Device memory a split launch (small batch) needs besides the inputs and outputs: the tree
+// shares' fp64 partial sums and, for the rank families, the rank tiles of the batch.
+struct Workspace {
+    double *partial = nullptr;
+    int64_t partial_doubles = 0;
+    uint32_t *rank_tiles = nullptr;
+    int64_t rank_tile_words = 0;
+};
+
+// Bytes of the rank tiles of `tiles` row tiles, and doubles of partial sums that never limit a split launch.
+inline size_t rank_tile_bytes(int rank_regs, int64_t tiles)
+{
+    const size_t b = sizeof(uint32_t) * 64 * static_cast<size_t>(rank_regs > 0 ? rank_regs : 0) * static_cast<size_t>(tiles);
+    return (b + 255) & ~size_t{255};
+}
+
+inline int64_t split_workspace_doubles(int n_outputs)
+{
+    // splits x rows stays below (SPLIT_TARGET_BLOCKS + SPLIT_BELOW_BLOCKS) workgroups x 128 rows
+    const int64_t want = (SPLIT_TARGET_BLOCKS + SPLIT_BELOW_BLOCKS) * 128 * n_outputs;
+    const int64_t cap = int64_t{4} << 20;  // 32 MB
+    return want < cap ? want : cap;
+}
+
+// Rows one workgroup of the model's dense kernel owns, and its number of wavefronts.
+inline int family_rows_per_block(const DevModel &m)
+{
+    if (m.path == PATH_RANK || m.path == PATH_RANK_LDS) return 128;
+    if (m.path == PATH_REG) return PLAN_ROWS * m.reg_r;
+    return PLAN_ROWS;
+}
+
+inline int family_waves_per_block(const DevModel &m) { return m.path == PATH_RANK_LDS ? m.lds_waves : 4; }
+
+// How many shares the trees are cut into for a batch of n_rows rows (1 = no split); `fits`
+// tells whether the workspace allowed the split the batch asks for.
+inline int choose_splits(const DevModel &m, const Workspace *ws, int64_t n_rows, bool needs_sums, bool &fits)
+{
+    fits = true;
+    const int64_t rb = family_rows_per_block(m);
+    const int64_t n_blocks = (n_rows + rb - 1) / rb;
+    if (n_blocks >= SPLIT_BELOW_BLOCKS) return 1;
+    const int64_t per_tree = m.n_trees > 0 ? (m.n_entries + m.n_trees - 1) / m.n_trees : 1;
+    const int64_t trees_per_wave = (SPLIT_MIN_ENTRIES_PER_WAVE + per_tree - 1) / (per_tree > 0 ? per_tree : 1);
+    int64_t s = m.n_trees / (family_waves_per_block(m) * (trees_per_wave > 0 ? trees_per_wave : 1));
+    const int64_t by_grid = (SPLIT_TARGET_BLOCKS + n_blocks - 1) / n_blocks;
+    if (by_grid < s) s = by_grid;
+    if (s < 2) return 1;  // the model is too small to be worth cutting
+    const bool ranks = m.path == PATH_RANK || m.path == PATH_RANK_LDS;
+    const int64_t tile_words = ranks ? n_blocks * m.rank_regs * 64 : 0;
+    if (tile_words > (ws ? ws->rank_tile_words : 0)) {
+        fits = false;
+        return 1;
+    }
+    if (needs_sums) {
+        const int64_t by_ws = (ws ? ws->partial_doubles : 0) / (n_rows * m.n_outputs);
+        if (by_ws < s) s = by_ws;
+        if (s < 2) {
+            fits = false;
+            return 1;
+        }
+    }
+    return static_cast<int>(s);
+}
+
+// The same for the models of the walk kernels, whose workgroups own 64 rows or more: as many shares
+// as fill the chip's workgroups once, each of its waves left two copies of trees to LDS or more.
+// (Against the dense kernels' shares with their rank tiles: 10,007 rows of 250 trees of depth 8, 64 features:
+// 63.6 -> 21.5 us a call; 1,021 rows of 2000 x depth 6, 128 features: 39.3 -> 22.4.  Half as many shares: 18.5
+// and 20.9 with a costly reduction, the same as now since it is cheap; at least 1 or 4 copies: no difference.)
+inline int choose_walk_splits(const DevModel &m, const Workspace *ws, int64_t n_rows, bool needs_sums)
+{
+    const int64_t n_blocks = (n_rows + PLAN_ROWS - 1) / PLAN_ROWS;
+    const int64_t copies = m.walk.depth > 0 ? m.walk.stages : m.n_trees;
+    // leaf ids are dealt four trees at a time
+    const int64_t waves = needs_sums ? copies / WALK_SPLIT_MIN_COPIES : (m.n_trees + 3) / 4;
+    int64_t s = WALK_RESIDENT / n_blocks;
+    if (waves / WALK_WAVES < s) s = waves / WALK_WAVES;
+    if (needs_sums && s > 1) {
+        const int64_t by_ws = (ws ? ws->partial_doubles : 0) / (n_rows * m.n_outputs);
+        if (by_ws < s) s = by_ws;
+    }
+    return s < 2 ? 1 : static_cast<int>(s);
+}
+
+// Row groups per workgroup.  More rows per workgroup amortise the copies of the trees to LDS (per
+// 64 rows, depth 6: 1, 1.07 and 1.25 of the time with 4, 2 and 1 groups), fewer leave smaller
+// batches enough workgroups; the last round of workgroups counts whole.
+inline int choose_walk_groups(const DevModel &m, int64_t n_rows, int n_splits)
+{
+    int best = 1;
+    double best_cost = 0.0;
+    for (int g = m.walk.groups; g >= 1; g /= 2) {
+        const int64_t blocks = (n_rows + PLAN_ROWS * g - 1) / (PLAN_ROWS * g) * n_splits;
+        const double cost = static_cast<double>((blocks + WALK_RESIDENT - 1) / WALK_RESIDENT) * g * (g == 4 ? 1.0 : g == 2 ? 1.07 : 1.25);
+        if (g == m.walk.groups || cost < best_cost) {
+            best = g;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+// Whether two workgroups fit a CU.
+inline bool deep_shares_cu(const DevModel &m, int groups)
+{
+    return deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups) <= CU_LDS_BYTES / 2;
+}
+
+// Row groups per workgroup: two rows per lane share the copies of the trees' tops and keep twice as
+// many walks in flight (300 irregular trees, 90 features, 103,069 rows: 94 us with two, 108 with one);
+// one leaves a small batch more workgroups.  The last round of workgroups counts whole.
+inline int choose_deep_groups(const DevModel &m, int64_t n_rows, int n_splits)
+{
+    if (m.deep.groups == 1) return 1;
+    double cost[2];
+    for (int g = 1; g <= 2; ++g) {
+        const int64_t per_cu = deep_shares_cu(m, g) ? 2 : 1;
+        const int64_t blocks = (n_rows + PLAN_ROWS * g - 1) / (PLAN_ROWS * g) * n_splits, round = 256 * per_cu;
+        cost[g - 1] = static_cast<double>((blocks + round - 1) / round * per_cu * g) * (g == 1 ? 1.15 : 1.0);
+    }
+    return cost[0] < cost[1] ? 1 : 2;
+}
+
+// One lane per (row, tree): the smallest batches of the walk kernels' models (forest_kernels_split.hip).
+// Up to a million tests the gathers take less than what a walk kernel's workgroups begin and end with.
+// Microseconds a call, this kernel / walk kernels with their reduction, 500 trees of depth 8: 1 row 5.2 / 10.4,
+// 64 rows 7.4 / 10.7, 256 rows 8.8 / 10.8, 1,024 rows 19.8 / 10.6; 2000 x depth 6, 10 columns: 64 rows 11.3 / 14.1,
+// 256 rows 17.7 / 14.4.  Ten trees of depth 4, which the walk kernels take in one launch: 1,000 rows 6.0 / 6.6,
+// 8,000 rows 6.2 / 6.6, 30,000 rows 10.0 / 6.9.
+constexpr int64_t POINT_MAX_TESTS = 1 << 20;  // rows x trees x depth
+constexpr int64_t POINT_MAX_ROWS = 8192;
+constexpr size_t POINT_MAX_LDS = 64 * 1024;
+constexpr int PT_THREADS = 1024, PT_MAX_ROWS = 16;
+
+inline int point_rows(const DevModel &m)
+{
+    const int rows = PT_THREADS / (m.n_trees > 0 ? m.n_trees : 1);
+    return rows < 1 ? 1 : rows > PT_MAX_ROWS ? PT_MAX_ROWS : rows;
+}
+
+inline size_t point_lds_bytes(const DevModel &m)
+{
+    return static_cast<size_t>(point_rows(m)) * (sizeof(double) * (m.n_outputs + 1) + sizeof(float) * (static_cast<size_t>(m.n_trees) + m.n_features));
+}
+
+inline int point_threads(const DevModel &m)
+{
+    const int64_t pairs = static_cast<int64_t>(point_rows(m)) * m.n_trees;
+    return pairs >= PT_THREADS ? PT_THREADS : static_cast<int>((pairs + PLAN_ROWS - 1) / PLAN_ROWS * PLAN_ROWS);
+}
+
+inline bool takes_point(const DevModel &m, int64_t n_rows)
+{
+    return m.walk.depth > 0 && n_rows <= POINT_MAX_ROWS && n_rows * m.n_trees * m.walk.depth <= POINT_MAX_TESTS && point_lds_bytes(m) <= POINT_MAX_LDS;
+}
+
+// Rows of one launch at most.  HIP takes fewer than 2^32 threads per grid axis, and the walk kernels spend
+// 1024 threads on 64 rows, the LDS rank kernel up to 768 on 128: a longer batch goes in ranges of this many
+// rows, one launch each.
+constexpr int64_t MAX_LAUNCH_ROWS = int64_t{1} << 27;
+
+struct LaunchPlan {
+    int32_t kernel = FOREST_KERNEL_LDS;
+    int32_t groups = 1;  // walk kernels: row groups of 64 rows per workgroup
+    int32_t splits = 1;  // shares the trees are cut into
+    bool fits = true;    // false: the dense kernels' split launch does not fit the workspace
+};
+
+// `sums`: scores or labels are asked for, not leaf ids.  A batch the dense kernels' workspace does not hold is
+// marked so whichever kernel runs it: what forest_predict_static takes does not depend on the kernel.
+inline LaunchPlan plan_launch(const DevModel &m, const Workspace *ws, int64_t n_rows, bool sums)
+{
+    LaunchPlan p;
+    p.splits = choose_splits(m, ws, n_rows, sums, p.fits);
+    if (takes_point(m, n_rows)) {
+        p.kernel = FOREST_KERNEL_POINT;
+        p.splits = 1;
+    } else if (m.walk.depth > 0) {
+        p.kernel = FOREST_KERNEL_WALK;
+        p.splits = choose_walk_splits(m, ws, n_rows, sums);
+        p.groups = choose_walk_groups(m, n_rows, p.splits);
+    } else if (m.deep.groups > 0) {
+        // trees deeper than 8, vector leaves, infinite thresholds: what a row does not meet is not tested
+        // (128 trees of depth 12: 2.9 ms against 14.5 with the register-bank kernel)
+        p.kernel = FOREST_KERNEL_DEEP;
+        p.splits = choose_walk_splits(m, ws, n_rows, sums);
+        p.groups = choose_deep_groups(m, n_rows, p.splits);
+    } else if (m.path == PATH_RANK) {
+        p.kernel = FOREST_KERNEL_RANK;
+    } else if (m.path == PATH_RANK_LDS) {
+        // large batches of the models it fits: rank registers banked over the waves' vector registers
+        p.kernel = p.splits == 1 && m.bank.enabled ? FOREST_KERNEL_RANK_BANK : FOREST_KERNEL_RANK_LDS;
+    } else if (m.path == PATH_REG) {
+        p.kernel = FOREST_KERNEL_REG;
+    }
+    return p;
+}
+
+// The shape of the launches of a plan.
+inline forest_launch_t launch_shape(const DevModel &m, const LaunchPlan &p, int64_t n_rows)
+{
+    forest_launch_t s{};
+    s.kernel = p.kernel;
+    s.shares = p.splits;
+    switch (p.kernel) {
+        case FOREST_KERNEL_POINT:
+            s.rows_per_workgroup = point_rows(m);
+            s.threads = point_threads(m);
+            break;
+        case FOREST_KERNEL_WALK:
+            s.rows_per_workgroup = PLAN_ROWS * p.groups;
+            s.threads = PLAN_ROWS * WALK_WAVES;
+            break;
+        case FOREST_KERNEL_DEEP:
+            s.rows_per_workgroup = PLAN_ROWS * p.groups;
+            s.threads = PLAN_ROWS * DEEP_WAVES;
+            break;
+        case FOREST_KERNEL_RANK_BANK:
+            s.rows_per_workgroup = BANK_ROWS;
+            s.threads = PLAN_ROWS * BANK_WAVES;
+            break;
+        default:
+            s.rows_per_workgroup = family_rows_per_block(m);
+            s.threads = PLAN_ROWS * family_waves_per_block(m);
+    }
+    s.launches = static_cast<int32_t>((n_rows + MAX_LAUNCH_ROWS - 1) / MAX_LAUNCH_ROWS);
+    const int64_t rows = n_rows < MAX_LAUNCH_ROWS ? n_rows : MAX_LAUNCH_ROWS;
+    s.workgroups = (rows + s.rows_per_workgroup - 1) / s.rows_per_workgroup;
+    return s;
+}
+
+}  // namespace forest_impl

@@ -1,0 +1,61 @@
+"""What a call launches: batches longer than one launch may be, and the kernels that calls reach."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from test_gpu_parity import _full_forest
+
+HIP_MAX_THREADS = 1 << 32  # threads per grid axis, exclusive
+
+
+def _vector_forest(outputs, features=1, trees=5):
+    return wl.random_forest(17 + outputs, n_trees=trees, n_features=features, max_depth=9, stop_prob=0.3, n_outputs=outputs,
+                            leaf_width=outputs, aggregate=wl.AGG_MEAN, transform=wl.TRANSFORM_NONE)
+
+
+@pytest.mark.parametrize("rows", [1, 8192, 1 << 27, (1 << 27) + 1, 1 << 28, 600_000_000, 10**9])
+@pytest.mark.parametrize("what", ["vector3", "vector2", "columns", "one_column", "wide", "ranklds", "lds"])
+def test_no_launch_asks_for_more_threads_than_hip_takes(what, rows):
+    from paper_2301_13441_amd import binding
+    f = {"vector3": lambda: _vector_forest(3), "vector2": lambda: _vector_forest(2),
+         "columns": lambda: _full_forest(1, 12, 5, 4, n_outputs=2), "one_column": lambda: _full_forest(1, 12, 8, 2),
+         "wide": lambda: _full_forest(1, 12, 5, 600), "ranklds": lambda: _vector_forest(17, 9),
+         "lds": lambda: _vector_forest(20, 300, 96)}[what]()
+    for leaves in (False, True):
+        s = binding.forest_packed_launch(f, rows, leaves)
+        assert s["workgroups"] * s["threads"] < HIP_MAX_THREADS
+        assert s["launches"] * s["workgroups"] * s["rows_per_workgroup"] >= rows
+        assert s["launches"] == 1 or s["shares"] == 1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what", ["vector3", "walk"])
+def test_batches_longer_than_a_launch(what):
+    """268 million rows and a ragged rest: the first rows, the last ones and those on both sides of every border
+    between two launches, scores, labels and leaf ids."""
+    import torch
+    import paper_2301_13441_amd as pk
+    from paper_2301_13441_amd import binding
+    f = _vector_forest(3) if what == "vector3" else _full_forest(9, 3, 5, 1, n_outputs=2)
+    n = (1 << 28) + 77
+    xd = torch.empty((n, 1), dtype=torch.float32, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    for at in range(0, n, 1 << 26):
+        xd[at:at + (1 << 26)].normal_(generator=gen)
+    border = [b + i for b in (1 << 26, 1 << 27, 3 << 26, 1 << 28) for i in range(-70, 70) if b + i < n]
+    pick = np.unique(np.concatenate([np.arange(300), border, np.arange(n - 300, n),
+                                     np.random.default_rng(1).integers(0, n, 3000)]))
+    idx = torch.from_numpy(pick).cuda()
+    ref = oracle.predict(f, xd[idx].cpu().numpy(), want_leaves=True, n_threads=8)
+    model = pk.forest_load(f)
+    try:
+        s = binding.forest_launch(model, n)
+        assert s["launches"] == 3 and s["kernel"] == ("deep" if what == "vector3" else "walk")
+        scores, labels = model.predict(xd)
+        np.testing.assert_array_equal(labels[idx].cpu().numpy(), ref.labels)
+        np.testing.assert_allclose(scores[idx].cpu().numpy(), ref.scores, rtol=1e-5, atol=1e-6)
+        del scores, labels
+        np.testing.assert_array_equal(model.predict_leaves(xd)[idx].cpu().numpy(), ref.leaf_node_id)
+    finally:
+        model.close()
