@@ -147,6 +147,13 @@ int forest_pack_view(const forest_packed *p, forest_packed_view *view);
 void forest_pack_free(forest_packed *p);
 
 /*
+ * forest_load and forest_pack without the walk programs, so that the dense kernels run the model whatever its
+ * shape: their tests would otherwise reach them only through the models that the walk kernels decline.
+ */
+int forest_load_dense(const forest_desc *desc, forest **out);
+int forest_pack_dense(const forest_desc *desc, forest_packed **out);
+
+/*
  * What a call launches for n_rows rows (leaves: leaf ids, else scores and labels), so that a test can see that it
  * reaches the kernel it is about.  forest_launch: of a loaded model; forest_packed_launch: of a packed one, no GPU
  * needed, with the workspace that a handle gives its calls.  Returns FOREST_OK, FOREST_EINVAL (null pointer, n_rows

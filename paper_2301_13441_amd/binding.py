@@ -74,7 +74,8 @@ EXPORTS = ["forest_load", "forest_free", "forest_info", "forest_out_bytes", "for
            "forest_predict", "forest_predict_static", "forest_predict_leaves", "forest_strerror"]
 # include/forest_testing.h: host-only views into the model compiler, for its tests
 TESTING_EXPORTS = ["forest_pack", "forest_pack_view", "forest_pack_free", "forest_rank_code",
-                   "forest_staged_position", "forest_probe_compare_rate", "forest_launch", "forest_packed_launch"]
+                   "forest_staged_position", "forest_probe_compare_rate", "forest_launch", "forest_packed_launch",
+                   "forest_load_dense", "forest_pack_dense"]
 
 
 def lib_path() -> str:
@@ -91,8 +92,9 @@ def load_library():
             f"{_LIB_PATH} is missing: build it with `python -m paper_2301_13441_amd.build` "
             "(there is no CPU fallback)")
     lib = ctypes.CDLL(_LIB_PATH)
-    lib.forest_load.restype = ctypes.c_int
-    lib.forest_load.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(_p)]
+    for fn in (lib.forest_load, lib.forest_load_dense, lib.forest_pack, lib.forest_pack_dense):
+        fn.restype = ctypes.c_int
+        fn.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(_p)]
     lib.forest_free.restype = None
     lib.forest_free.argtypes = [_p]
     lib.forest_info.restype = ctypes.c_int
@@ -107,8 +109,6 @@ def load_library():
     lib.forest_predict_static.argtypes = [_p, _p, _i64, _p, _p]
     lib.forest_predict_leaves.restype = ctypes.c_int
     lib.forest_predict_leaves.argtypes = [_p, _p, _i64, _p, _p]
-    lib.forest_pack.restype = ctypes.c_int
-    lib.forest_pack.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(_p)]
     lib.forest_pack_view.restype = ctypes.c_int
     lib.forest_pack_view.argtypes = [_p, ctypes.POINTER(_View)]
     lib.forest_pack_free.restype = None
@@ -294,12 +294,12 @@ def forest_launch(f, n_rows: int, leaves: bool = False) -> dict:
     return _launch(f._lib.forest_launch, f._h, "forest_launch", n_rows, leaves)
 
 
-def forest_packed_launch(forest, n_rows: int, leaves: bool = False) -> dict:
-    """The same for a model that is only packed: no GPU needed."""
+def forest_packed_launch(forest, n_rows: int, leaves: bool = False, dense: bool = False) -> dict:
+    """The same for a model that is only packed (dense: by forest_pack_dense): no GPU needed."""
     lib = load_library()
     d, keep = _desc_from(forest)
     h = _p()
-    rc = lib.forest_pack(ctypes.byref(d), ctypes.byref(h))
+    rc = (lib.forest_pack_dense if dense else lib.forest_pack)(ctypes.byref(d), ctypes.byref(h))
     if rc != 0:
         raise ForestError(rc, "forest_pack")
     try:
@@ -454,10 +454,19 @@ class Forest:
 
 def forest_load(forest) -> Forest:
     """forest_load: validate, pack and upload to the current HIP device."""
+    return _load(forest, "forest_load")
+
+
+def forest_load_dense(forest) -> Forest:
+    """The same without the walk programs (include/forest_testing.h): the dense kernels run the model."""
+    return _load(forest, "forest_load_dense")
+
+
+def _load(forest, what) -> Forest:
     lib = load_library()
     d, keep = _desc_from(forest)
     h = _p()
-    rc = lib.forest_load(ctypes.byref(d), ctypes.byref(h))
+    rc = getattr(lib, what)(ctypes.byref(d), ctypes.byref(h))
     if rc != 0:
-        raise ForestError(rc, "forest_load")
+        raise ForestError(rc, what)
     return Forest(h, lib)

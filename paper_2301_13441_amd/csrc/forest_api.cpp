@@ -115,14 +115,14 @@ int check_device(const forest *f)
 
 extern "C" {
 
-int forest_load(const forest_desc *desc, forest **out)
+static int load(const forest_desc *desc, forest **out, bool dense_only)
 {
     if (!desc || !out) return FOREST_EINVAL;
     forest *f = new (std::nothrow) forest;
     if (!f) return FOREST_ENOMEM;
     int rc;
     try {
-        rc = compile_forest(*desc, f->host);
+        rc = compile_forest(*desc, f->host, dense_only);
     } catch (const std::bad_alloc &) {
         rc = FOREST_ENOMEM;
     }
@@ -295,6 +295,10 @@ int forest_load(const forest_desc *desc, forest **out)
     *out = f;
     return FOREST_OK;
 }
+
+int forest_load(const forest_desc *desc, forest **out) { return load(desc, out, false); }
+
+int forest_load_dense(const forest_desc *desc, forest **out) { return load(desc, out, true); }
 
 void forest_free(forest *f)
 {

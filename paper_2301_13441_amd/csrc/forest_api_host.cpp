@@ -14,14 +14,14 @@ struct forest_packed {
 
 extern "C" {
 
-int forest_pack(const forest_desc *desc, forest_packed **out)
+static int pack(const forest_desc *desc, forest_packed **out, bool dense_only)
 {
     if (!desc || !out) return FOREST_EINVAL;
     forest_packed *p = new (std::nothrow) forest_packed;
     if (!p) return FOREST_ENOMEM;
     int rc;
     try {
-        rc = compile_forest(*desc, p->m);
+        rc = compile_forest(*desc, p->m, dense_only);
     } catch (const std::bad_alloc &) {
         rc = FOREST_ENOMEM;
     }
@@ -32,6 +32,10 @@ int forest_pack(const forest_desc *desc, forest_packed **out)
     *out = p;
     return FOREST_OK;
 }
+
+int forest_pack(const forest_desc *desc, forest_packed **out) { return pack(desc, out, false); }
+
+int forest_pack_dense(const forest_desc *desc, forest_packed **out) { return pack(desc, out, true); }
 
 int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out)
 {

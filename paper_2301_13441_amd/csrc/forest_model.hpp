@@ -424,7 +424,8 @@ inline size_t plain_lds_bytes(int n_features, int n_outputs, bool staged)
     return b;
 }
 
-// Validates `d` and fills `out`.  Returns FOREST_OK or a negative FOREST_E* code.
-int compile_forest(const forest_desc &d, PackedModel &out);
+// Validates `d` and fills `out`.  Returns FOREST_OK or a negative FOREST_E* code.  With `dense_only` the model gets
+// no walk program, so that the dense kernels run it (forest_testing.h).
+int compile_forest(const forest_desc &d, PackedModel &out, bool dense_only = false);
 
 }  // namespace forest_impl

@@ -374,7 +374,7 @@ static void build_deep(const forest_desc &d, const std::vector<TreeShape> &shape
     m.deep_position = std::move(p.deep_position);
 }
 
-int compile_forest(const forest_desc &d, PackedModel &m)
+int compile_forest(const forest_desc &d, PackedModel &m, bool dense_only)
 {
     if (int rc = check_desc(d)) return rc;
     const int32_t T = d.n_trees, K = d.n_outputs, W = d.leaf_width;
@@ -708,8 +708,10 @@ int compile_forest(const forest_desc &d, PackedModel &m)
         }
         m.tree.push_back(tm);
     }
-    build_walk(d, shape, order, m);
-    build_deep(d, shape, order, m);
+    if (!dense_only) {
+        build_walk(d, shape, order, m);
+        build_deep(d, shape, order, m);
+    }
     if (m.path == PATH_RANK_LDS) balance_waves(m);
     if (m.path == PATH_RANK_LDS && m.kind == KIND_GENERIC && m.rank_regs >= 1 &&
         m.rank_regs <= BANK_WAVES * BANK_REGS && ((K == 1 && W == 1) || (W == K && K <= 2))) {
