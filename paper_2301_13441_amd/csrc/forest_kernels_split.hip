@@ -119,7 +119,8 @@ __global__ __launch_bounds__(RS_THREADS) void forest_reduce_splits_kernel(DevMod
 // The smallest batches of the walk kernels' models: a lane is a (row, tree) pair and walks the tree through
 // global memory, so that a few rows still fill wavefronts and a call is one launch.  A workgroup owns
 // `rows` rows, whose features it holds in LDS; the leaf values meet there, [row][tree], and a wave adds
-// those of a (row, column), whose trees are neighbours in processing order.  What bounds it is the chain of
+// those of a (row, column), whose trees are neighbours in processing order, or, where there are more sums
+// than waves, a part of a wave does.  What bounds it is the chain of
 // dependent loads, one per level, and for more pairs the gathers: a cycle of the texture path per lane.
 
 
@@ -132,11 +133,19 @@ __global__ __launch_bounds__(PT_THREADS) void forest_point_kernel(DevModel m, co
     double *sum = reinterpret_cast<double *>(smem);                       // [rows][K]
     double *by_row = sum + rows * K;                                      // [rows]
     float *value = reinterpret_cast<float *>(by_row + rows);              // [rows][T]
-    float *xs = LEAVES ? reinterpret_cast<float *>(smem) : value + rows * T;  // [rows][F]
+    int32_t *first = reinterpret_cast<int32_t *>(value + rows * T);       // [K + 1] the columns' first trees
+    float *xs = LEAVES ? reinterpret_cast<float *>(smem) : reinterpret_cast<float *>(first + K + 1);  // [rows][F]
     const int64_t row0 = static_cast<int64_t>(blockIdx.x) * rows;
     const int here = n_rows - row0 < rows ? static_cast<int>(n_rows - row0) : rows;
     const int threads = static_cast<int>(blockDim.x);
     for (int i = threadIdx.x; i < here * F; i += threads) xs[i] = X[row0 * F + i];
+    if (!LEAVES && threadIdx.x == 0) {
+        int n = 0;  // the columns' trees follow each other; counts are small integers
+        for (int k = 0; k <= K; ++k) {
+            first[k] = n;
+            if (k < K) n += static_cast<int>(((ColumnTrees)m.col_trees)[k]);
+        }
+    }
     __syncthreads();
     const int shift = 8 + (m.walk.groups >> 1);  // x_offset = feature * 256 * groups, groups 1, 2 or 4
     for (int p = threadIdx.x; p < here * T; p += threads) {
@@ -154,18 +163,17 @@ __global__ __launch_bounds__(PT_THREADS) void forest_point_kernel(DevModel m, co
     }
     if (LEAVES) return;
     __syncthreads();
-    const int lane = threadIdx.x & (TILE - 1);
-    for (int p = uniform(threadIdx.x >> 6); p < rows * K; p += threads / TILE) {
+    // As many lanes per sum as there are threads for, a wave at most.  (Ten trees of five columns, 1,000 rows: 80 sums
+    // for three waves, 15.5 us a call with a wave per sum, 4.5 so.)
+    int lanes = TILE;
+    while (lanes > 1 && rows * K * lanes > threads) lanes >>= 1;
+    const int lane = threadIdx.x & (lanes - 1);
+    for (int p = threadIdx.x / lanes; p < rows * K; p += threads / lanes) {
         const int r = p / K, k = p - r * K;
         double s = 0.0;
-        if (r < here) {
-            int first = 0;  // the columns' trees follow each other; counts are small integers
-            for (int c = 0; c < k; ++c) first += static_cast<int>(m.col_trees[c]);
-            const int n = static_cast<int>(m.col_trees[k]);
-            for (int t = lane; t < n; t += TILE) s += static_cast<double>(value[r * T + first + t]);
-        }
-#pragma unroll
-        for (int d = TILE / 2; d >= 1; d >>= 1) s += __shfl_xor(s, d, TILE);
+        if (r < here)
+            for (int t = first[k] + lane; t < first[k + 1]; t += lanes) s += static_cast<double>(value[r * T + t]);
+        for (int d = lanes >> 1; d >= 1; d >>= 1) s += __shfl_xor(s, d, TILE);
         if (lane == 0) sum[p] = s;
     }
     __syncthreads();

@@ -277,7 +277,8 @@ inline int point_rows(const DevModel &m)
 
 inline size_t point_lds_bytes(const DevModel &m)
 {
-    return static_cast<size_t>(point_rows(m)) * (sizeof(double) * (m.n_outputs + 1) + sizeof(float) * (static_cast<size_t>(m.n_trees) + m.n_features));
+    return static_cast<size_t>(point_rows(m)) * (sizeof(double) * (m.n_outputs + 1) + sizeof(float) * (static_cast<size_t>(m.n_trees) + m.n_features)) +
+           sizeof(int32_t) * (m.n_outputs + 1);
 }
 
 inline int point_threads(const DevModel &m)

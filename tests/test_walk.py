@@ -92,7 +92,8 @@ def test_walk_kernels(depth, features, outputs, full):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("depth,trees,features,outputs", [(3, 1, 2, 1), (8, 500, 28, 1), (6, 2000, 128, 10), (7, 65, 300, 4), (4, 10, 9, 3)])
+@pytest.mark.parametrize("depth,trees,features,outputs", [(3, 1, 2, 1), (8, 500, 28, 1), (6, 2000, 128, 10), (7, 65, 300, 4), (4, 10, 9, 3),
+                                                          (5, 10, 10, 5), (3, 5, 4, 32), (4, 40, 7, 31)])
 def test_smallest_batches_with_a_lane_per_row_and_tree(depth, trees, features, outputs):
     """One row, whole and ragged workgroups of rows, more pairs than threads, and the first batches beyond
     the kernel's limit on rows and on tests."""
