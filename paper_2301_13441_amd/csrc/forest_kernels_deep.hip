@@ -365,7 +365,8 @@ KernelFn pick_mode(int groups, int mode, int width)
         case 2: return two ? forest_deep_kernel<2, DEEP_VECTOR, 2, SHARED> : forest_deep_kernel<1, DEEP_VECTOR, 2, SHARED>;
         case 4: return forest_deep_kernel<1, DEEP_VECTOR, 4, SHARED>;
         case 8: return forest_deep_kernel<1, DEEP_VECTOR, 8, SHARED>;
-        default: return forest_deep_kernel<1, DEEP_VECTOR, 16, SHARED>;
+        case 12: return forest_deep_kernel<1, DEEP_VECTOR, 12, SHARED>;  // shared: 9-wide leaves, whose sums let two workgroups on a CU
+        default: return forest_deep_kernel<1, DEEP_VECTOR, 16, false>;   // 13 columns of 16 waves' sums take more than half a CU's LDS
     }
 }
 
@@ -379,7 +380,7 @@ KernelFn pick(int groups, int mode, int width, bool shared)
 hipError_t init_deep_kernels(size_t lds_limit)
 {
     for (int mode : {DEEP_COLUMN, DEEP_COLUMNS, DEEP_VECTOR, DEEP_LEAVES})
-        for (int width : {2, 4, 8, 16})
+        for (int width : {2, 4, 8, 12, 16})
             for (int groups : {1, 2})
                 for (bool shared : {true, false}) {
                     const void *fn = reinterpret_cast<const void *>(pick(groups, mode, width, shared));

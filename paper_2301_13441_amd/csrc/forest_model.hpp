@@ -306,7 +306,7 @@ constexpr int DEEP_TOP_WORDS = 2 << DEEP_TOP;  // 8-byte words of a tree's top: 
 constexpr size_t DEEP_STAGE_BYTES = sizeof(WalkNode) * DEEP_TOP_WORDS;  // per wave
 
 // Values a leaf holds in the kernels: the leaf width, rounded up.
-constexpr int deep_width(int leaf_width) { return leaf_width <= 2 ? leaf_width : leaf_width <= 4 ? 4 : leaf_width <= 8 ? 8 : 16; }
+constexpr int deep_width(int leaf_width) { return leaf_width <= 2 ? leaf_width : leaf_width <= 12 ? (leaf_width + 3) / 4 * 4 : 16; }
 
 // Row groups of 64 rows per workgroup: the sums of wide leaves take the registers of a second group.
 constexpr int deep_max_groups(int leaf_width) { return leaf_width > 2 ? 1 : 2; }

@@ -36,3 +36,17 @@ def test_failed_register_check_selects_the_conservative_form(monkeypatch, tmp_pa
 def test_streaming_form_passes_the_register_check():
     n = csr.check(hb.HIPCC, list(hb.FLAGS), os.path.join(hb.CSRC, hb.RANKLDS), hb.OBJ)
     assert n >= 1
+
+
+def test_walk_kernels_keep_everything_in_registers(tmp_path):
+    """No variant spills or uses scratch memory: a call would then need the runtime's scratch, and every spill is a
+    trip to memory in the walk's inner loop."""
+    for source in ("forest_kernels_walk.hip", "forest_kernels_deep.hip"):
+        asm = str(tmp_path / (source + ".s"))
+        subprocess.run([hb.HIPCC, *hb.FLAGS, "-x", "hip", "-S", "--cuda-device-only", os.path.join(hb.CSRC, source), "-o", asm],
+                       check=True, stderr=subprocess.DEVNULL)
+        text = open(asm).read()
+        sizes = re.findall(r"\.private_segment_fixed_size: (\d+)", text)
+        spills = re.findall(r"\.vgpr_spill_count: +(\d+)", text)
+        assert len(sizes) == len(spills) >= 20
+        assert set(sizes) == set(spills) == {"0"}, source
