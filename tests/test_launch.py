@@ -59,3 +59,21 @@ def test_batches_longer_than_a_launch(what):
         np.testing.assert_array_equal(model.predict_leaves(xd)[idx].cpu().numpy(), ref.leaf_node_id)
     finally:
         model.close()
+
+
+def test_shares_of_shallow_trees():
+    """A copy of depth-3 trees is 16 of them: a wave with one copy has work enough, if three shares come of it."""
+    from paper_2301_13441_amd import binding
+    shares = lambda trees, depth: binding.forest_packed_launch(_full_forest(3, trees, depth, 10), 3000)["shares"]
+    assert shares(1000, 3) == shares(1000, 1) == 3 and shares(768, 3) == 3
+    assert shares(700, 3) == 1 and shares(300, 4) == 1 and shares(1000, 4) == 3
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("trees,outputs", [(768, 1), (1000, 5), (2000, 3)])
+def test_shares_of_shallow_trees_against_the_oracle(trees, outputs):
+    from test_gpu_parity import _check
+    rng = np.random.default_rng(trees)
+    f = _full_forest(trees, trees, 3, 10, n_outputs=outputs)
+    for rows in (517, 3000):
+        _check(f, rng.standard_normal((rows, 10)).astype(np.float32), leaves=False)
