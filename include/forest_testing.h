@@ -147,11 +147,14 @@ int forest_pack_view(const forest_packed *p, forest_packed_view *view);
 void forest_pack_free(forest_packed *p);
 
 /*
- * forest_load and forest_pack without the walk programs, so that the dense kernels run the model whatever its
- * shape: their tests would otherwise reach them only through the models that the walk kernels decline.
+ * forest_load and forest_pack with the choice between a model's two forms made by the caller: tests reach either
+ * form's kernels with any model and batch, and the two can be timed against each other.  FOREST_FORM_DENSE leaves the
+ * walk programs out; FOREST_FORM_WALK has the walk kernels run every batch of a model they take.  FOREST_EINVAL for
+ * another form.
  */
-int forest_load_dense(const forest_desc *desc, forest **out);
-int forest_pack_dense(const forest_desc *desc, forest_packed **out);
+enum { FOREST_FORM_AUTO = 0, FOREST_FORM_DENSE = 1, FOREST_FORM_WALK = 2 };
+int forest_load_form(const forest_desc *desc, int32_t form, forest **out);
+int forest_pack_form(const forest_desc *desc, int32_t form, forest_packed **out);
 
 /*
  * What a call launches for n_rows rows (leaves: leaf ids, else scores and labels), so that a test can see that it

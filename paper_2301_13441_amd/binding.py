@@ -67,6 +67,7 @@ class _Launch(ctypes.Structure):
 
 
 _KERNELS = ("lds", "reg", "rank", "rank_lds", "rank_bank", "point", "walk", "deep")  # FOREST_KERNEL_*
+_FORMS = {"auto": 0, "dense": 1, "walk": 2}  # FOREST_FORM_*
 
 
 # include/forest.h: the inference ABI
@@ -75,7 +76,7 @@ EXPORTS = ["forest_load", "forest_free", "forest_info", "forest_out_bytes", "for
 # include/forest_testing.h: host-only views into the model compiler, for its tests
 TESTING_EXPORTS = ["forest_pack", "forest_pack_view", "forest_pack_free", "forest_rank_code",
                    "forest_staged_position", "forest_probe_compare_rate", "forest_launch", "forest_packed_launch",
-                   "forest_load_dense", "forest_pack_dense"]
+                   "forest_load_form", "forest_pack_form"]
 
 
 def lib_path() -> str:
@@ -92,9 +93,12 @@ def load_library():
             f"{_LIB_PATH} is missing: build it with `python -m paper_2301_13441_amd.build` "
             "(there is no CPU fallback)")
     lib = ctypes.CDLL(_LIB_PATH)
-    for fn in (lib.forest_load, lib.forest_load_dense, lib.forest_pack, lib.forest_pack_dense):
+    for fn in (lib.forest_load, lib.forest_pack):
         fn.restype = ctypes.c_int
         fn.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(_p)]
+    for fn in (lib.forest_load_form, lib.forest_pack_form):
+        fn.restype = ctypes.c_int
+        fn.argtypes = [ctypes.POINTER(_Desc), _i32, ctypes.POINTER(_p)]
     lib.forest_free.restype = None
     lib.forest_free.argtypes = [_p]
     lib.forest_info.restype = ctypes.c_int
@@ -294,14 +298,14 @@ def forest_launch(f, n_rows: int, leaves: bool = False) -> dict:
     return _launch(f._lib.forest_launch, f._h, "forest_launch", n_rows, leaves)
 
 
-def forest_packed_launch(forest, n_rows: int, leaves: bool = False, dense: bool = False) -> dict:
-    """The same for a model that is only packed (dense: by forest_pack_dense): no GPU needed."""
+def forest_packed_launch(forest, n_rows: int, leaves: bool = False, form: str = "auto") -> dict:
+    """The same for a model that is only packed (form: as in forest_load_form): no GPU needed."""
     lib = load_library()
     d, keep = _desc_from(forest)
     h = _p()
-    rc = (lib.forest_pack_dense if dense else lib.forest_pack)(ctypes.byref(d), ctypes.byref(h))
+    rc = lib.forest_pack_form(ctypes.byref(d), _FORMS[form], ctypes.byref(h))
     if rc != 0:
-        raise ForestError(rc, "forest_pack")
+        raise ForestError(rc, "forest_pack_form")
     try:
         return _launch(lib.forest_packed_launch, h, "forest_packed_launch", n_rows, leaves)
     finally:
@@ -454,19 +458,22 @@ class Forest:
 
 def forest_load(forest) -> Forest:
     """forest_load: validate, pack and upload to the current HIP device."""
-    return _load(forest, "forest_load")
-
-
-def forest_load_dense(forest) -> Forest:
-    """The same without the walk programs (include/forest_testing.h): the dense kernels run the model."""
-    return _load(forest, "forest_load_dense")
-
-
-def _load(forest, what) -> Forest:
     lib = load_library()
     d, keep = _desc_from(forest)
     h = _p()
-    rc = getattr(lib, what)(ctypes.byref(d), ctypes.byref(h))
+    rc = lib.forest_load(ctypes.byref(d), ctypes.byref(h))
     if rc != 0:
-        raise ForestError(rc, what)
+        raise ForestError(rc, "forest_load")
+    return Forest(h, lib)
+
+
+def forest_load_form(forest, form: str) -> Forest:
+    """The same with the choice between the model's two forms made by the caller (include/forest_testing.h): "dense",
+    "walk" or "auto"."""
+    lib = load_library()
+    d, keep = _desc_from(forest)
+    h = _p()
+    rc = lib.forest_load_form(ctypes.byref(d), _FORMS[form], ctypes.byref(h))
+    if rc != 0:
+        raise ForestError(rc, "forest_load_form")
     return Forest(h, lib)

@@ -115,14 +115,14 @@ int check_device(const forest *f)
 
 extern "C" {
 
-static int load(const forest_desc *desc, forest **out, bool dense_only)
+int forest_load_form(const forest_desc *desc, int32_t form, forest **out)
 {
-    if (!desc || !out) return FOREST_EINVAL;
+    if (!desc || !out || form < FOREST_FORM_AUTO || form > FOREST_FORM_WALK) return FOREST_EINVAL;
     forest *f = new (std::nothrow) forest;
     if (!f) return FOREST_ENOMEM;
     int rc;
     try {
-        rc = compile_forest(*desc, f->host, dense_only);
+        rc = compile_forest(*desc, f->host, form);
     } catch (const std::bad_alloc &) {
         rc = FOREST_ENOMEM;
     }
@@ -296,9 +296,7 @@ static int load(const forest_desc *desc, forest **out, bool dense_only)
     return FOREST_OK;
 }
 
-int forest_load(const forest_desc *desc, forest **out) { return load(desc, out, false); }
-
-int forest_load_dense(const forest_desc *desc, forest **out) { return load(desc, out, true); }
+int forest_load(const forest_desc *desc, forest **out) { return forest_load_form(desc, FOREST_FORM_AUTO, out); }
 
 void forest_free(forest *f)
 {

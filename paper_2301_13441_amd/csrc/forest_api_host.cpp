@@ -14,14 +14,14 @@ struct forest_packed {
 
 extern "C" {
 
-static int pack(const forest_desc *desc, forest_packed **out, bool dense_only)
+int forest_pack_form(const forest_desc *desc, int32_t form, forest_packed **out)
 {
-    if (!desc || !out) return FOREST_EINVAL;
+    if (!desc || !out || form < FOREST_FORM_AUTO || form > FOREST_FORM_WALK) return FOREST_EINVAL;
     forest_packed *p = new (std::nothrow) forest_packed;
     if (!p) return FOREST_ENOMEM;
     int rc;
     try {
-        rc = compile_forest(*desc, p->m, dense_only);
+        rc = compile_forest(*desc, p->m, form);
     } catch (const std::bad_alloc &) {
         rc = FOREST_ENOMEM;
     }
@@ -33,9 +33,7 @@ static int pack(const forest_desc *desc, forest_packed **out, bool dense_only)
     return FOREST_OK;
 }
 
-int forest_pack(const forest_desc *desc, forest_packed **out) { return pack(desc, out, false); }
-
-int forest_pack_dense(const forest_desc *desc, forest_packed **out) { return pack(desc, out, true); }
+int forest_pack(const forest_desc *desc, forest_packed **out) { return forest_pack_form(desc, FOREST_FORM_AUTO, out); }
 
 int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out)
 {

@@ -326,6 +326,8 @@ struct PackedModel {
     int32_t aggregate = 0, transform = 0, output = 0;
     int32_t kind = KIND_GENERIC;
     int32_t max_depth = 0;
+    int32_t form = 0;       // FOREST_FORM_*
+    int64_t sum_depth = 0;  // of the trees
     int32_t max_words = 0;  // largest TreeMeta::n_words
     // register-resident kernel family: features live in 32 * reg_nv vector registers per row
     // slot, reg_r row slots per lane; the split program then stores plain feature indices
@@ -424,8 +426,8 @@ inline size_t plain_lds_bytes(int n_features, int n_outputs, bool staged)
     return b;
 }
 
-// Validates `d` and fills `out`.  Returns FOREST_OK or a negative FOREST_E* code.  With `dense_only` the model gets
-// no walk program, so that the dense kernels run it (forest_testing.h).
-int compile_forest(const forest_desc &d, PackedModel &out, bool dense_only = false);
+// Validates `d` and fills `out`.  Returns FOREST_OK or a negative FOREST_E* code.  `form`: FOREST_FORM_*
+// (forest_testing.h).
+int compile_forest(const forest_desc &d, PackedModel &out, int32_t form = FOREST_FORM_AUTO);
 
 }  // namespace forest_impl

@@ -374,7 +374,7 @@ static void build_deep(const forest_desc &d, const std::vector<TreeShape> &shape
     m.deep_position = std::move(p.deep_position);
 }
 
-int compile_forest(const forest_desc &d, PackedModel &m, bool dense_only)
+int compile_forest(const forest_desc &d, PackedModel &m, int32_t form)
 {
     if (int rc = check_desc(d)) return rc;
     const int32_t T = d.n_trees, K = d.n_outputs, W = d.leaf_width;
@@ -383,6 +383,7 @@ int compile_forest(const forest_desc &d, PackedModel &m, bool dense_only)
     m.n_features = d.n_features;
     m.n_outputs = K;
     m.leaf_width = W;
+    m.form = form;
     m.aggregate = d.aggregate;
     m.transform = d.transform;
     m.output = d.output;
@@ -398,6 +399,7 @@ int compile_forest(const forest_desc &d, PackedModel &m, bool dense_only)
         if (int rc = analyse_tree(d, base, n, shape[t])) return rc;
         const TreeShape &s = shape[t];
         m.max_depth = std::max(m.max_depth, s.depth);
+        m.sum_depth += s.depth;
         m.n_internal += static_cast<int64_t>(s.internal.size());
         m.n_leaves += static_cast<int64_t>(s.leaves.size());
         if (!s.full) all_full = false;
@@ -708,7 +710,7 @@ int compile_forest(const forest_desc &d, PackedModel &m, bool dense_only)
         }
         m.tree.push_back(tm);
     }
-    if (!dense_only) {
+    if (form != FOREST_FORM_DENSE) {
         build_walk(d, shape, order, m);
         build_deep(d, shape, order, m);
     }

@@ -86,7 +86,85 @@ struct DevModel {
     BankDev bank;
     WalkDev walk;
     DeepDev deep;
+    // Picoseconds a row of a large batch takes in the walk kernels and in the dense ones (estimates, forest_plan.hpp);
+    // 0: no choice between them
+    float walk_ps, dense_ps;
 };
+
+// Walk kernels or dense kernels: a node on the path costs two LDS reads of the lane's own, a node of the tree half a
+// vector instruction, and beside them every tree costs the walk kernels its copy to LDS (and those deeper than the top
+// DEEP_TOP levels whatever its depth) and a lane's row its place in LDS, which shallow trees over few features do not
+// pay back.  Picoseconds a row of a large batch takes, as sums of what grows with the features F, the output columns K,
+// the trees T, their levels, the entries of the split program and the values of a vector leaf: least squares on
+// the measured times of 1,500 models (full, irregular and mixed trees of depth 1 to 12, 4 to 1500 of them, 4 to 200
+// features, 1 to 20 columns) at 300,000 to 2,000,000 rows; nine in ten estimates are within 25 % of the time.
+// The walk kernels lose up to a factor of 3 where the rule does not choose them (1M rows, 10 features, us, walk /
+// dense: ten 10-wide vector trees of depth 3 311 / 128; 100 trees of depth 3, five columns 166 / 86; 1000 stumps with
+// an infinite threshold 1285 / 381), and win by more everywhere else.
+struct WalkCost {
+    double base, feature, output, tree, level, spread, idle;
+    // spread: per feature, where a tile has a CU or its CU's rows to itself; idle: per tree slot of a stage or wave without one
+};
+struct DenseCost {
+    double base, feature, reg, output, tree, level, entry, value;
+};
+
+inline double walk_row_ps(const PackedModel &m)
+{
+    const double F = m.n_features, K = m.n_outputs, T = m.n_trees;
+    WalkCost c;
+    double spread = 0.0, level = 0.0, idle = 0.0;
+    if (m.walk_depth > 0) {
+        c = K == 1 ? WalkCost{38.5, 0.657, 0, 0, 0.150, 0.673, 0.151} : WalkCost{57.4, 0.479, 4.49, 0.0832, 0.144, 0.813, 0.262};
+        const int trees = walk_stage_trees(m.walk_depth);
+        spread = m.walk_groups == 1 ? F : 0.0;
+        level = T * m.walk_depth;
+        idle = static_cast<double>((m.walk_stages + WALK_WAVES - 1) / WALK_WAVES * WALK_WAVES) * trees - T;
+    } else {
+        const int W = m.leaf_width;
+        c = W == 1   ? K == 1 ? WalkCost{71.0, 0.281, 0, 1.34, 0, 1.18, 0} : WalkCost{62.6, 0.365, 4.76, 1.37, 0, 1.15, 0}
+            : W == 2 ? WalkCost{0, 0.360, 30.0, 1.31, 0, 1.02, 0}
+            : W <= 4 ? WalkCost{92.5, 0.394, 5.18, 2.08, 0, 1.20, 0}
+            : W <= 8 ? WalkCost{106, 0.406, 2.83, 2.51, 0, 1.23, 0}
+            : W == 9 ? WalkCost{0, 0.471, 15.6, 2.87, 0, 1.25, 0}
+            : W <= 12 ? WalkCost{207, 0.296, 7.40, 3.68, 0, 0.572, 0}
+                      : WalkCost{0, 0.338, 21.1, 5.18, 0, 0.535, 0};
+        spread = F > 192 ? F : 0.0;
+    }
+    return c.base + c.feature * F + c.output * K + c.tree * T + c.level * level + c.spread * spread + c.idle * idle;
+}
+
+// 0: not measured as the faster of the two anywhere.
+inline double dense_row_ps(const PackedModel &m, int64_t n_entries)
+{
+    const int W = m.leaf_width, K = m.n_outputs;
+    DenseCost c;
+    if (m.n_features > 256) return 0.0;
+    if (m.path == PATH_RANK) {
+        const int regs = m.rank_regs <= 32 ? 0 : m.rank_regs <= 64 ? 1 : 2;
+        static const DenseCost scalar[3] = {{11.9, 2.25, 0, 3.70, 0.239, 0, 0.0219, 0}, {0, 2.78, 0.0867, 4.37, 0.262, 0, 0.0207, 0}, {28.8, 3.67, 0.965, 2.61, 0.334, 0, 0.0211, 0}};
+        static const DenseCost vec[3] = {{9.44, 2.20, 0.123, 3.79, 0, 0, 0.0231, 0.402}, {0, 2.73, 0.351, 1.23, 0.09, 0, 0.0230, 0.511}, {130, 3.57, 0.134, 0, 0.0638, 0, 0.0318, 0.631}};
+        static const DenseCost wide[3] = {{0, 2.55, 0, 6.52, 0, 0, 0.0362, 0.315}, {0, 2.54, 0, 9.48, 0, 0, 0.0390, 0.285}, {0, 0, 7.62, 14.4, 1.29, 0, 0.00802, 0.327}};
+        c = W == 1 ? scalar[regs] : W <= 8 ? vec[regs] : wide[regs];
+    } else if (m.path == PATH_RANK_LDS && m.bank_enabled) {
+        if (W > 1) return 0.0;
+        c = {0, 0.748, 1.64, 51.0, 3.41, 0.0338, 0.0263, 0};
+    } else if (m.path == PATH_RANK_LDS && W == 1) {
+        c = {59.7, 1.20, 1.21, 11.0, 0.322, 0.262, 0.0467, 0};
+    } else if (m.path == PATH_RANK_LDS) {
+        // by the wavefronts a CU holds
+        const size_t fit = CU_LDS_BYTES / ranklds_lds_bytes(m.rank_regs, K, W, m.lds_waves);
+        if (m.lds_waves == 12) c = fit > 1 ? DenseCost{81.9, 1.28, 0.654, 4.32, 0, 0.169, 0.0468, 0.438} : DenseCost{0, 1.79, 1.79, 20.7, 2.86, 0.145, 0.0652, 0.110};
+        else if (m.lds_waves == 8 && fit > 1) c = {5.27, 1.78, 1.01, 11.0, 0.616, 0.336, 0.0493, 0.383};
+        else if (m.lds_waves == 2 && fit >= 7) c = {0, 0, 7.29, 0, 0, 0.483, 0.0609, 0.324};
+        else return 0.0;
+    } else {
+        return 0.0;
+    }
+    const double F = m.n_features, T = m.n_trees;
+    return c.base + c.feature * F + c.reg * m.rank_regs + c.output * K + c.tree * T + c.level * m.sum_depth + c.entry * n_entries +
+           c.value * (W > 1 ? T * W : 0.0);
+}
 
 // What a PackedModel says about its kernels; the device tables are left null.
 inline DevModel describe(const PackedModel &m)
@@ -118,6 +196,10 @@ inline DevModel describe(const PackedModel &m)
     d.deep.groups = m.deep_groups;
     d.n_splits = 1;
     d.n_entries = static_cast<int64_t>(m.prog32.size() > m.prog.size() ? m.prog32.size() : m.prog.size());
+    if (m.form == FOREST_FORM_AUTO && (m.walk_depth > 0 || m.deep_groups > 0)) {
+        d.walk_ps = static_cast<float>(walk_row_ps(m));
+        d.dense_ps = static_cast<float>(dense_row_ps(m, d.n_entries));
+    }
     return d;
 }
 
@@ -301,6 +383,22 @@ inline bool takes_point(const DevModel &m, int64_t n_rows)
 // rows, one launch each.
 constexpr int64_t MAX_LAUNCH_ROWS = int64_t{1} << 27;
 
+// Whether the dense kernels are the faster ones for a batch (sums only: leaf ids ask less of the walk kernels).  The
+// margins keep the walk kernels where the estimates, or a batch of few rounds of workgroups, decide nothing.  A batch
+// that the dense kernels cut into shares costs them two more launches, and with vector leaves they gain nothing there.
+constexpr int64_t DENSE_MIN_ROWS = 8192;
+
+inline bool prefers_dense(const DevModel &m, int64_t n_rows)
+{
+    if (m.dense_ps <= 0.0f || n_rows < DENSE_MIN_ROWS) return false;
+    const double dense = m.dense_ps, walk = m.walk_ps;
+    const int64_t round = SPLIT_BELOW_BLOCKS * 128;
+    if (n_rows < round)
+        return m.path == PATH_RANK && m.leaf_width == 1 && dense < 0.9 * walk && (walk - dense) * static_cast<double>(n_rows) > 3e6;
+    if (n_rows < 2 * round) return dense < (m.leaf_width > 1 ? 0.75 : 0.9) * walk;
+    return dense < 0.97 * walk;
+}
+
 struct LaunchPlan {
     int32_t kernel = FOREST_KERNEL_LDS;
     int32_t groups = 1;  // walk kernels: row groups of 64 rows per workgroup
@@ -314,14 +412,15 @@ inline LaunchPlan plan_launch(const DevModel &m, const Workspace *ws, int64_t n_
 {
     LaunchPlan p;
     p.splits = choose_splits(m, ws, n_rows, sums, p.fits);
+    const bool dense = sums && p.fits && prefers_dense(m, n_rows);
     if (takes_point(m, n_rows)) {
         p.kernel = FOREST_KERNEL_POINT;
         p.splits = 1;
-    } else if (m.walk.depth > 0) {
+    } else if (m.walk.depth > 0 && !dense) {
         p.kernel = FOREST_KERNEL_WALK;
         p.splits = choose_walk_splits(m, ws, n_rows, sums);
         p.groups = choose_walk_groups(m, n_rows, p.splits);
-    } else if (m.deep.groups > 0) {
+    } else if (m.deep.groups > 0 && !dense) {
         // trees deeper than 8, vector leaves, infinite thresholds: what a row does not meet is not tested
         // (128 trees of depth 12: 2.9 ms against 14.5 with the register-bank kernel)
         p.kernel = FOREST_KERNEL_DEEP;
