@@ -321,6 +321,12 @@ inline size_t deep_lds_bytes(int n_features, int n_outputs, int leaf_width, int 
     return walk > sums ? walk : sums;
 }
 
+// Bytes a walk program may take: any up to PROGRAM_FREE_BYTES, beyond that PROGRAM_PADDING times what the model's
+// nodes and leaves are themselves.  The walk programs lay a tree out as a full one of the forest's depth, or of
+// DEEP_TOP levels: 500,000 stumps and one tree of depth 8 would take 2 GB for 16 MB of model.
+constexpr int64_t PROGRAM_FREE_BYTES = int64_t{64} << 20;
+constexpr int64_t PROGRAM_PADDING = 16;
+
 struct PackedModel {
     int32_t n_trees = 0, n_features = 0, n_outputs = 0, leaf_width = 1;
     int32_t aggregate = 0, transform = 0, output = 0;

@@ -194,6 +194,12 @@ static void balance_waves(PackedModel &m)
     for (int w = 0; w <= waves; ++w) m.wave_tree[w] = w < n ? cut[w] : T;  // spare waves get no trees
 }
 
+static bool program_too_large(const PackedModel &m, int64_t bytes)
+{
+    const int64_t model = sizeof(WalkNode) * (m.n_internal + m.n_leaves) + sizeof(float) * m.n_leaves * m.leaf_width;
+    return bytes > PROGRAM_FREE_BYTES && bytes > PROGRAM_PADDING * model;
+}
+
 // The walk program (forest_model.hpp).  `order`: the trees in processing order.
 static void build_walk(const forest_desc &d, const std::vector<TreeShape> &shape, const std::vector<int32_t> &order,
                        PackedModel &m)
@@ -215,6 +221,7 @@ static void build_walk(const forest_desc &d, const std::vector<TreeShape> &shape
     const int32_t stages = (T + stage_trees - 1) / stage_trees;
     const int64_t slots = static_cast<int64_t>(stages) * stage_trees << D;
     if (slots > FOREST_MAX_NODES) return;
+    if (program_too_large(m, slots * static_cast<int64_t>(sizeof(WalkNode) + sizeof(float) + sizeof(int32_t)))) return;
     auto column_of = [&](int32_t t) { return d.tree_output ? d.tree_output[t] : 0; };
     // A wave keeps the finished sums of its run's columns in registers.
     for (int w = 0; w < WALK_WAVES; ++w) {
@@ -277,6 +284,11 @@ static void build_deep(const forest_desc &d, const std::vector<TreeShape> &shape
         for (int g = deep_max_groups(W); g >= 1 && groups == 0; g /= 2)
             if (deep_lds_bytes(d.n_features, K, W, g) <= budget) groups = g;
     if (groups == 0) return;
+    const int WP = deep_width(W);
+    // a tree's top and its 128 first units at least, each of which may be a leaf
+    const int64_t tree_bytes = static_cast<int64_t>(DEEP_STAGE_BYTES) +
+                               (1 << DEEP_TOP) * static_cast<int64_t>(sizeof(WalkNode) + sizeof(int32_t) + (W > 2 ? sizeof(float) * WP : 0));
+    if (program_too_large(m, T * tree_bytes)) return;
     auto column_of = [&](int32_t t) { return (W == 1 && d.tree_output) ? d.tree_output[t] : 0; };
     // A wave keeps the finished sums of its run's columns in registers.
     for (int w = 0; w < DEEP_WAVES; ++w) {
@@ -286,7 +298,6 @@ static void build_deep(const forest_desc &d, const std::vector<TreeShape> &shape
         if (columns > WALK_MAX_COLUMNS) return;
     }
     PackedModel p;  // only the deep program's members, moved to m at the end
-    const int WP = deep_width(W);
     p.deep_position.assign(static_cast<size_t>(T), 0);
     std::vector<int32_t> level(1 << DEEP_TOP), below(1 << DEEP_TOP), block;
     for (int32_t i = 0; i < T; ++i) {

@@ -110,3 +110,19 @@ def test_shallow_trees_over_few_features_stay_with_the_dense_kernels():
     for name, rows, want in (("c2", 1_000_000, "walk"), ("c3", 1_000_000, "walk"), ("c4", 500_000, "walk"), ("c5", 4_000_000, "deep")):
         f = wl.make_workload(name, n_rows=1).forest
         assert kernel(f, rows) == want and kernel(f, rows, form="dense").startswith("rank")
+
+
+@pytest.mark.parametrize("what", ["walk", "deep", "vector"])
+def test_padding_of_the_walk_programs_is_bounded(what):
+    """Tens of thousands of stumps with one deep tree among them, and of stumps with vector leaves: the walk programs
+    would be a hundred times the model."""
+    import paper_2301_13441_amd as pk
+    for trees, taken in ((1000, True), (40_000, False)):
+        if what == "vector":
+            f = _vector_full(trees, 1, 10, 3)
+        else:
+            f = _mixed(trees, 1, 10, 8 if what == "walk" else 9)
+        v = pk.forest_pack(f)
+        assert (v["walk_depth"] > 0 or v["deep_groups"] > 0) == taken
+    full = pk.forest_pack(_full_forest(1, 20_000, 8, 10))                 # 82 MB, no padding in it
+    assert full["walk_depth"] == 8
