@@ -7,7 +7,7 @@ import pytest
 import oracle
 import workloads as wl
 from test_gpu_parity import _check
-from test_walk import _special_rows
+from test_walk import _launches, _special_rows
 
 
 def _forest(seed, trees, depth, features, outputs=1, width=1, stop=0.2):
@@ -84,7 +84,7 @@ def test_deep_takes_what_it_is_built_for():
 @pytest.mark.parametrize("features", [3, 16, 61, 130, 256, 300])
 @pytest.mark.parametrize("depth,outputs,width", [(9, 1, 1), (11, 4, 1), (12, 2, 2), (10, 3, 3), (9, 8, 8), (5, 10, 10)])
 def test_deep_kernels(features, depth, outputs, width):
-    """One and two row groups; every kind of sum; few trees (waves without any) and more trees than
+    """One row group per workgroup; every kind of sum; few trees (waves without any) and more trees than
     waves; leaf ids of a tree count that is no multiple of four."""
     import paper_2301_13441_amd as pk
     rng = np.random.default_rng(100 * depth + features)
@@ -93,3 +93,27 @@ def test_deep_kernels(features, depth, outputs, width):
         assert pk.forest_pack(f)["deep_groups"] > 0
         X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
         _check(f, X, leaves=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("features", [3, 90, 256])
+@pytest.mark.parametrize("depth,outputs,width", [(9, 1, 1), (11, 4, 1), (12, 2, 2)])
+def test_deep_kernels_with_two_rows_per_lane(features, depth, outputs, width):
+    """Two row groups with a ragged last workgroup, two workgroups on a CU and one; one column, several, and vector
+    leaves; trees in numbers that are no multiple of four or two."""
+    rng = np.random.default_rng(100 * depth + features)
+    rows = 65536 - 13
+    for trees in (5, 37):
+        f = _forest(9 * depth + features, trees, depth, features, outputs, width, stop=0.3)
+        _launches(f, rows, "deep", 128)
+        _check(f, _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng), leaves=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("width", [9, 11, 12, 13, 16])
+def test_deep_kernels_with_wide_leaves(width):
+    """9 values: the sums leave room for two workgroups on a CU; 10 to 12 and 13 to 16: one workgroup."""
+    rng = np.random.default_rng(width)
+    f = _forest(width, 37, 9, 20, width, width)
+    _launches(f, 70_001, "deep", 64)
+    _check(f, _special_rows(rng.standard_normal((70_001, 20)).astype(np.float32), f, rng), leaves=True)

@@ -12,11 +12,16 @@ pytestmark = pytest.mark.gpu
 RTOL, ATOL = 1e-5, 1e-6
 
 
-def _run(forest, X, leaves=True):
+DENSE_KERNELS = {0: ("lds",), 1: ("reg",), 2: ("rank",), 3: ("rank_lds", "rank_bank")}  # by forest_info.kernel_path
+
+
+def _run(forest, X, leaves=True, form="auto"):
     import torch
-    import paper_2301_13441_amd as pk
-    f = pk.forest_load(forest)
+    from paper_2301_13441_amd import binding
+    f = binding.forest_load_form(forest, form)
     try:
+        if form == "dense" and len(X):
+            assert binding.forest_launch(f, len(X))["kernel"] in DENSE_KERNELS[f.info["kernel_path"]]
         xd = torch.from_numpy(np.ascontiguousarray(X)).cuda()
         scores, labels = f.predict(xd)
         lv = f.predict_leaves(xd) if leaves and forest.n_trees > 0 else None
@@ -29,14 +34,21 @@ def _run(forest, X, leaves=True):
 
 
 def _check(forest, X, leaves=True):
+    """The model as a call runs it, and both of its forms where that is another one: the dense kernels, and the walk
+    kernels if they take the model."""
+    from paper_2301_13441_amd import binding
     ref = oracle.predict(forest, X, want_leaves=leaves, n_threads=8)
-    scores, labels, lv, info = _run(forest, X, leaves)
-    if lv is not None:
-        np.testing.assert_array_equal(lv, ref.leaf_node_id)
-    if labels is not None:
-        np.testing.assert_array_equal(labels, ref.labels)
-    if scores is not None:
-        np.testing.assert_allclose(scores, ref.scores, rtol=RTOL, atol=ATOL)
+    forms = ["auto", "dense"]
+    if binding.forest_packed_launch(forest, len(X), form="walk") != binding.forest_packed_launch(forest, len(X)):
+        forms.append("walk")
+    for form in forms:
+        scores, labels, lv, info = _run(forest, X, leaves, form)
+        if lv is not None:
+            np.testing.assert_array_equal(lv, ref.leaf_node_id)
+        if labels is not None:
+            np.testing.assert_array_equal(labels, ref.labels)
+        if scores is not None:
+            np.testing.assert_allclose(scores, ref.scores, rtol=RTOL, atol=ATOL)
     return info
 
 
@@ -96,18 +108,21 @@ def test_register_bank_kernel_on_large_batches(seed):
     X[6, :] = np.inf
     X[7, :] = -np.inf
     info = _check(f, X)
+    from paper_2301_13441_amd import binding
     if info["kernel_kind"] == 0:     # a draw of shallow trees that all came out full runs the rank kernel
         assert info["kernel_path"] == 3 and info["rank_banks"] == 1
+        assert binding.forest_packed_launch(f, rows, form="dense")["kernel"] == "rank_bank"
 
 
-def test_register_bank_kernel_lookup_paths():
+@pytest.mark.parametrize("form", ["dense", "auto"])
+def test_register_bank_kernel_lookup_paths(form):
     """The register-bank kernel's rank lookups, every path in one model: a feature whose 13,000
     thresholds take two registers, one with 7,000 (one register, codes of both signs), one with 3
     (no window), one whose 500 thresholds crowd into a millionth of its range (buckets fuller
     than a window), features in a second block of 64 columns with the block between unused, rows
     of 70 floats at a 4-byte aligned address, values on and between thresholds, NaN and Inf."""
     import torch
-    import paper_2301_13441_amd as pk
+    from paper_2301_13441_amd import binding
     rng = np.random.default_rng(77)
     F, n = 200, 65536 + 77
     f = wl.random_forest(4242, n_trees=600, n_features=F, max_depth=7, stop_prob=0.05)
@@ -141,9 +156,10 @@ def test_register_bank_kernel_lookup_paths():
     xd.copy_(torch.from_numpy(X))
     assert xd.data_ptr() % 8 == 4
     ref = oracle.predict(g, X, want_leaves=True, n_threads=8)
-    h = pk.forest_load(g)
+    h = binding.forest_load_form(g, form)
     try:
         assert h.info["kernel_path"] == 3 and h.info["rank_banks"] == 1
+        assert form == "auto" or binding.forest_launch(h, n)["kernel"] == "rank_bank"
         scores, labels = h.predict(xd)
         leaves = h.predict_leaves(xd)
         torch.cuda.synchronize()
@@ -279,14 +295,15 @@ def test_small_batches_other_families():
         assert info["kernel_path"] == 0
 
 
-@pytest.mark.parametrize("rows", [300, 70000])   # a split launch (three kernels) and a plain one
-def test_predict_replays_from_a_captured_graph(rows):
+@pytest.mark.parametrize("form", ["auto", "dense"])
+@pytest.mark.parametrize("rows", [300, 70000])   # a split launch (dense: three kernels) and a plain one
+def test_predict_replays_from_a_captured_graph(rows, form):
     """forest_predict allocates nothing and records only kernels, so a caller can capture it;
     every replay, with eager work and synchronisations in between, must match the oracle."""
     import torch
-    import paper_2301_13441_amd as pk
+    from paper_2301_13441_amd import binding
     w = wl.make_workload("c3", n_rows=rows, n_trees=100)
-    f = pk.forest_load(w.forest)
+    f = binding.forest_load_form(w.forest, form)
     try:
         rng = np.random.default_rng(rows)
         xs = [w.make_x(rows)] + [rng.standard_normal((rows, w.forest.n_features)).astype(np.float32)
@@ -315,15 +332,16 @@ def test_predict_replays_from_a_captured_graph(rows):
         f.close()
 
 
+@pytest.mark.parametrize("form", ["auto", "dense"])
 @pytest.mark.parametrize("n_streams", [2, 6])   # within the handle's workspaces, and more streams than it has
-def test_small_batches_from_several_streams_on_one_handle(n_streams):
+def test_small_batches_from_several_streams_on_one_handle(n_streams, form):
     """Calls on one handle from different streams may overlap whatever the batch size: every
     stream gets a workspace of its own, and a stream that finds none left runs unsplit."""
     import torch
-    import paper_2301_13441_amd as pk
+    from paper_2301_13441_amd import binding
     w = wl.make_workload("c2", n_rows=1, n_trees=200)
     F = w.forest.n_features
-    f = pk.forest_load(w.forest)
+    f = binding.forest_load_form(w.forest, form)
     try:
         rng = np.random.default_rng(n_streams)
         streams = [torch.cuda.Stream() for _ in range(n_streams)]
@@ -601,12 +619,13 @@ def test_every_rank_code_against_every_neighbouring_threshold(full):
     assert info["kernel_path"] == (2 if full else 3), info
 
 
+@pytest.mark.parametrize("form", ["auto", "dense", "walk"])
 @pytest.mark.parametrize("full", [True, False])
-def test_x_at_a_four_byte_aligned_address(full):
+def test_x_at_a_four_byte_aligned_address(full, form):
     """X is only promised to be float32-aligned: rows of 13 floats starting one float into an
     allocation (the kernels read neighbouring features of a row with wider loads)."""
     import torch
-    import paper_2301_13441_amd as pk
+    from paper_2301_13441_amd import binding
     F, n = 13, 700
     f = _full_forest(31, 20, 5, F) if full else wl.random_forest(31, n_trees=20, n_features=F, max_depth=9, stop_prob=0.1)
     X = np.random.default_rng(8).standard_normal((n, F)).astype(np.float32)
@@ -615,7 +634,7 @@ def test_x_at_a_four_byte_aligned_address(full):
     xd.copy_(torch.from_numpy(X))
     assert xd.data_ptr() % 8 == 4 and xd.is_contiguous()
     ref = oracle.predict(f, X, n_threads=8)
-    h = pk.forest_load(f)
+    h = binding.forest_load_form(f, form)
     try:
         scores, labels = h.predict(xd)
         torch.cuda.synchronize()
@@ -638,6 +657,9 @@ def test_duplicate_thresholds_and_unused_features():
 
 # ----------------------------------------------------------------------------- full-size runs
 
+FULL_SIZE_KERNELS = {"c2": ("walk", "rank"), "c3": ("walk", "rank"), "c4": ("walk", "rank"), "c5": ("deep", "rank_bank")}
+
+
 def _full_size(name):
     """The bench's launch configuration (full row count, device-resident X): scores and labels of
     EVERY row are compared with the oracle, and the leaf ids of every tree on the first 65 536
@@ -645,7 +667,7 @@ def _full_size(name):
     and through the oracle, so the host never holds more than one chunk and the sampled rows."""
     import os
     import torch
-    import paper_2301_13441_amd as pk
+    from paper_2301_13441_amd import binding
     w = wl.make_workload(name)
     n, F, K = w.n_rows, w.forest.n_features, w.forest.n_outputs
     threads = max(1, min(os.cpu_count() or 1, 16))
@@ -665,27 +687,31 @@ def _full_size(name):
         ref_scores[pos:pos + len(chunk)] = ref.scores
         ref_labels[pos:pos + len(chunk)] = ref.labels
         pos += len(chunk)
-    f = pk.forest_load(w.forest)
-    try:
-        scores, labels = f.predict(xd)
-        torch.cuda.synchronize()
-        got_scores = None if scores is None else scores.cpu().numpy()
-        got_labels = None if labels is None else labels.cpu().numpy()
-        # leaf ids: every tree, on the sampled rows (a batch large enough to run the same kernels)
-        lv = f.predict_leaves(xd[torch.from_numpy(pick).cuda()].contiguous())
-        torch.cuda.synchronize()
-        got_leaves = lv.cpu().numpy()
-        info = f.info
-    finally:
-        f.close()
-    assert len(pick) >= info["small_batch_rows"]
-    if got_labels is not None:
-        np.testing.assert_array_equal(got_labels, ref_labels)
-    if got_scores is not None:
-        np.testing.assert_allclose(got_scores, ref_scores, rtol=RTOL, atol=ATOL)
-    del got_scores, got_labels, ref_scores, ref_labels
     ref_leaves = oracle.predict(w.forest, xs, want_leaves=True, n_threads=threads).leaf_node_id
-    np.testing.assert_array_equal(got_leaves, ref_leaves)
+    for form in ("auto", "dense"):
+        f = binding.forest_load_form(w.forest, form)
+        try:
+            scores, labels = f.predict(xd)
+            torch.cuda.synchronize()
+            got_scores = None if scores is None else scores.cpu().numpy()
+            got_labels = None if labels is None else labels.cpu().numpy()
+            del scores, labels
+            # leaf ids: every tree, on the sampled rows (a batch large enough to run the same kernels)
+            lv = f.predict_leaves(xd[torch.from_numpy(pick).cuda()].contiguous())
+            torch.cuda.synchronize()
+            got_leaves = lv.cpu().numpy()
+            info = f.info
+            kernel = binding.forest_launch(f, n)["kernel"]
+        finally:
+            f.close()
+        assert kernel == FULL_SIZE_KERNELS[name][form == "dense"]
+        assert len(pick) >= info["small_batch_rows"]
+        if got_labels is not None:
+            np.testing.assert_array_equal(got_labels, ref_labels)
+        if got_scores is not None:
+            np.testing.assert_allclose(got_scores, ref_scores, rtol=RTOL, atol=ATOL)
+        del got_scores, got_labels
+        np.testing.assert_array_equal(got_leaves, ref_leaves)
     return info
 
 

@@ -76,17 +76,41 @@ def test_walk_takes_what_it_is_built_for():
     assert pk.forest_pack(f)["walk_depth"] == 0                                         # 7 columns in one wave's run
 
 
+def _launches(f, rows, kernel, rows_per_workgroup):
+    """What a test is about: the walk kernels with this many rows per workgroup, for sums and for leaf ids."""
+    from paper_2301_13441_amd import binding
+    for leaves in (False, True):
+        s = binding.forest_packed_launch(f, rows, leaves, form="walk")
+        assert s["kernel"] == kernel and s["rows_per_workgroup"] == rows_per_workgroup and s["shares"] == 1, s
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,groups", [(65536 - 13, 2), (131072 - 13, 4)])
+@pytest.mark.parametrize("depth", [3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("features,outputs,full", [(3, 1, True), (40, 1, False), (9, 4, False), (90, 4, True)])
+def test_walk_kernels_with_several_rows_per_lane(depth, features, outputs, full, rows, groups):
+    """Two and four row groups per workgroup with a ragged last one; few trees (waves without any) and more trees than
+    waves, in numbers that are no multiple of four."""
+    rng = np.random.default_rng(100 * depth + features)
+    for trees in (5, 83):
+        f = _forest(9 * depth + features, trees, depth, features, outputs, full)
+        _launches(f, rows, "walk", 64 * (groups if outputs == 1 else 2))
+        _check(f, _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng), leaves=True)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("depth", [1, 2, 3, 4, 5, 6, 7, 8])
 @pytest.mark.parametrize("features,outputs,full", [(3, 1, True), (40, 4, False), (61, 1, False), (130, 4, True), (300, 1, True)])
 def test_walk_kernels(depth, features, outputs, full):
-    """Every depth; tiles of 4, 2 and 1 row groups; one and several columns; few trees (waves without
-    any) and more trees than waves; leaf ids of a tree count that is no multiple of four."""
+    """Every depth; tiles laid out for 4, 2 and 1 row groups, one launched; one and several columns; few trees over
+    few rows (a lane per row and tree) and more trees than waves; leaf ids of a tree count that is no multiple of four."""
     import paper_2301_13441_amd as pk
     rng = np.random.default_rng(100 * depth + features)
     for trees, rows in ((5, 517), (83, 65536 + 77)):
         f = _forest(9 * depth + features, trees, depth, features, outputs, full)
         assert pk.forest_pack(f)["walk_depth"] > 0
+        if rows > 60000:
+            _launches(f, rows, "walk", 64)
         X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
         _check(f, X, leaves=True)
 

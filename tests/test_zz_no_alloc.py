@@ -19,11 +19,12 @@ def _models():
                                                     aggregate=wl.AGG_MEAN)
 
 
+@pytest.mark.parametrize("form", ["auto", "dense"])
 @pytest.mark.parametrize("what,forest", list(_models()), ids=lambda v: v if isinstance(v, str) else "")
-def test_static_entry_point_matches_forest_predict(what, forest):
+def test_static_entry_point_matches_forest_predict(what, forest, form):
     import torch
-    import paper_2301_13441_amd as pk
-    f = pk.forest_load(forest)
+    from paper_2301_13441_amd import binding
+    f = binding.forest_load_form(forest, form)
     try:
         rng = np.random.default_rng(len(what))
         for rows in (2500, 700, 1, 100000):       # smaller second call; one row; a batch that needs no workspace
