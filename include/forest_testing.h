@@ -178,6 +178,7 @@ typedef struct forest_launch_t {
     int32_t rows_per_workgroup;
     int32_t threads;            /* per workgroup */
     int32_t launches;           /* ranges of rows the batch goes in */
+    int32_t lds_bytes;          /* per workgroup; walk and deep walk kernels, else 0 */
     int64_t workgroups;         /* of the largest range, per share */
 } forest_launch_t;
 int forest_launch(const forest *f, int64_t n_rows, int32_t leaves, forest_launch_t *out);

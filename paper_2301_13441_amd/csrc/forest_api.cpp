@@ -414,7 +414,7 @@ int forest_launch(const forest *f, int64_t n_rows, int32_t leaves, forest_launch
     if (!out || n_rows < 1) return FOREST_EINVAL;
     if (int rc = check_out_args(f, n_rows)) return rc;
     const Workspace *ws = small_batch(f, n_rows) ? &f->slot[0] : nullptr;
-    *out = launch_shape(f->dev, plan_launch(f->dev, ws, n_rows, !leaves), n_rows);
+    *out = launch_shape(f->dev, plan_launch(f->dev, ws, n_rows, !leaves), n_rows, !leaves);
     return FOREST_OK;
 }
 

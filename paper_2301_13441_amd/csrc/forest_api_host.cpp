@@ -43,7 +43,7 @@ int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves,
     Workspace ws;
     ws.rank_tile_words = static_cast<int64_t>(rank_tile_bytes(d.rank_regs, SPLIT_BELOW_BLOCKS) / sizeof(uint32_t));
     ws.partial_doubles = split_workspace_doubles(d.n_outputs);
-    *out = launch_shape(d, plan_launch(d, &ws, n_rows, !leaves), n_rows);
+    *out = launch_shape(d, plan_launch(d, &ws, n_rows, !leaves), n_rows, !leaves);
     return FOREST_OK;
 }
 

@@ -397,11 +397,11 @@ hipError_t init_deep_kernels(size_t lds_limit)
 hipError_t launch_deep(const DevModel &m, int groups, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                        int32_t *leaf_out, hipStream_t stream)
 {
-    const bool shared = deep_shares_cu(m, groups);
+    const bool shared = deep_shares_cu(m, groups, leaf_out == nullptr);
     const int64_t n_blocks = (n_rows + TILE * groups - 1) / (TILE * groups);
     if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(n_blocks), static_cast<unsigned>(m.n_splits));
-    const size_t lds = deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups);
+    const size_t lds = deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups, leaf_out == nullptr);
     const int mode = leaf_out ? DEEP_LEAVES : m.leaf_width > 1 ? DEEP_VECTOR : m.n_outputs == 1 ? DEEP_COLUMN : DEEP_COLUMNS;
     hipLaunchKernelGGL(pick(groups, mode, deep_width(m.leaf_width), shared), grid, dim3(DEEP_WAVES * TILE), lds, stream, m, X,
                        n_rows, scores, labels, leaf_out);

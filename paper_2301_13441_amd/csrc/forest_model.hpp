@@ -312,10 +312,11 @@ constexpr int deep_width(int leaf_width) { return leaf_width <= 2 ? leaf_width :
 constexpr int deep_max_groups(int leaf_width) { return leaf_width > 2 ? 1 : 2; }
 
 // LDS of a workgroup that owns `groups` x 64 rows: the X tile and a stage per wave, or the sums,
-// which reuse the space at the end.
-inline size_t deep_lds_bytes(int n_features, int n_outputs, int leaf_width, int groups)
+// which reuse the space at the end; leaf ids need none.
+inline size_t deep_lds_bytes(int n_features, int n_outputs, int leaf_width, int groups, bool with_sums)
 {
     const size_t walk = DEEP_WAVES * DEEP_STAGE_BYTES + static_cast<size_t>(n_features) * groups * 256;
+    if (!with_sums) return walk;
     const size_t slots = leaf_width > 1 ? static_cast<size_t>(DEEP_WAVES) * n_outputs : static_cast<size_t>(DEEP_WAVES) + 2 * n_outputs - 1;
     const size_t sums = sizeof(double) * 64 * groups * slots + 2 * sizeof(int32_t) * DEEP_WAVES;
     return walk > sums ? walk : sums;

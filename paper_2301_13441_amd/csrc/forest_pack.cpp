@@ -282,7 +282,7 @@ static void build_deep(const forest_desc &d, const std::vector<TreeShape> &shape
     int groups = 0;
     for (const size_t budget : {CU_LDS_BYTES / 2, CU_LDS_BYTES})
         for (int g = deep_max_groups(W); g >= 1 && groups == 0; g /= 2)
-            if (deep_lds_bytes(d.n_features, K, W, g) <= budget) groups = g;
+            if (deep_lds_bytes(d.n_features, K, W, g, true) <= budget) groups = g;
     if (groups == 0) return;
     const int WP = deep_width(W);
     // a tree's top and its 128 first units at least, each of which may be a leaf

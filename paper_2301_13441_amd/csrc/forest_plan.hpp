@@ -324,20 +324,20 @@ inline int choose_walk_groups(const DevModel &m, int64_t n_rows, int n_splits)
 }
 
 // Whether two workgroups fit a CU.
-inline bool deep_shares_cu(const DevModel &m, int groups)
+inline bool deep_shares_cu(const DevModel &m, int groups, bool sums)
 {
-    return deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups) <= CU_LDS_BYTES / 2;
+    return deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups, sums) <= CU_LDS_BYTES / 2;
 }
 
 // Row groups per workgroup: two rows per lane share the copies of the trees' tops and keep twice as
 // many walks in flight (300 irregular trees, 90 features, 103,069 rows: 94 us with two, 108 with one);
 // one leaves a small batch more workgroups.  The last round of workgroups counts whole.
-inline int choose_deep_groups(const DevModel &m, int64_t n_rows, int n_splits)
+inline int choose_deep_groups(const DevModel &m, int64_t n_rows, int n_splits, bool sums)
 {
     if (m.deep.groups == 1) return 1;
     double cost[2];
     for (int g = 1; g <= 2; ++g) {
-        const int64_t per_cu = deep_shares_cu(m, g) ? 2 : 1;
+        const int64_t per_cu = deep_shares_cu(m, g, sums) ? 2 : 1;
         const int64_t blocks = (n_rows + PLAN_ROWS * g - 1) / (PLAN_ROWS * g) * n_splits, round = 256 * per_cu;
         cost[g - 1] = static_cast<double>((blocks + round - 1) / round * per_cu * g) * (g == 1 ? 1.15 : 1.0);
     }
@@ -425,7 +425,7 @@ inline LaunchPlan plan_launch(const DevModel &m, const Workspace *ws, int64_t n_
         // (128 trees of depth 12: 2.9 ms against 14.5 with the register-bank kernel)
         p.kernel = FOREST_KERNEL_DEEP;
         p.splits = choose_walk_splits(m, ws, n_rows, sums);
-        p.groups = choose_deep_groups(m, n_rows, p.splits);
+        p.groups = choose_deep_groups(m, n_rows, p.splits, sums);
     } else if (m.path == PATH_RANK) {
         p.kernel = FOREST_KERNEL_RANK;
     } else if (m.path == PATH_RANK_LDS) {
@@ -438,7 +438,7 @@ inline LaunchPlan plan_launch(const DevModel &m, const Workspace *ws, int64_t n_
 }
 
 // The shape of the launches of a plan.
-inline forest_launch_t launch_shape(const DevModel &m, const LaunchPlan &p, int64_t n_rows)
+inline forest_launch_t launch_shape(const DevModel &m, const LaunchPlan &p, int64_t n_rows, bool sums)
 {
     forest_launch_t s{};
     s.kernel = p.kernel;
@@ -451,10 +451,12 @@ inline forest_launch_t launch_shape(const DevModel &m, const LaunchPlan &p, int6
         case FOREST_KERNEL_WALK:
             s.rows_per_workgroup = PLAN_ROWS * p.groups;
             s.threads = PLAN_ROWS * WALK_WAVES;
+            s.lds_bytes = static_cast<int32_t>(walk_lds_bytes(m.walk.depth, m.n_features, m.n_outputs, m.walk.groups));
             break;
         case FOREST_KERNEL_DEEP:
             s.rows_per_workgroup = PLAN_ROWS * p.groups;
             s.threads = PLAN_ROWS * DEEP_WAVES;
+            s.lds_bytes = static_cast<int32_t>(deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, p.groups, sums));
             break;
         case FOREST_KERNEL_RANK_BANK:
             s.rows_per_workgroup = BANK_ROWS;

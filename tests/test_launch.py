@@ -126,3 +126,11 @@ def test_padding_of_the_walk_programs_is_bounded(what):
         assert (v["walk_depth"] > 0 or v["deep_groups"] > 0) == taken
     full = pk.forest_pack(_full_forest(1, 20_000, 8, 10))                 # 82 MB, no padding in it
     assert full["walk_depth"] == 8
+
+
+def test_leaf_ids_take_no_lds_for_sums():
+    """Leaf ids of a model whose sums fill more than half a CU's LDS: two workgroups on a CU, counted as such."""
+    from paper_2301_13441_amd import binding
+    f = _vector_full(20, 4, 10, 16)                # 16 waves x 16 columns x 64 rows of sums: 128 KB
+    lds = lambda leaves: binding.forest_packed_launch(f, 100_000, leaves, form="walk")["lds_bytes"]
+    assert lds(False) > 128 << 10 and lds(True) <= 80 << 10
