@@ -383,16 +383,19 @@ inline bool takes_point(const DevModel &m, int64_t n_rows)
 // rows, one launch each.
 constexpr int64_t MAX_LAUNCH_ROWS = int64_t{1} << 27;
 
-// Whether the dense kernels are the faster ones for a batch (sums only: leaf ids ask less of the walk kernels).  The
+// Whether the dense kernels are the faster ones for a batch.  The estimates are of sums; leaf ids ask less of the walk
+// kernels, of which only the deep one loses, where trees are fewer than a workgroup's waves (100,000 rows of twelve
+// trees of depth 3, 9 columns, 4 features: 13.0 us, dense 9.2; from 30 trees on they take 0.3 to 1.1 of the dense time).  The
 // margins keep the walk kernels where the estimates, or a batch of few rounds of workgroups, decide nothing.  A batch
 // that the dense kernels cut into shares costs them two more launches, and with vector leaves they gain nothing there.
 constexpr int64_t DENSE_MIN_ROWS = 8192;
 
-inline bool prefers_dense(const DevModel &m, int64_t n_rows)
+inline bool prefers_dense(const DevModel &m, int64_t n_rows, bool sums)
 {
     if (m.dense_ps <= 0.0f || n_rows < DENSE_MIN_ROWS) return false;
     const double dense = m.dense_ps, walk = m.walk_ps;
     const int64_t round = SPLIT_BELOW_BLOCKS * 128;
+    if (!sums) return n_rows >= round && m.deep.groups > 0 && m.n_trees < DEEP_WAVES && dense < 0.75 * walk;
     if (n_rows < round)
         return m.path == PATH_RANK && m.leaf_width == 1 && dense < 0.9 * walk && (walk - dense) * static_cast<double>(n_rows) > 3e6;
     if (n_rows < 2 * round) return dense < (m.leaf_width > 1 ? 0.75 : 0.9) * walk;
@@ -412,7 +415,7 @@ inline LaunchPlan plan_launch(const DevModel &m, const Workspace *ws, int64_t n_
 {
     LaunchPlan p;
     p.splits = choose_splits(m, ws, n_rows, sums, p.fits);
-    const bool dense = sums && p.fits && prefers_dense(m, n_rows);
+    const bool dense = p.fits && prefers_dense(m, n_rows, sums);
     if (takes_point(m, n_rows)) {
         p.kernel = FOREST_KERNEL_POINT;
         p.splits = 1;
