@@ -34,6 +34,10 @@ ORACLE_THREADS_MAX = 16   # the share of host cores one GPU's job may use on the
 # entry names the summary under profiles/ it comes from and the commit whose kernels were
 # measured; a workload without an entry reports null.
 MEASURED_TRAFFIC = {
+    "c2": {"bytes": 1.717e8, "profile": "profiles/forest_walk_kernels.md", "commit": "2101358"},
+    "c3": {"bytes": 3.355e8, "profile": "profiles/forest_walk_kernels.md", "commit": "2101358"},
+    "c4": {"bytes": 3.076e8, "profile": "profiles/forest_walk_kernels.md", "commit": "2101358"},
+    "c5": {"bytes": 4.330e9, "profile": "profiles/forest_walk_kernels.md", "commit": "2101358"},
     "l2": {"bytes": 1.456e9, "profile": "profiles/linear_kernels.md", "commit": "65bfc7c"},
     "l3": {"bytes": 1.120e9, "profile": "profiles/linear_kernels.md", "commit": "65bfc7c"},
     "l4": {"bytes": 9.600e8, "profile": "profiles/linear_kernels.md", "commit": "65bfc7c"},
@@ -231,12 +235,14 @@ class ForestRun:
 
         import paper_2301_13441_amd as pk
         import workloads as wl
+        from paper_2301_13441_amd.binding import forest_launch
 
         self.name, self.args = name, args
         self.w = wl.make_workload(name, n_rows=args.rows)
         self.n_rows, self.F = self.w.n_rows, self.w.forest.n_features
         self.f = pk.forest_load(self.w.forest)
         self.info = self.f.info
+        self.launch = forest_launch(self.f, self.n_rows)
         # X: generated on the host in chunks, copied to HBM before the timed region; the host copy
         # is kept for the oracle
         self.want_host = not args.no_cpu_baseline
@@ -330,7 +336,7 @@ class ForestRun:
             "config": {"workload": name, "n_rows": n_rows, "n_features": F,
                        "n_trees": info["n_trees"], "max_depth": info["max_depth"],
                        "n_internal_nodes": info["n_internal"], "n_outputs": info["n_outputs"],
-                       "kernel_kind": info["kernel_kind"], "kernel_path": info["kernel_path"],
+                       "kernel": self.launch["kernel"], "rows_per_workgroup": self.launch["rows_per_workgroup"],
                        "packed_bytes": info["packed_bytes"]},
             "roofline": roofline,
             "cpu_baseline": cpu_baseline,

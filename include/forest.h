@@ -49,7 +49,8 @@ enum {
 #define FOREST_MAX_NODES (1 << 27) /* internal nodes, and leaves, summed over the trees: the split
                                       program pads levels to groups of 8 and indexes entries with int32 */
 /* Limit of one call (FOREST_ELIMIT from the predict and size calls): */
-#define FOREST_MAX_ROWS 1000000000 /* n_rows: keeps every launch inside HIP's 2^32 threads per grid axis */
+#define FOREST_MAX_ROWS 1000000000 /* n_rows; batches beyond 2^27 rows go in ranges, a launch each, inside HIP's
+                                     2^32 threads per grid axis */
 
 /*
  * A forest as the caller holds it: per-node arrays, trees concatenated.  All pointers are
@@ -86,24 +87,30 @@ typedef struct forest_desc {
     int32_t output;            /* FOREST_OUT_* */
 } forest_desc;
 
+/*
+ * The model and the dense kernels' form of it.  kernel_kind, x_in_registers, kernel_path, rows_per_workgroup,
+ * workgroup_waves and rank_banks describe the dense form, which every model has; most calls run a walk kernel instead
+ * (what a call launches: forest_launch, forest_testing.h).
+ */
 typedef struct forest_info_t {
     int32_t n_trees, n_features, n_outputs, leaf_width;
-    int64_t n_internal;    /* sum of N_I over trees = comparisons evaluated per row */
+    int64_t n_internal;    /* sum of N_I over trees = comparisons the dense kernels evaluate per row */
     int64_t n_leaves;      /* sum of N_L over trees */
     int32_t max_depth;     /* longest root-to-leaf path */
-    int32_t kernel_kind;   /* which specialised kernel forest_predict launches (0 = generic) */
-    int64_t packed_bytes;  /* device-resident size of the packed model */
-    int32_t x_in_registers;     /* 1 if the kernel keeps the features in vector registers */
-    int32_t kernel_path;        /* dense kernels' form of the model.  0: features from the LDS tile; 1: float32 feature registers;
+    int32_t kernel_kind;   /* the specialised dense kernel: the common depth of full trees (0 = generic) */
+    int64_t packed_bytes;  /* device-resident size of the packed model, both forms */
+    int32_t x_in_registers;     /* 1 if the dense kernel keeps the features in vector registers */
+    int32_t kernel_path;        /* 0: features from the LDS tile; 1: float32 feature registers;
                                    2: packed f16 threshold-rank registers;
                                    3: packed f16 threshold ranks in LDS (any tree shape) */
-    int32_t rows_per_workgroup; /* rows one workgroup owns */
+    int32_t rows_per_workgroup; /* rows one workgroup of the dense kernel owns */
     int64_t workspace_bytes;    /* device workspaces (all of them) the handle owns besides the packed model */
-    int64_t small_batch_rows;   /* batches below this many rows also cut the trees into shares
-                                   (more workgroups for few rows) and use a workspace */
-    int32_t workgroup_waves;    /* wavefronts per workgroup of the kernel the model runs */
-    int32_t rank_banks;         /* kernel_path 3, models the walk kernels do not take: 1 if batches of small_batch_rows rows or more run the
-                                   register-bank kernel (rank registers dealt to the wavefronts of a
+    int64_t small_batch_rows;   /* batches of this many rows or more use no workspace; below it the trees may
+                                   be cut into shares (more workgroups for few rows), which meet in one, and
+                                   forest_predict_static may refuse the batch */
+    int32_t workgroup_waves;    /* wavefronts per workgroup of the dense kernel */
+    int32_t rank_banks;         /* kernel_path 3: 1 if batches of small_batch_rows rows or more run, in the dense
+                                   form, the register-bank kernel (rank registers dealt to the wavefronts of a
                                    workgroup, whole trees evaluated before the walk) */
 } forest_info_t;
 
@@ -142,9 +149,10 @@ int forest_out_layout(const forest *f, int64_t n_rows, int64_t *scores_offset, i
  * Asynchronous: enqueues kernels and returns; reports launch errors only.  n_rows == 0 is a
  * successful no-op.  The caller keeps X and out alive until the stream has run the work.
  * Allocates nothing.
- * Small batches (the latency regime of Table 6): below forest_info_t.small_batch_rows rows the
- * trees are cut into shares that run in separate workgroups, their fp64 partial sums meet in a
- * workspace the handle owns and a second kernel on the same stream finishes the rows.  The handle
+ * Small batches (the latency regime of Table 6): below forest_info_t.small_batch_rows rows (the walk
+ * kernels: up to 16,384) the trees may be cut into shares that run in separate workgroups, their fp64
+ * partial sums meet in a workspace the handle owns and a second kernel on the same stream finishes the
+ * rows; the smallest batches of shallow trees are one launch with a lane per (row, tree).  The handle
  * owns several such workspaces and gives every stream its own (a stream under graph capture gets
  * one for that capture), so calls on one handle may run concurrently from different streams
  * whatever their batch size; a caller that finds every workspace taken by other streams runs its
@@ -157,7 +165,8 @@ int forest_predict(const forest *f, const float *X, int64_t n_rows, void *out, v
  * allocated: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments, same results.  The workspace of a small batch is not the handle's but a static
  * array of FOREST_STATIC_SCRATCH_BYTES in the library's device image (every GPU the library runs
- * on holds one until the process ends); the call allocates and frees nothing.  A small batch
+ * on holds one until the process ends); the call allocates and frees nothing.  Whichever kernel
+ * would run it, a small batch
  * whose rank tiles (ceil(n_rows / 128) * rank registers * 256 bytes for the rank kernels) and at
  * least two shares of partial sums (n_rows * n_outputs * 8 bytes each) do not fit the array is
  * refused with FOREST_ELIMIT; batches of forest_info_t.small_batch_rows rows or more use no
