@@ -13,8 +13,8 @@
 //   workgroup, then the transform; labels are taken before the transform (Section 4.3.3).
 //
 // This file holds the kernels that read features from the LDS tile for every comparison
-// (any number of features, any tree shape), the choice of how many shares the trees of a small
-// batch are cut into, and the launcher.  The walk kernels run nearly every model:
+// (any number of features, any tree shape) and the launcher; what a call launches is decided in
+// forest_plan.hpp.  The walk kernels run most models:
 // forest_kernels_walk.hip (depth up to 8, scalar leaves) and forest_kernels_deep.hip (the rest).  The
 // other dense families: forest_kernels_rank.hip (packed f16 threshold ranks in vector registers),
 // forest_kernels_ranklds.hip (the same with the ranks in LDS, any tree shape), forest_kernels_rankbank.hip

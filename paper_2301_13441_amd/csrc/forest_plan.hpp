@@ -211,8 +211,9 @@ constexpr int64_t SPLIT_BELOW_BLOCKS = 512;
 // at least this many program entries together.
 constexpr int64_t SPLIT_TARGET_BLOCKS = 1024;
 constexpr int64_t SPLIT_MIN_ENTRIES_PER_WAVE = 512;
-// Walk kernels: workgroups of 16 waves, two per CU, and the copies of trees to LDS that a split launch
-// leaves a wave at least.
+// Walk kernels: workgroups of 16 waves that the chip is taken to hold, two per CU (a model whose tile leaves room for
+// one, or the deep kernel's of more than 64 registers, has half as many; the estimate is used for them too), and the
+// copies of trees to LDS that a split launch leaves a wave at least.
 constexpr int64_t WALK_RESIDENT = 512;
 constexpr int64_t WALK_SPLIT_MIN_COPIES = 2;
 
