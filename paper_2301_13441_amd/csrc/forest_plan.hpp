@@ -196,9 +196,9 @@ inline DevModel describe(const PackedModel &m)
     d.deep.groups = m.deep_groups;
     d.n_splits = 1;
     d.n_entries = static_cast<int64_t>(m.prog32.size() > m.prog.size() ? m.prog32.size() : m.prog.size());
-    if (m.form == FOREST_FORM_AUTO && (m.walk_depth > 0 || m.deep_groups > 0)) {
+    if (m.walk_depth > 0 || m.deep_groups > 0) {
         d.walk_ps = static_cast<float>(walk_row_ps(m));
-        d.dense_ps = static_cast<float>(dense_row_ps(m, d.n_entries));
+        if (m.form == FOREST_FORM_AUTO) d.dense_ps = static_cast<float>(dense_row_ps(m, d.n_entries));
     }
     return d;
 }
@@ -211,10 +211,11 @@ constexpr int64_t SPLIT_BELOW_BLOCKS = 512;
 // at least this many program entries together.
 constexpr int64_t SPLIT_TARGET_BLOCKS = 1024;
 constexpr int64_t SPLIT_MIN_ENTRIES_PER_WAVE = 512;
-// Walk kernels: workgroups of 16 waves that the chip is taken to hold, two per CU (a model whose tile leaves room for
-// one, or the deep kernel's of more than 64 registers, has half as many; the estimate is used for them too), and the
-// copies of trees to LDS that a split launch leaves a wave at least.
+// Walk kernels: workgroups of 16 waves that a split launch aims at, two per CU (a model whose tile leaves room for one
+// per CU has half as many places; it is cut into as many shares all the same), the chip's CUs, and the copies of trees
+// to LDS that a split launch leaves a wave at least.
 constexpr int64_t WALK_RESIDENT = 512;
+constexpr int64_t CUS = 256;
 constexpr int64_t WALK_SPLIT_MIN_COPIES = 2;
 
 // Device memory a split launch (small batch) needs besides the inputs and outputs: the tree
@@ -306,43 +307,25 @@ inline int choose_walk_splits(const DevModel &m, const Workspace *ws, int64_t n_
     return s < 2 ? 1 : static_cast<int>(s);
 }
 
-// Row groups per workgroup.  More rows per workgroup amortise the copies of the trees to LDS (per
-// 64 rows, depth 6: 1, 1.07 and 1.25 of the time with 4, 2 and 1 groups), fewer leave smaller
-// batches enough workgroups; the last round of workgroups counts whole.
-inline int choose_walk_groups(const DevModel &m, int64_t n_rows, int n_splits)
+// Row groups per workgroup, walk and deep walk kernels: as many as leave every CU a workgroup, or, with trees enough
+// for their copies to LDS to count, half of the CUs one of two groups.  More rows per workgroup share the copies of the trees to LDS and keep more walks in flight, and a
+// workgroup that has a CU to itself is nearly twice as fast as two that share one, so full rounds of two per CU are
+// not what counts: over 250 models and 20,000 to 270,000 rows this is within 0.5 % of the best choice for each (2 % at
+// 20,000 rows; 1.2 times it at worst), where counting rounds was 25 % off at 66,000 and 40 % at 150,000 rows (ten trees of depth 2,
+// 10 features, 66,000 rows: 19.2 us with one group, 14.9 with two, 11.5 with four).  Split launches have no
+// workgroups to spare.
+inline int choose_groups(const DevModel &m, int groups, int64_t n_rows, int n_splits)
 {
-    int best = 1;
-    double best_cost = 0.0;
-    for (int g = m.walk.groups; g >= 1; g /= 2) {
-        const int64_t blocks = (n_rows + PLAN_ROWS * g - 1) / (PLAN_ROWS * g) * n_splits;
-        const double cost = static_cast<double>((blocks + WALK_RESIDENT - 1) / WALK_RESIDENT) * g * (g == 4 ? 1.0 : g == 2 ? 1.07 : 1.25);
-        if (g == m.walk.groups || cost < best_cost) {
-            best = g;
-            best_cost = cost;
-        }
-    }
-    return best;
+    const auto workgroups = [&](int g) { return (n_rows + PLAN_ROWS * g - 1) / (PLAN_ROWS * g); };
+    if (n_splits > 1) return 1;
+    if (groups >= 4 && workgroups(4) >= CUS) return 4;
+    return groups >= 2 && workgroups(2) >= (m.n_trees >= 100 ? CUS / 2 : CUS) ? 2 : 1;
 }
 
 // Whether two workgroups fit a CU.
 inline bool deep_shares_cu(const DevModel &m, int groups, bool sums)
 {
     return deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups, sums) <= CU_LDS_BYTES / 2;
-}
-
-// Row groups per workgroup: two rows per lane share the copies of the trees' tops and keep twice as
-// many walks in flight (300 irregular trees, 90 features, 103,069 rows: 94 us with two, 108 with one);
-// one leaves a small batch more workgroups.  The last round of workgroups counts whole.
-inline int choose_deep_groups(const DevModel &m, int64_t n_rows, int n_splits, bool sums)
-{
-    if (m.deep.groups == 1) return 1;
-    double cost[2];
-    for (int g = 1; g <= 2; ++g) {
-        const int64_t per_cu = deep_shares_cu(m, g, sums) ? 2 : 1;
-        const int64_t blocks = (n_rows + PLAN_ROWS * g - 1) / (PLAN_ROWS * g) * n_splits, round = 256 * per_cu;
-        cost[g - 1] = static_cast<double>((blocks + round - 1) / round * per_cu * g) * (g == 1 ? 1.15 : 1.0);
-    }
-    return cost[0] < cost[1] ? 1 : 2;
 }
 
 // One lane per (row, tree): the smallest batches of the walk kernels' models (forest_kernels_split.hip).
@@ -423,13 +406,13 @@ inline LaunchPlan plan_launch(const DevModel &m, const Workspace *ws, int64_t n_
     } else if (m.walk.depth > 0 && !dense) {
         p.kernel = FOREST_KERNEL_WALK;
         p.splits = choose_walk_splits(m, ws, n_rows, sums);
-        p.groups = choose_walk_groups(m, n_rows, p.splits);
+        p.groups = choose_groups(m, m.walk.groups, n_rows, p.splits);
     } else if (m.deep.groups > 0 && !dense) {
         // trees deeper than 8, vector leaves, infinite thresholds: what a row does not meet is not tested
         // (128 trees of depth 12: 2.9 ms against 14.5 with the register-bank kernel)
         p.kernel = FOREST_KERNEL_DEEP;
         p.splits = choose_walk_splits(m, ws, n_rows, sums);
-        p.groups = choose_deep_groups(m, n_rows, p.splits, sums);
+        p.groups = choose_groups(m, m.deep.groups, n_rows, p.splits);
     } else if (m.path == PATH_RANK) {
         p.kernel = FOREST_KERNEL_RANK;
     } else if (m.path == PATH_RANK_LDS) {

@@ -84,7 +84,7 @@ def test_deep_takes_what_it_is_built_for():
 @pytest.mark.parametrize("features", [3, 16, 61, 130, 256, 300])
 @pytest.mark.parametrize("depth,outputs,width", [(9, 1, 1), (11, 4, 1), (12, 2, 2), (10, 3, 3), (9, 8, 8), (5, 10, 10)])
 def test_deep_kernels(features, depth, outputs, width):
-    """One row group per workgroup; every kind of sum; few trees (waves without any) and more trees than
+    """One and two row groups; every kind of sum; few trees (waves without any) and more trees than
     waves; leaf ids of a tree count that is no multiple of four."""
     import paper_2301_13441_amd as pk
     rng = np.random.default_rng(100 * depth + features)
@@ -98,14 +98,14 @@ def test_deep_kernels(features, depth, outputs, width):
 @pytest.mark.gpu
 @pytest.mark.parametrize("features", [3, 90, 256])
 @pytest.mark.parametrize("depth,outputs,width", [(9, 1, 1), (11, 4, 1), (12, 2, 2)])
-def test_deep_kernels_with_two_rows_per_lane(features, depth, outputs, width):
-    """Two row groups with a ragged last workgroup, two workgroups on a CU and one; one column, several, and vector
-    leaves; trees in numbers that are no multiple of four or two."""
+@pytest.mark.parametrize("rows,groups", [(12301, 1), (65536 - 13, 2)])
+def test_deep_kernels_by_rows_per_lane(features, depth, outputs, width, rows, groups):
+    """One and two row groups with a ragged last workgroup, two workgroups on a CU and one; one column, several, and
+    vector leaves; trees in numbers that are no multiple of four or two."""
     rng = np.random.default_rng(100 * depth + features)
-    rows = 65536 - 13
-    for trees in (5, 37):
+    for trees in (5, 29):
         f = _forest(9 * depth + features, trees, depth, features, outputs, width, stop=0.3)
-        _launches(f, rows, "deep", 128)
+        _launches(f, rows, "deep", 64 * groups)
         _check(f, _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng), leaves=True)
 
 

@@ -137,3 +137,16 @@ def test_leaf_ids_take_no_lds_for_sums():
     f = _vector_full(20, 4, 10, 16)                # 16 waves x 16 columns x 64 rows of sums: 128 KB
     lds = lambda leaves: binding.forest_packed_launch(f, 100_000, leaves, form="walk")["lds_bytes"]
     assert lds(False) > 128 << 10 and lds(True) <= 80 << 10
+
+
+def test_row_groups_leave_every_cu_a_workgroup():
+    """The most rows per workgroup of which there are 256 (of two groups and 100 trees: 128), and one group where trees
+    are cut into shares.  Rounds of 512 workgroups, counted whole, chose one group for a batch of 66,000 or 150,000 rows."""
+    from paper_2301_13441_amd import binding
+    group = lambda f, rows: binding.forest_packed_launch(f, rows, form="walk")["rows_per_workgroup"] // 64
+    few, many, deep = _full_forest(1, 10, 4, 10), _full_forest(1, 600, 8, 10), _vector_full(30, 4, 10, 2)
+    for rows, want in ((9_000, 1), (16_257, 2), (33_000, 2), (65_280, 2), (65_281, 4), (66_000, 4), (150_000, 4), (10**6, 4)):
+        less = want if rows != 16_257 else 1
+        assert group(few, rows) == less and group(deep, rows) == min(less, 2)
+        s = binding.forest_packed_launch(many, rows, form="walk")
+        assert s["rows_per_workgroup"] == 64 * (want if s["shares"] == 1 else 1)

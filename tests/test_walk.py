@@ -85,16 +85,16 @@ def _launches(f, rows, kernel, rows_per_workgroup):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("rows,groups", [(65536 - 13, 2), (131072 - 13, 4)])
+@pytest.mark.parametrize("rows,groups", [(12301, 1), (49152 - 13, 2), (131072 - 13, 4)])
 @pytest.mark.parametrize("depth", [3, 4, 5, 6, 7, 8])
 @pytest.mark.parametrize("features,outputs,full", [(3, 1, True), (40, 1, False), (9, 4, False), (90, 4, True)])
-def test_walk_kernels_with_several_rows_per_lane(depth, features, outputs, full, rows, groups):
-    """Two and four row groups per workgroup with a ragged last one; few trees (waves without any) and more trees than
-    waves, in numbers that are no multiple of four."""
+def test_walk_kernels_by_rows_per_lane(depth, features, outputs, full, rows, groups):
+    """One, two and four row groups per workgroup with a ragged last one; few trees (waves without any) and more trees
+    than waves, in numbers that are no multiple of four."""
     rng = np.random.default_rng(100 * depth + features)
-    for trees in (5, 83):
+    for trees in (5, 53):
         f = _forest(9 * depth + features, trees, depth, features, outputs, full)
-        _launches(f, rows, "walk", 64 * (groups if outputs == 1 else 2))
+        _launches(f, rows, "walk", 64 * min(groups, 4 if outputs == 1 else 2))
         _check(f, _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng), leaves=True)
 
 
@@ -102,15 +102,15 @@ def test_walk_kernels_with_several_rows_per_lane(depth, features, outputs, full,
 @pytest.mark.parametrize("depth", [1, 2, 3, 4, 5, 6, 7, 8])
 @pytest.mark.parametrize("features,outputs,full", [(3, 1, True), (40, 4, False), (61, 1, False), (130, 4, True), (300, 1, True)])
 def test_walk_kernels(depth, features, outputs, full):
-    """Every depth; tiles laid out for 4, 2 and 1 row groups, one launched; one and several columns; few trees over
-    few rows (a lane per row and tree) and more trees than waves; leaf ids of a tree count that is no multiple of four."""
+    """Every depth; tiles of 4, 2 and 1 row groups; one and several columns; few trees over few rows (a lane per row and
+    tree) and more trees than waves; leaf ids of a tree count that is no multiple of four."""
     import paper_2301_13441_amd as pk
     rng = np.random.default_rng(100 * depth + features)
     for trees, rows in ((5, 517), (83, 65536 + 77)):
         f = _forest(9 * depth + features, trees, depth, features, outputs, full)
         assert pk.forest_pack(f)["walk_depth"] > 0
         if rows > 60000:
-            _launches(f, rows, "walk", 64)
+            _launches(f, rows, "walk", 64 * pk.forest_pack(f)["walk_groups"])
         X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
         _check(f, X, leaves=True)
 
