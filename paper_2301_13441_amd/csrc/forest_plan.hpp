@@ -139,6 +139,7 @@ inline double dense_row_ps(const PackedModel &m, int64_t n_entries)
 {
     const int W = m.leaf_width, K = m.n_outputs;
     DenseCost c;
+    double scale = 1.0;
     if (m.n_features > 256) return 0.0;
     if (m.path == PATH_RANK) {
         const int regs = m.rank_regs <= 32 ? 0 : m.rank_regs <= 64 ? 1 : 2;
@@ -156,14 +157,14 @@ inline double dense_row_ps(const PackedModel &m, int64_t n_entries)
         const size_t fit = CU_LDS_BYTES / ranklds_lds_bytes(m.rank_regs, K, W, m.lds_waves);
         if (m.lds_waves == 12) c = fit > 1 ? DenseCost{81.9, 1.28, 0.654, 4.32, 0, 0.169, 0.0468, 0.438} : DenseCost{0, 1.79, 1.79, 20.7, 2.86, 0.145, 0.0652, 0.110};
         else if (m.lds_waves == 8 && fit > 1) c = {5.27, 1.78, 1.01, 11.0, 0.616, 0.336, 0.0493, 0.383};
-        else if (m.lds_waves == 2 && fit >= 7) c = {0, 0, 7.29, 0, 0, 0.483, 0.0609, 0.324};
+        else if (m.lds_waves == 2 && fit >= 4) c = {0, 0, 7.29, 0, 0, 0.483, 0.0609, 0.324}, scale = fit < 7 ? 7.0 / fit : 1.0;
         else return 0.0;
     } else {
         return 0.0;
     }
     const double F = m.n_features, T = m.n_trees;
-    return c.base + c.feature * F + c.reg * m.rank_regs + c.output * K + c.tree * T + c.level * m.sum_depth + c.entry * n_entries +
-           c.value * (W > 1 ? T * W : 0.0);
+    return scale * (c.base + c.feature * F + c.reg * m.rank_regs + c.output * K + c.tree * T + c.level * m.sum_depth + c.entry * n_entries +
+                    c.value * (W > 1 ? T * W : 0.0));
 }
 
 // What a PackedModel says about its kernels; the device tables are left null.
@@ -371,8 +372,9 @@ constexpr int64_t MAX_LAUNCH_ROWS = int64_t{1} << 27;
 // kernels, of which only the deep one loses, where trees are fewer than a workgroup's waves (100,000 rows of twelve
 // trees of depth 3, 9 columns, 4 features: 13.0 us, dense 9.2; from 30 trees on they take 0.3 to 1.1 of the dense time).  The
 // margins keep the walk kernels where the estimates, or a batch of few rounds of workgroups, decide nothing.  A batch
-// that the dense kernels cut into shares costs them two more launches, and with vector leaves they gain nothing there.
-constexpr int64_t DENSE_MIN_ROWS = 8192;
+// that the dense kernels cut into shares costs them two more launches, and with vector leaves they gain nothing there
+// (1500 stumps over 4 features, 5,000 rows: 27.1 us, dense 19.9; below 4,096 rows the gain is the launches').
+constexpr int64_t DENSE_MIN_ROWS = 4096;
 
 inline bool prefers_dense(const DevModel &m, int64_t n_rows, bool sums)
 {

@@ -108,7 +108,9 @@ def test_shallow_trees_over_few_features_stay_with_the_dense_kernels():
         assert kernel(f, 1_000_000, leaves=True) == ("rank" if few else "walk" if f.n_trees == 10 else "deep")
         assert kernel(f, 100) in ("point", "deep")
         assert kernel(f, 1_000_000, form="walk") in ("walk", "deep")
-    assert kernel(infinite, 20_000) == "rank"
+    assert kernel(infinite, 20_000) == kernel(infinite, 5_000) == "rank" and kernel(infinite, 4_000) == "deep"
+    few = wl.random_forest(312, n_trees=10, n_features=10, max_depth=3, stop_prob=0.15, n_outputs=12, leaf_width=12)
+    assert kernel(few, 1_000_000) == "rank_lds" and kernel(few, 1_000) == "deep"
     assert kernel(_mixed(1000, 5, 10, 8), 1_000_000) == "rank_lds"
     for name, rows, want in (("c2", 1_000_000, "walk"), ("c3", 1_000_000, "walk"), ("c4", 500_000, "walk"), ("c5", 4_000_000, "deep")):
         f = wl.make_workload(name, n_rows=1).forest
