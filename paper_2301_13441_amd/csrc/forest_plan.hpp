@@ -157,8 +157,9 @@ inline double dense_row_ps(const PackedModel &m, int64_t n_entries)
         const size_t fit = CU_LDS_BYTES / ranklds_lds_bytes(m.rank_regs, K, W, m.lds_waves);
         if (m.lds_waves == 12) c = fit > 1 ? DenseCost{81.9, 1.28, 0.654, 4.32, 0, 0.169, 0.0468, 0.438} : DenseCost{0, 1.79, 1.79, 20.7, 2.86, 0.145, 0.0652, 0.110};
         else if (m.lds_waves == 8 && fit > 1) c = {5.27, 1.78, 1.01, 11.0, 0.616, 0.336, 0.0493, 0.383};
-        else if (m.lds_waves == 2 && fit >= 4) c = {0, 0, 7.29, 0, 0, 0.483, 0.0609, 0.324}, scale = fit < 7 ? 7.0 / fit : 1.0;
+        else if (m.lds_waves == 2 && fit >= 4) c = {0, 0, 7.29, 0, 0, 0.483, 0.0609, 0.324};
         else return 0.0;
+        if (m.lds_waves == 2 && fit < 7) scale = 7.0 / static_cast<double>(fit);  // measured with seven workgroups on a CU
     } else {
         return 0.0;
     }
@@ -309,12 +310,12 @@ inline int choose_walk_splits(const DevModel &m, const Workspace *ws, int64_t n_
 }
 
 // Row groups per workgroup, walk and deep walk kernels: as many as leave every CU a workgroup, or, with trees enough
-// for their copies to LDS to count, half of the CUs one of two groups.  More rows per workgroup share the copies of the trees to LDS and keep more walks in flight, and a
-// workgroup that has a CU to itself is nearly twice as fast as two that share one, so full rounds of two per CU are
-// not what counts: over 250 models and 20,000 to 270,000 rows this is within 0.5 % of the best choice for each (2 % at
-// 20,000 rows; 1.2 times it at worst), where counting rounds was 25 % off at 66,000 and 40 % at 150,000 rows (ten trees of depth 2,
-// 10 features, 66,000 rows: 19.2 us with one group, 14.9 with two, 11.5 with four).  Split launches have no
-// workgroups to spare.
+// for their copies to LDS to count, half of the CUs one of two groups.  More rows per workgroup share those copies and
+// keep more walks in flight, and a workgroup that has a CU to itself is nearly twice as fast as one of two, so rounds
+// of two per CU are not what counts: over 250 models and 20,000 to 270,000 rows this is within 0.5 % of the best choice
+// for each (2 % at 20,000 rows; 1.2 times it at worst), where counting rounds was 25 % off at 66,000 and 40 % at
+// 150,000 rows (ten trees of depth 2, 10 features, 66,000 rows: 19.2 us with one group, 14.9 with two, 11.5 with
+// four).  Split launches have no workgroups to spare.
 inline int choose_groups(const DevModel &m, int groups, int64_t n_rows, int n_splits)
 {
     const auto workgroups = [&](int g) { return (n_rows + PLAN_ROWS * g - 1) / (PLAN_ROWS * g); };
@@ -370,10 +371,10 @@ constexpr int64_t MAX_LAUNCH_ROWS = int64_t{1} << 27;
 
 // Whether the dense kernels are the faster ones for a batch.  The estimates are of sums; leaf ids ask less of the walk
 // kernels, of which only the deep one loses, where trees are fewer than a workgroup's waves (100,000 rows of twelve
-// trees of depth 3, 9 columns, 4 features: 13.0 us, dense 9.2; from 30 trees on they take 0.3 to 1.1 of the dense time).  The
-// margins keep the walk kernels where the estimates, or a batch of few rounds of workgroups, decide nothing.  A batch
-// that the dense kernels cut into shares costs them two more launches, and with vector leaves they gain nothing there
-// (1500 stumps over 4 features, 5,000 rows: 27.1 us, dense 19.9; below 4,096 rows the gain is the launches').
+// trees of depth 3, 9 columns, 4 features: 13.0 us, dense 9.2; from 30 trees on they take 0.3 to 1.1 of the dense
+// time).  The margins keep the walk kernels where the estimates, or a batch of few rounds of workgroups, decide
+// nothing.  A batch that the dense kernels cut into shares costs them two more launches, which their faster tests have
+// to earn (1500 stumps over 4 features, 5,000 rows: 27.1 us, dense 19.9); with vector leaves they do not.
 constexpr int64_t DENSE_MIN_ROWS = 4096;
 
 inline bool prefers_dense(const DevModel &m, int64_t n_rows, bool sums)
