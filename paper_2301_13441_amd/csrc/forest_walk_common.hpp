@@ -27,13 +27,16 @@ __device__ __forceinline__ void lds_write(uint32_t at, T v)
     *reinterpret_cast<__attribute__((address_space(3))) T *>(at) = v;
 }
 
+typedef float FloatRun4 __attribute__((ext_vector_type(4), aligned(4)));
 #if defined(__HIP_DEVICE_COMPILE__)
+typedef const __attribute__((address_space(1))) FloatRun4 *GlobalRuns;
 typedef const __attribute__((address_space(4))) uint32_t *WalkTop;
 typedef const __attribute__((address_space(4))) int32_t *WalkTable;
 typedef const __attribute__((address_space(1))) char *GlobalBytes;
 typedef const __attribute__((address_space(1))) float *GlobalFloats;
 typedef const __attribute__((address_space(1))) int32_t *GlobalInts;
 #else
+typedef const FloatRun4 *GlobalRuns;
 typedef const uint32_t *WalkTop;  // host pass: the kernel body is only parsed
 typedef const int32_t *WalkTable;
 typedef const char *GlobalBytes;
@@ -41,10 +44,6 @@ typedef const float *GlobalFloats;
 typedef const int32_t *GlobalInts;
 #endif
 
-struct __attribute__((aligned(4))) Float4 {
-    float v[4];
-};
-typedef float FloatRun4 __attribute__((ext_vector_type(4), aligned(4)));
 struct __attribute__((aligned(4))) Int4 {
     int32_t v[4];
 };
@@ -54,83 +53,56 @@ struct __attribute__((aligned(4))) Int4 {
 // four neighbouring features of a row per lane: 64 bytes of a row of X, and LDS writes that fall into
 // 16 banks.  A wave takes a contiguous run of pieces, so that both halves of a 128-byte line are
 // requested by one wave one after the other, with the non-temporal policy: X is read once and should
-// not push the trees out of the L2.
-struct TileShape {
-    const float *X;
-    int64_t n_rows;
-    int F, blocks;  // blocks of 16 features
-    uint32_t xbase, group_stride, stride;
-};
-
-// The first of a run of pieces: 16 rows from 16 * rows, 16 features from 16 * block.
-struct TilePiece {
-    int rows, block;
-    __device__ __forceinline__ void next(int blocks)
-    {
-        if (++block == blocks) {
-            block = 0;
-            ++rows;
-        }
-    }
-};
-
-// The first P pieces of a run of n, those there are, to registers ...
-template <int P>
-__device__ __forceinline__ void tile_load(const TileShape &s, int64_t row0, TilePiece at, int n, int lane, Float4 (&v)[P])
-{
-    const int r = lane & 15, c = (lane >> 4) * 4;
-#pragma unroll
-    for (int u = 0; u < P; ++u, at.next(s.blocks)) {
-        if (u < n) {  // wave-uniform, as everything but the lane's own columns
-            const int f0 = at.block * 16;
-            const int64_t row = row0 + at.rows * 16 + r;
-            const float *p = s.X + (row < s.n_rows ? row : row0) * s.F + f0 + c;
-            if (f0 + 16 <= s.F) {
-                const FloatRun4 q = __builtin_nontemporal_load(reinterpret_cast<const FloatRun4 *>(p));
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[u].v[i] = q[i];
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[u].v[i] = f0 + c + i < s.F ? p[i] : 0.0f;
-            }
-        }
-    }
-}
-
-// ... and from there to the tile.  NAN_IS_INF: a NaN is stored as +Inf.
-template <int P, bool NAN_IS_INF>
-__device__ __forceinline__ TilePiece tile_store(const TileShape &s, TilePiece at, int n, int lane, const Float4 (&v)[P])
-{
-    const int r = lane & 15, c = (lane >> 4) * 4;
-#pragma unroll
-    for (int u = 0; u < P; ++u, at.next(s.blocks)) {
-        if (u < n) {
-            const int f0 = at.block * 16;
-            const uint32_t to = s.xbase + static_cast<uint32_t>(at.rows >> 2) * s.group_stride + static_cast<uint32_t>(f0 + c) * s.stride +
-                                static_cast<uint32_t>((at.rows & 3) * 16 + r) * 4;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (f0 + 16 <= s.F || f0 + c + i < s.F)
-                    lds_write<float>(to + i * s.stride, NAN_IS_INF ? fminf(v[u].v[i], __builtin_inff()) : v[u].v[i]);
-        }
-    }
-    return at;
-}
-
-// The tile of NR row groups, P pieces in flight per lane.
+// not push the trees out of the L2.  The four features of a lane that would reach beyond the row are the row's
+// last four (written twice, with the same values), and the rows beyond the batch are its last row, so that every
+// load is whole and none waits for another: a lane's features one by one under a mask of their own cost a
+// second round trip to memory, and the addresses as 64-bit products more instructions than the loads (256 features,
+// 4M rows of 128 deep trees: 2.89 -> 2.80 ms a call; 90 features, 103,069 rows of 300: 87.2 -> 84.5 us; 1,021 rows of
+// 2000 x depth 6: 18.15 -> 17.8).  NAN_IS_INF: a NaN is stored as +Inf.
 template <int NR, int P, bool NAN_IS_INF>
 __device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t n_rows, int F, uint32_t xbase, uint32_t group_stride,
                                           uint32_t stride, int wave, int lane)
 {
+    const char *tile = reinterpret_cast<const char *>(X + row0 * F);
+    const int rows = n_rows - row0 < NR * TILE ? static_cast<int>(n_rows - row0) : NR * TILE;
+    const auto value = [](float v) { return NAN_IS_INF ? fminf(v, __builtin_inff()) : v; };
+    if (F < 4) {  // a lane per row
+        for (int g = wave; g < NR; g += WALK_WAVES)
+            for (int f = 0; f < F; ++f) {
+                const int row = min(g * TILE + lane, rows - 1);
+                lds_write<float>(xbase + g * group_stride + f * stride + lane * 4, value(reinterpret_cast<const float *>(tile)[row * F + f]));
+            }
+        return;
+    }
     const int blocks = (F + 15) >> 4, pieces = blocks * (NR * 4);
-    const TileShape s{X, n_rows, F, blocks, xbase, group_stride, stride};
     const int begin = pieces * wave / WALK_WAVES, end = pieces * (wave + 1) / WALK_WAVES;
-    TilePiece at{begin / blocks, 0};
-    at.block = begin - at.rows * blocks;
+    const int r = lane & 15, c = (lane >> 4) * 4;
+    const uint32_t pitch = static_cast<uint32_t>(F) * 4;
+    int at_rows = begin / blocks, at_block = begin - at_rows * blocks;  // the piece: 16 rows from 16 * at_rows, 16 features from 16 * at_block
     for (int t = begin; t < end; t += P) {
-        Float4 v[P];
-        tile_load<P>(s, row0, at, end - t, lane, v);
-        at = tile_store<P, NAN_IS_INF>(s, at, end - t, lane, v);
+        FloatRun4 v[P];
+        uint32_t to[P];
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            if (t + u < end) {  // wave-uniform
+                const int f = min(at_block * 16 + c, F - 4), row = at_rows * 16 + r;
+                const uint32_t from = static_cast<uint32_t>(min(row, rows - 1)) * pitch + static_cast<uint32_t>(f) * 4;
+                v[u] = __builtin_nontemporal_load((GlobalRuns)((GlobalBytes)tile + from));
+                to[u] = xbase + static_cast<uint32_t>(at_rows >> 2) * group_stride + static_cast<uint32_t>(f) * stride +
+                        static_cast<uint32_t>(row & 63) * 4;
+                if (++at_block == blocks) {
+                    at_block = 0;
+                    ++at_rows;
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < P; ++u) {
+            if (t + u < end) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) lds_write<float>(to[u] + i * stride, value(v[u][i]));
+            }
+        }
     }
 }
 

@@ -129,3 +129,17 @@ def test_smallest_batches_with_a_lane_per_row_and_tree(depth, trees, features, o
         if rows >= 70:
             X = _special_rows(X, f, rng)
         _check(f, X, leaves=rows <= 70)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("features", [1, 2, 3, 4, 5, 15, 17, 35])
+def test_tiles_of_rows_that_end_inside_a_piece(features):
+    """Rows of fewer features than a lane loads at once, of just as many, and of one or three beyond a piece; a last
+    workgroup of one row; both walk kernels, which fill their tiles with the same code."""
+    rng = np.random.default_rng(features)
+    scalar = _forest(features, 9, 6, features)
+    vector = wl.random_forest(features, n_trees=9, n_features=features, max_depth=9, stop_prob=0.2, n_outputs=2, leaf_width=2,
+                              aggregate=wl.AGG_MEAN)
+    for f in (scalar, vector):
+        for rows in (16385, 20011):
+            _check(f, _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng), leaves=True)
