@@ -121,13 +121,15 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
     const uint32_t group_stride = static_cast<uint32_t>(F) * 256;
     const uint32_t stage = static_cast<uint32_t>(wave) * NODES_BYTES;
 
-    // This wave's trees: a contiguous run for the sums; for the leaf ids, fours dealt in turn, so
-    // that the waves write neighbouring ids at about the same time.
+    // This wave's trees: a contiguous run for the sums; for the leaf ids, which have the caller's order, up to four in
+    // turn, so that the waves have neighbouring ids at the same time (forest_kernels_walk.hip).
     const int unit = static_cast<int>(blockIdx.y) * DEEP_WAVES + wave, units = m.n_splits * DEEP_WAVES;
-    const int t_begin = LEAVES ? unit * 4 : static_cast<int>(static_cast<int64_t>(T) * unit / units);
+    constexpr int ROUND = 4 * DEEP_WAVES;
+    const auto share = [&](int k) { return T - k * ROUND >= ROUND ? 4 : (T - k * ROUND + DEEP_WAVES - 1) / DEEP_WAVES; };
+    const auto first_tree = [&](int k) { return k * ROUND + wave * share(k); };
+    const int t_begin = LEAVES ? first_tree(blockIdx.y) : static_cast<int>(static_cast<int64_t>(T) * unit / units);
     const int t_end = LEAVES ? T : static_cast<int>(static_cast<int64_t>(T) * (unit + 1) / units);
-    auto next_tree = [&](int t) { return !LEAVES || (t & 3) != 3 ? t + 1 : t + 1 + (units - 1) * 4; };
-    auto place = [&](int t) { return LEAVES ? ((WalkTable)m.deep.position)[t] : t; };  // leaf ids: caller's order
+    auto place = [&](int t) { return LEAVES ? ((WalkTable)m.deep.position)[t] : t; };
 
     const char *tops = reinterpret_cast<const char *>(m.deep.top);
     Vec4 ahead[2];
@@ -155,7 +157,6 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
 #pragma unroll
         for (int r = 0; r < NR; ++r) acc[k][r] = 0.0;
     if (MODE == DEEP_COLUMNS && t_begin < t_end) column = first_column = static_cast<int>(head.w[1]);
-    int32_t ids[NR][4];
 
     // The lanes' places in the units of the trees at hand: byte offset from the tree's first unit, and
     // what is there.
@@ -243,10 +244,9 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
         }
         deep_top<NR>(stage, xa, here, at[j], what[j]);
     };
-    for (int t = t_begin; t < t_end;) {
-        const int second = next_tree(t), after = next_tree(second);
-        const bool two = second < t_end;  // a four begins with an even tree: its pairs stay together
-        take(0, second);
+    // One or two trees, from their tops to their leaves; the tree after them.
+    const auto walk = [&](int t, bool two, int after) {
+        take(0, two ? t + 1 : after);
         if (two) {
             take(1, after);
         } else {
@@ -254,43 +254,68 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
             for (int r = 0; r < NR; ++r) what[1][r] = Vec2{0, 0};
         }
         go_on();
-        if constexpr (!LEAVES) {
+    };
+    if constexpr (!LEAVES) {
+        for (int t = t_begin; t < t_end; t += NT) {
+            const bool two = t + 1 < t_end;
+            walk(t, two, t + NT);
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 if (j > 0 && !two) break;
                 if (MODE == DEEP_COLUMNS && tree_column[j] != column) change_column(tree_column[j]);
                 add_values(j);
             }
-        } else {
+        }
+    } else {
+        const int rounds = (T + ROUND - 1) / ROUND;
+        for (int k = static_cast<int>(blockIdx.y); k < rounds; k += m.n_splits) {
+            const int n = share(k), first = first_tree(k), own = min(T - first, n);
+            const int next = k + m.n_splits < rounds ? first_tree(k + m.n_splits) : T;
+            uint32_t ids[NR][4] = {};
 #pragma unroll
-            for (int j = 0; j < NT; ++j) {
-                if (j > 0 && !two) break;
-                const int32_t *node = m.deep.unit_node + first_unit[j];
+            for (int p = 0; p < 4; p += NT) {
+                if (p < own) {
+                    walk(first + p, p + 1 < own, p + NT < own ? first + p + NT : next);
 #pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    const int32_t id = node[at[j][r] >> 3];
-                    ids[r][j] = (t & 2) == 0 ? id : ids[r][j];
-                    ids[r][2 + j] = (t & 2) != 0 ? id : ids[r][2 + j];
-                }
-            }
-            const int first = t & ~3;
-            if ((t & 2) != 0 || t + NT >= T) {
+                    for (int j = 0; j < NT; ++j) {
+                        if (j > 0 && p + j >= own) break;
+                        const int32_t *node = m.deep.unit_node + first_unit[j];
 #pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    const int64_t row = row0 + r * TILE + lane;
-                    if (row >= n_rows) continue;
-                    int32_t *dst = leaf_out + row * T + first;
-                    if (first + 4 <= T) {
-                        *reinterpret_cast<Int4 *>(dst) = Int4{{ids[r][0], ids[r][1], ids[r][2], ids[r][3]}};
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (first + j < T) dst[j] = ids[r][j];
+                        for (int r = 0; r < NR; ++r) ids[r][p + j] = static_cast<uint32_t>(node[at[j][r] >> 3]);
                     }
                 }
             }
+            const auto store = [&](int64_t row, int begin, int n, Vec4 v) {
+                int32_t *dst = leaf_out + row * T + begin;
+                if (n == 4 && begin + 4 <= T) {
+                    *reinterpret_cast<Int4 *>(dst) = Int4{{static_cast<int32_t>(v[0]), static_cast<int32_t>(v[1]), static_cast<int32_t>(v[2]), static_cast<int32_t>(v[3])}};
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (j < n && begin + j < T) dst[j] = static_cast<int32_t>(v[j]);
+                }
+            };
+            if (T <= 4) {  // a row's ids share 16 bytes: nothing to gain from an exchange
+#pragma unroll
+                for (int r = 0; r < NR; ++r)
+                    if (const int64_t row = row0 + r * TILE + lane; own > 0 && row < n_rows) leaf_out[row * T + first] = static_cast<int32_t>(ids[r][0]);
+                return;
+            }
+            // A row group's ids meet in one half of the stages, those of row i at place i + 4 * wave of its wave's part.
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                lds_write<Vec4>(r * DEEP_WAVES * NODES_BYTES + stage + ((lane + 4 * wave) & (TILE - 1)) * 16, Vec4{ids[r][0], ids[r][1], ids[r][2], ids[r][3]});
+            __syncthreads();
+            const int from = lane & (DEEP_WAVES - 1);  // the wave whose trees this lane writes
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const int li = wave * (TILE / DEEP_WAVES) + lane / DEEP_WAVES;
+                const Vec4 id = lds_read<Vec4>(r * DEEP_WAVES * NODES_BYTES + from * NODES_BYTES + ((li + 4 * from) & (TILE - 1)) * 16);
+                const int64_t row = row0 + r * TILE + li;
+                if (row < n_rows) store(row, k * ROUND + from * n, n, id);
+            }
+            __syncthreads();
         }
-        t = two ? after : second;
     }
     if constexpr (!LEAVES) {
         // The waves' sums meet in LDS, in the order of the waves.

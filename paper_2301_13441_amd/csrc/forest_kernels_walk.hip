@@ -76,18 +76,17 @@ __device__ __forceinline__ void walk_tree(uint32_t tree_at, uint32_t xa, WalkTop
 }
 
 // What a kernel leaves behind: the sums of one output column, those of several (trees sorted by
-// column), or the leaf ids of every tree.
+// column), or the leaf ids of every tree (a kernel of its own).
 enum { WALK_COLUMN = 0, WALK_COLUMNS = 1, WALK_LEAVES = 2 };
 
 template <int D, int NR, int MODE>
 __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevModel m, const float *__restrict__ X,
                                                                           int64_t n_rows, float *scores,
-                                                                          int32_t *labels, int32_t *leaf_out)
+                                                                          int32_t *labels, int32_t *)
 {
     constexpr int TREE_BYTES = 8 << D, STAGE_TREES = walk_stage_trees(D), STAGE_BYTES = TREE_BYTES * STAGE_TREES;
     constexpr int PIECES = STAGE_BYTES / 1024;  // 16 bytes per lane each
     constexpr int ROWS = NR * TILE;
-    constexpr bool LEAVES = MODE == WALK_LEAVES;
     static_assert(STAGE_BYTES % 1024 == 0, "whole 16-byte pieces per lane");
     extern __shared__ __align__(1024) char smem[];
     const int lane = threadIdx.x & (TILE - 1), wave = uniform(threadIdx.x >> 6);
@@ -95,26 +94,16 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
     const uint32_t stride = static_cast<uint32_t>(m.walk.groups) * 256, xbase = WALK_WAVES * STAGE_BYTES;
     const uint32_t mine = static_cast<uint32_t>(wave) * STAGE_BYTES;
 
-    // This wave's stages: a contiguous run for the sums; for the leaf ids, groups of at least four
-    // trees dealt in turn, so that the waves write neighbouring ids at about the same time.
-    constexpr int TURN = LEAVES && STAGE_TREES < 4 ? 4 / STAGE_TREES : 1;  // stages per group
+    // This wave's stages: a contiguous run.
     const int S = m.walk.stages;
     const int unit = static_cast<int>(blockIdx.y) * WALK_WAVES + wave, units = m.n_splits * WALK_WAVES;
-    const int s_begin = LEAVES ? unit * TURN : static_cast<int>(static_cast<int64_t>(S) * unit / units);
-    const int s_end = LEAVES ? S : static_cast<int>(static_cast<int64_t>(S) * (unit + 1) / units);
-    auto next_stage = [&](int s) {
-        if (!LEAVES) return s + 1;
-        return (s + 1) % TURN != 0 ? s + 1 : s + 1 + (units - 1) * TURN;
-    };
+    const int s_begin = static_cast<int>(static_cast<int64_t>(S) * unit / units);
+    const int s_end = static_cast<int>(static_cast<int64_t>(S) * (unit + 1) / units);
 
     const char *image = reinterpret_cast<const char *>(m.walk.node);
     Vec4 ahead[PIECES];
     auto fetch = [&](int s) {
-        int64_t at = static_cast<int64_t>(s) * STAGE_BYTES + lane * 16;
-        if (LEAVES) {  // caller's order: the tree this lane's pieces belong to sits anywhere
-            const int t = s * STAGE_TREES + (lane * 16) / TREE_BYTES;
-            at = static_cast<int64_t>(m.walk.position[t]) * TREE_BYTES + (lane * 16) % TREE_BYTES;
-        }
+        const int64_t at = static_cast<int64_t>(s) * STAGE_BYTES + lane * 16;
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) ahead[i] = *reinterpret_cast<const Vec4 *>(image + at + i * 1024);
     };
@@ -126,7 +115,6 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
     double acc[NR], done[WALK_MAX_COLUMNS - 1][NR];  // the running column, the columns before it
     int column = 0, done_column[WALK_MAX_COLUMNS - 1], n_done = 0, first_column = 0;
     float value[NR];  // the last tree's leaf values, not yet added
-    int32_t ids[NR][4];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         acc[r] = 0.0;
@@ -135,90 +123,42 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
     if (MODE == WALK_COLUMNS && s_begin < s_end)
         column = first_column = ((WalkTable)(image + static_cast<int64_t>(s_begin) * STAGE_BYTES))[0];
 
-    for (int s = s_begin; s < s_end;) {
+    for (int s = s_begin; s < s_end; ++s) {
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) lds_write<Vec4>(mine + i * 1024 + lane * 16, ahead[i]);
-        const int s_next = next_stage(s);
-        if (s_next < s_end) fetch(s_next);
-        const int t0 = s * STAGE_TREES;
-        auto one_tree = [&](int q, int j) {
-            const int t = t0 + q;
-            const int at = LEAVES ? ((WalkTable)m.walk.position)[t] : t;
-            const WalkTop top = (WalkTop)(image + static_cast<int64_t>(at) * TREE_BYTES);
+        if (s + 1 < s_end) fetch(s + 1);
+#pragma unroll 1
+        for (int q = 0; q < STAGE_TREES; ++q) {
+            const int t = s * STAGE_TREES + q;
+            const WalkTop top = (WalkTop)(image + static_cast<int64_t>(t) * TREE_BYTES);
             const uint32_t tree_at = mine + q * TREE_BYTES;
             uint32_t idx[NR];
             walk_tree<D, NR>(tree_at, xa, top, idx);
-            if (!LEAVES) {
 #pragma unroll
-                for (int r = 0; r < NR; ++r) acc[r] += static_cast<double>(value[r]);
-                if (const int c = static_cast<int>(top[0]); MODE == WALK_COLUMNS && c != column) {
+            for (int r = 0; r < NR; ++r) acc[r] += static_cast<double>(value[r]);
+            if (const int c = static_cast<int>(top[0]); MODE == WALK_COLUMNS && c != column) {
 #pragma unroll
-                    for (int k = WALK_MAX_COLUMNS - 2; k > 0; --k) {
-                        done_column[k] = done_column[k - 1];
+                for (int k = WALK_MAX_COLUMNS - 2; k > 0; --k) {
+                    done_column[k] = done_column[k - 1];
 #pragma unroll
-                        for (int r = 0; r < NR; ++r) done[k][r] = done[k - 1][r];
-                    }
-                    done_column[0] = column;
-                    ++n_done;
-                    column = c;
+                    for (int r = 0; r < NR; ++r) done[k][r] = done[k - 1][r];
+                }
+                done_column[0] = column;
+                ++n_done;
+                column = c;
 #pragma unroll
-                    for (int r = 0; r < NR; ++r) {
-                        done[0][r] = acc[r];
-                        acc[r] = 0.0;
-                    }
+                for (int r = 0; r < NR; ++r) {
+                    done[0][r] = acc[r];
+                    acc[r] = 0.0;
                 }
             }
             // half an index is the leaf's byte offset; the tree's address in it is taken off the base
-            const char *leaves = LEAVES ? reinterpret_cast<const char *>(m.walk.leaf_node) : reinterpret_cast<const char *>(m.walk.leaf);
-            leaves += (static_cast<int64_t>(at) << (D + 2)) - (tree_at >> 1);
+            const char *leaves = reinterpret_cast<const char *>(m.walk.leaf) + (static_cast<int64_t>(t) << (D + 2)) - (tree_at >> 1);
             asm volatile("" : "+s"(leaves));  // keeps the base whole, so that the loads take a 32-bit offset
 #pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                const GlobalBytes p = (GlobalBytes)leaves + (idx[r] >> 1);
-                if (LEAVES) ids[r][j] = *(GlobalInts)p;
-                else value[r] = *(GlobalFloats)p;
-            }
-        };
-        if (!LEAVES) {
-#pragma unroll 1
-            for (int q = 0; q < STAGE_TREES; ++q) one_tree(q, 0);
-        } else {
-            // four trees at a time: whole in a stage, or over the stages of a group
-            constexpr int STEP = STAGE_TREES < 4 ? STAGE_TREES : 4;
-            const int j0 = STAGE_TREES < 4 ? (s % TURN) * STAGE_TREES : 0;
-#pragma unroll 1
-            for (int q = 0; q < STAGE_TREES; q += STEP) {
-#pragma unroll
-                for (int j = 0; j < STEP; ++j) {
-                    if (STEP == 4) {
-                        one_tree(q + j, j);
-                    } else {  // the slot in ids[] has to be a constant
-#pragma unroll
-                        for (int k = 0; k < 4; k += STEP)
-                            if (k == j0) one_tree(q + j, k + j);
-                    }
-                }
-                const int last = t0 + q + STEP;  // trees [.., last) are in ids[]
-                if (last % 4 != 0 && last < m.n_trees) continue;
-                const int first = (last - 1) / 4 * 4;
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    const int64_t row = row0 + r * TILE + lane;
-                    if (row >= n_rows) continue;
-                    int32_t *dst = leaf_out + row * m.n_trees + first;
-                    if (first + 4 <= m.n_trees) {
-                        *reinterpret_cast<Int4 *>(dst) = Int4{{ids[r][0], ids[r][1], ids[r][2], ids[r][3]}};
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (first + j < m.n_trees) dst[j] = ids[r][j];
-                    }
-                }
-            }
+            for (int r = 0; r < NR; ++r) value[r] = *(GlobalFloats)((GlobalBytes)leaves + (idx[r] >> 1));
         }
-        s = s_next;
     }
-    if (LEAVES) return;
 #pragma unroll
     for (int r = 0; r < NR; ++r) acc[r] += static_cast<double>(value[r]);
 
@@ -261,10 +201,133 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
     }
 }
 
+// The leaf ids of every tree, caller's order.  A row's ids are neighbours in the output and a lane holds those of few
+// trees, so the waves take four trees each, side by side, and exchange the ids through their stages before they leave: a
+// store then writes whole 256-byte runs of four rows.  Straight from the lanes, 16 bytes at the pitch of a row, 100,003
+// rows of 200 x depth 6 took 65.6 us, three quarters of them for the stores; so 42.5, of which the stores are 10 (250,000
+// rows of 200 x depth 3: 235 -> 65; 66,000 of 700 x depth 3: 310 -> 98).  Ids of these trees, which have 511 nodes at
+// most, fit 16 bits.  What is left of the trees after the last whole round is dealt evenly.  Bound: the walk, with 391
+// workgroups for 256 CUs; two shares of the trees, or fewer rows per workgroup, fill the tile more often and took 54.7 and
+// 50.4.
+template <int D, int NR>
+__global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kernel(DevModel m, const float *__restrict__ X,
+                                                                                 int64_t n_rows, float *, int32_t *,
+                                                                                 int32_t *leaf_out)
+{
+    constexpr int TREE_BYTES = 8 << D, STEP = walk_stage_trees(D) < 4 ? walk_stage_trees(D) : 4;  // trees copied at a time
+    constexpr int STEP_BYTES = TREE_BYTES * STEP, STAGE_BYTES = walk_stage_bytes(D);
+    constexpr int PIECES = (STEP_BYTES + 1023) / 1024;
+    constexpr int ROWS = NR * TILE;
+    constexpr int EXCHANGE = NR * TILE * 8 <= STAGE_BYTES ? NR : STAGE_BYTES / (TILE * 8);  // row groups that a stage holds the ids of
+    static_assert(NR % EXCHANGE == 0, "whole exchanges");
+    extern __shared__ __align__(1024) char smem[];
+    const int lane = threadIdx.x & (TILE - 1), wave = uniform(threadIdx.x >> 6);
+    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * ROWS;
+    const int T = m.n_trees;
+    const uint32_t stride = static_cast<uint32_t>(m.walk.groups) * 256, xbase = WALK_WAVES * STAGE_BYTES;
+    const uint32_t mine = static_cast<uint32_t>(wave) * STAGE_BYTES;
+    const int round = 4 * WALK_WAVES, rounds = (T + round - 1) / round;
+
+    const char *image = reinterpret_cast<const char *>(m.walk.node);
+    // Trees each wave takes in a round, and the first of this one's.
+    const auto share = [&](int k) { return T - k * round >= round ? 4 : (T - k * round + WALK_WAVES - 1) / WALK_WAVES; };
+    const auto first_tree = [&](int k) { return k * round + wave * share(k); };
+    Vec4 ahead[PIECES];
+    const auto fetch = [&](int first) {  // caller's order: a tree sits anywhere
+        if (PIECES > 1 || lane * 16 < STEP_BYTES) {
+            const int t = min(first + (lane * 16) / TREE_BYTES, T - 1);
+            const int64_t at = static_cast<int64_t>(m.walk.position[t]) * TREE_BYTES + (lane * 16) % TREE_BYTES;
+#pragma unroll
+            for (int i = 0; i < PIECES; ++i) ahead[i] = *reinterpret_cast<const Vec4 *>(image + at + i * 1024);
+        }
+    };
+    int k = static_cast<int>(blockIdx.y);
+    if (k < rounds) fetch(first_tree(k));
+    tile_fill<NR, NR == 4 ? 8 : 4, true>(X, row0, n_rows, m.n_features, xbase, 256, stride, wave, lane);
+    __syncthreads();
+
+    const uint32_t xa = xbase + lane * 4;
+    for (; k < rounds; k += m.n_splits) {
+        const int n = share(k), first = first_tree(k);
+        uint32_t ids[NR][2] = {}, id[NR];  // of up to four trees, 16 bits each; of the last tree, not yet among them
+        const auto keep = [&](int j) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) ids[r][j >> 1] = (j & 1) ? ids[r][j >> 1] | id[r] << 16 : id[r];
+        };
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (j < n) {
+                if (j % STEP == 0) {
+                    if (PIECES > 1 || lane * 16 < STEP_BYTES) {
+#pragma unroll
+                        for (int i = 0; i < PIECES; ++i) lds_write<Vec4>(mine + i * 1024 + lane * 16, ahead[i]);
+                    }
+                    if (j + STEP < n) fetch(first + j + STEP);
+                    else if (k + m.n_splits < rounds) fetch(first_tree(k + m.n_splits));
+                }
+                const int at = ((WalkTable)m.walk.position)[min(first + j, T - 1)];
+                const WalkTop top = (WalkTop)(image + static_cast<int64_t>(at) * TREE_BYTES);
+                const uint32_t tree_at = mine + (j % STEP) * TREE_BYTES;
+                uint32_t idx[NR];
+                walk_tree<D, NR>(tree_at, xa, top, idx);
+                const char *leaves = reinterpret_cast<const char *>(m.walk.leaf_node) + (static_cast<int64_t>(at) << (D + 2)) - (tree_at >> 1);
+                asm volatile("" : "+s"(leaves));  // keeps the base whole, so that the loads take a 32-bit offset
+                if (j > 0) keep(j - 1);
+#pragma unroll
+                for (int r = 0; r < NR; ++r) id[r] = static_cast<uint32_t>(*(GlobalInts)((GlobalBytes)leaves + (idx[r] >> 1)));
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (j == n - 1) keep(j);
+        const auto store = [&](int64_t row, int begin, int n, Vec2 id) {
+            int32_t *dst = leaf_out + row * T + begin;
+            const int32_t v[4] = {static_cast<int32_t>(id.x & 0xffff), static_cast<int32_t>(id.x >> 16),
+                                  static_cast<int32_t>(id.y & 0xffff), static_cast<int32_t>(id.y >> 16)};
+            if (n == 4 && begin + 4 <= T) {
+                *reinterpret_cast<Int4 *>(dst) = Int4{{v[0], v[1], v[2], v[3]}};
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (j < n && begin + j < T) dst[j] = v[j];
+            }
+        };
+        if (T <= 4) {  // a row's ids share 16 bytes: nothing to gain from an exchange
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+                if (const int64_t row = row0 + r * TILE + lane; first < T && row < n_rows) leaf_out[row * T + first] = static_cast<int32_t>(ids[r][0]);
+            return;
+        }
+        // A wave leaves the ids of its rows in its stage, those of row i at place i + 4 * wave, so that the 16 lanes
+        // that read a row's ids from the 16 stages find them in different banks.
+#pragma unroll
+        for (int g = 0; g < NR; g += EXCHANGE) {
+            constexpr int PLACES = EXCHANGE * TILE;
+            if (g > 0) __syncthreads();  // the ids before are out of the stages
+#pragma unroll
+            for (int r = 0; r < EXCHANGE; ++r)
+                lds_write<Vec2>(mine + ((r * TILE + lane + 4 * wave) & (PLACES - 1)) * 8, Vec2{ids[g + r][0], ids[g + r][1]});
+            __syncthreads();
+            const int from = lane & (WALK_WAVES - 1);  // the wave whose trees this lane writes
+            const int begin = k * round + from * n;
+#pragma unroll
+            for (int i = 0; i < EXCHANGE; ++i) {
+                const int li = (wave * EXCHANGE + i) * (TILE / WALK_WAVES) + lane / WALK_WAVES;  // a row of the exchange
+                const Vec2 id = lds_read<Vec2>(from * STAGE_BYTES + ((li + 4 * from) & (PLACES - 1)) * 8);
+                const int64_t row = row0 + g * TILE + li;
+                if (row < n_rows) store(row, begin, n, id);
+            }
+        }
+        __syncthreads();
+    }
+}
+
 template <int D, int MODE>
 KernelFn pick_groups(int groups)
 {
-    switch (groups) {
+    if constexpr (MODE == WALK_LEAVES)
+        return groups == 1 ? forest_walk_leaves_kernel<D, 1> : groups == 2 ? forest_walk_leaves_kernel<D, 2> : forest_walk_leaves_kernel<D, 4>;
+    else switch (groups) {
         case 1: return forest_walk_kernel<D, 1, MODE>;
         case 2: return forest_walk_kernel<D, 2, MODE>;
         default: return forest_walk_kernel<D, MODE == WALK_COLUMNS ? 2 : 4, MODE>;  // walk_max_groups

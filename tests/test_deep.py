@@ -117,3 +117,24 @@ def test_deep_kernels_with_wide_leaves(width):
     f = _forest(width, 37, 9, 20, width, width)
     _launches(f, 70_001, "deep", 64)
     _check(f, _special_rows(rng.standard_normal((70_001, 20)).astype(np.float32), f, rng), leaves=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [9001, 49157])
+@pytest.mark.parametrize("trees", [1, 4, 5, 17, 33, 63, 64, 65, 130])
+def test_deep_leaf_ids_by_rounds_of_trees(trees, rows):
+    """One and two row groups per workgroup (with shares of the trees at 9,001 rows); tree counts below, at and beyond a
+    round of four trees for each of 16 waves, and rests of one to four trees per wave."""
+    import torch
+    from paper_2301_13441_amd import binding
+    rng = np.random.default_rng(trees)
+    f = _forest(trees, trees, 9, 7, stop=0.3)
+    s = binding.forest_packed_launch(f, rows, True, form="walk")
+    assert s["kernel"] == "deep" and s["shares"] == (2 if rows == 9001 and trees >= 128 else 1), s
+    X = _special_rows(rng.standard_normal((rows, 7)).astype(np.float32), f, rng)
+    model = binding.forest_load_form(f, "walk")
+    try:
+        got = model.predict_leaves(torch.from_numpy(X).cuda()).cpu().numpy()
+    finally:
+        model.close()
+    np.testing.assert_array_equal(got, oracle.predict(f, X, want_leaves=True, n_threads=8).leaf_node_id)

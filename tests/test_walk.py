@@ -143,3 +143,25 @@ def test_tiles_of_rows_that_end_inside_a_piece(features):
     for f in (scalar, vector):
         for rows in (16385, 20011):
             _check(f, _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng), leaves=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [9001, 49157, 131075])
+@pytest.mark.parametrize("depth,trees", [(3, 1), (3, 4), (3, 5), (3, 65), (4, 63), (5, 16), (6, 33), (6, 64), (6, 130), (7, 49), (8, 17), (8, 129)])
+def test_leaf_ids_by_rounds_of_trees(depth, trees, rows):
+    """One, two and four row groups per workgroup (with shares of the trees at 9,001 rows); tree counts below, at and
+    beyond a round of four trees for each of 16 waves, and rests of one to four trees per wave."""
+    import torch
+    from paper_2301_13441_amd import binding
+    rng = np.random.default_rng(depth + trees)
+    f = _forest(depth + trees, trees, depth, 7, full=depth != 7)
+    s = binding.forest_packed_launch(f, rows, True, form="walk")
+    assert s["kernel"] == "walk" and s["rows_per_workgroup"] == {9001: 64, 49157: 128, 131075: 256}[rows] or trees < 100, s
+    assert s["shares"] == (2 if rows == 9001 and trees >= 128 else 1), s
+    X = _special_rows(rng.standard_normal((rows, 7)).astype(np.float32), f, rng)
+    model = binding.forest_load_form(f, "walk")
+    try:
+        got = model.predict_leaves(torch.from_numpy(X).cuda()).cpu().numpy()
+    finally:
+        model.close()
+    np.testing.assert_array_equal(got, oracle.predict(f, X, want_leaves=True, n_threads=8).leaf_node_id)
