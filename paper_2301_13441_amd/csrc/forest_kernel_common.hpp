@@ -84,8 +84,12 @@ __device__ __forceinline__ void finish_values(const DevModel &m, double *raw, in
     float *dst = scores + row * K;
     if (m.transform == FOREST_TRANSFORM_SOFTMAX) {
         double z = 0.0;
-        for (int k = 0; k < K; ++k) z += exp(raw[k * stride] - best);
-        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(exp(raw[k * stride] - best) / z);
+        for (int k = 0; k < K; ++k) {
+            const double e = exp(raw[k * stride] - best);
+            raw[k * stride] = e;
+            z += e;
+        }
+        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(raw[k * stride] / z);
     } else if (m.transform == FOREST_TRANSFORM_SIGMOID) {
         for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(1.0 / (1.0 + exp(-raw[k * stride])));
     } else {

@@ -150,13 +150,13 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
 #pragma unroll
     for (int r = 0; r < NR; ++r) xa[r] = XBASE + static_cast<uint32_t>(r) * group_stride + lane * 4;
 
-    double acc[W][NR], done[MODE == DEEP_COLUMNS ? WALK_MAX_COLUMNS - 1 : 1][NR];
-    int column = 0, done_column[MODE == DEEP_COLUMNS ? WALK_MAX_COLUMNS - 1 : 1] = {}, n_done = 0, first_column = 0;
+    double acc[W][NR];  // vector leaves
 #pragma unroll
     for (int k = 0; k < W; ++k)
 #pragma unroll
         for (int r = 0; r < NR; ++r) acc[k][r] = 0.0;
-    if (MODE == DEEP_COLUMNS && t_begin < t_end) column = first_column = static_cast<int>(head.w[1]);
+    ColumnSums<NR, MODE == DEEP_COLUMNS ? WALK_MAX_COLUMNS : 1> sums;
+    sums.begin(MODE == DEEP_COLUMNS && t_begin < t_end ? static_cast<int>(head.w[1]) : 0);
 
     // The lanes' places in the units of the trees at hand: byte offset from the tree's first unit, and
     // what is there.
@@ -190,7 +190,10 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
         }
     };
     auto add_values = [&](int j) {
-        if (WP <= 2) {
+        if (MODE != DEEP_VECTOR) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) sums.acc[r] += static_cast<double>(__uint_as_float(what[j][r].x));
+        } else if (WP <= 2) {
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
                 acc[0][r] += static_cast<double>(__uint_as_float(what[j][r].x));
@@ -209,25 +212,6 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
             }
         }
     };
-    auto change_column = [&](int c) {  // the column of the values added next
-        if constexpr (MODE == DEEP_COLUMNS) {
-#pragma unroll
-            for (int k = WALK_MAX_COLUMNS - 2; k > 0; --k) {
-                done_column[k] = done_column[k - 1];
-#pragma unroll
-                for (int r = 0; r < NR; ++r) done[k][r] = done[k - 1][r];
-            }
-            done_column[0] = column;
-            ++n_done;
-            column = c;
-#pragma unroll
-            for (int r = 0; r < NR; ++r) {
-                done[0][r] = acc[0][r];
-                acc[0][r] = 0.0;
-            }
-        }
-    };
-
     // The top of tree t (j: its place in the pair); the next tree's top is on its way from here on.
     auto take = [&](int j, int t_after) {
         lds_write<Vec4>(stage + lane * 16, ahead[0]);
@@ -262,7 +246,7 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
 #pragma unroll
             for (int j = 0; j < NT; ++j) {
                 if (j > 0 && !two) break;
-                if (MODE == DEEP_COLUMNS && tree_column[j] != column) change_column(tree_column[j]);
+                if (MODE == DEEP_COLUMNS && tree_column[j] != sums.column) sums.change(tree_column[j]);
                 add_values(j);
             }
         }
@@ -317,65 +301,33 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
             __syncthreads();
         }
     }
-    if constexpr (!LEAVES) {
-        // The waves' sums meet in LDS, in the order of the waves.
-        __syncthreads();
+    if constexpr (MODE == DEEP_VECTOR) {
+        // The waves' sums meet in LDS, in the order of the waves: [DEEP_WAVES][K][ROWS], of which the first takes the totals.
         const int K = m.n_outputs;
         double *slot = reinterpret_cast<double *>(smem);
-        double *sum;  // [K][ROWS]
-        if constexpr (MODE == DEEP_VECTOR) {
-            sum = slot;  // [DEEP_WAVES][K][ROWS]
-#pragma unroll
-            for (int k = 0; k < W; ++k)
-                if (k < K) {
-#pragma unroll
-                    for (int r = 0; r < NR; ++r) slot[(wave * K + k) * ROWS + r * TILE + lane] = acc[k][r];
-                }
-            __syncthreads();
-            for (int i = threadIdx.x; i < K * ROWS; i += DEEP_WAVES * TILE) {
-                double s = 0.0;
-#pragma unroll
-                for (int w = 0; w < DEEP_WAVES; ++w) s += slot[w * K * ROWS + i];
-                sum[i] = s;
-            }
-        } else {
-            // a wave's run of trees feeds consecutive columns, so the sum of (wave, column) has the
-            // slot wave + column to itself
-            sum = slot + static_cast<size_t>(DEEP_WAVES + K - 1) * ROWS;
-            int32_t *fed = reinterpret_cast<int32_t *>(sum + static_cast<size_t>(K) * ROWS);  // first and last column of a wave
-            for (int i = threadIdx.x; i < (DEEP_WAVES + K - 1) * ROWS; i += DEEP_WAVES * TILE) slot[i] = 0.0;
-            if (lane == 0) {
-                fed[2 * wave] = t_begin < t_end ? first_column : 1;
-                fed[2 * wave + 1] = t_begin < t_end ? column : 0;
-            }
-            __syncthreads();
-            if (t_begin < t_end) {
-#pragma unroll
-                for (int r = 0; r < NR; ++r) slot[(wave + column) * ROWS + r * TILE + lane] = acc[0][r];
-                if constexpr (MODE == DEEP_COLUMNS) {
-#pragma unroll
-                    for (int k = 0; k < WALK_MAX_COLUMNS - 1; ++k)
-                        if (k < n_done) {
-#pragma unroll
-                            for (int r = 0; r < NR; ++r) slot[(wave + done_column[k]) * ROWS + r * TILE + lane] = done[k][r];
-                        }
-                }
-            }
-            __syncthreads();
-            for (int i = threadIdx.x; i < K * ROWS; i += DEEP_WAVES * TILE) {
-                const int k = i / ROWS, li = i - k * ROWS;
-                double s = 0.0;
-#pragma unroll
-                for (int w = 0; w < DEEP_WAVES; ++w)
-                    if (fed[2 * w] <= k && k <= fed[2 * w + 1]) s += slot[(w + k) * ROWS + li];
-                sum[i] = s;
-            }
-        }
         __syncthreads();
-        for (int li = threadIdx.x; li < ROWS; li += DEEP_WAVES * TILE) {
-            const int64_t row = row0 + li;
-            finish_summed_row(m, sum, ROWS, li, row, row < n_rows, scores, labels);
+#pragma unroll
+        for (int k = 0; k < W; ++k)
+            if (k < K) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) slot[(wave * K + k) * ROWS + r * TILE + lane] = acc[k][r];
+            }
+        __syncthreads();
+        for (int i = threadIdx.x; i < K * ROWS; i += DEEP_WAVES * TILE) {
+            double s = 0.0;
+#pragma unroll
+            for (int w = 0; w < DEEP_WAVES; ++w) s += slot[w * K * ROWS + i];
+            const int k = i / ROWS;
+            const int64_t row = row0 + (i - k * ROWS);
+            if (m.n_splits == 1) slot[i] = s;
+            else if (row < n_rows) m.partial[(static_cast<int64_t>(blockIdx.y) * m.split_rows + row) * K + k] = s;
         }
+        if (m.n_splits > 1) return;
+        __syncthreads();
+        for (int li = threadIdx.x; li < ROWS; li += DEEP_WAVES * TILE)
+            if (row0 + li < n_rows) finish_values(m, slot + li, ROWS, row0 + li, scores, labels);
+    } else if constexpr (!LEAVES) {
+        finish_columns<NR, DEEP_WAVES>(m, smem, wave, lane, t_begin < t_end, sums, row0, n_rows, scores, labels);
     }
 }
 

@@ -20,15 +20,20 @@
 // is exact in sign for finite thresholds: it is 0 for equal operands and never underflows to 0
 // otherwise.  NaN, which belongs on the right of every threshold, is stored in the tile as +Inf.)
 // Leaf values are gathered from global memory, which the LDS traffic leaves idle, and added one
-// tree later, in fp64.
+// tree later, in fp64.  Trees of depth up to 6, of which a stage holds two, are walked two at a time: a level is two LDS
+// round trips, and the second tree's fill the first one's (2000 x depth 6, 128 features, two row groups, 500,000 rows:
+// 922 -> 828 us; 1000 x depth 6, 50 features, four row groups, 1M rows: 777 -> 758; 1,021 rows of the former, one row
+// group: 17.4 -> 15.6 us a call).  Deeper trees would need a second stage in LDS, at the price of a workgroup's place.
 //
-// Bound: at depth 8 the LDS (89 % busy), at depth 6 the vector ALU (96 %) with the LDS (82 %) behind it.  Per (64 rows,
+// Bound: the LDS (82 to 89 % busy).  Per (64 rows,
 // tree of depth D): 3 + 2 (D - 2) LDS reads of 2 clocks each, more at levels 6 and 7 whose 64 and 128 nodes share the
-// 32 banks.  500 trees of depth 8, 28 features, 1M rows: 2.70 -> 0.63 ms against every node tested
-// (forest_kernels_rank.hip); 1000 of depth 6, 50 features: 1.57 -> 0.79 ms.
+// 32 banks (4 and 6 clocks).  500 trees of depth 8, 28 features, 1M rows: 2.70 -> 0.62 ms against every node tested
+// (forest_kernels_rank.hip); 1000 of depth 6, 50 features: 1.57 -> 0.76 ms.  Leaf values held as float64, which saves
+// their conversion and a shift: 633 and 802 us against 629 and 788.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "forest_device.hpp"
 #include "forest_kernel_common.hpp"
@@ -37,41 +42,65 @@
 namespace forest_impl {
 namespace {
 
-// One tree, all row groups: idx[r] = LDS address of the tree | 8 * (index of the leaf reached).
-template <int D, int NR>
-__device__ __forceinline__ void walk_tree(uint32_t tree_at, uint32_t xa, WalkTop top, uint32_t (&idx)[NR])
+// The first words of a tree, wave-uniform: its output column, its caller's index, the nodes of two levels.
+struct TreeHead {
+    uint32_t w[8];
+};
+
+__device__ __forceinline__ TreeHead tree_head(const char *tree)
 {
-    const float t1 = __uint_as_float(top[2]), t2 = __uint_as_float(top[4]), t3 = __uint_as_float(top[6]);
-    const uint32_t a1 = xa + top[3], a2 = xa + top[5], a3 = xa + top[7];
-    float x1[NR], x2[NR], x3[NR];
+    TreeHead h;
 #pragma unroll
-    for (int r = 0; r < NR; ++r) x1[r] = lds_read<float>(a1 + r * 256);
+    for (int i = 0; i < 8; ++i) h.w[i] = ((WalkTop)tree)[i];
+    return h;
+}
+
+// NT trees, TREE_BYTES apart, all row groups: idx[j][r] = LDS address of tree j | 8 * (index of the leaf reached).
+template <int D, int NR, int NT>
+__device__ __forceinline__ void walk_trees(uint32_t tree_at, uint32_t xa, const TreeHead (&head)[NT], uint32_t (&idx)[NT][NR])
+{
+    float x1[NT][NR], x2[NT][NR], x3[NT][NR];
 #pragma unroll
-    for (int r = 0; r < NR; ++r) x2[r] = lds_read<float>(a2 + r * 256);
+    for (int j = 0; j < NT; ++j) {
 #pragma unroll
-    for (int r = 0; r < NR; ++r) x3[r] = lds_read<float>(a3 + r * 256);
+        for (int r = 0; r < NR; ++r) x1[j][r] = lds_read<float>(xa + head[j].w[3] + r * 256);
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        const uint64_t m1 = __ballot(!(x1[r] <= t1)), m2 = __ballot(!(x2[r] <= t2)), m3 = __ballot(!(x3[r] <= t3));
-        const uint64_t second = (m1 & m3) | (~m1 & m2);
-        uint32_t b0, b1;
-        asm("v_cndmask_b32 %0, 0, 8, %1" : "=v"(b0) : "s"(m1));
-        asm("v_cndmask_b32 %0, 0, 16, %1" : "=v"(b1) : "s"(second));
-        idx[r] = tree_at | b0 | b1;
+        for (int r = 0; r < NR; ++r) x2[j][r] = lds_read<float>(xa + head[j].w[5] + r * 256);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) x3[j][r] = lds_read<float>(xa + head[j].w[7] + r * 256);
+    }
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const float t1 = __uint_as_float(head[j].w[2]), t2 = __uint_as_float(head[j].w[4]), t3 = __uint_as_float(head[j].w[6]);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const uint64_t m1 = __ballot(!(x1[j][r] <= t1)), m2 = __ballot(!(x2[j][r] <= t2)), m3 = __ballot(!(x3[j][r] <= t3));
+            const uint64_t second = (m1 & m3) | (~m1 & m2);
+            uint32_t b0, b1;
+            asm("v_cndmask_b32 %0, 0, 8, %1" : "=v"(b0) : "s"(m1));
+            asm("v_cndmask_b32 %0, 0, 16, %1" : "=v"(b1) : "s"(second));
+            idx[j][r] = (tree_at + j * (8u << D)) | b0 | b1;
+        }
     }
 #pragma unroll
     for (int l = 2; l < D; ++l) {
-        Vec2 node[NR];
-        float x[NR];
+        Vec2 node[NT][NR];
+        float x[NT][NR];
 #pragma unroll
-        for (int r = 0; r < NR; ++r) node[r] = lds_read<Vec2>(idx[r] + (8u << l));
+        for (int j = 0; j < NT; ++j)
 #pragma unroll
-        for (int r = 0; r < NR; ++r) x[r] = lds_read<float>(xa + node[r].y + r * 256);
+            for (int r = 0; r < NR; ++r) node[j][r] = lds_read<Vec2>(idx[j][r] + (8u << l));
 #pragma unroll
-        for (int r = 0; r < NR; ++r) {
-            const int right = __float_as_int(__uint_as_float(node[r].x) - x[r]) >> 31;
-            asm("v_and_or_b32 %0, %1, %2, %0" : "+v"(idx[r]) : "v"(right), "s"(8 << l));
-        }
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) x[j][r] = lds_read<float>(xa + node[j][r].y + r * 256);
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const int right = __float_as_int(__uint_as_float(node[j][r].x) - x[j][r]) >> 31;
+                asm("v_and_or_b32 %0, %1, %2, %0" : "+v"(idx[j][r]) : "v"(right), "s"(8 << l));
+            }
     }
 }
 
@@ -112,93 +141,55 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
     __syncthreads();
 
     const uint32_t xa = xbase + lane * 4;
-    double acc[NR], done[WALK_MAX_COLUMNS - 1][NR];  // the running column, the columns before it
-    int column = 0, done_column[WALK_MAX_COLUMNS - 1], n_done = 0, first_column = 0;
-    float value[NR];  // the last tree's leaf values, not yet added
+    constexpr int NT = STAGE_TREES > 1 ? 2 : 1;  // trees walked together
+    ColumnSums<NR, MODE == WALK_COLUMNS ? WALK_MAX_COLUMNS : 1> sums;
+    sums.begin(MODE == WALK_COLUMNS && s_begin < s_end ? ((WalkTable)(image + static_cast<int64_t>(s_begin) * STAGE_BYTES))[0] : 0);
+    float value[NT][NR];  // the last trees' leaf values, not yet added to the running column
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-        acc[r] = 0.0;
-        value[r] = 0.0f;
-    }
-    if (MODE == WALK_COLUMNS && s_begin < s_end)
-        column = first_column = ((WalkTable)(image + static_cast<int64_t>(s_begin) * STAGE_BYTES))[0];
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) value[j][r] = 0.0f;
+    const auto add_value = [&](int j) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) sums.acc[r] += static_cast<double>(value[j][r]);
+    };
 
     for (int s = s_begin; s < s_end; ++s) {
 #pragma unroll
         for (int i = 0; i < PIECES; ++i) lds_write<Vec4>(mine + i * 1024 + lane * 16, ahead[i]);
         if (s + 1 < s_end) fetch(s + 1);
 #pragma unroll 1
-        for (int q = 0; q < STAGE_TREES; ++q) {
+        for (int q = 0; q < STAGE_TREES; q += NT) {
             const int t = s * STAGE_TREES + q;
-            const WalkTop top = (WalkTop)(image + static_cast<int64_t>(t) * TREE_BYTES);
+            TreeHead head[NT];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) head[j] = tree_head(image + static_cast<int64_t>(t + j) * TREE_BYTES);
             const uint32_t tree_at = mine + q * TREE_BYTES;
-            uint32_t idx[NR];
-            walk_tree<D, NR>(tree_at, xa, top, idx);
+            uint32_t idx[NT][NR];
+            walk_trees<D, NR, NT>(tree_at, xa, head, idx);
 #pragma unroll
-            for (int r = 0; r < NR; ++r) acc[r] += static_cast<double>(value[r]);
-            if (const int c = static_cast<int>(top[0]); MODE == WALK_COLUMNS && c != column) {
-#pragma unroll
-                for (int k = WALK_MAX_COLUMNS - 2; k > 0; --k) {
-                    done_column[k] = done_column[k - 1];
-#pragma unroll
-                    for (int r = 0; r < NR; ++r) done[k][r] = done[k - 1][r];
-                }
-                done_column[0] = column;
-                ++n_done;
-                column = c;
-#pragma unroll
-                for (int r = 0; r < NR; ++r) {
-                    done[0][r] = acc[r];
-                    acc[r] = 0.0;
-                }
-            }
+            for (int j = 0; j < NT; ++j) add_value(j);
             // half an index is the leaf's byte offset; the tree's address in it is taken off the base
             const char *leaves = reinterpret_cast<const char *>(m.walk.leaf) + (static_cast<int64_t>(t) << (D + 2)) - (tree_at >> 1);
             asm volatile("" : "+s"(leaves));  // keeps the base whole, so that the loads take a 32-bit offset
 #pragma unroll
-            for (int r = 0; r < NR; ++r) value[r] = *(GlobalFloats)((GlobalBytes)leaves + (idx[r] >> 1));
+            for (int j = 0; j < NT; ++j) {
+                if (const int c = static_cast<int>(head[j].w[0]); MODE == WALK_COLUMNS && c != sums.column) {
+                    if (j > 0) {  // the first of the two ends its column
+                        add_value(0);
+#pragma unroll
+                        for (int r = 0; r < NR; ++r) value[0][r] = 0.0f;
+                    }
+                    sums.change(c);
+                }
+#pragma unroll
+                for (int r = 0; r < NR; ++r) value[j][r] = *(GlobalFloats)((GlobalBytes)leaves + (idx[j][r] >> 1));
+            }
         }
     }
 #pragma unroll
-    for (int r = 0; r < NR; ++r) acc[r] += static_cast<double>(value[r]);
-
-    // The waves' column sums meet in LDS: a wave's run of trees feeds consecutive columns, so the
-    // sum of (wave, column) has the slot wave + column to itself.
-    __syncthreads();
-    const int K = m.n_outputs;
-    double *slot = reinterpret_cast<double *>(smem);                 // [WALK_WAVES + K - 1][ROWS]
-    double *sum = slot + static_cast<size_t>(WALK_WAVES + K - 1) * ROWS;  // [K][ROWS]
-    int32_t *fed = reinterpret_cast<int32_t *>(sum + static_cast<size_t>(K) * ROWS);  // first and last column of a wave
-    for (int i = threadIdx.x; i < (WALK_WAVES + K - 1) * ROWS; i += WALK_WAVES * TILE) slot[i] = 0.0;
-    if (lane == 0) {
-        fed[2 * wave] = s_begin < s_end ? first_column : 1;
-        fed[2 * wave + 1] = s_begin < s_end ? column : 0;
-    }
-    __syncthreads();
-    if (s_begin < s_end) {
-#pragma unroll
-        for (int r = 0; r < NR; ++r) slot[(wave + column) * ROWS + r * TILE + lane] = acc[r];
-#pragma unroll
-        for (int k = 0; k < WALK_MAX_COLUMNS - 1; ++k)
-            if (k < n_done) {
-#pragma unroll
-                for (int r = 0; r < NR; ++r) slot[(wave + done_column[k]) * ROWS + r * TILE + lane] = done[k][r];
-            }
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < K * ROWS; i += WALK_WAVES * TILE) {
-        const int k = i / ROWS, li = i - k * ROWS;
-        double s = 0.0;
-#pragma unroll
-        for (int w = 0; w < WALK_WAVES; ++w)
-            if (fed[2 * w] <= k && k <= fed[2 * w + 1]) s += slot[(w + k) * ROWS + li];
-        sum[i] = s;
-    }
-    __syncthreads();
-    for (int li = threadIdx.x; li < ROWS; li += WALK_WAVES * TILE) {
-        const int64_t row = row0 + li;
-        finish_summed_row(m, sum, ROWS, li, row, row < n_rows, scores, labels);
-    }
+    for (int j = 0; j < NT; ++j) add_value(j);
+    finish_columns<NR, WALK_WAVES>(m, smem, wave, lane, s_begin < s_end, sums, row0, n_rows, scores, labels);
 }
 
 // The leaf ids of every tree, caller's order.  A row's ids are neighbours in the output and a lane holds those of few
@@ -254,8 +245,32 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
 #pragma unroll
             for (int r = 0; r < NR; ++r) ids[r][j >> 1] = (j & 1) ? ids[r][j >> 1] | id[r] << 16 : id[r];
         };
+        const auto walk = [&](int j, auto trees) {  // trees j and, of two, j + 1
+            constexpr int NT = decltype(trees)::value;
+            int at[NT];
+            TreeHead head[NT];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+            for (int i = 0; i < NT; ++i) {
+                at[i] = ((WalkTable)m.walk.position)[min(first + j + i, T - 1)];
+                head[i] = tree_head(image + static_cast<int64_t>(at[i]) * TREE_BYTES);
+            }
+            const uint32_t tree_at = mine + (j % STEP) * TREE_BYTES;
+            uint32_t idx[NT][NR];
+            walk_trees<D, NR, NT>(tree_at, xa, head, idx);
+            if (j > 0) keep(j - 1);
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                if (i > 0) keep(j);
+                const char *leaves = reinterpret_cast<const char *>(m.walk.leaf_node) + (static_cast<int64_t>(at[i]) << (D + 2)) -
+                                     ((tree_at + i * TREE_BYTES) >> 1);
+                asm volatile("" : "+s"(leaves));  // keeps the base whole, so that the loads take a 32-bit offset
+#pragma unroll
+                for (int r = 0; r < NR; ++r) id[r] = static_cast<uint32_t>(*(GlobalInts)((GlobalBytes)leaves + (idx[i][r] >> 1)));
+            }
+        };
+        constexpr int NT = STEP > 1 && NR < 4 ? 2 : 1;  // trees walked together: four row groups' would spill (42.5 -> 44.5 us)
+#pragma unroll
+        for (int j = 0; j < 4; j += NT) {
             if (j < n) {
                 if (j % STEP == 0) {
                     if (PIECES > 1 || lane * 16 < STEP_BYTES) {
@@ -265,16 +280,8 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
                     if (j + STEP < n) fetch(first + j + STEP);
                     else if (k + m.n_splits < rounds) fetch(first_tree(k + m.n_splits));
                 }
-                const int at = ((WalkTable)m.walk.position)[min(first + j, T - 1)];
-                const WalkTop top = (WalkTop)(image + static_cast<int64_t>(at) * TREE_BYTES);
-                const uint32_t tree_at = mine + (j % STEP) * TREE_BYTES;
-                uint32_t idx[NR];
-                walk_tree<D, NR>(tree_at, xa, top, idx);
-                const char *leaves = reinterpret_cast<const char *>(m.walk.leaf_node) + (static_cast<int64_t>(at) << (D + 2)) - (tree_at >> 1);
-                asm volatile("" : "+s"(leaves));  // keeps the base whole, so that the loads take a 32-bit offset
-                if (j > 0) keep(j - 1);
-#pragma unroll
-                for (int r = 0; r < NR; ++r) id[r] = static_cast<uint32_t>(*(GlobalInts)((GlobalBytes)leaves + (idx[r] >> 1)));
+                if (NT > 1 && j + 1 < n) walk(j, std::integral_constant<int, NT>{});
+                else walk(j, std::integral_constant<int, 1>{});
             }
         }
 #pragma unroll

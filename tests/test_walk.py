@@ -165,3 +165,16 @@ def test_leaf_ids_by_rounds_of_trees(depth, trees, rows):
     finally:
         model.close()
     np.testing.assert_array_equal(got, oracle.predict(f, X, want_leaves=True, n_threads=8).leaf_node_id)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("depth", [3, 6, 8, 9])
+@pytest.mark.parametrize("trees,rows", [(41, 9001), (300, 9001), (41, 70_001)])
+def test_columns_without_trees_between_columns_with_some(depth, trees, rows):
+    """A wave's run of trees that goes from one column to one further on leaves zeros for those between; odd tree
+    counts, which end a pair of trees walked together; with and without shares of the trees."""
+    rng = np.random.default_rng(depth + trees)
+    f = _forest(trees + depth, trees, min(depth, 8), 9, outputs=7) if depth < 9 else \
+        wl.random_forest(trees, n_trees=trees, n_features=9, max_depth=9, stop_prob=0.3, n_outputs=7, aggregate=wl.AGG_SUM)
+    f = wl.Forest(**{**f.__dict__, "tree_output": rng.choice([0, 3, 6], trees).astype(np.int32)})
+    _check(f, _special_rows(rng.standard_normal((rows, 9)).astype(np.float32), f, rng))
