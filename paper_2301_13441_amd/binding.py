@@ -336,37 +336,22 @@ def _check_x(X, n_features: int) -> None:
         raise ValueError(f"X must be a contiguous float32 CUDA tensor of shape [n_rows, {n_features}]")
 
 
-# Batches of fewer rows take predict()'s short way.  Below the C ABI's limit on rows (forest.h), so that what it
-# refuses is still refused before anything is allocated.
+# Batches of fewer rows take predict()'s and predict_leaves()'s short way (csrc/short_call.cpp).  Below the C ABI's limit
+# on rows (forest.h), so that what it refuses is still refused before anything is allocated.
 _SHORT_ROWS = 1 << 20
+_SCORES, _LABELS, _LEAVES = 1, 2, 4  # what a short call returns
 
 
-def _short_predict(handle, predict, error, what, X, n_outputs, n_rows, has_scores, has_labels):
-    """One call with a buffer of its own on the current stream: scores, then labels, as the C ABI lays them
-    out.  A call is a few kernels of some microseconds, so what the host does between them is the call's time:
-    no questions to the library whose answer the handle has already, and as few tensor views as it takes
-    (1,000 rows, 10 trees of depth 4: 14.4 us a call without this way, 9.1 with it)."""
-    import torch
-    words = n_rows * (n_outputs * has_scores + has_labels)
-    out = torch.empty(4 * words, dtype=torch.uint8, device=X.device)
-    rc = predict(handle, X.data_ptr(), n_rows, out.data_ptr(), _raw_stream(X))
-    if rc != 0:
-        raise error(rc, what)
-    scores = labels = None
-    if has_scores:
-        scores = out.view(torch.float32).as_strided((n_rows, n_outputs), (n_outputs, 1), 0)
-    if has_labels:
-        labels = out.view(torch.int32)
-        if has_scores:
-            labels = labels.as_strided((n_rows,), (1,), n_rows * n_outputs)
-    return scores, labels
+def short_call():
+    """The native call; raises if it has not been built."""
+    import torch  # noqa: F401 - the extension is linked against its libraries
+    from . import _short_call
+    return _short_call.call
 
 
-def _raw_stream(X) -> int:
-    """The current stream of X's device as a hipStream_t."""
-    import torch
-    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-    return torch.cuda.current_stream(X.device).cuda_stream if raw is None else raw(X.get_device())
+def entry_point(fn) -> int:
+    """The address of a function of the library."""
+    return ctypes.cast(fn, _p).value
 
 
 class Forest:
@@ -383,10 +368,14 @@ class Forest:
         self.n_outputs = info.n_outputs
         self.n_features = info.n_features
         self.n_trees = info.n_trees
-        self._parts = tuple(offset >= 0 for offset in self.out_layout(1))  # scores, labels
+        scores, labels = (offset >= 0 for offset in self.out_layout(1))
+        self._parts = _SCORES * scores | _LABELS * labels
+        self._call, self._address = short_call(), handle.value
+        self._predict, self._predict_leaves = entry_point(lib.forest_predict), entry_point(lib.forest_predict_leaves)
 
     def close(self):
         if self._h is not None:
+            self._address = 0  # which the entry points refuse
             self._lib.forest_free(self._h)
             self._h = None
 
@@ -418,14 +407,17 @@ class Forest:
 
     def predict(self, X, out=None, stream=None, static: bool = False):
         """X: torch float32 CUDA tensor [n_rows, F], contiguous.  Returns (scores, labels) views
-        into one uint8 output buffer (either may be None, per the model's output kind).  With
+        into one output buffer (either may be None, per the model's output kind).  With
         `static` the call goes through forest_predict_static (pass `out`: it allocates nothing)."""
+        if out is None and stream is None and not static:
+            got = self._call(self._predict, self._address, X, self.n_features, self.n_outputs, self._parts, _SHORT_ROWS)
+            if type(got) is int:
+                raise ForestError(got, "forest_predict")
+            if got is not None:
+                return got
         import torch
         _check_x(X, self.n_features)
         n = X.shape[0]
-        if out is None and stream is None and not static and 0 < n < _SHORT_ROWS:
-            return _short_predict(self._h, self._lib.forest_predict, ForestError, "forest_predict", X, self.n_outputs, n,
-                                  *self._parts)
         nbytes = self.out_bytes(n)
         if out is None:
             out = torch.empty(max(nbytes, 4), dtype=torch.uint8, device=X.device)
@@ -444,6 +436,12 @@ class Forest:
         return scores, labels
 
     def predict_leaves(self, X, stream=None):
+        if stream is None:
+            got = self._call(self._predict_leaves, self._address, X, self.n_features, self.n_trees, _LEAVES, _SHORT_ROWS)
+            if type(got) is int:
+                raise ForestError(got, "forest_predict_leaves")
+            if got is not None:
+                return got
         import torch
         _check_x(X, self.n_features)
         n = X.shape[0]

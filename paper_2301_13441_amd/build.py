@@ -10,6 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libforest_hip.so")
+SHORT_CALL = os.path.join(HERE, "_short_call.so")  # CPython extension: predict() as one native call
 SOURCES = ["forest_pack.cpp", "forest_api_host.cpp", "forest_api.cpp", "forest_kernels.hip", "forest_kernels_reg.hip",
            "forest_kernels_rank.hip", "forest_kernels_ranklds.hip", "forest_kernels_rankbank.hip", "forest_kernels_split.hip",
            "forest_kernels_walk.hip", "forest_kernels_deep.hip", "forest_probe.hip",
@@ -56,14 +57,33 @@ def ranklds_variant_flags(flags: list[str], verbose: bool = False) -> list[str]:
         return [CONSERVATIVE]
 
 
+def build_short_call(verbose: bool = False) -> str:
+    """Host code against torch's headers and libraries; importing torch brings the libraries it needs."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    include = [*cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *(f"-I{d}" for d in include),
+           os.path.join(CSRC, "short_call.cpp"), "-o", SHORT_CALL, "-L" + os.path.join(os.path.dirname(torch.__file__), "lib"),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return SHORT_CALL
+
+
 def build(verbose: bool = False, extra: list[str] | None = None) -> str:
     os.makedirs(OBJ, exist_ok=True)
     extra = list(extra or [])
-    with ThreadPoolExecutor(max_workers=len(SOURCES) + 1) as pool:
+    with ThreadPoolExecutor(max_workers=len(SOURCES) + 2) as pool:
+        short_call = pool.submit(build_short_call, verbose)
         variant = pool.submit(ranklds_variant_flags, [*FLAGS, *extra], verbose)
         others = [s for s in SOURCES if s != RANKLDS]
         objs = list(pool.map(lambda s: _compile(s, extra, verbose), others))
         objs.append(_compile(RANKLDS, [*extra, *variant.result()], verbose))
+        short_call.result()
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", LIB]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -6,7 +6,7 @@ import ctypes
 
 import numpy as np
 
-from .binding import _SHORT_ROWS, _short_predict, load_library
+from .binding import _LABELS, _SCORES, _SHORT_ROWS, entry_point, load_library, short_call
 
 _p = ctypes.c_void_p
 _i32, _i64 = ctypes.c_int32, ctypes.c_int64
@@ -87,10 +87,13 @@ class Linear:
         self._h = handle
         self.n_features = n_features
         self.n_outputs = n_outputs
-        self._parts = tuple(offset >= 0 for offset in self.out_layout(1))  # scores, labels
+        scores, labels = (offset >= 0 for offset in self.out_layout(1))
+        self._parts = _SCORES * scores | _LABELS * labels
+        self._call, self._address, self._predict = short_call(), handle.value, entry_point(_lib().linear_predict)
 
     def close(self):
         if self._h is not None:
+            self._address = 0  # which the entry point refuses
             _lib().linear_free(self._h)
             self._h = None
 
@@ -120,13 +123,16 @@ class Linear:
 
     def predict(self, X, out=None, stream=None):
         """X: torch float32 CUDA tensor [n_rows, F], contiguous.  Returns (scores, labels) views
-        into one uint8 output buffer (either may be None, per the model's output kind)."""
+        into one output buffer (either may be None, per the model's output kind)."""
+        if out is None and stream is None:
+            got = self._call(self._predict, self._address, X, self.n_features, self.n_outputs, self._parts, _SHORT_ROWS)
+            if type(got) is int:
+                raise LinearError(got, "linear_predict")
+            if got is not None:
+                return got
         import torch
         _check_x(X, self.n_features)
         n = X.shape[0]
-        if out is None and stream is None and 0 < n < _SHORT_ROWS:
-            return _short_predict(self._h, _lib().linear_predict, LinearError, "linear_predict", X, self.n_outputs, n,
-                                  *self._parts)
         nbytes = self.out_bytes(n)
         if out is None:
             out = torch.empty(max(nbytes, 4), dtype=torch.uint8, device=X.device)

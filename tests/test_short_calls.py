@@ -58,3 +58,52 @@ def test_linear_scores_of_whole_and_ragged_tiles(features, outputs):
         np.testing.assert_allclose(scores.cpu().numpy(), ref.scores, rtol=2e-7, atol=1e-30)
         assert bool((out[f.out_bytes(rows):] == 0xAB).all())
     f.close()
+
+
+@pytest.mark.parametrize("family", ["forest", "linear"])
+def test_what_the_native_call_declines_goes_the_general_way(family):
+    """Tensors it does not take are refused as before or give the same bits; a closed model is refused; leaf ids and
+    sums follow the current stream; several threads on their own streams."""
+    import threading
+
+    import torch
+    import paper_2301_13441_amd as pk
+    rng = np.random.default_rng(8)
+    if family == "forest":
+        model = pk.forest_load(wl.random_forest(4, 30, 9, 6, n_outputs=2))
+    else:
+        model = pk.linear_load(LinearModel(9, 2, rng.standard_normal((9, 2)).astype(np.float32),
+                                           np.zeros(2, np.float32), wl.TRANSFORM_NONE, wl.OUT_BOTH))
+    X = torch.from_numpy(rng.standard_normal((500, 9)).astype(np.float32)).cuda()
+    want = model.predict(X)
+    for same in (torch.nn.Parameter(X), X.clone().requires_grad_(), torch.cat([X, X])[:500]):
+        for a, b in zip(model.predict(same), want):
+            assert torch.equal(a, b)
+    for wrong in (X.double(), X.cpu(), X.half(), X[:, :8], X[::2].t(), X.t(), X[0], X.repeat(1, 2)[:, ::2], None, X.cpu().numpy()):
+        calls = [model.predict] + ([model.predict_leaves] if family == "forest" else [])
+        for call in calls:
+            with pytest.raises(ValueError):
+                call(wrong)
+    got = [None] * 4
+
+    def work(i):
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.default_stream())
+        with torch.cuda.stream(side):
+            Y = X * 1.0
+            for _ in range(20):
+                got[i] = model.predict(Y) + ((model.predict_leaves(Y),) if family == "forest" else ())
+        side.synchronize()
+
+    torch.cuda.synchronize()
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    leaves = (model.predict_leaves(X),) if family == "forest" else ()
+    for result in got:
+        assert all(torch.equal(a, b) for a, b in zip(result, want + leaves))
+    model.close()
+    with pytest.raises(RuntimeError):
+        model.predict(X)
