@@ -338,6 +338,11 @@ inline bool deep_shares_cu(const DevModel &m, int groups, bool sums)
 // 8,000 rows 6.2 / 6.6, 30,000 rows 10.0 / 6.9.
 constexpr int64_t POINT_MAX_TESTS = 1 << 20;  // rows x trees x depth
 constexpr int64_t POINT_MAX_ROWS = 8192;
+// Tests of one row, all by one workgroup, whose CU's texture path they queue at; trees of depth 4 and less are a line
+// each and queue for less.  1 row, this kernel / walk kernels with their reduction: 1500 x depth 7 9.4 / 9.8 us, 2000 x
+// depth 6 10.5 / 9.6 (ten columns 10.7 / 11.1), 1600 x depth 8 10.4 / 9.6, 1900 x depth 8 11.7 / 10.0, 4000 x depth 5
+// 15.9 / 10.8, 6000 x depth 3 11.9 / 12.9.  (Two pairs of a thread at a time: 11.7 for 2000 x depth 6.)
+constexpr int64_t POINT_MAX_ROW_TESTS = 12000;
 constexpr size_t POINT_MAX_LDS = 64 * 1024;
 constexpr int PT_THREADS = 1024, PT_MAX_ROWS = 16;
 
@@ -361,6 +366,7 @@ inline int point_threads(const DevModel &m)
 
 inline bool takes_point(const DevModel &m, int64_t n_rows)
 {
+    if (m.walk.depth >= 5 && static_cast<int64_t>(m.n_trees) * m.walk.depth > POINT_MAX_ROW_TESTS) return false;
     return m.walk.depth > 0 && n_rows <= POINT_MAX_ROWS && n_rows * m.n_trees * m.walk.depth <= POINT_MAX_TESTS && point_lds_bytes(m) <= POINT_MAX_LDS;
 }
 

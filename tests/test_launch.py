@@ -152,3 +152,27 @@ def test_row_groups_leave_every_cu_a_workgroup():
         assert group(few, rows) == less and group(deep, rows) == min(less, 2)
         s = binding.forest_packed_launch(many, rows, form="walk")
         assert s["rows_per_workgroup"] == 64 * (want if s["shares"] == 1 else 1)
+
+
+def test_a_row_of_many_tests_is_cut_into_shares():
+    """One workgroup tests a row in the kernel with a lane per (row, tree): up to 12,000 tests, or trees of a line each."""
+    from paper_2301_13441_amd import binding
+    for trees, depth, kernel in ((2000, 6, "point"), (2001, 6, "walk"), (1500, 8, "point"), (1501, 8, "walk"), (2400, 5, "point"),
+                                 (2401, 5, "walk"), (4000, 4, "point")):
+        f = _full_forest(1, trees, depth, 10)
+        s = binding.forest_packed_launch(f, 1)
+        assert s["kernel"] == kernel and (s["shares"] > 1) == (kernel == "walk"), s
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("trees,depth,outputs", [(2001, 6, 10), (1501, 8, 1), (2403, 5, 32)])
+def test_few_rows_of_many_tests(trees, depth, outputs):
+    """The same through the reduction: shares of 1 to 40 rows, up to as many columns as a model may have; and 100 trees of
+    the same shapes, which the kernel with a lane per (row, tree) takes and whose columns' first trees it counts."""
+    from test_gpu_parity import _check
+    f = _full_forest(trees, trees, depth, 12, n_outputs=outputs, transform=wl.TRANSFORM_SOFTMAX if outputs > 1 else wl.TRANSFORM_SIGMOID)
+    few = _full_forest(trees, 100, depth, 12, n_outputs=outputs, aggregate=wl.AGG_MEAN)
+    X = np.random.default_rng(depth).standard_normal((40, 12)).astype(np.float32)
+    for rows in (1, 3, 40):
+        _check(f, X[:rows], leaves=True)
+        _check(few, X[:rows], leaves=True)
