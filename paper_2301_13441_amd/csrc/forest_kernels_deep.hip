@@ -13,7 +13,7 @@
 // ([group][feature][row]); every wave walks its own run of trees for all the rows, two trees at a time
 // below their tops.
 //
-// 128 trees of depth 12, 256 features, 4,000,000 rows: 2.88 ms (14.5 with every node tested,
+// 128 trees of depth 12, 256 features, 4,000,000 rows: 2.83 ms (14.5 with every node tested,
 // forest_kernels_rankbank.hip).  1.1 ms are the tile's (X once from memory, which one workgroup per
 // CU does not overlap with its walk, and 0.4 ms of launches and sums), 0.8 the tops (LDS round trips),
 // 1.0 the units (a gather costs the texture path about a cycle per active lane; with the first units
