@@ -29,7 +29,7 @@ LDS_PEAK_TESTS = 256 * 2.4e9 * 64 / 4
 HBM_PEAK = 8.0e12
 ORACLE_THREADS_MAX = 16   # the share of host cores one GPU's job may use on the bench machine
 
-# HBM bytes per launch from rocprofv3 --pmc runs of this script (FETCH_SIZE and WRITE_SIZE, each
+# HBM bytes per launch from rocprofv3 --pmc runs of these workloads (FETCH_SIZE and WRITE_SIZE, each
 # scaled by what the same counter reads for a plain copy of known size).  Not taken live: every
 # entry names the summary under profiles/ it comes from and the commit whose kernels were
 # measured; a workload without an entry reports null.
