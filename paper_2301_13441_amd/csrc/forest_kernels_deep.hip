@@ -33,8 +33,8 @@ namespace forest_impl {
 namespace {
 
 // What a kernel leaves behind: the sums of one output column, those of several (trees sorted by
-// column), those of vector leaves, or the leaf ids of every tree.
-enum { DEEP_COLUMN = 0, DEEP_COLUMNS = 1, DEEP_VECTOR = 2, DEEP_LEAVES = 3 };
+// column), those of vector leaves, or the leaf ids of every tree (FEW: of few trees, leaves_by_fours in forest_plan.hpp).
+enum { DEEP_COLUMN = 0, DEEP_COLUMNS = 1, DEEP_VECTOR = 2, DEEP_LEAVES = 3, DEEP_FEW_LEAVES = 4 };
 
 constexpr uint32_t TOP_BYTES = DEEP_TOP_WORDS * sizeof(WalkNode);     // of a tree
 constexpr uint32_t NODES_BYTES = TOP_BYTES / 2;                        // its nodes, and as much for its first units
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
                                                                                        int32_t *labels, int32_t *leaf_out)
 {
     constexpr int ROWS = NR * TILE;
-    constexpr bool LEAVES = MODE == DEEP_LEAVES;
+    constexpr bool FEW = MODE == DEEP_FEW_LEAVES, LEAVES = MODE == DEEP_LEAVES || FEW;
     constexpr int W = LEAVES ? 1 : WP;
     constexpr int NT = 2;  // trees whose units are walked together
     static_assert(MODE == DEEP_VECTOR || WP == 1, "scalar leaves");
@@ -125,9 +125,9 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
     // turn, so that the waves have neighbouring ids at the same time (forest_kernels_walk.hip).
     const int unit = static_cast<int>(blockIdx.y) * DEEP_WAVES + wave, units = m.n_splits * DEEP_WAVES;
     constexpr int ROUND = 4 * DEEP_WAVES;
-    const auto share = [&](int k) { return T - k * ROUND >= ROUND ? 4 : (T - k * ROUND + DEEP_WAVES - 1) / DEEP_WAVES; };
+    const auto share = [&](int k) { return FEW || T - k * ROUND >= ROUND ? 4 : (T - k * ROUND + DEEP_WAVES - 1) / DEEP_WAVES; };
     const auto first_tree = [&](int k) { return k * ROUND + wave * share(k); };
-    const int t_begin = LEAVES ? first_tree(blockIdx.y) : static_cast<int>(static_cast<int64_t>(T) * unit / units);
+    const int t_begin = LEAVES ? first_tree(FEW ? 0 : blockIdx.y) : static_cast<int>(static_cast<int64_t>(T) * unit / units);
     const int t_end = LEAVES ? T : static_cast<int>(static_cast<int64_t>(T) * (unit + 1) / units);
     auto place = [&](int t) { return LEAVES ? ((WalkTable)m.deep.position)[t] : t; };
 
@@ -251,10 +251,11 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
             }
         }
     } else {
-        const int rounds = (T + ROUND - 1) / ROUND;
-        for (int k = static_cast<int>(blockIdx.y); k < rounds; k += m.n_splits) {
+        const int rounds = FEW ? 1 : (T + ROUND - 1) / ROUND;
+        for (int k = FEW ? 0 : static_cast<int>(blockIdx.y); k < rounds; k += m.n_splits) {
             const int n = share(k), first = first_tree(k), own = min(T - first, n);
-            const int next = k + m.n_splits < rounds ? first_tree(k + m.n_splits) : T;
+            if (FEW && own <= 0) return;
+            const int next = !FEW && k + m.n_splits < rounds ? first_tree(k + m.n_splits) : T;
             uint32_t ids[NR][4] = {};
 #pragma unroll
             for (int p = 0; p < 4; p += NT) {
@@ -279,10 +280,14 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
                         if (j < n && begin + j < T) dst[j] = static_cast<int32_t>(v[j]);
                 }
             };
-            if (T <= 4) {  // a row's ids share 16 bytes: nothing to gain from an exchange
+            if (FEW || T <= 4) {  // straight from the lanes
 #pragma unroll
-                for (int r = 0; r < NR; ++r)
-                    if (const int64_t row = row0 + r * TILE + lane; own > 0 && row < n_rows) leaf_out[row * T + first] = static_cast<int32_t>(ids[r][0]);
+                for (int r = 0; r < NR; ++r) {
+                    const int64_t row = row0 + r * TILE + lane;
+                    if (row >= n_rows || own <= 0) continue;
+                    if (FEW) store(row, first, 4, Vec4{ids[r][0], ids[r][1], ids[r][2], ids[r][3]});
+                    else leaf_out[row * T + first] = static_cast<int32_t>(ids[r][0]);
+                }
                 return;
             }
             // A row group's ids meet in one half of the stages, those of row i at place i + 4 * wave of its wave's part.
@@ -335,6 +340,7 @@ template <bool SHARED>
 KernelFn pick_mode(int groups, int mode, int width)
 {
     const bool two = groups > 1;
+    if (mode == DEEP_FEW_LEAVES) return two ? forest_deep_kernel<2, DEEP_FEW_LEAVES, 1, SHARED> : forest_deep_kernel<1, DEEP_FEW_LEAVES, 1, SHARED>;
     if (mode == DEEP_LEAVES) return two ? forest_deep_kernel<2, DEEP_LEAVES, 1, SHARED> : forest_deep_kernel<1, DEEP_LEAVES, 1, SHARED>;
     if (mode == DEEP_COLUMN) return two ? forest_deep_kernel<2, DEEP_COLUMN, 1, SHARED> : forest_deep_kernel<1, DEEP_COLUMN, 1, SHARED>;
     if (mode == DEEP_COLUMNS) return two ? forest_deep_kernel<2, DEEP_COLUMNS, 1, SHARED> : forest_deep_kernel<1, DEEP_COLUMNS, 1, SHARED>;
@@ -356,7 +362,7 @@ KernelFn pick(int groups, int mode, int width, bool shared)
 
 hipError_t init_deep_kernels(size_t lds_limit)
 {
-    for (int mode : {DEEP_COLUMN, DEEP_COLUMNS, DEEP_VECTOR, DEEP_LEAVES})
+    for (int mode : {DEEP_COLUMN, DEEP_COLUMNS, DEEP_VECTOR, DEEP_LEAVES, DEEP_FEW_LEAVES})
         for (int width : {2, 4, 8, 12, 16})
             for (int groups : {1, 2})
                 for (bool shared : {true, false}) {
@@ -379,7 +385,7 @@ hipError_t launch_deep(const DevModel &m, int groups, const float *X, int64_t n_
     if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(n_blocks), static_cast<unsigned>(m.n_splits));
     const size_t lds = deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups, leaf_out == nullptr);
-    const int mode = leaf_out ? DEEP_LEAVES : m.leaf_width > 1 ? DEEP_VECTOR : m.n_outputs == 1 ? DEEP_COLUMN : DEEP_COLUMNS;
+    const int mode = leaf_out ? leaves_by_fours(m, groups, n_rows) ? DEEP_FEW_LEAVES : DEEP_LEAVES : m.leaf_width > 1 ? DEEP_VECTOR : m.n_outputs == 1 ? DEEP_COLUMN : DEEP_COLUMNS;
     hipLaunchKernelGGL(pick(groups, mode, deep_width(m.leaf_width), shared), grid, dim3(DEEP_WAVES * TILE), lds, stream, m, X,
                        n_rows, scores, labels, leaf_out);
     return hipGetLastError();

@@ -105,8 +105,8 @@ __device__ __forceinline__ void walk_trees(uint32_t tree_at, uint32_t xa, const 
 }
 
 // What a kernel leaves behind: the sums of one output column, those of several (trees sorted by
-// column), or the leaf ids of every tree (a kernel of its own).
-enum { WALK_COLUMN = 0, WALK_COLUMNS = 1, WALK_LEAVES = 2 };
+// column), or the leaf ids of every tree (a kernel of its own, in two forms).
+enum { WALK_COLUMN = 0, WALK_COLUMNS = 1, WALK_LEAVES = 2, WALK_FEW_LEAVES = 3 };
 
 template <int D, int NR, int MODE>
 __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevModel m, const float *__restrict__ X,
@@ -197,10 +197,12 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
 // store then writes whole 256-byte runs of four rows.  Straight from the lanes, 16 bytes at the pitch of a row, 100,003
 // rows of 200 x depth 6 took 65.6 us, three quarters of them for the stores; so 42.5, of which the stores are 10 (250,000
 // rows of 200 x depth 3: 235 -> 65; 66,000 of 700 x depth 3: 310 -> 98).  Ids of these trees, which have 511 nodes at
-// most, fit 16 bits.  What is left of the trees after the last whole round is dealt evenly.  Bound: the walk, with 391
+// most, fit 16 bits.  What is left of the trees after the last whole round is dealt evenly; waves that get none walk none
+// (one tree of depth 7, 3 features, 60,000 rows: 4.6 us a call with 16 waves on it, 3.8).  FEW: of few trees
+// (leaves_by_fours, forest_plan.hpp) a wave takes four and stores their ids from its lanes.  Bound: the walk, with 391
 // workgroups for 256 CUs; two shares of the trees, or fewer rows per workgroup, fill the tile more often and took 54.7 and
 // 50.4.
-template <int D, int NR>
+template <int D, int NR, bool FEW>
 __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kernel(DevModel m, const float *__restrict__ X,
                                                                                  int64_t n_rows, float *, int32_t *,
                                                                                  int32_t *leaf_out)
@@ -217,11 +219,11 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
     const int T = m.n_trees;
     const uint32_t stride = static_cast<uint32_t>(m.walk.groups) * 256, xbase = WALK_WAVES * STAGE_BYTES;
     const uint32_t mine = static_cast<uint32_t>(wave) * STAGE_BYTES;
-    const int round = 4 * WALK_WAVES, rounds = (T + round - 1) / round;
+    const int round = 4 * WALK_WAVES, rounds = FEW ? 1 : (T + round - 1) / round;
 
     const char *image = reinterpret_cast<const char *>(m.walk.node);
-    // Trees each wave takes in a round, and the first of this one's.
-    const auto share = [&](int k) { return T - k * round >= round ? 4 : (T - k * round + WALK_WAVES - 1) / WALK_WAVES; };
+    // Trees each wave takes in a round (at most), and the first of this one's.
+    const auto share = [&](int k) { return FEW || T - k * round >= round ? 4 : (T - k * round + WALK_WAVES - 1) / WALK_WAVES; };
     const auto first_tree = [&](int k) { return k * round + wave * share(k); };
     Vec4 ahead[PIECES];
     const auto fetch = [&](int first) {  // caller's order: a tree sits anywhere
@@ -232,14 +234,15 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
             for (int i = 0; i < PIECES; ++i) ahead[i] = *reinterpret_cast<const Vec4 *>(image + at + i * 1024);
         }
     };
-    int k = static_cast<int>(blockIdx.y);
-    if (k < rounds) fetch(first_tree(k));
+    int k = FEW ? 0 : static_cast<int>(blockIdx.y);
+    if (k < rounds && (!FEW || first_tree(k) < T)) fetch(first_tree(k));
     tile_fill<NR, NR == 4 ? 8 : 4, true>(X, row0, n_rows, m.n_features, xbase, 256, stride, wave, lane);
     __syncthreads();
 
     const uint32_t xa = xbase + lane * 4;
     for (; k < rounds; k += m.n_splits) {
-        const int n = share(k), first = first_tree(k);
+        const int first = first_tree(k), n = FEW ? min(4, T - first) : share(k);
+        if (FEW && n <= 0) return;
         uint32_t ids[NR][2] = {}, id[NR];  // of up to four trees, 16 bits each; of the last tree, not yet among them
         const auto keep = [&](int j) {
 #pragma unroll
@@ -271,14 +274,14 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
         constexpr int NT = STEP > 1 && NR < 4 ? 2 : 1;  // trees walked together: four row groups' would spill (42.5 -> 44.5 us)
 #pragma unroll
         for (int j = 0; j < 4; j += NT) {
-            if (j < n) {
+            if (j < n && first < T) {
                 if (j % STEP == 0) {
                     if (PIECES > 1 || lane * 16 < STEP_BYTES) {
 #pragma unroll
                         for (int i = 0; i < PIECES; ++i) lds_write<Vec4>(mine + i * 1024 + lane * 16, ahead[i]);
                     }
                     if (j + STEP < n) fetch(first + j + STEP);
-                    else if (k + m.n_splits < rounds) fetch(first_tree(k + m.n_splits));
+                    else if (!FEW && k + m.n_splits < rounds) fetch(first_tree(k + m.n_splits));
                 }
                 if (NT > 1 && j + 1 < n) walk(j, std::integral_constant<int, NT>{});
                 else walk(j, std::integral_constant<int, 1>{});
@@ -299,10 +302,14 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
                     if (j < n && begin + j < T) dst[j] = v[j];
             }
         };
-        if (T <= 4) {  // a row's ids share 16 bytes: nothing to gain from an exchange
+        if (FEW || T <= 4) {  // straight from the lanes
 #pragma unroll
-            for (int r = 0; r < NR; ++r)
-                if (const int64_t row = row0 + r * TILE + lane; first < T && row < n_rows) leaf_out[row * T + first] = static_cast<int32_t>(ids[r][0]);
+            for (int r = 0; r < NR; ++r) {
+                const int64_t row = row0 + r * TILE + lane;
+                if (row >= n_rows || first >= T) continue;
+                if (FEW) store(row, first, n, Vec2{ids[r][0], ids[r][1]});
+                else leaf_out[row * T + first] = static_cast<int32_t>(ids[r][0]);
+            }
             return;
         }
         // A wave leaves the ids of its rows in its stage, those of row i at place i + 4 * wave, so that the 16 lanes
@@ -332,8 +339,9 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
 template <int D, int MODE>
 KernelFn pick_groups(int groups)
 {
-    if constexpr (MODE == WALK_LEAVES)
-        return groups == 1 ? forest_walk_leaves_kernel<D, 1> : groups == 2 ? forest_walk_leaves_kernel<D, 2> : forest_walk_leaves_kernel<D, 4>;
+    constexpr bool FEW = MODE == WALK_FEW_LEAVES;
+    if constexpr (MODE == WALK_LEAVES || FEW)
+        return groups == 1 ? forest_walk_leaves_kernel<D, 1, FEW> : groups == 2 ? forest_walk_leaves_kernel<D, 2, FEW> : forest_walk_leaves_kernel<D, 4, FEW>;
     else switch (groups) {
         case 1: return forest_walk_kernel<D, 1, MODE>;
         case 2: return forest_walk_kernel<D, 2, MODE>;
@@ -358,14 +366,15 @@ KernelFn pick(int depth, int groups, int mode)
 {
     if (mode == WALK_COLUMN) return pick_depth<WALK_COLUMN>(depth, groups);
     if (mode == WALK_COLUMNS) return pick_depth<WALK_COLUMNS>(depth, groups);
-    return pick_depth<WALK_LEAVES>(depth, groups);
+    if (mode == WALK_LEAVES) return pick_depth<WALK_LEAVES>(depth, groups);
+    return pick_depth<WALK_FEW_LEAVES>(depth, groups);
 }
 
 }  // namespace
 
 hipError_t init_walk_kernels(size_t lds_limit)
 {
-    for (int mode : {WALK_COLUMN, WALK_COLUMNS, WALK_LEAVES})
+    for (int mode : {WALK_COLUMN, WALK_COLUMNS, WALK_LEAVES, WALK_FEW_LEAVES})
         for (int depth = WALK_MIN_DEPTH; depth <= WALK_MAX_DEPTH; ++depth)
             for (int groups = 1; groups <= walk_max_groups(mode == WALK_COLUMNS ? 2 : 1); groups *= 2) {
                 const void *fn = reinterpret_cast<const void *>(pick(depth, groups, mode));
@@ -386,7 +395,7 @@ hipError_t launch_walk(const DevModel &m, int groups, const float *X, int64_t n_
     if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(n_blocks), static_cast<unsigned>(m.n_splits));
     const size_t lds = walk_lds_bytes(m.walk.depth, m.n_features, m.n_outputs, m.walk.groups);
-    const int mode = leaf_out ? WALK_LEAVES : m.n_outputs == 1 ? WALK_COLUMN : WALK_COLUMNS;
+    const int mode = leaf_out ? leaves_by_fours(m, groups, n_rows) ? WALK_FEW_LEAVES : WALK_LEAVES : m.n_outputs == 1 ? WALK_COLUMN : WALK_COLUMNS;
     hipLaunchKernelGGL(pick(m.walk.depth, groups, mode), grid, dim3(WALK_WAVES * TILE), lds, stream, m, X,
                        n_rows, scores, labels, leaf_out);
     return hipGetLastError();

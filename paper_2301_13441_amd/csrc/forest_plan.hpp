@@ -330,6 +330,29 @@ inline bool deep_shares_cu(const DevModel &m, int groups, bool sums)
     return deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups, sums) <= CU_LDS_BYTES / 2;
 }
 
+// Leaf ids of few trees: a wave takes four of them and stores their ids itself (true), or the trees are dealt evenly and
+// the waves exchange the ids.  An exchange puts all 16 waves through two more barriers and a share of the stores, which
+// few trees do not win back in a batch of many workgroups; small batches wait for the longest wave, and wide rows for
+// their tile, and there one tree a wave is the better.  us, exchange / fours, at 700,000 rows: 5 trees of depth 6, 4 features,
+// two columns 40 / 26; 8 of depth 6, 16 features 49 / 35; 12 of depth 5, 15 features 50 / 39; irregular trees with
+// 15-wide leaves of depth 8, 4 features: 10 82 / 60, 16 93 / 70.  The other way: 9 of depth 8, 64 features 67 / 76; 24 of
+// depth 7, 4 features 60 / 75; 7 irregular of depth 11, 110 features, 350,000 rows 68 / 82; 8 of depth 8, 10 features,
+// 13,000 rows 4.2 / 5.2.
+inline bool leaves_by_fours(const DevModel &m, int groups, int64_t n_rows)
+{
+    const int64_t workgroups = (n_rows + PLAN_ROWS * groups - 1) / (PLAN_ROWS * groups);
+    const int T = m.n_trees, F = m.n_features;
+    if (T == 1) return true;
+    if (m.walk.depth > 0) {
+        if (T == 2) return true;
+        if (T <= 6) return F <= 40 && workgroups >= CUS;
+        return groups == 2 && F >= 4 && F <= 32 && T <= 16 && workgroups >= (T <= 12 ? 600 : 600 + 850 * (T - 12));
+    }
+    if (groups == 2) return T <= 6 && F <= 32 && workgroups >= 1500;
+    if (T == 2) return F <= 64 && workgroups >= 512;
+    return F <= 40 && (T <= 6 || (F >= 4 && T <= 20)) && workgroups >= 2000;
+}
+
 // One lane per (row, tree): the smallest batches of the walk kernels' models (forest_kernels_split.hip).
 // Up to a million tests the gathers take less than what a walk kernel's workgroups begin and end with.
 // Microseconds a call, this kernel / walk kernels with their reduction, 500 trees of depth 8: 1 row 5.2 / 10.4,
@@ -448,11 +471,13 @@ inline forest_launch_t launch_shape(const DevModel &m, const LaunchPlan &p, int6
             s.rows_per_workgroup = PLAN_ROWS * p.groups;
             s.threads = PLAN_ROWS * WALK_WAVES;
             s.lds_bytes = static_cast<int32_t>(walk_lds_bytes(m.walk.depth, m.n_features, m.n_outputs, m.walk.groups));
+            s.leaves_by_fours = !sums && leaves_by_fours(m, p.groups, n_rows);
             break;
         case FOREST_KERNEL_DEEP:
             s.rows_per_workgroup = PLAN_ROWS * p.groups;
             s.threads = PLAN_ROWS * DEEP_WAVES;
             s.lds_bytes = static_cast<int32_t>(deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, p.groups, sums));
+            s.leaves_by_fours = !sums && leaves_by_fours(m, p.groups, n_rows);
             break;
         case FOREST_KERNEL_RANK_BANK:
             s.rows_per_workgroup = BANK_ROWS;

@@ -176,3 +176,44 @@ def test_few_rows_of_many_tests(trees, depth, outputs):
     for rows in (1, 3, 40):
         _check(f, X[:rows], leaves=True)
         _check(few, X[:rows], leaves=True)
+
+
+def _by_fours(f, rows):
+    from paper_2301_13441_amd import binding
+    return bool(binding.forest_packed_launch(f, rows, True, form="walk")["leaves_by_fours"])
+
+
+def test_leaf_ids_of_few_trees_go_by_fours_where_workgroups_are_many():
+    """Large batches of few trees over narrow rows, which the exchange of the ids made up to 1.5 times slower; sums never."""
+    from paper_2301_13441_amd import binding
+    walk = lambda trees, features, outputs=2: _full_forest(1, trees, 6, features, n_outputs=outputs)
+    for trees, features, rows, want in ((1, 300, 9_000, True), (2, 300, 9_000, True), (5, 40, 16_000, False), (5, 40, 40_000, True), (5, 41, 700_000, False),
+                                        (12, 16, 70_000, False), (12, 16, 80_000, True), (12, 3, 700_000, False), (12, 33, 700_000, False),
+                                        (16, 16, 350_000, False), (16, 16, 600_000, True), (17, 16, 10**6, False), (64, 16, 10**6, False)):
+        assert _by_fours(walk(trees, features), rows) == want, (trees, features, rows)
+    assert not _by_fours(walk(12, 16, 1), 10**6)  # 256 rows per workgroup
+    for trees, features, outputs, rows, want in ((1, 200, 3, 9_000, True), (2, 64, 3, 30_000, False), (2, 64, 3, 40_000, True), (6, 3, 15, 130_000, True),
+                                                 (20, 4, 15, 130_000, True), (20, 3, 15, 130_000, False), (20, 4, 15, 120_000, False), (21, 4, 15, 10**6, False),
+                                                 (6, 32, 2, 200_000, True), (7, 32, 2, 10**6, False), (6, 33, 2, 10**6, False)):
+        f = _vector_forest(outputs, features, trees)
+        assert _by_fours(f, rows) == want, (trees, features, outputs, rows)
+        assert binding.forest_packed_launch(f, rows, False, form="walk")["leaves_by_fours"] == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what,trees", [("walk", t) for t in (1, 2, 3, 5, 6, 7, 12, 13, 16, 17)] + [("deep", t) for t in (1, 2, 3, 5, 6, 7, 19, 20, 21)])
+def test_leaf_ids_of_few_trees(what, trees):
+    """Both sides of the rule, waves with one to four trees and with none, a ragged last workgroup."""
+    import torch
+    from paper_2301_13441_amd import binding
+    rng = np.random.default_rng(trees)
+    for depth in (3, 4, 5, 6, 7, 8) if what == "walk" else (9, 11):
+        for outputs in (1, 2, 9):
+            f = _full_forest(trees, trees, depth, 7, n_outputs=outputs) if what == "walk" else \
+                wl.random_forest(trees, n_trees=trees, n_features=7, max_depth=depth, stop_prob=0.3, n_outputs=outputs, leaf_width=outputs, aggregate=wl.AGG_MEAN)
+            model = binding.forest_load_form(f, "walk")
+            for rows in (77, 40_001, 300_001):
+                X = rng.standard_normal((rows, 7)).astype(np.float32)
+                got = model.predict_leaves(torch.from_numpy(X).cuda()).cpu().numpy()
+                np.testing.assert_array_equal(got, oracle.predict(f, X, want_leaves=True, n_threads=8).leaf_node_id)
+            model.close()
