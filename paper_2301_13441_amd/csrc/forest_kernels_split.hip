@@ -162,11 +162,12 @@ __global__ __launch_bounds__(PT_THREADS) void forest_point_kernel(DevModel m, co
     for (int i = threadIdx.x; i < here * F; i += threads) xs[i] = X[row0 * F + i];
     if (!LEAVES && threadIdx.x < TILE) {
         // The columns' trees follow each other; counts are small integers.  A scan by the first wave: one after the other
-        // the counts are as many trips to memory.
+        // the counts are as many trips to memory; as many steps as the columns need (one column, 1 row of 59 x depth 2: 3.94
+        // us with all six, 3.77 with none).
         static_assert(FOREST_MAX_OUTPUTS <= TILE, "a lane per column");
         const int lane = threadIdx.x;
         int n = lane < K ? static_cast<int>(m.col_trees[lane]) : 0;
-        for (int d = 1; d < TILE; d <<= 1) {
+        for (int d = 1; d < K; d <<= 1) {
             const int below = __shfl_up(n, d, TILE);
             if (lane >= d) n += below;
         }

@@ -167,13 +167,16 @@ def test_a_row_of_many_tests_is_cut_into_shares():
 @pytest.mark.gpu
 @pytest.mark.parametrize("trees,depth,outputs", [(2001, 6, 10), (1501, 8, 1), (2403, 5, 32)])
 def test_few_rows_of_many_tests(trees, depth, outputs):
-    """The same through the reduction: shares of 1 to 40 rows, up to as many columns as a model may have; and 100 trees of
+    """The same through the reduction: shares of 1 to 40 rows, up to as many columns as a model may have; and 200 trees of
     the same shapes, which the kernel with a lane per (row, tree) takes and whose columns' first trees it counts."""
+    from paper_2301_13441_amd import binding
     from test_gpu_parity import _check
     f = _full_forest(trees, trees, depth, 12, n_outputs=outputs, transform=wl.TRANSFORM_SOFTMAX if outputs > 1 else wl.TRANSFORM_SIGMOID)
-    few = _full_forest(trees, 100, depth, 12, n_outputs=outputs, aggregate=wl.AGG_MEAN)
+    few = _full_forest(trees, 200, depth, 12, n_outputs=outputs, aggregate=wl.AGG_MEAN)
     X = np.random.default_rng(depth).standard_normal((40, 12)).astype(np.float32)
     for rows in (1, 3, 40):
+        s = binding.forest_packed_launch(f, rows)
+        assert s["kernel"] == "walk" and s["shares"] > 1 and binding.forest_packed_launch(few, rows)["kernel"] == "point"
         _check(f, X[:rows], leaves=True)
         _check(few, X[:rows], leaves=True)
 

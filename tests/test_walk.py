@@ -117,14 +117,18 @@ def test_walk_kernels(depth, features, outputs, full):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("depth,trees,features,outputs", [(3, 1, 2, 1), (8, 500, 28, 1), (6, 2000, 128, 10), (7, 65, 300, 4), (4, 10, 9, 3),
-                                                          (5, 10, 10, 5), (3, 5, 4, 32), (4, 40, 7, 31)])
+                                                          (5, 10, 10, 5), (3, 5, 4, 32), (4, 40, 7, 31), (5, 300, 4, 32), (8, 104, 7, 31),
+                                                          (6, 30, 5, 2), (6, 60, 5, 7)])
 def test_smallest_batches_with_a_lane_per_row_and_tree(depth, trees, features, outputs):
     """One row, whole and ragged workgroups of rows, more pairs than threads, and the first batches beyond
-    the kernel's limit on rows and on tests."""
+    the kernel's limit on rows and on tests; one column up to as many as a model may have, whose first trees it counts.
+    (More than four columns in a wave's run of trees: the deep walk kernel's.)"""
+    from paper_2301_13441_amd import binding
     rng = np.random.default_rng(depth + trees)
     f = _forest(trees + depth, trees, depth, features, outputs, full=True)
     limit = min(8192, (1 << 20) // (trees * depth))
     for rows in sorted({1, 2, 15, 17, 70, limit, limit + 1}):
+        assert binding.forest_packed_launch(f, rows)["kernel"] == ("deep" if trees < outputs * 2 and outputs > 30 else "point" if rows <= limit else "walk")
         X = rng.standard_normal((rows, features)).astype(np.float32)
         if rows >= 70:
             X = _special_rows(X, f, rng)
