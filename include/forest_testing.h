@@ -185,6 +185,9 @@ typedef struct forest_launch_t {
 int forest_launch(const forest *f, int64_t n_rows, int32_t leaves, forest_launch_t *out);
 int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out);
 
+/* forest_packed_launch of a call that finds every workspace of its handle taken (forest.h, concurrency). */
+int forest_packed_launch_no_workspace(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out);
+
 /*
  * Host-only view of the rank coding of kernel_path 2 and 3 (the input's dtype rewriting,
  * Section 4.3.1; no GPU needed): a rank register stores the local rank q of a row among the

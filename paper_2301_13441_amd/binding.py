@@ -76,6 +76,7 @@ EXPORTS = ["forest_load", "forest_free", "forest_info", "forest_out_bytes", "for
 # include/forest_testing.h: host-only views into the model compiler, for its tests
 TESTING_EXPORTS = ["forest_pack", "forest_pack_view", "forest_pack_free", "forest_rank_code",
                    "forest_staged_position", "forest_probe_compare_rate", "forest_launch", "forest_packed_launch",
+                   "forest_packed_launch_no_workspace",
                    "forest_load_form", "forest_pack_form"]
 
 
@@ -121,7 +122,7 @@ def load_library():
     lib.forest_rank_code.argtypes = [_i32, ctypes.POINTER(ctypes.c_uint16), ctypes.POINTER(ctypes.c_uint16)]
     lib.forest_staged_position.restype = ctypes.c_int
     lib.forest_staged_position.argtypes = [_i32, _i32, ctypes.POINTER(_i32)]
-    for fn in (lib.forest_launch, lib.forest_packed_launch):
+    for fn in (lib.forest_launch, lib.forest_packed_launch, lib.forest_packed_launch_no_workspace):
         fn.restype = ctypes.c_int
         fn.argtypes = [_p, _i64, _i32, ctypes.POINTER(_Launch)]
     lib.forest_strerror.restype = ctypes.c_char_p
@@ -298,8 +299,9 @@ def forest_launch(f, n_rows: int, leaves: bool = False) -> dict:
     return _launch(f._lib.forest_launch, f._h, "forest_launch", n_rows, leaves)
 
 
-def forest_packed_launch(forest, n_rows: int, leaves: bool = False, form: str = "auto") -> dict:
-    """The same for a model that is only packed (form: as in forest_load_form): no GPU needed."""
+def forest_packed_launch(forest, n_rows: int, leaves: bool = False, form: str = "auto", workspace: bool = True) -> dict:
+    """The same for a model that is only packed (form: as in forest_load_form): no GPU needed.  Without `workspace`: of
+    a call that finds every workspace of its handle taken."""
     lib = load_library()
     d, keep = _desc_from(forest)
     h = _p()
@@ -307,7 +309,8 @@ def forest_packed_launch(forest, n_rows: int, leaves: bool = False, form: str = 
     if rc != 0:
         raise ForestError(rc, "forest_pack_form")
     try:
-        return _launch(lib.forest_packed_launch, h, "forest_packed_launch", n_rows, leaves)
+        call = lib.forest_packed_launch if workspace else lib.forest_packed_launch_no_workspace
+        return _launch(call, h, "forest_packed_launch", n_rows, leaves)
     finally:
         lib.forest_pack_free(h)
 

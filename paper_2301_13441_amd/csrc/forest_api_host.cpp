@@ -35,7 +35,9 @@ int forest_pack_form(const forest_desc *desc, int32_t form, forest_packed **out)
 
 int forest_pack(const forest_desc *desc, forest_packed **out) { return forest_pack_form(desc, FOREST_FORM_AUTO, out); }
 
-int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out)
+namespace {
+
+int packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, bool workspace, forest_launch_t *out)
 {
     if (!p || !out || n_rows < 1) return FOREST_EINVAL;
     if (n_rows > FOREST_MAX_ROWS) return FOREST_ELIMIT;
@@ -43,8 +45,20 @@ int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves,
     Workspace ws;
     ws.rank_tile_words = static_cast<int64_t>(rank_tile_bytes(d.rank_regs, SPLIT_BELOW_BLOCKS) / sizeof(uint32_t));
     ws.partial_doubles = split_workspace_doubles(d.n_outputs);
-    *out = launch_shape(d, plan_launch(d, &ws, n_rows, !leaves), n_rows, !leaves);
+    *out = launch_shape(d, plan_launch(d, workspace ? &ws : nullptr, n_rows, !leaves), n_rows, !leaves);
     return FOREST_OK;
+}
+
+}  // namespace
+
+int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out)
+{
+    return packed_launch(p, n_rows, leaves, true, out);
+}
+
+int forest_packed_launch_no_workspace(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out)
+{
+    return packed_launch(p, n_rows, leaves, false, out);
 }
 
 int forest_rank_code(int32_t q, uint16_t *code, uint16_t *entry)

@@ -387,10 +387,15 @@ inline int point_threads(const DevModel &m)
     return pairs >= PT_THREADS ? PT_THREADS : static_cast<int>((pairs + PLAN_ROWS - 1) / PLAN_ROWS * PLAN_ROWS);
 }
 
-inline bool takes_point(const DevModel &m, int64_t n_rows)
+// Shares need a workspace for their sums: a call that gets none, or one too small for the shares it asks for, keeps this
+// kernel (1 row of 2001 trees of depth 6: 10.3 us; one workgroup of the walk kernels takes them all in 44.3).
+inline bool takes_point(const DevModel &m, const Workspace *ws, int64_t n_rows, bool sums)
 {
-    if (m.walk.depth >= 5 && static_cast<int64_t>(m.n_trees) * m.walk.depth > POINT_MAX_ROW_TESTS) return false;
-    return m.walk.depth > 0 && n_rows <= POINT_MAX_ROWS && n_rows * m.n_trees * m.walk.depth <= POINT_MAX_TESTS && point_lds_bytes(m) <= POINT_MAX_LDS;
+    if (m.walk.depth == 0 || n_rows > POINT_MAX_ROWS || n_rows * m.n_trees * m.walk.depth > POINT_MAX_TESTS || point_lds_bytes(m) > POINT_MAX_LDS) return false;
+    if (m.walk.depth < 5 || static_cast<int64_t>(m.n_trees) * m.walk.depth <= POINT_MAX_ROW_TESTS) return true;
+    Workspace ample;
+    ample.partial_doubles = split_workspace_doubles(m.n_outputs);
+    return choose_walk_splits(m, ws, n_rows, sums) < choose_walk_splits(m, &ample, n_rows, sums);
 }
 
 // Rows of one launch at most.  HIP takes fewer than 2^32 threads per grid axis, and the walk kernels spend
@@ -432,7 +437,7 @@ inline LaunchPlan plan_launch(const DevModel &m, const Workspace *ws, int64_t n_
     LaunchPlan p;
     p.splits = choose_splits(m, ws, n_rows, sums, p.fits);
     const bool dense = p.fits && prefers_dense(m, n_rows, sums);
-    if (takes_point(m, n_rows)) {
+    if (takes_point(m, ws, n_rows, sums)) {
         p.kernel = FOREST_KERNEL_POINT;
         p.splits = 1;
     } else if (m.walk.depth > 0 && !dense) {

@@ -164,6 +164,21 @@ def test_a_row_of_many_tests_is_cut_into_shares():
         assert s["kernel"] == kernel and (s["shares"] > 1) == (kernel == "walk"), s
 
 
+def test_a_row_of_many_tests_without_a_workspace():
+    """A call that finds every workspace taken cannot be cut into shares; one workgroup of the walk kernels would take all
+    the trees.  Leaf ids need no workspace."""
+    from paper_2301_13441_amd import binding
+    for trees, depth, outputs in ((2001, 6, 1), (2001, 6, 10), (1501, 8, 1), (4000, 5, 1)):
+        f = _full_forest(1, trees, depth, 10, n_outputs=outputs)
+        for rows in (1, 40):
+            plan = lambda **kw: binding.forest_packed_launch(f, rows, **kw)
+            assert plan()["kernel"] == "walk" and plan()["shares"] > 1
+            assert plan(workspace=False)["kernel"] == "point"
+            assert plan(workspace=False, leaves=True) == plan(leaves=True)
+    few = _full_forest(1, 100, 6, 10)
+    assert binding.forest_packed_launch(few, 1, workspace=False)["kernel"] == "point"
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("trees,depth,outputs", [(2001, 6, 10), (1501, 8, 1), (2403, 5, 32)])
 def test_few_rows_of_many_tests(trees, depth, outputs):
@@ -179,6 +194,28 @@ def test_few_rows_of_many_tests(trees, depth, outputs):
         assert s["kernel"] == "walk" and s["shares"] > 1 and binding.forest_packed_launch(few, rows)["kernel"] == "point"
         _check(f, X[:rows], leaves=True)
         _check(few, X[:rows], leaves=True)
+
+
+@pytest.mark.gpu
+def test_few_rows_of_many_tests_on_more_streams_than_workspaces():
+    """Four streams have a workspace of the handle each, the others none; all of them get the same rows."""
+    import torch
+    import paper_2301_13441_amd as pk
+    f = _full_forest(5, 2001, 6, 12, n_outputs=3)
+    X = np.random.default_rng(6).standard_normal((3, 12)).astype(np.float32)
+    ref = oracle.predict(f, X, want_leaves=True)
+    model, xd = pk.forest_load(f), torch.from_numpy(X).cuda()
+    streams, got = [torch.cuda.Stream() for _ in range(7)], []
+    torch.cuda.synchronize()
+    for s in streams:
+        with torch.cuda.stream(s):
+            got.append(model.predict(xd) + (model.predict_leaves(xd),))
+    torch.cuda.synchronize()
+    for scores, labels, leaves in got:
+        np.testing.assert_array_equal(leaves.cpu().numpy(), ref.leaf_node_id)
+        np.testing.assert_array_equal(labels.cpu().numpy(), ref.labels)
+        np.testing.assert_allclose(scores.cpu().numpy(), ref.scores, rtol=2e-7, atol=1e-30)  # fp64 sums, one rounding apart
+    model.close()
 
 
 def _by_fours(f, rows):
