@@ -361,11 +361,20 @@ inline bool leaves_by_fours(const DevModel &m, int groups, int64_t n_rows)
 // 8,000 rows 6.2 / 6.6, 30,000 rows 10.0 / 6.9.
 constexpr int64_t POINT_MAX_TESTS = 1 << 20;  // rows x trees x depth
 constexpr int64_t POINT_MAX_ROWS = 8192;
-// Tests of one row, all by one workgroup, whose CU's texture path they queue at; trees of depth 4 and less are a line
-// each and queue for less.  1 row, this kernel / walk kernels with their reduction: 1500 x depth 7 9.4 / 9.8 us, 2000 x
-// depth 6 10.5 / 9.6 (ten columns 10.7 / 11.1), 1600 x depth 8 10.4 / 9.6, 1900 x depth 8 11.7 / 10.0, 4000 x depth 5
-// 15.9 / 10.8, 6000 x depth 3 11.9 / 12.9.  (Two pairs of a thread at a time: 11.7 for 2000 x depth 6.)
-constexpr int64_t POINT_MAX_ROW_TESTS = 12000;
+// Tests of one row of trees deeper than four levels, all by one workgroup, whose CU's texture path they queue at; above
+// this many the walk kernels' shares and their reduction are the faster.  us a call, this kernel / the shares, 1 row of 12,000
+// tests: depth 5 10.7 / 10.6, 6 10.2 / 9.5, 7 9.8 / 9.6, 8 9.6 / 9.9; at 10,500 9.3 / 9.4 of depth 6; at 15,000 12.4 / 10.6,
+// 11.9 / 9.6, 12.3 / 9.8, 11.3 / 10.0.  (Two pairs of a thread at a time: 11.7 for 2000 x depth 6.)  Several columns make the
+// reduction dearer: of depth 5, whose shares are few and long, ten columns 11.5 / 11.7 at 15,000 and three 11.5 / 11.5 (12.5 /
+// 11.7 for 40 rows); deeper trees gain little (ten columns, 13,000 tests, depths 6 to 8: 10.9 / 10.4, 10.1 / 10.0, 10.0 / 10.3, and 13.1 /
+// 10.9 for 40 rows of depth 8) unless the columns are many (32: 11.6 / 12.1, 11.0 / 11.8, 10.8 / 12.4; 40 rows of depth 8 13.8 /
+// 12.9).  Leaf ids, which need no reduction, cross at fewer tests up to depth 6 (12,000 of depth 6: 8.8 / 5.8), and trees of
+// up to four levels at more (15,000 of depth 4, 20,000 of depth 3; ten columns 21,000 and 37,000); both follow the rule as
+// it stands.
+inline int64_t point_max_row_tests(const DevModel &m, int64_t n_rows, bool sums)
+{
+    return sums && m.n_outputs > 1 && (m.walk.depth == 5 || (m.n_outputs > 16 && n_rows <= 16)) ? 14000 : 12000;
+}
 constexpr size_t POINT_MAX_LDS = 64 * 1024;
 constexpr int PT_THREADS = 1024, PT_MAX_ROWS = 16;
 
@@ -392,7 +401,7 @@ inline int point_threads(const DevModel &m)
 inline bool takes_point(const DevModel &m, const Workspace *ws, int64_t n_rows, bool sums)
 {
     if (m.walk.depth == 0 || n_rows > POINT_MAX_ROWS || n_rows * m.n_trees * m.walk.depth > POINT_MAX_TESTS || point_lds_bytes(m) > POINT_MAX_LDS) return false;
-    if (m.walk.depth < 5 || static_cast<int64_t>(m.n_trees) * m.walk.depth <= POINT_MAX_ROW_TESTS) return true;
+    if (m.walk.depth < 5 || static_cast<int64_t>(m.n_trees) * m.walk.depth <= point_max_row_tests(m, n_rows, sums)) return true;
     Workspace ample;
     ample.partial_doubles = split_workspace_doubles(m.n_outputs);
     return choose_walk_splits(m, ws, n_rows, sums) < choose_walk_splits(m, &ample, n_rows, sums);

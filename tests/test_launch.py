@@ -162,6 +162,12 @@ def test_a_row_of_many_tests_is_cut_into_shares():
         f = _full_forest(1, trees, depth, 10)
         s = binding.forest_packed_launch(f, 1)
         assert s["kernel"] == kernel and (s["shares"] > 1) == (kernel == "walk"), s
+    # several columns make the reduction of the shares dearer, most against the fewest tests of a copy, or where they are many
+    for trees, depth, outputs, rows, kernel in ((2800, 5, 3, 1, "point"), (2801, 5, 3, 1, "walk"), (2800, 5, 10, 40, "point"), (2001, 6, 10, 1, "walk"),
+                                                (1750, 8, 20, 16, "point"), (1751, 8, 20, 16, "walk"), (1501, 8, 20, 17, "walk"), (1501, 8, 16, 1, "walk")):
+        s = binding.forest_packed_launch(_full_forest(1, trees, depth, 10, n_outputs=outputs), rows)
+        assert s["kernel"] == kernel, (trees, depth, outputs, rows)
+    assert binding.forest_packed_launch(_full_forest(1, 2800, 5, 10, n_outputs=10), 1, leaves=True)["kernel"] == "walk"
 
 
 def test_a_row_of_many_tests_without_a_workspace():
@@ -180,7 +186,7 @@ def test_a_row_of_many_tests_without_a_workspace():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("trees,depth,outputs", [(2001, 6, 10), (1501, 8, 1), (2403, 5, 32)])
+@pytest.mark.parametrize("trees,depth,outputs", [(2001, 6, 10), (1501, 8, 1), (2803, 5, 32)])
 def test_few_rows_of_many_tests(trees, depth, outputs):
     """The same through the reduction: shares of 1 to 40 rows, up to as many columns as a model may have; and 200 trees of
     the same shapes, which the kernel with a lane per (row, tree) takes and whose columns' first trees it counts."""
