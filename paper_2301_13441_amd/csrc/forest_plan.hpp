@@ -355,10 +355,11 @@ inline bool leaves_by_fours(const DevModel &m, int groups, int64_t n_rows)
 
 // One lane per (row, tree): the smallest batches of the walk kernels' models (forest_kernels_split.hip).
 // Up to a million tests the gathers take less than what a walk kernel's workgroups begin and end with.
-// Microseconds a call, this kernel / walk kernels with their reduction, 500 trees of depth 8: 1 row 5.2 / 10.4,
-// 64 rows 7.4 / 10.7, 256 rows 8.8 / 10.8, 1,024 rows 19.8 / 10.6; 2000 x depth 6, 10 columns: 64 rows 11.3 / 14.1,
-// 256 rows 17.7 / 14.4.  Ten trees of depth 4, which the walk kernels take in one launch: 1,000 rows 6.0 / 6.6,
-// 8,000 rows 6.2 / 6.6, 30,000 rows 10.0 / 6.9.
+// Microseconds a call, this kernel / walk kernels with their reduction, 500 trees of depth 8: 32 rows 7.5 / 9.3,
+// 131 rows 8.0 / 9.6, 262 rows (a million tests) 9.4 / 9.8, 370 rows 10.8 / 9.8, 1,048 rows 23.5 / 10.0; 2000 x depth 6, 10 columns:
+// 21 rows 10.4 / 10.5, 87 rows (a million) 11.9 / 10.5, 174 rows 14.8 / 10.7; 1000 x depth 3: 349 rows 6.7 / 12.8, 699 rows (two)
+// 11.1 / 12.9.  Few trees, which the walk kernels take in one launch, are bounded by rows: ten of depth 4 6,000 rows
+// 4.5 / 5.4, 20,000 5.2 / 5.8, 30,000 6.1 / 5.9; three of depth 6 4,000 rows 4.9 / 4.5, with five columns 5.7 / 5.8.
 constexpr int64_t POINT_MAX_TESTS = 1 << 20;  // rows x trees x depth
 constexpr int64_t POINT_MAX_ROWS = 8192;
 // Tests of one row of trees deeper than four levels, all by one workgroup, whose CU's texture path they queue at; above
