@@ -3,6 +3,8 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import warnings
 from typing import Optional
 
 import numpy as np
@@ -346,10 +348,21 @@ _SCORES, _LABELS, _LEAVES = 1, 2, 4  # what a short call returns
 
 
 def short_call():
-    """The native call; raises if it has not been built."""
-    import torch  # noqa: F401 - the extension is linked against its libraries
-    from . import _short_call
-    return _short_call.call
+    """The native call.  Without the extension, or with one built against another torch, a call that declines
+    everything: the general way is complete without it."""
+    try:
+        import torch  # noqa: F401 - the extension is linked against its libraries
+        from . import _short_call
+        return _short_call.call
+    except ImportError as exc:
+        warnings.warn(f"the native call of predict() cannot be imported ({exc}): calls take a few microseconds more; "
+                      "build it with `python -m paper_2301_13441_amd.build`", RuntimeWarning, stacklevel=3)
+        return lambda *args: None
+
+
+def short_call_if_torch():
+    """The native call for a model that is loaded where torch is; a host of predict_raw() alone does not import it."""
+    return short_call() if "torch" in sys.modules else None
 
 
 def entry_point(fn) -> int:
@@ -373,7 +386,7 @@ class Forest:
         self.n_trees = info.n_trees
         scores, labels = (offset >= 0 for offset in self.out_layout(1))
         self._parts = _SCORES * scores | _LABELS * labels
-        self._call, self._address = short_call(), handle.value
+        self._call, self._address = short_call_if_torch(), handle.value
         self._predict, self._predict_leaves = entry_point(lib.forest_predict), entry_point(lib.forest_predict_leaves)
 
     def close(self):
@@ -413,7 +426,10 @@ class Forest:
         into one output buffer (either may be None, per the model's output kind).  With
         `static` the call goes through forest_predict_static (pass `out`: it allocates nothing)."""
         if out is None and stream is None and not static:
-            got = self._call(self._predict, self._address, X, self.n_features, self.n_outputs, self._parts, _SHORT_ROWS)
+            call = self._call
+            if call is None:
+                call = self._call = short_call()
+            got = call(self._predict, self._address, X, self.n_features, self.n_outputs, self._parts, _SHORT_ROWS)
             if type(got) is int:
                 raise ForestError(got, "forest_predict")
             if got is not None:
@@ -440,7 +456,10 @@ class Forest:
 
     def predict_leaves(self, X, stream=None):
         if stream is None:
-            got = self._call(self._predict_leaves, self._address, X, self.n_features, self.n_trees, _LEAVES, _SHORT_ROWS)
+            call = self._call
+            if call is None:
+                call = self._call = short_call()
+            got = call(self._predict_leaves, self._address, X, self.n_features, self.n_trees, _LEAVES, _SHORT_ROWS)
             if type(got) is int:
                 raise ForestError(got, "forest_predict_leaves")
             if got is not None:

@@ -83,11 +83,11 @@ def build(verbose: bool = False, extra: list[str] | None = None) -> str:
         others = [s for s in SOURCES if s != RANKLDS]
         objs = list(pool.map(lambda s: _compile(s, extra, verbose), others))
         objs.append(_compile(RANKLDS, [*extra, *variant.result()], verbose))
-        short_call.result()
-    cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", LIB]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+        cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", LIB]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
+        short_call.result()  # last: the library does not need it
     return LIB
 
 

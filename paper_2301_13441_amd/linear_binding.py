@@ -6,7 +6,7 @@ import ctypes
 
 import numpy as np
 
-from .binding import _LABELS, _SCORES, _SHORT_ROWS, entry_point, load_library, short_call
+from .binding import _LABELS, _SCORES, _SHORT_ROWS, entry_point, load_library, short_call, short_call_if_torch
 
 _p = ctypes.c_void_p
 _i32, _i64 = ctypes.c_int32, ctypes.c_int64
@@ -89,7 +89,7 @@ class Linear:
         self.n_outputs = n_outputs
         scores, labels = (offset >= 0 for offset in self.out_layout(1))
         self._parts = _SCORES * scores | _LABELS * labels
-        self._call, self._address, self._predict = short_call(), handle.value, entry_point(_lib().linear_predict)
+        self._call, self._address, self._predict = short_call_if_torch(), handle.value, entry_point(_lib().linear_predict)
 
     def close(self):
         if self._h is not None:
@@ -125,7 +125,10 @@ class Linear:
         """X: torch float32 CUDA tensor [n_rows, F], contiguous.  Returns (scores, labels) views
         into one output buffer (either may be None, per the model's output kind)."""
         if out is None and stream is None:
-            got = self._call(self._predict, self._address, X, self.n_features, self.n_outputs, self._parts, _SHORT_ROWS)
+            call = self._call
+            if call is None:
+                call = self._call = short_call()
+            got = call(self._predict, self._address, X, self.n_features, self.n_outputs, self._parts, _SHORT_ROWS)
             if type(got) is int:
                 raise LinearError(got, "linear_predict")
             if got is not None:

@@ -6,9 +6,8 @@ import pytest
 import workloads as wl
 from workloads.linear import LinearModel
 
-pytestmark = pytest.mark.gpu
 
-
+@pytest.mark.gpu
 @pytest.mark.parametrize("outputs", [1, 3])
 @pytest.mark.parametrize("kind", [wl.OUT_SCORES, wl.OUT_LABELS, wl.OUT_BOTH])
 @pytest.mark.parametrize("family", ["forest", "linear"])
@@ -39,6 +38,42 @@ def test_own_buffer_and_the_callers(family, kind, outputs):
     model.close()
 
 
+@pytest.fixture
+def without_the_extension(monkeypatch):
+    import sys
+    import paper_2301_13441_amd as pk
+    monkeypatch.delattr(pk, "_short_call", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2301_13441_amd._short_call", None)  # its import raises ImportError
+
+
+def test_a_missing_extension_declines(without_the_extension):
+    from paper_2301_13441_amd import binding
+    with pytest.warns(RuntimeWarning, match="paper_2301_13441_amd.build"):
+        call = binding.short_call()
+    assert call(0, 0, None, 1, 1, 1, 1) is None
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("family", ["forest", "linear"])
+def test_models_load_and_predict_without_the_extension(family, without_the_extension):
+    import torch
+    import paper_2301_13441_amd as pk
+    rng = np.random.default_rng(8)
+    X = torch.from_numpy(rng.standard_normal((50, 9)).astype(np.float32)).cuda()
+    with pytest.warns(RuntimeWarning):
+        if family == "forest":
+            model = pk.forest_load(wl.random_forest(4, 30, 9, 6, n_outputs=2))
+        else:
+            model = pk.linear_load(LinearModel(9, 2, rng.standard_normal((9, 2)).astype(np.float32), np.zeros(2, np.float32), wl.TRANSFORM_NONE, wl.OUT_BOTH))
+    out = torch.empty(model.out_bytes(50), dtype=torch.uint8, device="cuda")
+    got = model.predict(X)
+    assert all(torch.equal(a, b) for a, b in zip(got, model.predict(X, out=out)))
+    if family == "forest":
+        assert torch.equal(model.predict_leaves(X), model.predict_leaves(X, stream=torch.cuda.current_stream()))
+    model.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("features,outputs", [(2, 12), (12, 12), (7, 3), (90, 2), (96, 32), (97, 5), (128, 10), (130, 24)])
 def test_linear_scores_of_whole_and_ragged_tiles(features, outputs):
     import torch
@@ -60,6 +95,7 @@ def test_linear_scores_of_whole_and_ragged_tiles(features, outputs):
     f.close()
 
 
+@pytest.mark.gpu
 @pytest.mark.parametrize("family", ["forest", "linear"])
 def test_what_the_native_call_declines_goes_the_general_way(family):
     """Tensors it does not take are refused as before or give the same bits; a closed model is refused; leaf ids and
