@@ -345,7 +345,7 @@ inline bool leaves_by_fours(const DevModel &m, int groups, int64_t n_rows)
     if (T == 1) return true;
     if (m.walk.depth > 0) {
         if (T == 2) return true;
-        if (T <= 6) return F <= 40 && workgroups >= CUS;
+        if (T <= (m.walk.depth <= 6 ? 7 : 6)) return F <= 40 && workgroups >= CUS;
         return groups == 2 && F >= 4 && F <= 32 && T <= 16 && workgroups >= (T <= 12 ? 600 : 600 + 850 * (T - 12));
     }
     if (groups == 2) return T <= 6 && F <= 32 && workgroups >= 1500;
