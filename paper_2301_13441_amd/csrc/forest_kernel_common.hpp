@@ -57,7 +57,7 @@ typedef const float *ColumnBase;
 #endif
 
 // Aggregate, label, transform, store for one row whose K summed leaf values are raw[k * stride];
-// raw[] is overwritten with the aggregated values.
+// raw[] is overwritten: with the aggregated values, or with their exponentials where a softmax is stored.
 __device__ __forceinline__ void finish_values(const DevModel &m, double *raw, int64_t stride, int64_t row,
                                               float *scores, int32_t *labels)
 {

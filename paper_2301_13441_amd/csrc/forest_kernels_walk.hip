@@ -25,8 +25,8 @@
 // 922 -> 828 us; 1000 x depth 6, 50 features, four row groups, 1M rows: 777 -> 758; 1,021 rows of the former, one row
 // group: 17.4 -> 15.6 us a call).  Deeper trees would need a second stage in LDS, at the price of a workgroup's place.
 //
-// Bound: the LDS (82 to 89 % busy).  Per (64 rows,
-// tree of depth D): 3 + 2 (D - 2) LDS reads of 2 clocks each, more at levels 6 and 7 whose 64 and 128 nodes share the
+// Bound: at depth 8 the LDS (89 % busy, vector ALU 78 %), at depth 6 the vector ALU (93 to 97 %) with the LDS (82 to 85 %)
+// behind it.  Per (64 rows, tree of depth D): 3 + 2 (D - 2) LDS reads of 2 clocks each, more at levels 6 and 7 whose 64 and 128 nodes share the
 // 32 banks (4 and 6 clocks).  500 trees of depth 8, 28 features, 1M rows: 2.70 -> 0.62 ms against every node tested
 // (forest_kernels_rank.hip); 1000 of depth 6, 50 features: 1.57 -> 0.76 ms.  Leaf values held as float64, which saves
 // their conversion and a shift: 633 and 802 us against 629 and 788.

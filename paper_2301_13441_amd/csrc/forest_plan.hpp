@@ -97,7 +97,10 @@ struct DevModel {
 // pay back.  Picoseconds a row of a large batch takes, as sums of what grows with the features F, the output columns K,
 // the trees T, their levels, the entries of the split program and the values of a vector leaf: least squares on
 // the measured times of 1,500 models (full, irregular and mixed trees of depth 1 to 12, 4 to 1500 of them, 4 to 200
-// features, 1 to 20 columns) at 300,000 to 2,000,000 rows; nine in ten estimates are within 25 % of the time.
+// features, 1 to 20 columns) at 300,000 to 2,000,000 rows; nine in ten estimates were within 25 % of the time.  The walk
+// kernels have become a tenth faster since: their estimate is 0.92 to 1.29 of the time for eight in ten models, 1.10 at the
+// median, and the choice costs 0.7 % over 1,200 drawn models at six batches each of 6,000 to 1,000,000 rows; 4.7 % of the
+// cells lose more than 3 % and 1.7 times is the worst (12 to 16 columns over few features, which the dense kernels get).
 // The walk kernels lose up to a factor of 3 where the rule does not choose them (1M rows, 10 features, us, walk /
 // dense: ten 10-wide vector trees of depth 3 311 / 128; 100 trees of depth 3, five columns 166 / 86; 1000 stumps with
 // an infinite threshold 1285 / 381), and win by more everywhere else.
@@ -312,8 +315,9 @@ inline int choose_walk_splits(const DevModel &m, const Workspace *ws, int64_t n_
 // Row groups per workgroup, walk and deep walk kernels: as many as leave every CU a workgroup, or, with trees enough
 // for their copies to LDS to count, half of the CUs one of two groups.  More rows per workgroup share those copies and
 // keep more walks in flight, and a workgroup that has a CU to itself is nearly twice as fast as one of two, so rounds
-// of two per CU are not what counts: over 250 models and 20,000 to 270,000 rows this is within 0.5 % of the best choice
-// for each (2 % at 20,000 rows; 1.2 times it at worst), where counting rounds was 25 % off at 66,000 and 40 % at
+// of two per CU are not what counts: over 240 models and 20,000 to 270,000 rows this is within 0.8 % of the best choice
+// for each (sums 2 and leaf ids 5 % at 20,000 rows; 1.3 times it at worst: 90,000 rows of 500 to 900 trees, which get four
+// groups and would do better with two), where counting rounds was 25 % off at 66,000 and 40 % at
 // 150,000 rows (ten trees of depth 2, 10 features, 66,000 rows: 19.2 us with one group, 14.9 with two, 11.5 with
 // four).  Split launches have no workgroups to spare.
 inline int choose_groups(const DevModel &m, int groups, int64_t n_rows, int n_splits)

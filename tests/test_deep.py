@@ -130,7 +130,7 @@ def test_deep_leaf_ids_by_rounds_of_trees(trees, rows):
     rng = np.random.default_rng(trees)
     f = _forest(trees, trees, 9, 7, stop=0.3)
     s = binding.forest_packed_launch(f, rows, True, form="walk")
-    assert s["kernel"] == "deep" and s["shares"] == (2 if rows == 9001 and trees >= 128 else 1), s
+    assert s["kernel"] == "deep" and s["rows_per_workgroup"] == (64 if rows == 9001 else 128) and s["shares"] == (2 if rows == 9001 and trees >= 128 else 1), s
     X = _special_rows(rng.standard_normal((rows, 7)).astype(np.float32), f, rng)
     model = binding.forest_load_form(f, "walk")
     try:

@@ -160,7 +160,7 @@ def test_leaf_ids_by_rounds_of_trees(depth, trees, rows):
     rng = np.random.default_rng(depth + trees)
     f = _forest(depth + trees, trees, depth, 7, full=depth != 7)
     s = binding.forest_packed_launch(f, rows, True, form="walk")
-    assert s["kernel"] == "walk" and s["rows_per_workgroup"] == {9001: 64, 49157: 128, 131075: 256}[rows] or trees < 100, s
+    assert s["kernel"] == "walk" and s["rows_per_workgroup"] == {9001: 64, 49157: 128, 131075: 256}[rows], s
     assert s["shares"] == (2 if rows == 9001 and trees >= 128 else 1), s
     X = _special_rows(rng.standard_normal((rows, 7)).astype(np.float32), f, rng)
     model = binding.forest_load_form(f, "walk")
@@ -173,12 +173,16 @@ def test_leaf_ids_by_rounds_of_trees(depth, trees, rows):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("depth", [3, 6, 8, 9])
-@pytest.mark.parametrize("trees,rows", [(41, 9001), (300, 9001), (41, 70_001)])
+@pytest.mark.parametrize("trees,rows", [(41, 9001), (300, 9001), (1000, 9001), (41, 70_001)])
 def test_columns_without_trees_between_columns_with_some(depth, trees, rows):
     """A wave's run of trees that goes from one column to one further on leaves zeros for those between; odd tree
     counts, which end a pair of trees walked together; with and without shares of the trees."""
+    from paper_2301_13441_amd import binding
     rng = np.random.default_rng(depth + trees)
     f = _forest(trees + depth, trees, min(depth, 8), 9, outputs=7) if depth < 9 else \
         wl.random_forest(trees, n_trees=trees, n_features=9, max_depth=9, stop_prob=0.3, n_outputs=7, aggregate=wl.AGG_SUM)
     f = wl.Forest(**{**f.__dict__, "tree_output": rng.choice([0, 3, 6], trees).astype(np.int32)})
+    s = binding.forest_packed_launch(f, rows, form="walk")
+    assert s["kernel"] == ("walk" if depth < 9 else "deep") and s["rows_per_workgroup"] == (64 if rows == 9001 else 128), s
+    assert s["shares"] == (1 if trees == 41 or (trees, depth) == (300, 3) else 3), s
     _check(f, _special_rows(rng.standard_normal((rows, 9)).astype(np.float32), f, rng))
