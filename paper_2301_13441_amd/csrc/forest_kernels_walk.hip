@@ -243,7 +243,8 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
     for (; k < rounds; k += m.n_splits) {
         const int first = first_tree(k), n = FEW ? min(4, T - first) : share(k);
         if (FEW && n <= 0) return;
-        uint32_t ids[NR][2] = {}, id[NR];  // of up to four trees, 16 bits each; of the last tree, not yet among them
+        // of up to four trees, 16 bits each where they are exchanged; of the last tree, not yet among them
+        uint32_t ids[NR][FEW ? 4 : 2] = {}, id[NR];
         const auto keep = [&](int j) {
 #pragma unroll
             for (int r = 0; r < NR; ++r) ids[r][j >> 1] = (j & 1) ? ids[r][j >> 1] | id[r] << 16 : id[r];
@@ -260,15 +261,18 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
             const uint32_t tree_at = mine + (j % STEP) * TREE_BYTES;
             uint32_t idx[NT][NR];
             walk_trees<D, NR, NT>(tree_at, xa, head, idx);
-            if (j > 0) keep(j - 1);
+            if (!FEW && j > 0) keep(j - 1);
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
-                if (i > 0) keep(j);
+                if (!FEW && i > 0) keep(j);
                 const char *leaves = reinterpret_cast<const char *>(m.walk.leaf_node) + (static_cast<int64_t>(at[i]) << (D + 2)) -
                                      ((tree_at + i * TREE_BYTES) >> 1);
                 asm volatile("" : "+s"(leaves));  // keeps the base whole, so that the loads take a 32-bit offset
 #pragma unroll
-                for (int r = 0; r < NR; ++r) id[r] = static_cast<uint32_t>(*(GlobalInts)((GlobalBytes)leaves + (idx[i][r] >> 1)));
+                for (int r = 0; r < NR; ++r) {
+                    uint32_t &to = FEW ? ids[r][FEW ? j + i : 0] : id[r];
+                    to = static_cast<uint32_t>(*(GlobalInts)((GlobalBytes)leaves + (idx[i][r] >> 1)));
+                }
             }
         };
         constexpr int NT = STEP > 1 && NR < 4 ? 2 : 1;  // trees walked together: four row groups' would spill (42.5 -> 44.5 us)
@@ -289,17 +293,15 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (j == n - 1) keep(j);
-        const auto store = [&](int64_t row, int begin, int n, Vec2 id) {
+            if (!FEW && j == n - 1) keep(j);
+        const auto store = [&](int64_t row, int begin, int n, Vec4 id) {
             int32_t *dst = leaf_out + row * T + begin;
-            const int32_t v[4] = {static_cast<int32_t>(id.x & 0xffff), static_cast<int32_t>(id.x >> 16),
-                                  static_cast<int32_t>(id.y & 0xffff), static_cast<int32_t>(id.y >> 16)};
             if (n == 4 && begin + 4 <= T) {
-                *reinterpret_cast<Int4 *>(dst) = Int4{{v[0], v[1], v[2], v[3]}};
+                *reinterpret_cast<Int4 *>(dst) = Int4{{static_cast<int32_t>(id[0]), static_cast<int32_t>(id[1]), static_cast<int32_t>(id[2]), static_cast<int32_t>(id[3])}};
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    if (j < n && begin + j < T) dst[j] = v[j];
+                    if (j < n && begin + j < T) dst[j] = static_cast<int32_t>(id[j]);
             }
         };
         if (FEW || T <= 4) {  // straight from the lanes
@@ -307,7 +309,7 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
             for (int r = 0; r < NR; ++r) {
                 const int64_t row = row0 + r * TILE + lane;
                 if (row >= n_rows || first >= T) continue;
-                if (FEW) store(row, first, n, Vec2{ids[r][0], ids[r][1]});
+                if constexpr (FEW) store(row, first, n, Vec4{ids[r][0], ids[r][1], ids[r][2], ids[r][3]});
                 else leaf_out[row * T + first] = static_cast<int32_t>(ids[r][0]);
             }
             return;
@@ -329,7 +331,7 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
                 const int li = (wave * EXCHANGE + i) * (TILE / WALK_WAVES) + lane / WALK_WAVES;  // a row of the exchange
                 const Vec2 id = lds_read<Vec2>(from * STAGE_BYTES + ((li + 4 * from) & (PLACES - 1)) * 8);
                 const int64_t row = row0 + g * TILE + li;
-                if (row < n_rows) store(row, begin, n, id);
+                if (row < n_rows) store(row, begin, n, Vec4{id.x & 0xffff, id.x >> 16, id.y & 0xffff, id.y >> 16});
             }
         }
         __syncthreads();

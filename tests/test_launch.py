@@ -234,11 +234,11 @@ def test_leaf_ids_of_few_trees_go_by_fours_where_workgroups_are_many():
     from paper_2301_13441_amd import binding
     walk = lambda trees, features, outputs=2: _full_forest(1, trees, 6, features, n_outputs=outputs)
     for trees, features, rows, want in ((1, 300, 9_000, True), (2, 300, 9_000, True), (5, 40, 16_000, False), (5, 40, 40_000, True), (5, 41, 700_000, False),
-                                        (7, 40, 40_000, True), (8, 40, 700_000, False), (12, 16, 70_000, False), (12, 16, 80_000, True), (12, 3, 700_000, False), (12, 33, 700_000, False),
+                                        (9, 40, 40_000, True), (8, 3, 40_000, False), (10, 40, 700_000, False), (12, 16, 70_000, False), (12, 16, 80_000, True), (12, 3, 700_000, False), (12, 33, 700_000, False),
                                         (16, 16, 350_000, False), (16, 16, 600_000, True), (17, 16, 10**6, False), (64, 16, 10**6, False)):
         assert _by_fours(walk(trees, features), rows) == want, (trees, features, rows)
     assert not _by_fours(walk(12, 16, 1), 10**6)  # 256 rows per workgroup
-    assert _by_fours(walk(7, 16, 1), 10**6) and not _by_fours(_full_forest(1, 7, 7, 16), 10**6)
+    assert _by_fours(walk(9, 16, 1), 10**6) and not _by_fours(_full_forest(1, 7, 7, 16), 10**6)
     for trees, features, outputs, rows, want in ((1, 200, 3, 9_000, True), (2, 64, 3, 30_000, False), (2, 64, 3, 40_000, True), (6, 3, 15, 130_000, True),
                                                  (20, 4, 15, 130_000, True), (20, 3, 15, 130_000, False), (20, 4, 15, 120_000, False), (21, 4, 15, 10**6, False),
                                                  (6, 32, 2, 200_000, True), (7, 32, 2, 10**6, False), (6, 33, 2, 10**6, False)):
@@ -248,7 +248,7 @@ def test_leaf_ids_of_few_trees_go_by_fours_where_workgroups_are_many():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("what,trees", [("walk", t) for t in (1, 2, 3, 5, 6, 7, 12, 13, 16, 17)] + [("deep", t) for t in (1, 2, 3, 5, 6, 7, 19, 20, 21)])
+@pytest.mark.parametrize("what,trees", [("walk", t) for t in (1, 2, 3, 5, 6, 7, 9, 10, 12, 13, 16, 17)] + [("deep", t) for t in (1, 2, 3, 5, 6, 7, 19, 20, 21)])
 def test_leaf_ids_of_few_trees(what, trees):
     """Both sides of the rule, waves with one to four trees and with none, a ragged last workgroup."""
     import torch
