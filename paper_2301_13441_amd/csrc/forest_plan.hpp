@@ -337,11 +337,11 @@ inline bool deep_shares_cu(const DevModel &m, int groups, bool sums)
 // Leaf ids of few trees: a wave takes four of them and stores their ids itself (true), or the trees are dealt evenly and
 // the waves exchange the ids.  An exchange puts all 16 waves through two more barriers and a share of the stores, which
 // few trees do not win back in a batch of many workgroups; small batches wait for the longest wave, and wide rows for
-// their tile, and there one tree a wave is the better.  us, exchange / fours, at 700,000 rows: 5 trees of depth 6, 4 features,
-// two columns 40 / 26; 8 of depth 6, 16 features 49 / 35; 9 of depth 3, 8 features, one column 33 / 26; 12 of depth 5, 15 features 50 / 39; irregular trees with
-// 15-wide leaves of depth 8, 4 features: 10 82 / 60, 16 93 / 70.  The other way: 9 of depth 8, 64 features 67 / 76; 8 of depth 6, 2 features, one column 24 / 31; 24 of
-// depth 7, 4 features 60 / 75; 7 irregular of depth 11, 110 features, 350,000 rows 68 / 82; 8 of depth 8, 10 features,
-// 13,000 rows 4.2 / 5.2.
+// their tile, and there one tree a wave is the better.  us, exchange / fours, at 700,000 rows: 5 trees of depth 6, 4
+// features, two columns 40 / 26; 8 of depth 6, 16 features 49 / 35; 9 of depth 3, 8 features, one column 33 / 26; 12 of
+// depth 5, 15 features 50 / 39; irregular trees with 15-wide leaves of depth 8, 4 features: 10 82 / 60, 16 93 / 70.  The
+// other way: 9 of depth 8, 64 features 67 / 76; 8 of depth 6, 2 features, one column 24 / 31; 24 of depth 7, 4 features
+// 60 / 75; 7 irregular of depth 11, 110 features, 350,000 rows 68 / 82; 8 of depth 8, 10 features, 13,000 rows 4.2 / 5.2.
 inline bool leaves_by_fours(const DevModel &m, int groups, int64_t n_rows)
 {
     const int64_t workgroups = (n_rows + PLAN_ROWS * groups - 1) / (PLAN_ROWS * groups);
