@@ -141,9 +141,14 @@ struct ColumnSums {
 // The rows of a walk kernel's workgroup from its waves' sums, which meet in LDS in the order of the waves.  A wave's run
 // of trees feeds consecutive columns (the trees are sorted by column), so the sum of (wave, column) has the slot wave +
 // column to itself and every wave fills its own slots, zeros for columns of its range that no tree feeds, behind one
-// barrier.  LDS: slots [WAVES + K - 1][ROWS], sums [K][ROWS], the waves' first and last columns.  A split launch stores
-// the sums as they come.  (All slots cleared by all threads first, and a split launch's rows stored by a thread each, was
-// two barriers and a serial loop more: 10,007 rows of 250 x depth 8, 5 columns, 17.8 us a call against 17.2.)
+// barrier.  LDS: slots [WAVES + K - 1][ROWS], sums [K][ROWS], the waves' first columns and how many follow.  A split launch
+// stores the sums as they come.  (All slots cleared by all threads first, and a split launch's rows stored by a thread each,
+// was two barriers and a serial loop more: 10,007 rows of 250 x depth 8, 5 columns, 17.8 us a call against 17.2.)
+// What bounds it is the round trips to LDS: a sum's slots are read together, of several columns only those of the waves
+// that feed the column, which a ballot finds.  One wave's slot after the other under a test of its own was 16 trips in turn
+// (calls, us: 1,021 rows of 2000 x depth 6, 10 columns 15.35 -> 14.72; 10,007 rows of 250 x depth 8, 5 columns 16.20 -> 15.38;
+// 103,069 rows of 300 irregular trees of depth 9 83.2 -> 80.8; 1M rows of 500 x depth 8 624 -> 621; 500,000 rows of
+// 2000 x depth 6, 10 columns 831 -> 824, where all 16 slots of every column would take 844).
 template <int NR, int WAVES, int COLUMNS>
 __device__ __forceinline__ void finish_columns(const DevModel &m, char *smem, int wave, int lane, bool any, const ColumnSums<NR, COLUMNS> &sums,
                                                int64_t row0, int64_t n_rows, float *scores, int32_t *labels)
@@ -154,13 +159,16 @@ __device__ __forceinline__ void finish_columns(const DevModel &m, char *smem, in
     double *sum = slot + static_cast<size_t>(WAVES + K - 1) * ROWS;
     int32_t *fed = reinterpret_cast<int32_t *>(sum + static_cast<size_t>(K) * ROWS);
     __syncthreads();
-    if (lane == 0) {
-        fed[2 * wave] = any ? sums.first : 1;
-        fed[2 * wave + 1] = any ? sums.column : 0;
-    }
-    if (any) {
-        const auto at = [&](int k, int r) -> double & { return slot[(wave + k) * ROWS + r * TILE + lane]; };
-        if constexpr (COLUMNS > 1) {
+    const auto at = [&](int k, int r) -> double & { return slot[(wave + k) * ROWS + r * TILE + lane]; };
+    if constexpr (COLUMNS == 1) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r) at(0, r) = sums.acc[r];
+    } else {
+        if (lane == 0) {
+            fed[2 * wave] = any ? sums.first : K;
+            fed[2 * wave + 1] = sums.column - sums.first;
+        }
+        if (any) {
             if (sums.column - sums.first > sums.n_done)
                 for (int k = sums.first; k < sums.column; ++k)
 #pragma unroll
@@ -171,17 +179,36 @@ __device__ __forceinline__ void finish_columns(const DevModel &m, char *smem, in
 #pragma unroll
                     for (int r = 0; r < NR; ++r) at(sums.done_column[k], r) = sums.done[k][r];
                 }
-        }
 #pragma unroll
-        for (int r = 0; r < NR; ++r) at(sums.column, r) = sums.acc[r];
+            for (int r = 0; r < NR; ++r) at(sums.column, r) = sums.acc[r];
+        }
     }
     __syncthreads();
     for (int i = threadIdx.x; i < K * ROWS; i += WAVES * TILE) {
         const int k = i / ROWS, li = i - k * ROWS;
         double s = 0.0;
+        if constexpr (COLUMNS == 1) {
+            double v[WAVES];
 #pragma unroll
-        for (int w = 0; w < WAVES; ++w)
-            if (fed[2 * w] <= k && k <= fed[2 * w + 1]) s += slot[(w + k) * ROWS + li];
+            for (int w = 0; w < WAVES; ++w) v[w] = slot[w * ROWS + li];
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) s += v[w];
+        } else {
+            // k is one for the wave: a lane per wave of the workgroup finds out which of them feed it
+            const int w = lane & (WAVES - 1);
+            uint32_t waves = static_cast<uint32_t>(__ballot(static_cast<uint32_t>(k - fed[2 * w]) <= static_cast<uint32_t>(fed[2 * w + 1]))) & ((1u << WAVES) - 1);
+            while (waves) {
+                double v[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    v[j] = 0.0;
+                    if (waves) v[j] = slot[(__builtin_ctz(waves) + uniform(k)) * ROWS + li];
+                    waves &= waves - 1;  // 0 stays 0
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s += v[j];
+            }
+        }
         if (m.n_splits == 1) sum[i] = s;
         else if (row0 + li < n_rows) m.partial[(static_cast<int64_t>(blockIdx.y) * m.split_rows + row0 + li) * K + k] = s;
     }
