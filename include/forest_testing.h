@@ -181,6 +181,7 @@ typedef struct forest_launch_t {
     int32_t lds_bytes;          /* per workgroup; walk and deep walk kernels, else 0 */
     int64_t workgroups;         /* of the largest range, per share */
     int32_t leaves_by_fours;    /* walk and deep walk kernels, leaf ids: 1 if each wave stores those of its own four trees */
+    int32_t last_rows_per_workgroup; /* of the workgroups that the largest range ends with; walk kernels may take smaller ones there */
 } forest_launch_t;
 int forest_launch(const forest *f, int64_t n_rows, int32_t leaves, forest_launch_t *out);
 int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out);

@@ -103,11 +103,10 @@ __device__ __forceinline__ void deep_top(uint32_t stage, const uint32_t (&xa)[NR
     for (int r = 0; r < NR; ++r) at[r] = idx[r] - stage;
 }
 
-// SHARED: two workgroups on a CU (64 vector registers per lane), or one.
-template <int NR, int MODE, int WP, bool SHARED>
-__global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep_kernel(DevModel m, const float *__restrict__ X,
-                                                                                       int64_t n_rows, float *scores,
-                                                                                       int32_t *labels, int32_t *leaf_out)
+// A workgroup's rows, from row0.
+template <int NR, int MODE, int WP>
+__device__ __forceinline__ void deep_rows(const DevModel m, const float *__restrict__ X, int64_t row0, int64_t n_rows, float *scores,
+                                          int32_t *labels, int32_t *leaf_out)
 {
     constexpr int ROWS = NR * TILE;
     constexpr bool FEW = MODE == DEEP_FEW_LEAVES, LEAVES = MODE == DEEP_LEAVES || FEW;
@@ -116,7 +115,6 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
     static_assert(MODE == DEEP_VECTOR || WP == 1, "scalar leaves");
     extern __shared__ __align__(1024) char smem[];
     const int lane = threadIdx.x & (TILE - 1), wave = uniform(threadIdx.x >> 6);
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * ROWS;
     const int F = m.n_features, T = m.n_trees;
     const uint32_t group_stride = static_cast<uint32_t>(F) * 256;
     const uint32_t stage = static_cast<uint32_t>(wave) * NODES_BYTES;
@@ -336,26 +334,48 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
     }
 }
 
-template <bool SHARED>
-KernelFn pick_mode(int groups, int mode, int width)
+// SHARED: two workgroups on a CU (64 vector registers per lane), or one.
+template <int NR, int LAST, int MODE, int WP, bool SHARED>
+__global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep_kernel(DevModel m, const float *__restrict__ X,
+                                                                                       int64_t n_rows, float *scores,
+                                                                                       int32_t *labels, int32_t *leaf_out)
 {
-    const bool two = groups > 1;
-    if (mode == DEEP_FEW_LEAVES) return two ? forest_deep_kernel<2, DEEP_FEW_LEAVES, 1, SHARED> : forest_deep_kernel<1, DEEP_FEW_LEAVES, 1, SHARED>;
-    if (mode == DEEP_LEAVES) return two ? forest_deep_kernel<2, DEEP_LEAVES, 1, SHARED> : forest_deep_kernel<1, DEEP_LEAVES, 1, SHARED>;
-    if (mode == DEEP_COLUMN) return two ? forest_deep_kernel<2, DEEP_COLUMN, 1, SHARED> : forest_deep_kernel<1, DEEP_COLUMN, 1, SHARED>;
-    if (mode == DEEP_COLUMNS) return two ? forest_deep_kernel<2, DEEP_COLUMNS, 1, SHARED> : forest_deep_kernel<1, DEEP_COLUMNS, 1, SHARED>;
+    bool after;
+    const int64_t row0 = first_row(m, NR, LAST, after);
+    if (after) deep_rows<LAST, MODE, WP>(m, X, row0, n_rows, scores, labels, leaf_out);
+    else deep_rows<NR, MODE, WP>(m, X, row0, n_rows, scores, labels, leaf_out);
+}
+
+template <int MODE, int WP, bool SHARED>
+KernelFn pick_groups(int groups, int last)
+{
+    if (groups == 1) return forest_deep_kernel<1, 1, MODE, WP, SHARED>;
+    if constexpr (MODE != DEEP_FEW_LEAVES)
+        if (last == 1) return forest_deep_kernel<2, 1, MODE, WP, SHARED>;
+    return forest_deep_kernel<2, 2, MODE, WP, SHARED>;
+}
+
+template <bool SHARED>
+KernelFn pick_mode(int groups, int last, int mode, int width)
+{
+    switch (mode) {
+        case DEEP_FEW_LEAVES: return pick_groups<DEEP_FEW_LEAVES, 1, SHARED>(groups, last);
+        case DEEP_LEAVES: return pick_groups<DEEP_LEAVES, 1, SHARED>(groups, last);
+        case DEEP_COLUMN: return pick_groups<DEEP_COLUMN, 1, SHARED>(groups, last);
+        case DEEP_COLUMNS: return pick_groups<DEEP_COLUMNS, 1, SHARED>(groups, last);
+    }
     switch (width) {
-        case 2: return two ? forest_deep_kernel<2, DEEP_VECTOR, 2, SHARED> : forest_deep_kernel<1, DEEP_VECTOR, 2, SHARED>;
-        case 4: return forest_deep_kernel<1, DEEP_VECTOR, 4, SHARED>;
-        case 8: return forest_deep_kernel<1, DEEP_VECTOR, 8, SHARED>;
-        case 12: return forest_deep_kernel<1, DEEP_VECTOR, 12, SHARED>;  // shared: 9-wide leaves, whose sums let two workgroups on a CU
-        default: return forest_deep_kernel<1, DEEP_VECTOR, 16, false>;   // 13 columns of 16 waves' sums take more than half a CU's LDS
+        case 2: return pick_groups<DEEP_VECTOR, 2, SHARED>(groups, last);
+        case 4: return forest_deep_kernel<1, 1, DEEP_VECTOR, 4, SHARED>;
+        case 8: return forest_deep_kernel<1, 1, DEEP_VECTOR, 8, SHARED>;
+        case 12: return forest_deep_kernel<1, 1, DEEP_VECTOR, 12, SHARED>;  // shared: 9-wide leaves, whose sums let two workgroups on a CU
+        default: return forest_deep_kernel<1, 1, DEEP_VECTOR, 16, false>;   // 13 columns of 16 waves' sums take more than half a CU's LDS
     }
 }
 
-KernelFn pick(int groups, int mode, int width, bool shared)
+KernelFn pick(int groups, int last, int mode, int width, bool shared)
 {
-    return shared ? pick_mode<true>(groups, mode, width) : pick_mode<false>(groups, mode, width);
+    return shared ? pick_mode<true>(groups, last, mode, width) : pick_mode<false>(groups, last, mode, width);
 }
 
 }  // namespace
@@ -365,15 +385,16 @@ hipError_t init_deep_kernels(size_t lds_limit)
     for (int mode : {DEEP_COLUMN, DEEP_COLUMNS, DEEP_VECTOR, DEEP_LEAVES, DEEP_FEW_LEAVES})
         for (int width : {2, 4, 8, 12, 16})
             for (int groups : {1, 2})
-                for (bool shared : {true, false}) {
-                    const void *fn = reinterpret_cast<const void *>(pick(groups, mode, width, shared));
-                    hipFuncAttributes attr;
-                    if (hipError_t e = hipFuncGetAttributes(&attr, fn); e != hipSuccess) return e;
-                    if (attr.sharedSizeBytes != 0) return hipErrorInvalidValue;  // the kernels address LDS from 0
-                    if (hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_limit));
-                        e != hipSuccess)
-                        return e;
-                }
+                for (int last = 1; last <= groups; ++last)
+                    for (bool shared : {true, false}) {
+                        const void *fn = reinterpret_cast<const void *>(pick(groups, last, mode, width, shared));
+                        hipFuncAttributes attr;
+                        if (hipError_t e = hipFuncGetAttributes(&attr, fn); e != hipSuccess) return e;
+                        if (attr.sharedSizeBytes != 0) return hipErrorInvalidValue;  // the kernels address LDS from 0
+                        if (hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_limit));
+                            e != hipSuccess)
+                            return e;
+                    }
     return hipSuccess;
 }
 
@@ -381,12 +402,14 @@ hipError_t launch_deep(const DevModel &m, int groups, const float *X, int64_t n_
                        int32_t *leaf_out, hipStream_t stream)
 {
     const bool shared = deep_shares_cu(m, groups, leaf_out == nullptr);
-    const int64_t n_blocks = (n_rows + TILE * groups - 1) / (TILE * groups);
-    if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid(static_cast<unsigned>(n_blocks), static_cast<unsigned>(m.n_splits));
-    const size_t lds = deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups, leaf_out == nullptr);
     const int mode = leaf_out ? leaves_by_fours(m, groups, n_rows) ? DEEP_FEW_LEAVES : DEEP_LEAVES : m.leaf_width > 1 ? DEEP_VECTOR : m.n_outputs == 1 ? DEEP_COLUMN : DEEP_COLUMNS;
-    hipLaunchKernelGGL(pick(groups, mode, deep_width(m.leaf_width), shared), grid, dim3(DEEP_WAVES * TILE), lds, stream, m, X,
+    const TailPlan t = ends_in_smaller(m, FOREST_KERNEL_DEEP, groups, n_rows, leaf_out == nullptr) ? choose_tail(groups, n_rows, m.n_splits) : whole(groups, n_rows);
+    if (t.full + t.after > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<unsigned>(t.full + t.after), static_cast<unsigned>(m.n_splits));
+    const size_t lds = deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups, leaf_out == nullptr);
+    DevModel launched = m;
+    launched.full_workgroups = t.full;
+    hipLaunchKernelGGL(pick(groups, t.groups, mode, deep_width(m.leaf_width), shared), grid, dim3(DEEP_WAVES * TILE), lds, stream, launched, X,
                        n_rows, scores, labels, leaf_out);
     return hipGetLastError();
 }

@@ -108,18 +108,16 @@ __device__ __forceinline__ void walk_trees(uint32_t tree_at, uint32_t xa, const 
 // column), or the leaf ids of every tree (a kernel of its own, in two forms).
 enum { WALK_COLUMN = 0, WALK_COLUMNS = 1, WALK_LEAVES = 2, WALK_FEW_LEAVES = 3 };
 
+// The sums of a workgroup's rows, from row0.
 template <int D, int NR, int MODE>
-__global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevModel m, const float *__restrict__ X,
-                                                                          int64_t n_rows, float *scores,
-                                                                          int32_t *labels, int32_t *)
+__device__ __forceinline__ void walk_rows(const DevModel m, const float *__restrict__ X, int64_t row0, int64_t n_rows, float *scores,
+                                          int32_t *labels)
 {
     constexpr int TREE_BYTES = 8 << D, STAGE_TREES = walk_stage_trees(D), STAGE_BYTES = TREE_BYTES * STAGE_TREES;
     constexpr int PIECES = STAGE_BYTES / 1024;  // 16 bytes per lane each
-    constexpr int ROWS = NR * TILE;
     static_assert(STAGE_BYTES % 1024 == 0, "whole 16-byte pieces per lane");
     extern __shared__ __align__(1024) char smem[];
     const int lane = threadIdx.x & (TILE - 1), wave = uniform(threadIdx.x >> 6);
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * ROWS;
     const uint32_t stride = static_cast<uint32_t>(m.walk.groups) * 256, xbase = WALK_WAVES * STAGE_BYTES;
     const uint32_t mine = static_cast<uint32_t>(wave) * STAGE_BYTES;
 
@@ -192,6 +190,17 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
     finish_columns<NR, WALK_WAVES>(m, smem, wave, lane, s_begin < s_end, sums, row0, n_rows, scores, labels);
 }
 
+template <int D, int NR, int LAST, int MODE>
+__global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevModel m, const float *__restrict__ X,
+                                                                          int64_t n_rows, float *scores,
+                                                                          int32_t *labels, int32_t *)
+{
+    bool after;
+    const int64_t row0 = first_row(m, NR, LAST, after);
+    if (after) walk_rows<D, LAST, MODE>(m, X, row0, n_rows, scores, labels);
+    else walk_rows<D, NR, MODE>(m, X, row0, n_rows, scores, labels);
+}
+
 // The leaf ids of every tree, caller's order.  A row's ids are neighbours in the output and a lane holds those of few
 // trees, so the waves take four trees each, side by side, and exchange the ids through their stages before they leave: a
 // store then writes whole 256-byte runs of four rows.  Straight from the lanes, 16 bytes at the pitch of a row, 100,003
@@ -203,19 +212,15 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
 // workgroups for 256 CUs; two shares of the trees, or fewer rows per workgroup, fill the tile more often and took 54.7 and
 // 50.4.
 template <int D, int NR, bool FEW>
-__global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kernel(DevModel m, const float *__restrict__ X,
-                                                                                 int64_t n_rows, float *, int32_t *,
-                                                                                 int32_t *leaf_out)
+__device__ __forceinline__ void walk_leaves(const DevModel m, const float *__restrict__ X, int64_t row0, int64_t n_rows, int32_t *leaf_out)
 {
     constexpr int TREE_BYTES = 8 << D, STEP = walk_stage_trees(D) < 4 ? walk_stage_trees(D) : 4;  // trees copied at a time
     constexpr int STEP_BYTES = TREE_BYTES * STEP, STAGE_BYTES = walk_stage_bytes(D);
     constexpr int PIECES = (STEP_BYTES + 1023) / 1024;
-    constexpr int ROWS = NR * TILE;
     constexpr int EXCHANGE = NR * TILE * 8 <= STAGE_BYTES ? NR : STAGE_BYTES / (TILE * 8);  // row groups that a stage holds the ids of
     static_assert(NR % EXCHANGE == 0, "whole exchanges");
     extern __shared__ __align__(1024) char smem[];
     const int lane = threadIdx.x & (TILE - 1), wave = uniform(threadIdx.x >> 6);
-    const int64_t row0 = static_cast<int64_t>(blockIdx.x) * ROWS;
     const int T = m.n_trees;
     const uint32_t stride = static_cast<uint32_t>(m.walk.groups) * 256, xbase = WALK_WAVES * STAGE_BYTES;
     const uint32_t mine = static_cast<uint32_t>(wave) * STAGE_BYTES;
@@ -338,38 +343,62 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kerne
     }
 }
 
-template <int D, int MODE>
-KernelFn pick_groups(int groups)
+template <int D, int NR, int LAST, bool FEW>
+__global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kernel(DevModel m, const float *__restrict__ X,
+                                                                                 int64_t n_rows, float *, int32_t *,
+                                                                                 int32_t *leaf_out)
 {
-    constexpr bool FEW = MODE == WALK_FEW_LEAVES;
-    if constexpr (MODE == WALK_LEAVES || FEW)
-        return groups == 1 ? forest_walk_leaves_kernel<D, 1, FEW> : groups == 2 ? forest_walk_leaves_kernel<D, 2, FEW> : forest_walk_leaves_kernel<D, 4, FEW>;
-    else switch (groups) {
-        case 1: return forest_walk_kernel<D, 1, MODE>;
-        case 2: return forest_walk_kernel<D, 2, MODE>;
-        default: return forest_walk_kernel<D, MODE == WALK_COLUMNS ? 2 : 4, MODE>;  // walk_max_groups
+    if constexpr (NR == LAST) {
+        walk_leaves<D, NR, FEW>(m, X, static_cast<int64_t>(blockIdx.x) * (NR * TILE), n_rows, leaf_out);
+    } else {
+        bool after;
+        const int64_t row0 = first_row(m, NR, LAST, after);
+        if (after) walk_leaves<D, LAST, FEW>(m, X, row0, n_rows, leaf_out);
+        else walk_leaves<D, NR, FEW>(m, X, row0, n_rows, leaf_out);
+    }
+}
+
+template <int D, int NR, int LAST, int MODE>
+KernelFn kernel()
+{
+    if constexpr (MODE == WALK_LEAVES) return forest_walk_leaves_kernel<D, NR, LAST, false>;
+    else if constexpr (MODE == WALK_FEW_LEAVES) return forest_walk_leaves_kernel<D, NR, NR, true>;
+    else return forest_walk_kernel<D, NR, LAST, MODE>;
+}
+
+// last: as groups where a launch has workgroups of one size.  Only leaf ids have a kernel of their own for that (0.5 %).
+template <int D, int MODE>
+KernelFn pick_groups(int groups, int last)
+{
+    constexpr int MOST = MODE == WALK_COLUMNS ? 2 : 4;  // walk_max_groups
+    if constexpr (MODE == WALK_LEAVES)
+        if (last == groups && groups > 1) return groups == 2 ? kernel<D, 2, 2, MODE>() : kernel<D, MOST, MOST, MODE>();
+    switch (groups) {
+        case 1: return kernel<D, 1, 1, MODE>();
+        case 2: return kernel<D, 2, 1, MODE>();
+        default: return last == 1 ? kernel<D, MOST, 1, MODE>() : kernel<D, MOST, MOST / 2, MODE>();
     }
 }
 
 template <int MODE>
-KernelFn pick_depth(int depth, int groups)
+KernelFn pick_depth(int depth, int groups, int last)
 {
     switch (depth) {
-        case 3: return pick_groups<3, MODE>(groups);
-        case 4: return pick_groups<4, MODE>(groups);
-        case 5: return pick_groups<5, MODE>(groups);
-        case 6: return pick_groups<6, MODE>(groups);
-        case 7: return pick_groups<7, MODE>(groups);
-        default: return pick_groups<8, MODE>(groups);
+        case 3: return pick_groups<3, MODE>(groups, last);
+        case 4: return pick_groups<4, MODE>(groups, last);
+        case 5: return pick_groups<5, MODE>(groups, last);
+        case 6: return pick_groups<6, MODE>(groups, last);
+        case 7: return pick_groups<7, MODE>(groups, last);
+        default: return pick_groups<8, MODE>(groups, last);
     }
 }
 
-KernelFn pick(int depth, int groups, int mode)
+KernelFn pick(int depth, int groups, int last, int mode)
 {
-    if (mode == WALK_COLUMN) return pick_depth<WALK_COLUMN>(depth, groups);
-    if (mode == WALK_COLUMNS) return pick_depth<WALK_COLUMNS>(depth, groups);
-    if (mode == WALK_LEAVES) return pick_depth<WALK_LEAVES>(depth, groups);
-    return pick_depth<WALK_FEW_LEAVES>(depth, groups);
+    if (mode == WALK_COLUMN) return pick_depth<WALK_COLUMN>(depth, groups, last);
+    if (mode == WALK_COLUMNS) return pick_depth<WALK_COLUMNS>(depth, groups, last);
+    if (mode == WALK_LEAVES) return pick_depth<WALK_LEAVES>(depth, groups, last);
+    return pick_depth<WALK_FEW_LEAVES>(depth, groups, last);
 }
 
 }  // namespace
@@ -378,27 +407,30 @@ hipError_t init_walk_kernels(size_t lds_limit)
 {
     for (int mode : {WALK_COLUMN, WALK_COLUMNS, WALK_LEAVES, WALK_FEW_LEAVES})
         for (int depth = WALK_MIN_DEPTH; depth <= WALK_MAX_DEPTH; ++depth)
-            for (int groups = 1; groups <= walk_max_groups(mode == WALK_COLUMNS ? 2 : 1); groups *= 2) {
-                const void *fn = reinterpret_cast<const void *>(pick(depth, groups, mode));
-                hipFuncAttributes attr;
-                if (hipError_t e = hipFuncGetAttributes(&attr, fn); e != hipSuccess) return e;
-                if (attr.sharedSizeBytes != 0) return hipErrorInvalidValue;  // the kernels address LDS from 0
-                if (hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_limit));
-                    e != hipSuccess)
-                    return e;
-            }
+            for (int groups = 1; groups <= walk_max_groups(mode == WALK_COLUMNS ? 2 : 1); groups *= 2)
+                for (int last = 1; last <= groups; last *= 2) {
+                    const void *fn = reinterpret_cast<const void *>(pick(depth, groups, last, mode));
+                    hipFuncAttributes attr;
+                    if (hipError_t e = hipFuncGetAttributes(&attr, fn); e != hipSuccess) return e;
+                    if (attr.sharedSizeBytes != 0) return hipErrorInvalidValue;  // the kernels address LDS from 0
+                    if (hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_limit));
+                        e != hipSuccess)
+                        return e;
+                }
     return hipSuccess;
 }
 
 hipError_t launch_walk(const DevModel &m, int groups, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                        int32_t *leaf_out, hipStream_t stream)
 {
-    const int64_t n_blocks = (n_rows + TILE * groups - 1) / (TILE * groups);
-    if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid(static_cast<unsigned>(n_blocks), static_cast<unsigned>(m.n_splits));
-    const size_t lds = walk_lds_bytes(m.walk.depth, m.n_features, m.n_outputs, m.walk.groups);
     const int mode = leaf_out ? leaves_by_fours(m, groups, n_rows) ? WALK_FEW_LEAVES : WALK_LEAVES : m.n_outputs == 1 ? WALK_COLUMN : WALK_COLUMNS;
-    hipLaunchKernelGGL(pick(m.walk.depth, groups, mode), grid, dim3(WALK_WAVES * TILE), lds, stream, m, X,
+    const TailPlan t = ends_in_smaller(m, FOREST_KERNEL_WALK, groups, n_rows, leaf_out == nullptr) ? choose_tail(groups, n_rows, m.n_splits) : whole(groups, n_rows);
+    if (t.full + t.after > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid(static_cast<unsigned>(t.full + t.after), static_cast<unsigned>(m.n_splits));
+    const size_t lds = walk_lds_bytes(m.walk.depth, m.n_features, m.n_outputs, m.walk.groups);
+    DevModel launched = m;
+    launched.full_workgroups = t.full;
+    hipLaunchKernelGGL(pick(m.walk.depth, groups, t.groups, mode), grid, dim3(WALK_WAVES * TILE), lds, stream, launched, X,
                        n_rows, scores, labels, leaf_out);
     return hipGetLastError();
 }

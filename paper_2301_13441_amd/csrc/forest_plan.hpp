@@ -79,6 +79,7 @@ struct DevModel {
     double *partial;
     int64_t partial_capacity;  // doubles available at `partial`
     int64_t n_entries;         // entries of the split program, all trees (padding included)
+    int64_t full_workgroups;  // walk kernels: workgroups before the smaller ones that the launch ends with (choose_tail); set per launch
     // Rank families, split launches: the rank tiles ([tile][rank register][lane] packed f16 pairs)
     // are computed once per row tile by forest_rank_tiles_kernel instead of by every workgroup.
     uint32_t *rank_tiles;
@@ -328,6 +329,41 @@ inline int choose_groups(const DevModel &m, int groups, int64_t n_rows, int n_sp
     return groups >= 2 && workgroups(2) >= (m.n_trees >= 100 ? CUS / 2 : CUS) ? 2 : 1;
 }
 
+// The workgroups that a launch ends with.  Workgroups of one size come to every CU as often but for the rest of a division
+// by the CUs, and the CUs that get one of that rest finish a whole workgroup later than the others: boosted trees of depth
+// 9, 103,069 rows, are 806 workgroups of 128 rows, three for every CU and a fourth for 38 of them, 81 us where 768 take 64.
+// So the rows of the rest go in workgroups of fewer row groups, those that leave the CU with most of them fewest row groups,
+// if these are half of a whole workgroup's at most (a workgroup of the rest copies the trees to LDS for fewer rows: leaf ids
+// of 100,003 rows, whose rest is 135 workgroups of four groups, 540 of one group: 42.1 -> 46.9).  us a call, whole / smaller
+// at the end: 1M rows of 500 x depth 8, 28 features (15.3 rounds) 617 / 598; 1M of 1000 x depth 6 753 / 731; 500,000 of 2000
+// x depth 6, 10 columns 822 / 805; the 103,069 rows 80.7 / 73.2; 80,896 rows (1.2 rounds) of 500 x depth 8 86.6 / 60.7, of
+// ten such trees 7.31 / 6.37, leaf ids of 200 x depth 6 41.5 / 32.4; 40,000 rows of 30 irregular trees 9.2 / 8.5.
+struct TailPlan {
+    int64_t full;    // workgroups of the plan's row groups
+    int64_t after;   // workgroups after them
+    int32_t groups;  // row groups of those
+};
+
+inline TailPlan whole(int groups, int64_t n_rows)
+{
+    return TailPlan{(n_rows + PLAN_ROWS * groups - 1) / (PLAN_ROWS * groups), 0, groups};
+}
+
+inline TailPlan choose_tail(int groups, int64_t n_rows, int n_splits)
+{
+    TailPlan t = whole(groups, n_rows);
+    const int64_t n = t.full, rest = n % CUS;
+    if (n_splits > 1 || n < CUS || rest == 0) return t;
+    int64_t best = groups;
+    for (int g = groups / 2; g >= 1; g /= 2)
+        if (const int64_t most = (rest * (groups / g) + CUS - 1) / CUS * g; 2 * most <= groups && most < best) {
+            best = most;
+            const int64_t rows = n_rows - (n - rest) * PLAN_ROWS * groups;
+            t = TailPlan{n - rest, (rows + PLAN_ROWS * g - 1) / (PLAN_ROWS * g), g};
+        }
+    return t;
+}
+
 // Whether two workgroups fit a CU.
 inline bool deep_shares_cu(const DevModel &m, int groups, bool sums)
 {
@@ -355,6 +391,19 @@ inline bool leaves_by_fours(const DevModel &m, int groups, int64_t n_rows)
     if (groups == 2) return T <= 6 && F <= 32 && workgroups >= 1500;
     if (T == 2) return F <= 64 && workgroups >= 512;
     return F <= 40 && (T <= 6 || (F >= 4 && T <= 20)) && workgroups >= 2000;
+}
+
+// Whether a launch may end in smaller workgroups.  Not leaf ids by fours, whose few trees are walked in less time than a
+// workgroup takes to begin and end.  Where a CU holds one workgroup of the deep kernel, the form with both sizes walks 1.3 %
+// slower (4M rows of 128 x depth 12, 256 features, 122 rounds of the CUs: 2811 / 2853 us whole / smaller at the end; 20 rounds
+// 491 / 490, 5 140 / 135, one 47.0 / 39.7).
+constexpr int64_t TAIL_MAX_ROUNDS = 20;
+
+inline bool ends_in_smaller(const DevModel &m, int kernel, int groups, int64_t n_rows, bool sums)
+{
+    if (!sums && leaves_by_fours(m, groups, n_rows)) return false;
+    if (kernel == FOREST_KERNEL_WALK) return true;
+    return kernel == FOREST_KERNEL_DEEP && (deep_shares_cu(m, groups, sums) || n_rows < TAIL_MAX_ROUNDS * CUS * PLAN_ROWS * groups);
 }
 
 // One lane per (row, tree): the smallest batches of the walk kernels' models (forest_kernels_split.hip).
@@ -509,6 +558,14 @@ inline forest_launch_t launch_shape(const DevModel &m, const LaunchPlan &p, int6
     s.launches = static_cast<int32_t>((n_rows + MAX_LAUNCH_ROWS - 1) / MAX_LAUNCH_ROWS);
     const int64_t rows = n_rows < MAX_LAUNCH_ROWS ? n_rows : MAX_LAUNCH_ROWS;
     s.workgroups = (rows + s.rows_per_workgroup - 1) / s.rows_per_workgroup;
+    s.last_rows_per_workgroup = s.rows_per_workgroup;
+    if (ends_in_smaller(m, p.kernel, p.groups, rows, sums)) {
+        const TailPlan t = choose_tail(p.groups, rows, p.splits);
+        if (t.after > 0) {
+            s.workgroups = t.full + t.after;
+            s.last_rows_per_workgroup = PLAN_ROWS * t.groups;
+        }
+    }
     return s;
 }
 

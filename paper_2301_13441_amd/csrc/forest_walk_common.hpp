@@ -106,6 +106,14 @@ __device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t 
     }
 }
 
+// The first row of a workgroup: the first workgroups of a launch own groups x 64 rows, those after them last x 64 (choose_tail, forest_plan.hpp).
+__device__ __forceinline__ int64_t first_row(const DevModel &m, int groups, int last, bool &after)
+{
+    const int64_t block = blockIdx.x;
+    after = groups != last && block >= m.full_workgroups;
+    return after ? (m.full_workgroups * groups + (block - m.full_workgroups) * last) * TILE : block * groups * TILE;
+}
+
 // The column sums of one wave's run of trees for NR row groups: the running column's, those of the columns before it.
 template <int NR, int COLUMNS>
 struct ColumnSums {

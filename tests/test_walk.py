@@ -186,3 +186,39 @@ def test_columns_without_trees_between_columns_with_some(depth, trees, rows):
     assert s["kernel"] == ("walk" if depth < 9 else "deep") and s["rows_per_workgroup"] == (64 if rows == 9001 else 128), s
     assert s["shares"] == (1 if trees == 41 or (trees, depth) == (300, 3) else 3), s
     _check(f, _special_rows(rng.standard_normal((rows, 9)).astype(np.float32), f, rng))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what,rows,groups,last", [
+    ("one", 65536 + 61 * 256 + 3, 4, 1), ("one", 65536 + 64 * 256, 4, 1), ("one", 65536 + 64 * 256 + 1, 4, 2),
+    ("one", 65536 + 128 * 256 - 255, 4, 2), ("one", 65536 + 128 * 256 + 1, 4, 4), ("depth8", 65536 + 9 * 256 + 65, 4, 1),
+    ("depth8", 65536 + 70 * 256 + 129, 4, 2), ("columns", 32768 + 50 * 128 + 1, 2, 1), ("columns", 32768 + 128 * 128 + 1, 2, 2),
+    ("deep", 32768 + 7, 2, 1), ("deep", 3 * 32768 + 127 * 128 + 65, 2, 1), ("deep_alone", 32768 + 3 * 128 + 70, 2, 1),
+    ("deep_alone", 21 * 32768 + 3 * 128, 2, 2), ("vector", 32768 + 40 * 128 + 64, 2, 1)])
+def test_launches_that_end_in_smaller_workgroups(what, rows, groups, last):
+    """The rest of a division by the CUs in workgroups of fewer rows: both smaller sizes, the first and last rests that
+    take them, ragged ends, and leaf ids, which have the same rows per workgroup."""
+    import torch
+    from paper_2301_13441_amd import binding
+    rng = np.random.default_rng(rows)
+    f = {"one": lambda: _forest(5, 18, 5, 9), "depth8": lambda: _forest(6, 18, 8, 7), "columns": lambda: _forest(7, 31, 6, 9, outputs=4),
+         "deep": lambda: wl.random_forest(8, n_trees=40, n_features=9, max_depth=10, stop_prob=0.25, aggregate=wl.AGG_SUM),
+         "deep_alone": lambda: wl.random_forest(9, n_trees=33, n_features=200, max_depth=9, stop_prob=0.25, aggregate=wl.AGG_SUM),
+         "vector": lambda: wl.random_forest(10, n_trees=35, n_features=9, max_depth=9, stop_prob=0.25, n_outputs=2, leaf_width=2,
+                                            aggregate=wl.AGG_MEAN)}[what]()
+    model = binding.forest_load_form(f, "walk")
+    try:
+        for leaves in (False, True):
+            s = binding.forest_packed_launch(f, rows, leaves, form="walk")
+            assert (s["rows_per_workgroup"], s["last_rows_per_workgroup"]) == (64 * groups, 64 * last) and s["shares"] == 1, s
+        X = _special_rows(rng.standard_normal((rows, f.n_features)).astype(np.float32), f, rng)
+        # the whole workgroups' last rows and everything after them, and the first rows
+        pick = np.unique(np.concatenate([np.arange(300), np.arange(max(0, rows - 256 * 200), rows)]))
+        ref = oracle.predict(f, X[pick], want_leaves=True, n_threads=8)
+        xd, at = torch.from_numpy(X).cuda(), torch.from_numpy(pick).cuda()
+        scores, labels = model.predict(xd)
+        np.testing.assert_allclose(scores[at].cpu().numpy(), ref.scores, rtol=1e-5, atol=1e-6)
+        np.testing.assert_array_equal(labels[at].cpu().numpy(), ref.labels)
+        np.testing.assert_array_equal(model.predict_leaves(xd)[at].cpu().numpy(), ref.leaf_node_id)
+    finally:
+        model.close()
