@@ -286,22 +286,13 @@ __device__ __forceinline__ void deep_rows(const DevModel m, const float *__restr
                     }
                 }
             }
-            const auto store = [&](int64_t row, int begin, int n, Vec4 v) {
-                int32_t *dst = leaf_out + row * T + begin;
-                if (n == 4 && begin + 4 <= T) {
-                    *reinterpret_cast<Int4 *>(dst) = Int4{{static_cast<int32_t>(v[0]), static_cast<int32_t>(v[1]), static_cast<int32_t>(v[2]), static_cast<int32_t>(v[3])}};
-                } else {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j)
-                        if (j < n && begin + j < T) dst[j] = static_cast<int32_t>(v[j]);
-                }
-            };
+            const IdStore store{leaf_out + row0 * T, T, !FEW && ids_go_through(T)};
             if (FEW || T <= 4) {  // straight from the lanes
 #pragma unroll
                 for (int r = 0; r < NR; ++r) {
                     const int64_t row = row0 + r * TILE + lane;
                     if (row >= n_rows || own <= 0) continue;
-                    if (FEW) store(row, first, 4, Vec4{ids[r][0], ids[r][1], ids[r][2], ids[r][3]});
+                    if (FEW) store(r * TILE + lane, first, 4, Vec4{ids[r][0], ids[r][1], ids[r][2], ids[r][3]});
                     else leaf_out[row * T + first] = static_cast<int32_t>(ids[r][0]);
                 }
                 return;
@@ -316,8 +307,7 @@ __device__ __forceinline__ void deep_rows(const DevModel m, const float *__restr
             for (int r = 0; r < NR; ++r) {
                 const int li = wave * (TILE / DEEP_WAVES) + lane / DEEP_WAVES;
                 const Vec4 id = lds_read<Vec4>(r * DEEP_WAVES * NODES_BYTES + from * NODES_BYTES + ((li + 4 * from) & (TILE - 1)) * 16);
-                const int64_t row = row0 + r * TILE + li;
-                if (row < n_rows) store(row, k * ROUND + from * n, n, id);
+                if (row0 + r * TILE + li < n_rows) store(r * TILE + li, k * ROUND + from * n, n, id);
             }
             __syncthreads();
         }

@@ -204,8 +204,8 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
 // The leaf ids of every tree, caller's order.  A row's ids are neighbours in the output and a lane holds those of few
 // trees, so the waves take four trees each, side by side, and exchange the ids through their stages before they leave: a
 // store then writes whole 256-byte runs of four rows.  Straight from the lanes, 16 bytes at the pitch of a row, 100,003
-// rows of 200 x depth 6 took 65.6 us, three quarters of them for the stores; so 42.5, of which the stores are 10 (250,000
-// rows of 200 x depth 3: 235 -> 65; 66,000 of 700 x depth 3: 310 -> 98).  Ids of these trees, which have 511 nodes at
+// rows of 200 x depth 6 took 65.6 us, three quarters of them for the stores; so 42.5 (250,000
+// rows of 200 x depth 3: 235 -> 65; 66,000 of 700 x depth 3: 310 -> 98), and 35.3 since they go past the L2 (IdStore).  Ids of these trees, which have 511 nodes at
 // most, fit 16 bits.  What is left of the trees after the last whole round is dealt evenly; waves that get none walk none
 // (one tree of depth 7, 3 features, 60,000 rows: 4.6 us a call with 16 waves on it, 3.8).  FEW: of few trees
 // (leaves_by_fours, forest_plan.hpp) a wave takes four and stores their ids from its lanes.  Bound: the walk, with 391
@@ -299,22 +299,13 @@ __device__ __forceinline__ void walk_leaves(const DevModel m, const float *__res
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             if (!FEW && j == n - 1) keep(j);
-        const auto store = [&](int64_t row, int begin, int n, Vec4 id) {
-            int32_t *dst = leaf_out + row * T + begin;
-            if (n == 4 && begin + 4 <= T) {
-                *reinterpret_cast<Int4 *>(dst) = Int4{{static_cast<int32_t>(id[0]), static_cast<int32_t>(id[1]), static_cast<int32_t>(id[2]), static_cast<int32_t>(id[3])}};
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (j < n && begin + j < T) dst[j] = static_cast<int32_t>(id[j]);
-            }
-        };
+        const IdStore store{leaf_out + row0 * T, T, !FEW && ids_go_through(T)};
         if (FEW || T <= 4) {  // straight from the lanes
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
                 const int64_t row = row0 + r * TILE + lane;
                 if (row >= n_rows || first >= T) continue;
-                if constexpr (FEW) store(row, first, n, Vec4{ids[r][0], ids[r][1], ids[r][2], ids[r][3]});
+                if constexpr (FEW) store(r * TILE + lane, first, 4, Vec4{ids[r][0], ids[r][1], ids[r][2], ids[r][3]});
                 else leaf_out[row * T + first] = static_cast<int32_t>(ids[r][0]);
             }
             return;
@@ -335,8 +326,7 @@ __device__ __forceinline__ void walk_leaves(const DevModel m, const float *__res
             for (int i = 0; i < EXCHANGE; ++i) {
                 const int li = (wave * EXCHANGE + i) * (TILE / WALK_WAVES) + lane / WALK_WAVES;  // a row of the exchange
                 const Vec2 id = lds_read<Vec2>(from * STAGE_BYTES + ((li + 4 * from) & (PLACES - 1)) * 8);
-                const int64_t row = row0 + g * TILE + li;
-                if (row < n_rows) store(row, begin, n, Vec4{id.x & 0xffff, id.x >> 16, id.y & 0xffff, id.y >> 16});
+                if (row0 + g * TILE + li < n_rows) store(g * TILE + li, begin, n, Vec4{id.x & 0xffff, id.x >> 16, id.y & 0xffff, id.y >> 16});
             }
         }
         __syncthreads();

@@ -461,6 +461,18 @@ inline bool takes_point(const DevModel &m, const Workspace *ws, int64_t n_rows, 
     return choose_walk_splits(m, ws, n_rows, sums) < choose_walk_splits(m, &ample, n_rows, sums);
 }
 
+// Whether the leaf ids of T trees are written past the L2, where their lines would wait to be put out by others and go to
+// memory in no order of use.  A row's ids are then pieces of 16 aligned bytes; with other counts pieces share lines and a line
+// goes to memory once for each (us, kept in the L2 / past it: 50 trees, 262,144 rows 36 / 43, 75 trees 48 / 61, 101 59 / 62; 52
+// trees 34.2 / 32.8, 128 55.4 / 52.7, 200 trees, 100,003 rows 39.1 / 36).  The stores count the workgroup's ids in 32 bits.
+#if defined(__HIPCC__)
+__host__ __device__
+#endif
+inline bool ids_go_through(int T)
+{
+    return T % 4 == 0 && T <= 1 << 20;
+}
+
 // Rows of one launch at most.  HIP takes fewer than 2^32 threads per grid axis, and the walk kernels spend
 // 1024 threads on 64 rows, the LDS rank kernel up to 768 on 128: a longer batch goes in ranges of this many
 // rows, one launch each.

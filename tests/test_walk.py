@@ -222,3 +222,23 @@ def test_launches_that_end_in_smaller_workgroups(what, rows, groups, last):
         np.testing.assert_array_equal(model.predict_leaves(xd)[at].cpu().numpy(), ref.leaf_node_id)
     finally:
         model.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [9001, 40_001, 70_003])
+@pytest.mark.parametrize("depth,trees", [(4, 12), (6, 20), (6, 68), (3, 76), (8, 96), (5, 128), (7, 204), (9, 12), (10, 36), (9, 68), (10, 128), (9, 133)])
+def test_leaf_ids_past_the_l2(depth, trees, rows):
+    """Tree counts that are multiples of four, whose ids go past the L2 by fours and by ones, and are kept there by twos and
+    threes; one that is not; both walk kernels, with shares and without, whole workgroups and smaller ones at the end."""
+    import torch
+    from paper_2301_13441_amd import binding
+    rng = np.random.default_rng(depth * trees)
+    f = _forest(depth + trees, trees, depth, 9) if depth < 9 else \
+        wl.random_forest(depth + trees, n_trees=trees, n_features=9, max_depth=depth, stop_prob=0.3, aggregate=wl.AGG_SUM)
+    X = rng.standard_normal((rows, 9)).astype(np.float32)
+    model = binding.forest_load_form(f, "walk")
+    try:
+        got = model.predict_leaves(torch.from_numpy(X).cuda()).cpu().numpy()
+    finally:
+        model.close()
+    np.testing.assert_array_equal(got, oracle.predict(f, X, want_leaves=True, n_threads=8).leaf_node_id)
