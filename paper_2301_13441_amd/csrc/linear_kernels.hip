@@ -35,14 +35,15 @@ constexpr int STRIDE = CHUNK + 4;  // row pitch of the LDS tile in floats: 16-by
                                    // 8 lanes of a 128-bit read phase fall into 8 different bank groups
 
 // Label, transform and store of one row whose K raw values (bias included) are acc[0..K).
-// A score to its place.  With one output per row the lanes of a wave write one contiguous piece
-// and nothing reads it again here: a non-temporal store (l2: 5 % faster).  With several outputs
-// a lane's values are a short run of its own, and stores that skip the cache would each become
-// a partial write to memory (l3: twice as slow), so those go the ordinary way.
+// A score to its place.  Scores and labels go past the L2 (device scope): beside X, of which every line is new, written lines
+// that wait in the L2 leave it in no order, and every write there costs the reads of X more than its bytes (2M x 128, 10
+// classes: 194.4 us a call, 169 with no scores written, 189.1 so; 8M x 28, sigmoid and label 156.4 -> 149.2; 8M x 20, 3
+// classes 122.9 -> 118; 4M x 90, one output 211.6 -> 209.8; non-temporal stores took as long as ordinary ones or longer).  With
+// several outputs a lane's own values are a short run of its own, each would be a partial write, and they go the ordinary way.
 template <int KP>
 __device__ __forceinline__ void store_score(float v, float *p)
 {
-    if (KP == 1) __builtin_nontemporal_store(v, p);
+    if (KP == 1) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     else *p = v;
 }
 template <int KP>
@@ -61,8 +62,7 @@ __device__ __forceinline__ void finish_linear_row(const LinDev &m, double (&acc)
     if (labels) {
         int lab = best_k;
         if (K == 1) lab = (m.transform == LINEAR_TRANSFORM_SIGMOID) ? (best > 0.0) : (best > 0.5);
-        if (KP == 1) __builtin_nontemporal_store(lab, &labels[row]);  // as the scores below
-        else labels[row] = lab;
+        __hip_atomic_store(&labels[row], lab, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (!scores) return;
     float *dst = scores + row * K;
@@ -93,7 +93,7 @@ __device__ __forceinline__ void finish_linear_row(const LinDev &m, double (&acc)
 // The rows of a wave's tile, one per lane.  With several outputs their scores are one contiguous piece of
 // the result: the lanes leave theirs in `out` (LDS of the wave, 64 K floats that nothing else needs any more)
 // and the wave copies the piece, 16 bytes per lane.  (A lane storing its own K values touches a line per
-// lane and value: 2M x 128, 10 classes: 216 us so, 195 with the copy; no difference with non-temporal stores.)
+// lane and value: 2M x 128, 10 classes: 216 us so, 195 with the copy.)
 template <int KP>
 __device__ __forceinline__ void finish_linear_tile(const LinDev &m, double (&acc)[KP], float *out, int64_t row0, int rows_here,
                                                    int lane, float *scores, int32_t *labels)
@@ -106,10 +106,13 @@ __device__ __forceinline__ void finish_linear_tile(const LinDev &m, double (&acc
     finish_linear_row<KP>(m, acc, lane, scores ? out : nullptr, labels && lane < rows_here ? labels + row0 : nullptr);
     if (!scores) return;
     float *dst = scores + row0 * K;
-    typedef float F4 __attribute__((ext_vector_type(4), aligned(4)));
+    typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+    typedef uint32_t LooseU4 __attribute__((ext_vector_type(4), aligned(4)));
+    const auto piece = __builtin_amdgcn_make_buffer_rsrc(dst, 0, n * 4, 0x00027000);
     for (int i = lane * 4; i < n; i += LANES * 4) {
         if (i + 4 <= n) {
-            *reinterpret_cast<F4 *>(dst + i) = *reinterpret_cast<const F4 *>(out + i);
+            const LooseU4 v = *reinterpret_cast<const LooseU4 *>(out + i);
+            __builtin_amdgcn_raw_buffer_store_b128(U4{v.x, v.y, v.z, v.w}, piece, i * 4, 0, 16 /* sc1 */);
         } else {
             for (int j = i; j < n; ++j) dst[j] = out[j];
         }
