@@ -160,7 +160,7 @@ __device__ __forceinline__ void load_chunk(Piece<V> (&pre)[CHUNK / V], const flo
 // but the last ones): nothing to test, and nothing is done to the values once they are requested,
 // so the loads stay in flight until the chunk is parked.  `chunk` is the tile's first row at the
 // chunk's first column (wave-uniform), `lane_bytes` the lane's place in piece 0.
-template <int V>
+template <int V, bool ONCE>
 __device__ __forceinline__ void load_chunk_full(Piece<V> (&pre)[CHUNK / V], const float *__restrict__ chunk, int F,
                                                 uint32_t lane_bytes)
 {
@@ -170,7 +170,9 @@ __device__ __forceinline__ void load_chunk_full(Piece<V> (&pre)[CHUNK / V], cons
         const char *q = reinterpret_cast<const char *>(chunk + static_cast<int64_t>(i) * RPI * F) + lane_bytes;
         if (V == 4) {
             typedef float F4 __attribute__((ext_vector_type(4)));
-            const F4 t = __builtin_nontemporal_load(reinterpret_cast<const F4 *>(q));  // read once, not to be kept
+            F4 t;
+            if constexpr (ONCE) t = __builtin_nontemporal_load(reinterpret_cast<const F4 *>(q));
+            else t = *reinterpret_cast<const F4 *>(q);
             pre[i].v[0] = t.x, pre[i].v[1 % V] = t.y, pre[i].v[2 % V] = t.z, pre[i].v[3 % V] = t.w;
         } else if (V == 2) {
             const float2 t = *reinterpret_cast<const float2 *>(q);
@@ -196,8 +198,10 @@ __device__ __forceinline__ void park_chunk(float *xs, const Piece<V> (&pre)[CHUN
     }
 }
 
-// V: floats per global load (4 when rows are 16-byte aligned, i.e. F % 4 == 0; else 2 or 1).
-template <int KP, int V>
+// V: floats per global load (4 when rows are 16-byte aligned, i.e. F % 4 == 0; else 2 or 1).  ONCE: a chunk is whole lines,
+// which nothing reads again and the caches need not keep; elsewhere two chunks share a line, and with that policy it came from
+// memory twice (1M x 300, 2 classes 319 us a call, 240 so; 1.5M x 200 287 and 221; 2M x 128, 10 classes the other way 191 and 215).
+template <int KP, int V, bool ONCE>
 __global__ __launch_bounds__(LANES *LWAVES) void linear_kernel(LinDev m, const float *__restrict__ X,
                                                                 int64_t n_rows, float *scores, int32_t *labels)
 {
@@ -229,7 +233,7 @@ __global__ __launch_bounds__(LANES *LWAVES) void linear_kernel(LinDev m, const f
         static_cast<uint32_t>(sizeof(float)) * (static_cast<uint32_t>(lane / (CHUNK / V)) * static_cast<uint32_t>(F) + (lane % (CHUNK / V)) * V);
     auto fetch = [&](Piece<V> (&pre)[CHUNK / V], int chunk) {
         const bool there = chunk < n_whole;
-        load_chunk_full<V>(pre, there ? src + chunk * CHUNK : src, there ? F : 0, there ? lane_bytes : 0u);
+        load_chunk_full<V, ONCE>(pre, there ? src + chunk * CHUNK : src, there ? F : 0, there ? lane_bytes : 0u);
     };
     // The feature loop runs through all chunks as one stream of weights.
     WeightPtr w = (WeightPtr)m.weight;
@@ -283,19 +287,38 @@ __global__ __launch_bounds__(LANES *LWAVES) void linear_kernel(LinDev m, const f
 // in 1 KB pieces, and all of a tile's loads are in flight at once.  Rows whose size is not a
 // multiple of the 128-byte line would otherwise be fetched twice by the chunked kernel, once for
 // each chunk a line straddles.
+// PADDED: 16 bytes are left free behind every 1 KB piece.  A lane reads its own row, and rows of a multiple of 16 floats begin
+// in two banks, those of a multiple of 32 in one: a read took 16 or 32 trips to LDS (300M values, one output, us a call: 32, 64
+// and 96 features 503, 48 features 255), with the padding two to eight.  The 16 features of a step lie in one piece.
+// Beyond 96 features multiples of 32 go by chunks, whose lines are whole; of the others those of which three workgroups fit a
+// CU (up to 104 features) go by rows, and, with one output, those of which two do (us, chunks with the cache / rows: 100
+// features, one output 243 / 178, 5 classes 178 / 166; 130, one output 271 / 183; 112 features, 5 classes 189 / 198; 150, 12
+// classes 217 / 279).
 constexpr int ROWS_WAVES = 2;
-constexpr int ROWS_MAX_FEATURES = 96;
+constexpr int ROWS_MAX_FEATURES = 96, ROWS_MAX_OF_THREE = 104, ROWS_MAX_OF_TWO = 156;
+constexpr int PIECE = LANES * 4;  // floats of a piece
+constexpr int PAD = 4;
+constexpr int STEP = 16;  // features of a step of the padded form
 
-template <int KP>
+inline bool takes_rows(int n_features, int n_outputs)
+{
+    if (n_features <= ROWS_MAX_FEATURES) return true;
+    return n_features % CHUNK != 0 && n_features <= (n_outputs == 1 ? ROWS_MAX_OF_TWO : ROWS_MAX_OF_THREE);
+}
+inline bool padded_rows(int n_features) { return n_features % STEP == 0; }
+// Floats of a wave's tile: 64 rows of F are F / 4 pieces.
+__host__ __device__ constexpr int rows_tile_floats(int n_features, bool padded) { return LANES * n_features + (padded ? n_features / 4 * PAD : 0); }
+
+template <int KP, bool PADDED>
 __global__ __launch_bounds__(LANES *ROWS_WAVES) void linear_rows_kernel(LinDev m, const float *__restrict__ X,
                                                                          int64_t n_rows, float *scores,
                                                                          int32_t *labels)
 {
-    extern __shared__ __align__(16) float rows_tile[];  // [ROWS_WAVES][64 * F]
+    extern __shared__ __align__(16) float rows_tile[];  // [ROWS_WAVES][rows_tile_floats]
     const int lane = threadIdx.x & (LANES - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int F = m.n_features;
-    float *xs = rows_tile + wave * LANES * F;
+    float *xs = rows_tile + wave * rows_tile_floats(F, PADDED);
     const int64_t row0 = (static_cast<int64_t>(blockIdx.x) * ROWS_WAVES + wave) * LANES;
     if (row0 >= n_rows) return;  // wave-uniform
     const int64_t left = n_rows - row0;
@@ -307,21 +330,34 @@ __global__ __launch_bounds__(LANES *ROWS_WAVES) void linear_rows_kernel(LinDev m
     typedef __attribute__((address_space(3))) void *LdsPtr;
     for (int i = 0; i * LANES < n4; ++i) {
         if (i * LANES + lane < n4)  // the LDS address is the wave-uniform base plus 16 bytes per lane
-            __builtin_amdgcn_global_load_lds((GlobalPtr)(src + (i * LANES + lane) * 4), (LdsPtr)(xs + i * LANES * 4), 16, 0, 2 /* non-temporal: X is read once, not to be kept (l4 12 % faster, l2 8 %) */);
+            __builtin_amdgcn_global_load_lds((GlobalPtr)(src + (i * LANES + lane) * 4), (LdsPtr)(xs + i * (PIECE + (PADDED ? PAD : 0))), 16, 0, 2 /* non-temporal: X is read once, not to be kept (l4 12 % faster, l2 8 %) */);
     }
 #endif
-    for (int e = n4 * 4 + lane; e < n; e += LANES) xs[e] = src[e];  // at most three floats of a partial tile
+    for (int e = n4 * 4 + lane; e < n; e += LANES) xs[e + (PADDED ? e / PIECE * PAD : 0)] = src[e];  // at most three floats of a partial tile
     double acc[KP];
 #pragma unroll
     for (int k = 0; k < KP; ++k) acc[k] = ((WeightPtr)m.bias)[k];
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    const float *row = xs + (lane < rows_here ? lane : 0) * F;
+    const int first = (lane < rows_here ? lane : 0) * F;  // of the lane's row
     WeightPtr w = (WeightPtr)m.weight;
-#pragma unroll 8
-    for (int f = 0; f < F; ++f) {
-        const double x = static_cast<double>(row[f]);
+    if constexpr (PADDED) {
+        for (int f = 0; f < F; f += STEP) {
+            const float *row = xs + first + f + ((first + f) / PIECE) * PAD;
 #pragma unroll
-        for (int k = 0; k < KP; ++k) acc[k] = __builtin_fma(x, w[f * KP + k], acc[k]);
+            for (int j = 0; j < STEP; ++j) {
+                const double x = static_cast<double>(row[j]);
+#pragma unroll
+                for (int k = 0; k < KP; ++k) acc[k] = __builtin_fma(x, w[(f + j) * KP + k], acc[k]);
+            }
+        }
+    } else {
+        const float *row = xs + first;
+#pragma unroll 8
+        for (int f = 0; f < F; ++f) {
+            const double x = static_cast<double>(row[f]);
+#pragma unroll
+            for (int k = 0; k < KP; ++k) acc[k] = __builtin_fma(x, w[f * KP + k], acc[k]);
+        }
     }
     // the rows' own space takes their scores unless there are more scores than features
     if (KP == 1 || m.n_outputs <= F) finish_linear_tile<KP>(m, acc, xs, row0, rows_here, lane, scores, labels);
@@ -330,41 +366,42 @@ __global__ __launch_bounds__(LANES *ROWS_WAVES) void linear_rows_kernel(LinDev m
 
 using LinearFn = void (*)(LinDev, const float *, int64_t, float *, int32_t *);
 
-template <int V>
+template <int V, bool ONCE>
 LinearFn pick_k(int kp)
 {
     switch (kp) {
-        case 1: return linear_kernel<1, V>;
-        case 2: return linear_kernel<2, V>;
-        case 3: return linear_kernel<3, V>;
-        case 4: return linear_kernel<4, V>;
-        case 5: return linear_kernel<5, V>;
-        case 6: return linear_kernel<6, V>;
-        case 8: return linear_kernel<8, V>;
-        case 10: return linear_kernel<10, V>;
-        case 12: return linear_kernel<12, V>;
-        case 16: return linear_kernel<16, V>;
-        case 24: return linear_kernel<24, V>;
-        case 32: return linear_kernel<32, V>;
+        case 1: return linear_kernel<1, V, ONCE>;
+        case 2: return linear_kernel<2, V, ONCE>;
+        case 3: return linear_kernel<3, V, ONCE>;
+        case 4: return linear_kernel<4, V, ONCE>;
+        case 5: return linear_kernel<5, V, ONCE>;
+        case 6: return linear_kernel<6, V, ONCE>;
+        case 8: return linear_kernel<8, V, ONCE>;
+        case 10: return linear_kernel<10, V, ONCE>;
+        case 12: return linear_kernel<12, V, ONCE>;
+        case 16: return linear_kernel<16, V, ONCE>;
+        case 24: return linear_kernel<24, V, ONCE>;
+        case 32: return linear_kernel<32, V, ONCE>;
         default: return nullptr;
     }
 }
 
+template <bool PADDED>
 LinearFn pick_rows(int kp)
 {
     switch (kp) {
-        case 1: return linear_rows_kernel<1>;
-        case 2: return linear_rows_kernel<2>;
-        case 3: return linear_rows_kernel<3>;
-        case 4: return linear_rows_kernel<4>;
-        case 5: return linear_rows_kernel<5>;
-        case 6: return linear_rows_kernel<6>;
-        case 8: return linear_rows_kernel<8>;
-        case 10: return linear_rows_kernel<10>;
-        case 12: return linear_rows_kernel<12>;
-        case 16: return linear_rows_kernel<16>;
-        case 24: return linear_rows_kernel<24>;
-        case 32: return linear_rows_kernel<32>;
+        case 1: return linear_rows_kernel<1, PADDED>;
+        case 2: return linear_rows_kernel<2, PADDED>;
+        case 3: return linear_rows_kernel<3, PADDED>;
+        case 4: return linear_rows_kernel<4, PADDED>;
+        case 5: return linear_rows_kernel<5, PADDED>;
+        case 6: return linear_rows_kernel<6, PADDED>;
+        case 8: return linear_rows_kernel<8, PADDED>;
+        case 10: return linear_rows_kernel<10, PADDED>;
+        case 12: return linear_rows_kernel<12, PADDED>;
+        case 16: return linear_rows_kernel<16, PADDED>;
+        case 24: return linear_rows_kernel<24, PADDED>;
+        case 32: return linear_rows_kernel<32, PADDED>;
         default: return nullptr;
     }
 }
@@ -373,9 +410,10 @@ LinearFn pick_rows(int kp)
 LinearFn pick(int kp, int n_features, const float *X)
 {
     const bool a16 = (reinterpret_cast<uintptr_t>(X) & 15) == 0, a8 = (reinterpret_cast<uintptr_t>(X) & 7) == 0;
-    if (n_features % 4 == 0 && a16) return pick_k<4>(kp);
-    if (n_features % 2 == 0 && a8) return pick_k<2>(kp);
-    return pick_k<1>(kp);
+    if (n_features % CHUNK == 0 && (reinterpret_cast<uintptr_t>(X) & 127) == 0) return pick_k<4, true>(kp);
+    if (n_features % 4 == 0 && a16) return pick_k<4, false>(kp);
+    if (n_features % 2 == 0 && a8) return pick_k<2, false>(kp);
+    return pick_k<1, false>(kp);
 }
 
 }  // namespace
@@ -392,13 +430,14 @@ hipError_t launch_linear(const LinDev &m, const float *X, int64_t n_rows, float 
                          hipStream_t stream)
 {
     if (n_rows <= 0) return hipSuccess;
-    if (m.n_features <= ROWS_MAX_FEATURES && (reinterpret_cast<uintptr_t>(X) & 15) == 0) {
-        LinearFn fn = pick_rows(m.kp);
+    if (takes_rows(m.n_features, m.n_outputs) && (reinterpret_cast<uintptr_t>(X) & 15) == 0) {
+        const bool padded = padded_rows(m.n_features);
+        LinearFn fn = padded ? pick_rows<true>(m.kp) : pick_rows<false>(m.kp);
         if (!fn) return hipErrorInvalidValue;
         const int64_t rows_per_block = LANES * ROWS_WAVES;
         const int64_t n_blocks = (n_rows + rows_per_block - 1) / rows_per_block;
         if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-        const size_t lds = sizeof(float) * ROWS_WAVES * LANES * m.n_features;
+        const size_t lds = sizeof(float) * ROWS_WAVES * rows_tile_floats(m.n_features, padded);
         hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(n_blocks)), dim3(LANES * ROWS_WAVES), lds, stream, m, X,
                            n_rows, scores, labels);
         return hipGetLastError();

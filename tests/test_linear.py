@@ -116,6 +116,16 @@ def test_rows_of_whole_16_byte_pieces(F):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("F", [4, 15, 16, 32, 48, 80, 95, 96, 97, 100, 104, 105, 112, 128, 144, 155, 156, 157, 160, 200])
+@pytest.mark.parametrize("K,rows", [(1, 64 * 130 + 3), (1, 1), (3, 64 * 70 + 63), (12, 64 * 5 + 1), (20, 130)])
+def test_tiles_of_rows_with_and_without_padding(F, K, rows):
+    """Rows of a multiple of 16 floats, whose tile has padding, and of others; the widest rows that go as whole tiles, for one
+    output and several, and the narrowest by chunks; partial tiles, whose last floats are copied one by one."""
+    m = _rand_model(5 * F + K, F, K, TRANSFORM_SOFTMAX if K > 1 else TRANSFORM_SIGMOID)
+    _check(m, np.random.default_rng(F + rows).standard_normal((rows, F)).astype(np.float32))
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("F", [28, 40, 64, 90, 100, 130])
 def test_x_that_starts_off_a_16_byte_boundary_and_absent_bias(F):
     """X may start at any float: 4, 8 or 12 bytes past a 16-byte boundary the kernels fall back
