@@ -37,14 +37,18 @@ constexpr int STRIDE = CHUNK + 4;  // row pitch of the LDS tile in floats: 16-by
 // Label, transform and store of one row whose K raw values (bias included) are acc[0..K).
 // A score to its place.  Scores and labels go past the L2 (device scope): beside X, of which every line is new, written lines
 // that wait in the L2 leave it in no order, and every write there costs the reads of X more than its bytes (2M x 128, 10
-// classes: 194.4 us a call, 169 with no scores written, 189.1 so; 8M x 28, sigmoid and label 156.4 -> 149.2; 8M x 20, 3
-// classes 122.9 -> 118; 4M x 90, one output 211.6 -> 209.8; non-temporal stores took as long as ordinary ones or longer).  With
-// several outputs a lane's own values are a short run of its own, each would be a partial write, and they go the ordinary way.
+// classes: 194.4 us a call, 169 with no scores written, 189.1 so; 8M x 28, sigmoid and label 158.4 -> 149.5; 8M x 20, 3
+// classes 122.9 -> 118).  Few writes, one score a row of 64 features or more without a label, do better with the non-temporal
+// policy (4M x 90 213.9 / past the L2 217.8 us, 3M x 64 119 / 119, 8M x 20 106.5 / 103.9).  With several outputs a lane's own
+// values are a short run of its own, each would be a partial write, and they go the ordinary way.
+constexpr int FEW_WRITES_FEATURES = 64;
+
 template <int KP>
-__device__ __forceinline__ void store_score(float v, float *p)
+__device__ __forceinline__ void store_score(float v, float *p, bool few_writes)
 {
-    if (KP == 1) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    else *p = v;
+    if (KP > 1) *p = v;
+    else if (few_writes) __builtin_nontemporal_store(v, p);
+    else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <int KP>
 __device__ __forceinline__ void finish_linear_row(const LinDev &m, double (&acc)[KP], int64_t row, float *scores,
@@ -66,6 +70,7 @@ __device__ __forceinline__ void finish_linear_row(const LinDev &m, double (&acc)
     }
     if (!scores) return;
     float *dst = scores + row * K;
+    const bool few_writes = !labels && m.n_features >= FEW_WRITES_FEATURES;
     if (m.transform == LINEAR_TRANSFORM_SOFTMAX) {
         double z = 0.0;
 #pragma unroll
@@ -78,15 +83,15 @@ __device__ __forceinline__ void finish_linear_row(const LinDev &m, double (&acc)
                                      // at most an ulp of float64, far below the float32 rounding
 #pragma unroll
         for (int k = 0; k < KP; ++k)
-            if (k < K) store_score<KP>(static_cast<float>(acc[k] * inv), &dst[k]);
+            if (k < K) store_score<KP>(static_cast<float>(acc[k] * inv), &dst[k], few_writes);
     } else if (m.transform == LINEAR_TRANSFORM_SIGMOID) {
 #pragma unroll
         for (int k = 0; k < KP; ++k)
-            if (k < K) store_score<KP>(static_cast<float>(1.0 / (1.0 + exp(-acc[k]))), &dst[k]);
+            if (k < K) store_score<KP>(static_cast<float>(1.0 / (1.0 + exp(-acc[k]))), &dst[k], few_writes);
     } else {
 #pragma unroll
         for (int k = 0; k < KP; ++k)
-            if (k < K) store_score<KP>(static_cast<float>(acc[k]), &dst[k]);
+            if (k < K) store_score<KP>(static_cast<float>(acc[k]), &dst[k], few_writes);
     }
 }
 
