@@ -3,10 +3,12 @@
 
 #include <cmath>
 #include <cstdint>
+#include <mutex>
 #include <new>
 #include <vector>
 
 #include "../../include/linear.h"
+#include "../../include/linear_testing.h"
 #include "linear_device.hpp"
 
 using namespace linear_impl;
@@ -36,6 +38,26 @@ int check(const linear_desc &d)
     return LINEAR_OK;
 }
 
+// Kernel attributes are per device: set once for every device a model is loaded on.
+constexpr int MAX_DEVICES = 64;
+std::mutex g_init_mutex;
+bool g_init_done[MAX_DEVICES] = {};
+int g_lds_limit[MAX_DEVICES] = {};
+
+hipError_t init_device(int device, int64_t &lds_limit)
+{
+    if (device < 0 || device >= MAX_DEVICES) return hipErrorInvalidDevice;
+    std::lock_guard<std::mutex> lock(g_init_mutex);
+    if (!g_init_done[device]) {
+        hipError_t e = hipDeviceGetAttribute(&g_lds_limit[device], hipDeviceAttributeMaxSharedMemoryPerBlock, device);
+        if (e == hipSuccess) e = init_linear_kernels(g_lds_limit[device]);
+        if (e != hipSuccess) return e;
+        g_init_done[device] = true;
+    }
+    lds_limit = g_lds_limit[device];
+    return hipSuccess;
+}
+
 }  // namespace
 
 extern "C" {
@@ -61,7 +83,7 @@ int linear_load(const linear_desc *desc, linear_model **out)
     if (desc->bias)
         for (int k = 0; k < K; ++k) host[static_cast<size_t>(f_pad) * kp + k] = desc->bias[k];
     // Everything below needs a device.
-    if (hipGetDevice(&m->device) != hipSuccess) {
+    if (hipGetDevice(&m->device) != hipSuccess || init_device(m->device, m->dev.lds_limit) != hipSuccess) {
         (void)hipGetLastError();
         delete m;
         return LINEAR_EHIP;
@@ -145,6 +167,15 @@ int linear_predict(const linear_model *m, const float *X, int64_t n_rows, void *
     int32_t *labels = lo >= 0 ? reinterpret_cast<int32_t *>(base + lo) : nullptr;
     const hipError_t e = launch_linear(m->dev, X, n_rows, scores, labels, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? LINEAR_OK : LINEAR_EHIP;
+}
+
+int linear_launch_shape(int32_t n_features, int32_t n_outputs, uintptr_t x, int64_t lds_limit, linear_launch_t *out)
+{
+    if (!out || n_features < 1 || n_outputs < 1) return LINEAR_EINVAL;
+    if (n_features > LINEAR_MAX_FEATURES || n_outputs > LINEAR_MAX_OUTPUTS) return LINEAR_ELIMIT;
+    const LinearPlan p = plan_linear(n_features, n_outputs, x, lds_limit);
+    *out = linear_launch_t{p.rows, p.padded, p.width, p.once, p.lds_bytes};
+    return LINEAR_OK;
 }
 
 const char *linear_strerror(int code)

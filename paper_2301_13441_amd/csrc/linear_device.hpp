@@ -5,6 +5,8 @@
 
 #include <cstdint>
 
+#include "linear_plan.hpp"
+
 namespace linear_impl {
 
 struct LinDev {
@@ -12,10 +14,11 @@ struct LinDev {
     const double *bias;    // [kp]
     int32_t n_features, n_outputs, kp;
     int32_t transform, output;
+    int64_t lds_limit;  // bytes of LDS that a workgroup may have
 };
 
-// Column counts the kernel is instantiated for; a model uses the smallest one >= n_outputs.
-int padded_outputs(int n_outputs);
+// Lets the kernels have `lds_limit` bytes of LDS on the current device.
+hipError_t init_linear_kernels(int64_t lds_limit);
 
 hipError_t launch_linear(const LinDev &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                          hipStream_t stream);

@@ -28,9 +28,7 @@ typedef const __attribute__((address_space(4))) double *WeightPtr;
 typedef const double *WeightPtr;  // host pass: the kernel body is only parsed
 #endif
 
-constexpr int LANES = 64;
 constexpr int LWAVES = 4;
-constexpr int CHUNK = 32;          // features per pass
 constexpr int STRIDE = CHUNK + 4;  // row pitch of the LDS tile in floats: 16-byte aligned rows, and the
                                    // 8 lanes of a 128-bit read phase fall into 8 different bank groups
 
@@ -295,25 +293,7 @@ __global__ __launch_bounds__(LANES *LWAVES) void linear_kernel(LinDev m, const f
 // PADDED: 16 bytes are left free behind every 1 KB piece.  A lane reads its own row, and rows of a multiple of 16 floats begin
 // in two banks, those of a multiple of 32 in one: a read took 16 or 32 trips to LDS (300M values, one output, us a call: 32, 64
 // and 96 features 503, 48 features 255), with the padding two to eight.  The 16 features of a step lie in one piece.
-// Beyond 96 features multiples of 32 go by chunks, whose lines are whole; of the others those of which three workgroups fit a
-// CU (up to 104 features) go by rows, and, with one output, those of which two do (us, chunks with the cache / rows: 100
-// features, one output 243 / 178, 5 classes 178 / 166; 130, one output 271 / 183; 112 features, 5 classes 189 / 198; 150, 12
-// classes 217 / 279).
-constexpr int ROWS_WAVES = 2;
-constexpr int ROWS_MAX_FEATURES = 96, ROWS_MAX_OF_THREE = 104, ROWS_MAX_OF_TWO = 156;
-constexpr int PIECE = LANES * 4;  // floats of a piece
-constexpr int PAD = 4;
-constexpr int STEP = 16;  // features of a step of the padded form
-
-inline bool takes_rows(int n_features, int n_outputs)
-{
-    if (n_features <= ROWS_MAX_FEATURES) return true;
-    return n_features % CHUNK != 0 && n_features <= (n_outputs == 1 ? ROWS_MAX_OF_TWO : ROWS_MAX_OF_THREE);
-}
-inline bool padded_rows(int n_features) { return n_features % STEP == 0; }
-// Floats of a wave's tile: 64 rows of F are F / 4 pieces.
-__host__ __device__ constexpr int rows_tile_floats(int n_features, bool padded) { return LANES * n_features + (padded ? n_features / 4 * PAD : 0); }
-
+// Which widths go this way: takes_rows, linear_plan.hpp.
 template <int KP, bool PADDED>
 __global__ __launch_bounds__(LANES *ROWS_WAVES) void linear_rows_kernel(LinDev m, const float *__restrict__ X,
                                                                          int64_t n_rows, float *scores,
@@ -411,47 +391,40 @@ LinearFn pick_rows(int kp)
     }
 }
 
-// Widest load that every row start and every chunk start is aligned for.
-LinearFn pick(int kp, int n_features, const float *X)
+LinearFn pick(const LinearPlan &p, int kp)
 {
-    const bool a16 = (reinterpret_cast<uintptr_t>(X) & 15) == 0, a8 = (reinterpret_cast<uintptr_t>(X) & 7) == 0;
-    if (n_features % CHUNK == 0 && (reinterpret_cast<uintptr_t>(X) & 127) == 0) return pick_k<4, true>(kp);
-    if (n_features % 4 == 0 && a16) return pick_k<4, false>(kp);
-    if (n_features % 2 == 0 && a8) return pick_k<2, false>(kp);
-    return pick_k<1, false>(kp);
+    if (p.rows) return p.padded ? pick_rows<true>(kp) : pick_rows<false>(kp);
+    if (p.width == 4) return p.once ? pick_k<4, true>(kp) : pick_k<4, false>(kp);
+    return p.width == 2 ? pick_k<2, false>(kp) : pick_k<1, false>(kp);
 }
 
 }  // namespace
 
-int padded_outputs(int n_outputs)
+// Tiles of more than 96 features may pass the LDS that a workgroup gets unasked.
+hipError_t init_linear_kernels(int64_t lds_limit)
 {
-    static const int sizes[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16, 24, 32};
-    for (int s : sizes)
-        if (s >= n_outputs) return s;
-    return 0;
+    for (int kp = 1; kp <= LINEAR_MAX_OUTPUTS; kp = padded_outputs(kp + 1)) {
+        for (LinearFn fn : {pick_rows<true>(kp), pick_rows<false>(kp)})
+            if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                   static_cast<int>(lds_limit));
+                e != hipSuccess)
+                return e;
+        if (kp == LINEAR_MAX_OUTPUTS) break;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_linear(const LinDev &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                          hipStream_t stream)
 {
     if (n_rows <= 0) return hipSuccess;
-    if (takes_rows(m.n_features, m.n_outputs) && (reinterpret_cast<uintptr_t>(X) & 15) == 0) {
-        const bool padded = padded_rows(m.n_features);
-        LinearFn fn = padded ? pick_rows<true>(m.kp) : pick_rows<false>(m.kp);
-        if (!fn) return hipErrorInvalidValue;
-        const int64_t rows_per_block = LANES * ROWS_WAVES;
-        const int64_t n_blocks = (n_rows + rows_per_block - 1) / rows_per_block;
-        if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-        const size_t lds = sizeof(float) * ROWS_WAVES * rows_tile_floats(m.n_features, padded);
-        hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(n_blocks)), dim3(LANES * ROWS_WAVES), lds, stream, m, X,
-                           n_rows, scores, labels);
-        return hipGetLastError();
-    }
-    LinearFn fn = pick(m.kp, m.n_features, X);
+    const LinearPlan p = plan_linear(m.n_features, m.n_outputs, reinterpret_cast<uintptr_t>(X), m.lds_limit);
+    LinearFn fn = pick(p, m.kp);
     if (!fn) return hipErrorInvalidValue;
-    const int64_t n_blocks = (n_rows + LANES * LWAVES - 1) / (LANES * LWAVES);
+    const int waves = p.rows ? ROWS_WAVES : LWAVES;
+    const int64_t n_blocks = (n_rows + LANES * waves - 1) / (LANES * waves);
     if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(n_blocks)), dim3(LANES * LWAVES), 0, stream, m, X, n_rows,
+    hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(n_blocks)), dim3(LANES * waves), p.lds_bytes, stream, m, X, n_rows,
                        scores, labels);
     return hipGetLastError();
 }

@@ -13,11 +13,16 @@ _i32, _i64 = ctypes.c_int32, ctypes.c_int64
 
 LINEAR_EXPORTS = ["linear_load", "linear_free", "linear_out_bytes", "linear_out_layout", "linear_predict",
                   "linear_strerror"]
+LINEAR_TESTING_EXPORTS = ["linear_launch_shape"]
 
 
 class _LinearDesc(ctypes.Structure):
     _fields_ = [("n_features", _i32), ("n_outputs", _i32), ("weight", _p), ("bias", _p),
                 ("transform", _i32), ("output", _i32)]
+
+
+class _LinearLaunch(ctypes.Structure):
+    _fields_ = [(name, _i32) for name in ("whole_rows", "padded", "load_width", "once", "lds_bytes")]
 
 
 class LinearError(RuntimeError):
@@ -44,6 +49,8 @@ def _lib():
         lib.linear_out_layout.argtypes = [_p, _i64, ctypes.POINTER(_i64), ctypes.POINTER(_i64)]
         lib.linear_predict.restype = ctypes.c_int
         lib.linear_predict.argtypes = [_p, _p, _i64, _p, _p]
+        lib.linear_launch_shape.restype = ctypes.c_int
+        lib.linear_launch_shape.argtypes = [_i32, _i32, ctypes.c_size_t, _i64, ctypes.POINTER(_LinearLaunch)]
         lib.linear_strerror.restype = ctypes.c_char_p
         lib.linear_strerror.argtypes = [ctypes.c_int]
         _ready = True
@@ -164,3 +171,12 @@ def linear_load(model) -> Linear:
     if rc != 0:
         raise LinearError(rc, "linear_load")
     return Linear(h, int(model.n_features), int(model.n_outputs))
+
+
+def linear_launch_shape(n_features: int, n_outputs: int, x: int = 0, lds_limit: int = 160 * 1024) -> dict:
+    """What a call launches whose X is at address `x` (include/linear_testing.h); no GPU needed."""
+    s = _LinearLaunch()
+    rc = _lib().linear_launch_shape(n_features, n_outputs, x, lds_limit, ctypes.byref(s))
+    if rc != 0:
+        raise LinearError(rc, "linear_launch_shape")
+    return {name: int(getattr(s, name)) for name, _ in _LinearLaunch._fields_}

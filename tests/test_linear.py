@@ -57,6 +57,32 @@ def test_validation_happens_before_any_device_call():
     lib.linear_free(None)
 
 
+def test_testing_header_declares_what_the_library_exports():
+    header = open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "include", "linear_testing.h")).read()
+    assert set(re.findall(r"\b(linear_[a-z_]+)\s*\(", header)) == set(lb.LINEAR_TESTING_EXPORTS)
+    lib = lb._lib()
+    assert all(hasattr(lib, name) for name in lb.LINEAR_TESTING_EXPORTS)
+    for bad in ((0, 1, -1), (4, 0, -1), (65537, 1, -7), (4, 33, -7)):
+        with pytest.raises(lb.LinearError) as e:
+            lb.linear_launch_shape(*bad[:2])
+        assert e.value.code == bad[2]
+
+
+@pytest.mark.parametrize("F", [96, 104, 112, 128, 129, 130, 144, 150, 155, 156])
+def test_whole_rows_only_where_their_tile_fits_the_workgroup(F):
+    """64 KB of LDS, which a workgroup has anywhere, hold 127 features of two waves' rows at most: wider tiles need what
+    the device says, and go by chunks where it says less."""
+    most = lb.linear_launch_shape(F, 1)
+    assert most["lds_bytes"] <= 160 * 1024 and most["whole_rows"] == (F % 32 != 0 or F <= 96)
+    if most["whole_rows"]:
+        assert most["lds_bytes"] >= 2 * 64 * 4 * F
+        at, less = (lb.linear_launch_shape(F, 1, lds_limit=n) for n in (most["lds_bytes"], most["lds_bytes"] - 1))
+        assert at == most
+        assert (less["whole_rows"], less["padded"], less["lds_bytes"]) == (0, 0, 0)
+        assert less["load_width"] == (4 if F % 4 == 0 else 2 if F % 2 == 0 else 1)
+    assert lb.linear_launch_shape(F, 1, lds_limit=64 * 1024)["lds_bytes"] <= 64 * 1024
+
+
 # ---------------------------------------------------------------- GPU parity
 def _run(model, X):
     import torch
