@@ -19,13 +19,16 @@ typedef struct linear_launch_t {
     int32_t load_width; /* chunks: floats per load of X */
     int32_t once;       /* chunks: loads of X are non-temporal */
     int32_t lds_bytes;  /* dynamic LDS per workgroup */
+    int32_t scores_past, labels_past; /* 1: stored past the L2 */
 } linear_launch_t;
 
 /*
- * The launch of a call whose X is at address `x`, on a device whose workgroups may have `lds_limit` bytes of LDS.
+ * The launch of a call whose X, scores and labels are at these addresses (0: not asked for), on a device whose workgroups
+ * may have `lds_limit` bytes of LDS.
  * Returns LINEAR_OK, LINEAR_EINVAL (null pointer, counts below 1) or LINEAR_ELIMIT.
  */
-int linear_launch_shape(int32_t n_features, int32_t n_outputs, uintptr_t x, int64_t lds_limit, linear_launch_t *out);
+int linear_launch_shape(int32_t n_features, int32_t n_outputs, uintptr_t x, uintptr_t scores, uintptr_t labels,
+                        int64_t lds_limit, linear_launch_t *out);
 
 #ifdef __cplusplus
 }

@@ -14,6 +14,7 @@ struct LinDev {
     const double *bias;    // [kp]
     int32_t n_features, n_outputs, kp;
     int32_t transform, output;
+    int32_t scores_past, labels_past;  // set per launch (LinearPlan)
     int64_t lds_limit;  // bytes of LDS that a workgroup may have
 };
 

@@ -33,20 +33,14 @@ constexpr int STRIDE = CHUNK + 4;  // row pitch of the LDS tile in floats: 16-by
                                    // 8 lanes of a 128-bit read phase fall into 8 different bank groups
 
 // Label, transform and store of one row whose K raw values (bias included) are acc[0..K).
-// A score to its place.  Scores and labels go past the L2 (device scope): beside X, of which every line is new, written lines
-// that wait in the L2 leave it in no order, and every write there costs the reads of X more than its bytes (2M x 128, 10
-// classes: 194.4 us a call, 169 with no scores written, 189.1 so; 8M x 28, sigmoid and label 158.4 -> 149.5; 8M x 20, 3
-// classes 122.9 -> 118).  Few writes, one score a row of 64 features or more without a label, do better with the non-temporal
-// policy (4M x 90 213.9 / past the L2 217.8 us, 3M x 64 119 / 119, 8M x 20 106.5 / 103.9).  With several outputs a lane's own
-// values are a short run of its own, each would be a partial write, and they go the ordinary way.
-constexpr int FEW_WRITES_FEATURES = 64;
-
+// A score to its place: past the L2 (device scope) where the plan says so (LinearPlan), else non-temporally.  With several
+// outputs a lane's own values are a short run of its own, each would be a partial write, and they go the ordinary way.
 template <int KP>
-__device__ __forceinline__ void store_score(float v, float *p, bool few_writes)
+__device__ __forceinline__ void store_score(float v, float *p, bool past)
 {
     if (KP > 1) *p = v;
-    else if (few_writes) __builtin_nontemporal_store(v, p);
-    else __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else if (past) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else __builtin_nontemporal_store(v, p);
 }
 template <int KP>
 __device__ __forceinline__ void finish_linear_row(const LinDev &m, double (&acc)[KP], int64_t row, float *scores,
@@ -64,11 +58,13 @@ __device__ __forceinline__ void finish_linear_row(const LinDev &m, double (&acc)
     if (labels) {
         int lab = best_k;
         if (K == 1) lab = (m.transform == LINEAR_TRANSFORM_SIGMOID) ? (best > 0.0) : (best > 0.5);
-        __hip_atomic_store(&labels[row], lab, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (m.labels_past) __hip_atomic_store(&labels[row], lab, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else if (KP == 1) __builtin_nontemporal_store(lab, &labels[row]);
+        else labels[row] = lab;
     }
     if (!scores) return;
     float *dst = scores + row * K;
-    const bool few_writes = !labels && m.n_features >= FEW_WRITES_FEATURES;
+    const bool past = m.scores_past;
     if (m.transform == LINEAR_TRANSFORM_SOFTMAX) {
         double z = 0.0;
 #pragma unroll
@@ -81,15 +77,15 @@ __device__ __forceinline__ void finish_linear_row(const LinDev &m, double (&acc)
                                      // at most an ulp of float64, far below the float32 rounding
 #pragma unroll
         for (int k = 0; k < KP; ++k)
-            if (k < K) store_score<KP>(static_cast<float>(acc[k] * inv), &dst[k], few_writes);
+            if (k < K) store_score<KP>(static_cast<float>(acc[k] * inv), &dst[k], past);
     } else if (m.transform == LINEAR_TRANSFORM_SIGMOID) {
 #pragma unroll
         for (int k = 0; k < KP; ++k)
-            if (k < K) store_score<KP>(static_cast<float>(1.0 / (1.0 + exp(-acc[k]))), &dst[k], few_writes);
+            if (k < K) store_score<KP>(static_cast<float>(1.0 / (1.0 + exp(-acc[k]))), &dst[k], past);
     } else {
 #pragma unroll
         for (int k = 0; k < KP; ++k)
-            if (k < K) store_score<KP>(static_cast<float>(acc[k]), &dst[k], few_writes);
+            if (k < K) store_score<KP>(static_cast<float>(acc[k]), &dst[k], past);
     }
 }
 
@@ -115,7 +111,8 @@ __device__ __forceinline__ void finish_linear_tile(const LinDev &m, double (&acc
     for (int i = lane * 4; i < n; i += LANES * 4) {
         if (i + 4 <= n) {
             const LooseU4 v = *reinterpret_cast<const LooseU4 *>(out + i);
-            __builtin_amdgcn_raw_buffer_store_b128(U4{v.x, v.y, v.z, v.w}, piece, i * 4, 0, 16 /* sc1 */);
+            if (m.scores_past) __builtin_amdgcn_raw_buffer_store_b128(U4{v.x, v.y, v.z, v.w}, piece, i * 4, 0, 16 /* sc1 */);
+            else *reinterpret_cast<LooseU4 *>(dst + i) = v;
         } else {
             for (int j = i; j < n; ++j) dst[j] = out[j];
         }
@@ -418,13 +415,17 @@ hipError_t launch_linear(const LinDev &m, const float *X, int64_t n_rows, float 
                          hipStream_t stream)
 {
     if (n_rows <= 0) return hipSuccess;
-    const LinearPlan p = plan_linear(m.n_features, m.n_outputs, reinterpret_cast<uintptr_t>(X), m.lds_limit);
+    const LinearPlan p = plan_linear(m.n_features, m.n_outputs, reinterpret_cast<uintptr_t>(X), reinterpret_cast<uintptr_t>(scores),
+                                     reinterpret_cast<uintptr_t>(labels), m.lds_limit);
     LinearFn fn = pick(p, m.kp);
     if (!fn) return hipErrorInvalidValue;
     const int waves = p.rows ? ROWS_WAVES : LWAVES;
     const int64_t n_blocks = (n_rows + LANES * waves - 1) / (LANES * waves);
     if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(n_blocks)), dim3(LANES * waves), p.lds_bytes, stream, m, X, n_rows,
+    LinDev launched = m;
+    launched.scores_past = p.scores_past;
+    launched.labels_past = p.labels_past;
+    hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(n_blocks)), dim3(LANES * waves), p.lds_bytes, stream, launched, X, n_rows,
                        scores, labels);
     return hipGetLastError();
 }

@@ -40,18 +40,35 @@ inline bool padded_rows(int n_features) { return n_features % STEP == 0; }
 // Floats of a wave's tile: 64 rows of F are F / 4 pieces.
 constexpr int rows_tile_floats(int n_features, bool padded) { return LANES * n_features + (padded ? n_features / 4 * PAD : 0); }
 
+// Scores and labels go past the L2 (device scope): beside X, of which every line is new, written lines that wait in the L2 leave
+// it in no order, and every write there costs the reads of X more than its bytes (us, non-temporal or kept / past it: 2M x 128,
+// 10 classes 194.4 / 189.1, 169 with no scores written; 8M x 28, sigmoid and label 158.4 / 149.5; 8M x 20, 3 classes 122.9 /
+// 118).  Few writes, one score a row of 64 features or more without a label, do not need it (4M x 90 213.1 / 212.6, 5.6M x 90
+// 296.2 / 298.4, 667,000 x 150 67.9 / 69.6).
+// A wave's 64 scores of one output, or its labels, are whole pieces of 64 bytes only if the first of them begins one.  Elsewhere
+// two waves share a piece, which past the L2 goes to memory once for each (one output and label, where labels begin behind the
+// scores of an odd number of rows, and results that are not written over and over, us, both past the L2 / labels kept: 20M x 10
+// 198 / 165, 16M x 13 196 / 167, 7.1M x 28 163 / 143, 7.5M x 48 273 / 247; two outputs, 31M x 8 249 / 234).  16 bytes per lane
+// of a tile's several scores do not mind (5.4M x 28, 5 outputs, 4 to 12 bytes off: 119.9, on the boundary 118.9).
+constexpr int FEW_WRITES_FEATURES = 64;
+constexpr uintptr_t WRITE_PIECE = 64;
+
 struct LinearPlan {
     int32_t rows = 0;       // 1: the whole-row kernel, 0: chunks
     int32_t padded = 0;     // whole-row kernel: the padded tile
     int32_t width = 0;      // chunks: floats per load of X
     int32_t once = 0;       // chunks: loads of X are non-temporal
     int32_t lds_bytes = 0;  // dynamic LDS per workgroup
+    int32_t scores_past = 0, labels_past = 0;  // 1: stored past the L2
 };
 
-// x: the address of X.  lds_limit: bytes of LDS that a workgroup may have; a tile beyond it goes by chunks.
-inline LinearPlan plan_linear(int n_features, int n_outputs, uintptr_t x, int64_t lds_limit)
+// x, scores, labels: addresses, 0 of what is not asked for.  lds_limit: bytes of LDS that a workgroup may have; a tile beyond it goes by chunks.
+inline LinearPlan plan_linear(int n_features, int n_outputs, uintptr_t x, uintptr_t scores, uintptr_t labels, int64_t lds_limit)
 {
     LinearPlan p;
+    const bool few_writes = n_features >= FEW_WRITES_FEATURES;
+    p.scores_past = scores && (n_outputs > 1 || (scores % WRITE_PIECE == 0 && !(few_writes && !labels)));
+    p.labels_past = labels && (labels % WRITE_PIECE == 0 || (n_outputs == 1 && few_writes));
     if (takes_rows(n_features, n_outputs) && x % 16 == 0) {
         p.padded = padded_rows(n_features);
         const int64_t lds = static_cast<int64_t>(sizeof(float)) * ROWS_WAVES * rows_tile_floats(n_features, p.padded);

@@ -83,6 +83,21 @@ def test_whole_rows_only_where_their_tile_fits_the_workgroup(F):
     assert lb.linear_launch_shape(F, 1, lds_limit=64 * 1024)["lds_bytes"] <= 64 * 1024
 
 
+@pytest.mark.parametrize("rows", [64, 65, 70, 1000, 4096 + 16, 20_000_005])
+@pytest.mark.parametrize("F", [8, 28, 48, 63])
+def test_only_whole_pieces_of_one_value_a_row_go_past_the_l2(F, rows):
+    """Labels lie behind the scores, and the buffer may begin at any float: where that leaves a wave's run of them off a
+    64-byte boundary, two waves would write the same piece of memory past the L2 one after the other."""
+    for at in (1 << 20, (1 << 20) + 4, (1 << 20) + 32, (1 << 20) + 64):
+        for K in (1, 2, 7):
+            labels = at + 4 * rows * K
+            s = lb.linear_launch_shape(F, K, 1 << 12, at, labels)
+            assert s["labels_past"] == (labels % 64 == 0), (at, K)
+            assert s["scores_past"] == (K > 1 or at % 64 == 0), (at, K)
+            assert lb.linear_launch_shape(F, K, 1 << 12, 0, at)["scores_past"] == 0
+            assert lb.linear_launch_shape(F, K, 1 << 12, at, 0)["labels_past"] == 0
+
+
 # ---------------------------------------------------------------- GPU parity
 def _run(model, X):
     import torch
@@ -173,6 +188,35 @@ def test_x_that_starts_off_a_16_byte_boundary_and_absent_bias(F):
                 ref = predict_linear(model, X)
                 np.testing.assert_array_equal(labels.cpu().numpy(), ref.labels)
                 np.testing.assert_allclose(scores.cpu().numpy(), ref.scores, rtol=RTOL, atol=ATOL)
+    finally:
+        m.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("F", [12, 28, 64, 90, 128, 130])
+@pytest.mark.parametrize("K", [1, 2, 3, 10, 20])
+def test_results_that_start_off_a_16_byte_boundary(F, K):
+    """The buffer of scores and labels may start at any float and labels follow the scores of any number of rows; nothing
+    before or behind them is touched.  Full and ragged last tiles."""
+    import torch
+    model = _rand_model(F + K, F, K, TRANSFORM_SOFTMAX if K > 1 else TRANSFORM_SIGMOID)
+    rng = np.random.default_rng(F * K)
+    m = lb.linear_load(model)
+    try:
+        for rows in (1, 64, 129, 1000):
+            X = rng.standard_normal((rows, F)).astype(np.float32)
+            xd, ref = torch.from_numpy(X).cuda(), predict_linear(model, X)
+            for off in (0, 1, 2, 3, 16):
+                n = rows * (K + 1)
+                buf = torch.full((n + 64,), -1, dtype=torch.int32, device="cuda")
+                out = buf[off + 16:off + 16 + n]
+                assert out.data_ptr() % 64 == 4 * (off % 16)
+                scores, labels = m.predict(xd, out=out)
+                torch.cuda.synchronize()
+                np.testing.assert_allclose(scores.cpu().numpy(), ref.scores, rtol=RTOL, atol=ATOL)
+                np.testing.assert_array_equal(labels.cpu().numpy(), ref.labels)
+                guard = torch.cat([buf[:off + 16], buf[off + 16 + n:]]).cpu().numpy()
+                assert (guard == -1).all()
     finally:
         m.close()
 
