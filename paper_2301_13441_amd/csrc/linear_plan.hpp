@@ -43,8 +43,10 @@ constexpr int rows_tile_floats(int n_features, bool padded) { return LANES * n_f
 // Scores and labels go past the L2 (device scope): beside X, of which every line is new, written lines that wait in the L2 leave
 // it in no order, and every write there costs the reads of X more than its bytes (us, non-temporal or kept / past it: 2M x 128,
 // 10 classes 194.4 / 189.1, 169 with no scores written; 8M x 28, sigmoid and label 158.4 / 149.5; 8M x 20, 3 classes 122.9 /
-// 118).  Few writes, one score a row of 64 features or more without a label, do not need it (4M x 90 213.1 / 212.6, 5.6M x 90
-// 296.2 / 298.4, 667,000 x 150 67.9 / 69.6).
+// 118).  One score a row of 64 features or more does not need it, and a label beside it goes past the L2 alone, wherever it begins
+// (us, scores non-temporal / past the L2: 4M x 90 213.1 / 212.6, 5.6M x 90 296.2 / 298.4, 667,000 x 150 67.9 / 69.6, 1.56M x 64
+// 63.4 / 62.3; with a label, results written over 4M x 90 223.5 / 226.4, 2.2M x 90 124.8 / 126.2, 3.1M x 64 128.6 / 127.2, and in
+// new places 4M x 90 224.0 / 235.8, 4.5M x 80 235.8 / 245.6, 5.6M x 64 and five more rows 235.8 / 263.3).
 // A wave's 64 scores of one output, or its labels, are whole pieces of 64 bytes only if the first of them begins one.  Elsewhere
 // two waves share a piece, which past the L2 goes to memory once for each (one output and label, where labels begin behind the
 // scores of an odd number of rows, and results that are not written over and over, us, both past the L2 / labels kept: 20M x 10
@@ -67,7 +69,7 @@ inline LinearPlan plan_linear(int n_features, int n_outputs, uintptr_t x, uintpt
 {
     LinearPlan p;
     const bool few_writes = n_features >= FEW_WRITES_FEATURES;
-    p.scores_past = scores && (n_outputs > 1 || (scores % WRITE_PIECE == 0 && !(few_writes && !labels)));
+    p.scores_past = scores && (n_outputs > 1 || (scores % WRITE_PIECE == 0 && !few_writes));
     p.labels_past = labels && (labels % WRITE_PIECE == 0 || (n_outputs == 1 && few_writes));
     if (takes_rows(n_features, n_outputs) && x % 16 == 0) {
         p.padded = padded_rows(n_features);

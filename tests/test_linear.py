@@ -98,6 +98,18 @@ def test_only_whole_pieces_of_one_value_a_row_go_past_the_l2(F, rows):
             assert lb.linear_launch_shape(F, K, 1 << 12, at, 0)["labels_past"] == 0
 
 
+@pytest.mark.parametrize("rows", [64, 1000, 4_000_000, 4_000_005])
+def test_one_score_of_a_wide_row_stays_out_of_the_way_of_its_label(rows):
+    """From 64 features on the score is stored non-temporally with and without a label, and the label past the L2; below,
+    and with several outputs, scores go past the L2."""
+    at = 1 << 20
+    for F, K in ((64, 1), (90, 1), (300, 1), (63, 1), (90, 7)):
+        past = F < 64 or K > 1
+        assert lb.linear_launch_shape(F, K, 1 << 12, at, 0)["scores_past"] == past
+        s = lb.linear_launch_shape(F, K, 1 << 12, at, at + 4 * rows * K)
+        assert s["scores_past"] == past and s["labels_past"] == (rows % 16 == 0 or (K == 1 and F >= 64))
+
+
 # ---------------------------------------------------------------- GPU parity
 def _run(model, X):
     import torch
