@@ -23,12 +23,12 @@ typedef struct linear_launch_t {
 } linear_launch_t;
 
 /*
- * The launch of a call whose X, scores and labels are at these addresses (0: not asked for), on a device whose workgroups
+ * The launch of a call on n_rows rows whose X, scores and labels are at these addresses (0: not asked for), on a device whose workgroups
  * may have `lds_limit` bytes of LDS.
  * Returns LINEAR_OK, LINEAR_EINVAL (null pointer, counts below 1) or LINEAR_ELIMIT.
  */
-int linear_launch_shape(int32_t n_features, int32_t n_outputs, uintptr_t x, uintptr_t scores, uintptr_t labels,
-                        int64_t lds_limit, linear_launch_t *out);
+int linear_launch_shape(int32_t n_features, int32_t n_outputs, int64_t n_rows, uintptr_t x, uintptr_t scores,
+                        uintptr_t labels, int64_t lds_limit, linear_launch_t *out);
 
 #ifdef __cplusplus
 }

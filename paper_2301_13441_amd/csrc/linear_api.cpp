@@ -169,12 +169,12 @@ int linear_predict(const linear_model *m, const float *X, int64_t n_rows, void *
     return e == hipSuccess ? LINEAR_OK : LINEAR_EHIP;
 }
 
-int linear_launch_shape(int32_t n_features, int32_t n_outputs, uintptr_t x, uintptr_t scores, uintptr_t labels, int64_t lds_limit,
-                        linear_launch_t *out)
+int linear_launch_shape(int32_t n_features, int32_t n_outputs, int64_t n_rows, uintptr_t x, uintptr_t scores, uintptr_t labels,
+                        int64_t lds_limit, linear_launch_t *out)
 {
-    if (!out || n_features < 1 || n_outputs < 1) return LINEAR_EINVAL;
-    if (n_features > LINEAR_MAX_FEATURES || n_outputs > LINEAR_MAX_OUTPUTS) return LINEAR_ELIMIT;
-    const LinearPlan p = plan_linear(n_features, n_outputs, x, scores, labels, lds_limit);
+    if (!out || n_features < 1 || n_outputs < 1 || n_rows < 1) return LINEAR_EINVAL;
+    if (n_features > LINEAR_MAX_FEATURES || n_outputs > LINEAR_MAX_OUTPUTS || n_rows > LINEAR_MAX_ROWS) return LINEAR_ELIMIT;
+    const LinearPlan p = plan_linear(n_features, n_outputs, n_rows, x, scores, labels, lds_limit);
     *out = linear_launch_t{p.rows, p.padded, p.width, p.once, p.lds_bytes, p.scores_past, p.labels_past};
     return LINEAR_OK;
 }

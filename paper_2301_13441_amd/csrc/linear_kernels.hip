@@ -415,7 +415,7 @@ hipError_t launch_linear(const LinDev &m, const float *X, int64_t n_rows, float 
                          hipStream_t stream)
 {
     if (n_rows <= 0) return hipSuccess;
-    const LinearPlan p = plan_linear(m.n_features, m.n_outputs, reinterpret_cast<uintptr_t>(X), reinterpret_cast<uintptr_t>(scores),
+    const LinearPlan p = plan_linear(m.n_features, m.n_outputs, n_rows, reinterpret_cast<uintptr_t>(X), reinterpret_cast<uintptr_t>(scores),
                                      reinterpret_cast<uintptr_t>(labels), m.lds_limit);
     LinearFn fn = pick(p, m.kp);
     if (!fn) return hipErrorInvalidValue;

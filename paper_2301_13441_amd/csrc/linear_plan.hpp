@@ -47,11 +47,18 @@ constexpr int rows_tile_floats(int n_features, bool padded) { return LANES * n_f
 // (us, scores non-temporal / past the L2: 4M x 90 213.1 / 212.6, 5.6M x 90 296.2 / 298.4, 667,000 x 150 67.9 / 69.6, 1.56M x 64
 // 63.4 / 62.3; with a label, results written over 4M x 90 223.5 / 226.4, 2.2M x 90 124.8 / 126.2, 3.1M x 64 128.6 / 127.2, and in
 // new places 4M x 90 224.0 / 235.8, 4.5M x 80 235.8 / 245.6, 5.6M x 64 and five more rows 235.8 / 263.3).
+// Two or three scores of a row of 56 features or more, and their label, do not either as long as X is small beside the 256 MB
+// cache before the memory, which then serves the reads that the writes would hold up (us, kept / past the L2: two 234,000 x 64
+// 13.2 / 14.1, 1.09M x 64 46.1 / 46.8, 1.25M x 80 68.8 / 72.6, 667,000 x 90 42.2 / 44.0, 313,000 x 128 26.1 / 26.9, three 500,000 x
+// 80 33.9 / 35.4; from 2^27 floats of X on two 2.3M x 64 99.5 / 96.1, 1.7M x 90 98.1 / 96.6, three 1.9M x 80 114.3 / 111.9; five
+// 444,000 x 90 38.1 / 38.7, 625,000 x 64 35.1 / 34.7; two 1M x 48 35.8 / 34.9).
 // A wave's 64 scores of one output, or its labels, are whole pieces of 64 bytes only if the first of them begins one.  Elsewhere
 // two waves share a piece, which past the L2 goes to memory once for each (one output and label, where labels begin behind the
 // scores of an odd number of rows, and results that are not written over and over, us, both past the L2 / labels kept: 20M x 10
 // 198 / 165, 16M x 13 196 / 167, 7.1M x 28 163 / 143, 7.5M x 48 273 / 247; two outputs, 31M x 8 249 / 234).  16 bytes per lane
 // of a tile's several scores do not mind (5.4M x 28, 5 outputs, 4 to 12 bytes off: 119.9, on the boundary 118.9).
+constexpr int FEW_COLUMNS = 3, FEW_COLUMNS_FEATURES = 56;
+constexpr int64_t FEW_COLUMNS_X = int64_t{1} << 27;  // floats
 constexpr int FEW_WRITES_FEATURES = 64;
 constexpr uintptr_t WRITE_PIECE = 64;
 
@@ -65,12 +72,13 @@ struct LinearPlan {
 };
 
 // x, scores, labels: addresses, 0 of what is not asked for.  lds_limit: bytes of LDS that a workgroup may have; a tile beyond it goes by chunks.
-inline LinearPlan plan_linear(int n_features, int n_outputs, uintptr_t x, uintptr_t scores, uintptr_t labels, int64_t lds_limit)
+inline LinearPlan plan_linear(int n_features, int n_outputs, int64_t n_rows, uintptr_t x, uintptr_t scores, uintptr_t labels, int64_t lds_limit)
 {
     LinearPlan p;
     const bool few_writes = n_features >= FEW_WRITES_FEATURES;
-    p.scores_past = scores && (n_outputs > 1 || (scores % WRITE_PIECE == 0 && !few_writes));
-    p.labels_past = labels && (labels % WRITE_PIECE == 0 || (n_outputs == 1 && few_writes));
+    const bool kept = n_outputs > 1 && n_outputs <= FEW_COLUMNS && n_features >= FEW_COLUMNS_FEATURES && n_rows * n_features < FEW_COLUMNS_X;
+    p.scores_past = scores && (n_outputs > 1 ? !kept : scores % WRITE_PIECE == 0 && !few_writes);
+    p.labels_past = labels && !kept && (labels % WRITE_PIECE == 0 || (n_outputs == 1 && few_writes));
     if (takes_rows(n_features, n_outputs) && x % 16 == 0) {
         p.padded = padded_rows(n_features);
         const int64_t lds = static_cast<int64_t>(sizeof(float)) * ROWS_WAVES * rows_tile_floats(n_features, p.padded);

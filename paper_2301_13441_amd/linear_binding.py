@@ -50,7 +50,7 @@ def _lib():
         lib.linear_predict.restype = ctypes.c_int
         lib.linear_predict.argtypes = [_p, _p, _i64, _p, _p]
         lib.linear_launch_shape.restype = ctypes.c_int
-        lib.linear_launch_shape.argtypes = [_i32, _i32, *[ctypes.c_size_t] * 3, _i64, ctypes.POINTER(_LinearLaunch)]
+        lib.linear_launch_shape.argtypes = [_i32, _i32, _i64, *[ctypes.c_size_t] * 3, _i64, ctypes.POINTER(_LinearLaunch)]
         lib.linear_strerror.restype = ctypes.c_char_p
         lib.linear_strerror.argtypes = [ctypes.c_int]
         _ready = True
@@ -173,10 +173,11 @@ def linear_load(model) -> Linear:
     return Linear(h, int(model.n_features), int(model.n_outputs))
 
 
-def linear_launch_shape(n_features: int, n_outputs: int, x: int = 0, scores: int = 0, labels: int = 0, lds_limit: int = 160 * 1024) -> dict:
-    """What a call launches whose X, scores and labels are at these addresses (include/linear_testing.h); no GPU needed."""
+def linear_launch_shape(n_features: int, n_outputs: int, x: int = 0, scores: int = 0, labels: int = 0, lds_limit: int = 160 * 1024,
+                        n_rows: int = 1) -> dict:
+    """What a call on n_rows rows launches whose X, scores and labels are at these addresses (include/linear_testing.h); no GPU needed."""
     s = _LinearLaunch()
-    rc = _lib().linear_launch_shape(n_features, n_outputs, x, scores, labels, lds_limit, ctypes.byref(s))
+    rc = _lib().linear_launch_shape(n_features, n_outputs, n_rows, x, scores, labels, lds_limit, ctypes.byref(s))
     if rc != 0:
         raise LinearError(rc, "linear_launch_shape")
     return {name: int(getattr(s, name)) for name, _ in _LinearLaunch._fields_}

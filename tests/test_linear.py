@@ -62,10 +62,10 @@ def test_testing_header_declares_what_the_library_exports():
     assert set(re.findall(r"\b(linear_[a-z_]+)\s*\(", header)) == set(lb.LINEAR_TESTING_EXPORTS)
     lib = lb._lib()
     assert all(hasattr(lib, name) for name in lb.LINEAR_TESTING_EXPORTS)
-    for bad in ((0, 1, -1), (4, 0, -1), (65537, 1, -7), (4, 33, -7)):
+    for bad in ((0, 1, 1, -1), (4, 0, 1, -1), (4, 1, 0, -1), (65537, 1, 1, -7), (4, 33, 1, -7), (4, 1, 10**9 + 1, -7)):
         with pytest.raises(lb.LinearError) as e:
-            lb.linear_launch_shape(*bad[:2])
-        assert e.value.code == bad[2]
+            lb.linear_launch_shape(*bad[:2], n_rows=bad[2])
+        assert e.value.code == bad[3]
 
 
 @pytest.mark.parametrize("F", [96, 104, 112, 128, 129, 130, 144, 150, 155, 156])
@@ -84,7 +84,7 @@ def test_whole_rows_only_where_their_tile_fits_the_workgroup(F):
 
 
 @pytest.mark.parametrize("rows", [64, 65, 70, 1000, 4096 + 16, 20_000_005])
-@pytest.mark.parametrize("F", [8, 28, 48, 63])
+@pytest.mark.parametrize("F", [8, 28, 48, 55])
 def test_only_whole_pieces_of_one_value_a_row_go_past_the_l2(F, rows):
     """Labels lie behind the scores, and the buffer may begin at any float: where that leaves a wave's run of them off a
     64-byte boundary, two waves would write the same piece of memory past the L2 one after the other."""
@@ -108,6 +108,17 @@ def test_one_score_of_a_wide_row_stays_out_of_the_way_of_its_label(rows):
         assert lb.linear_launch_shape(F, K, 1 << 12, at, 0)["scores_past"] == past
         s = lb.linear_launch_shape(F, K, 1 << 12, at, at + 4 * rows * K)
         assert s["scores_past"] == past and s["labels_past"] == (rows % 16 == 0 or (K == 1 and F >= 64))
+
+
+def test_results_of_two_or_three_outputs_of_a_small_batch_of_wide_rows_are_kept_in_the_l2():
+    past = lambda F, K, rows: lb.linear_launch_shape(F, K, 1 << 12, 1 << 20, 0, n_rows=rows)["scores_past"]
+    for F in (56, 64, 90, 128, 300):
+        most = (1 << 27) // F
+        for K, kept in ((2, True), (3, True), (4, False), (10, False)):
+            assert past(F, K, 1) == past(F, K, most - 1) == (not kept)
+            assert lb.linear_launch_shape(F, K, 1 << 12, 1 << 20, 1 << 21, n_rows=most - 1)["labels_past"] == (not kept)
+            assert past(F, K, most + 1) == past(F, K, 10**9) == 1
+    assert past(55, 2, 1000) == past(28, 3, 1000) == 1
 
 
 # ---------------------------------------------------------------- GPU parity
