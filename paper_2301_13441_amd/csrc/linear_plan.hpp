@@ -62,6 +62,13 @@ constexpr int64_t FEW_COLUMNS_X = int64_t{1} << 27;  // floats
 constexpr int FEW_WRITES_FEATURES = 64;
 constexpr uintptr_t WRITE_PIECE = 64;
 
+// Chunks that are whole lines are read with the non-temporal policy: nothing reads them again and the caches need not keep them.
+// Elsewhere two chunks share a line, and with that policy it came from memory twice (1M x 300, 2 classes 319 us a call, 240 so;
+// 1.5M x 200 287 and 221; 2M x 128, 10 classes the other way 191 and 215).  More than 16 outputs take longer than that line and
+// do better with it all the same (100M values, with the cache / non-temporal: 17 outputs, 200 features 210 / 191, 112 226 / 197;
+// 20 outputs, 132 225 / 211, 300 203.6 / 202.3, 108 232 / 234; 32 outputs, 200 300 / 270; 16 outputs, 132 133 / 149).
+constexpr int ONCE_OUTPUTS = 16;
+
 struct LinearPlan {
     int32_t rows = 0;       // 1: the whole-row kernel, 0: chunks
     int32_t padded = 0;     // whole-row kernel: the padded tile
@@ -91,7 +98,7 @@ inline LinearPlan plan_linear(int n_features, int n_outputs, int64_t n_rows, uin
     }
     // chunks: the widest load that every row start and every chunk start is aligned for
     p.width = n_features % 4 == 0 && x % 16 == 0 ? 4 : n_features % 2 == 0 && x % 8 == 0 ? 2 : 1;
-    p.once = n_features % CHUNK == 0 && x % 128 == 0;
+    p.once = p.width == 4 && ((n_features % CHUNK == 0 && x % 128 == 0) || n_outputs > ONCE_OUTPUTS);
     return p;
 }
 

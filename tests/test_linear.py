@@ -121,6 +121,16 @@ def test_results_of_two_or_three_outputs_of_a_small_batch_of_wide_rows_are_kept_
     assert past(55, 2, 1000) == past(28, 3, 1000) == 1
 
 
+@pytest.mark.parametrize("F", [108, 112, 128, 130, 132, 160, 200, 201, 300])
+def test_chunks_are_kept_in_the_caches_where_they_share_lines_and_outputs_are_few(F):
+    for K in (2, 10, 16, 17, 20, 32):
+        for x in (0, 4, 8, 16, 64, 128):
+            s = lb.linear_launch_shape(F, K, (1 << 20) + x)
+            width = 4 if F % 4 == 0 and x % 16 == 0 else 2 if F % 2 == 0 and x % 8 == 0 else 1
+            assert s["whole_rows"] == 0 and s["load_width"] == width
+            assert s["once"] == (width == 4 and (K > 16 or (F % 32 == 0 and x % 128 == 0)))
+
+
 # ---------------------------------------------------------------- GPU parity
 def _run(model, X):
     import torch
