@@ -109,7 +109,7 @@ int linear_load(const linear_desc *desc, linear_model **out)
     m->dev.n_features = F;
     m->dev.n_outputs = K;
     m->dev.kp = kp;
-    m->dev.transform = desc->transform;
+    m->dev.finish = desc->transform;
     m->dev.output = desc->output;
     *out = m;
     return LINEAR_OK;

@@ -9,12 +9,14 @@
 
 namespace linear_impl {
 
+enum { TRANSFORM = 255, SCORES_PAST = 256, LABELS_PAST = 512 };  // LinDev::finish
+
 struct LinDev {
     const double *weight;  // [n_features rounded up to a multiple of 32][kp]: float64, zero-padded
     const double *bias;    // [kp]
     int32_t n_features, n_outputs, kp;
-    int32_t transform, output;
-    int32_t scores_past, labels_past;  // set per launch (LinearPlan)
+    int32_t finish;  // LINEAR_TRANSFORM_*, and per launch SCORES_PAST and LABELS_PAST: one register, of which many outputs spill some
+    int32_t output;
     int64_t lds_limit;  // bytes of LDS that a workgroup may have
 };
 

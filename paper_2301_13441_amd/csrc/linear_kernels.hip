@@ -46,7 +46,7 @@ template <int KP>
 __device__ __forceinline__ void finish_linear_row(const LinDev &m, double (&acc)[KP], int64_t row, float *scores,
                                                   int32_t *labels)
 {
-    const int K = m.n_outputs;
+    const int K = m.n_outputs, transform = m.finish & TRANSFORM;
     double best = acc[0];
     int best_k = 0;
 #pragma unroll
@@ -57,15 +57,15 @@ __device__ __forceinline__ void finish_linear_row(const LinDev &m, double (&acc)
         }
     if (labels) {
         int lab = best_k;
-        if (K == 1) lab = (m.transform == LINEAR_TRANSFORM_SIGMOID) ? (best > 0.0) : (best > 0.5);
-        if (m.labels_past) __hip_atomic_store(&labels[row], lab, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (K == 1) lab = (transform == LINEAR_TRANSFORM_SIGMOID) ? (best > 0.0) : (best > 0.5);
+        if (m.finish & LABELS_PAST) __hip_atomic_store(&labels[row], lab, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         else if (KP == 1) __builtin_nontemporal_store(lab, &labels[row]);
         else labels[row] = lab;
     }
     if (!scores) return;
     float *dst = scores + row * K;
-    const bool past = m.scores_past;
-    if (m.transform == LINEAR_TRANSFORM_SOFTMAX) {
+    const bool past = m.finish & SCORES_PAST;
+    if (transform == LINEAR_TRANSFORM_SOFTMAX) {
         double z = 0.0;
 #pragma unroll
         for (int k = 0; k < KP; ++k)
@@ -78,7 +78,7 @@ __device__ __forceinline__ void finish_linear_row(const LinDev &m, double (&acc)
 #pragma unroll
         for (int k = 0; k < KP; ++k)
             if (k < K) store_score<KP>(static_cast<float>(acc[k] * inv), &dst[k], past);
-    } else if (m.transform == LINEAR_TRANSFORM_SIGMOID) {
+    } else if (transform == LINEAR_TRANSFORM_SIGMOID) {
 #pragma unroll
         for (int k = 0; k < KP; ++k)
             if (k < K) store_score<KP>(static_cast<float>(1.0 / (1.0 + exp(-acc[k]))), &dst[k], past);
@@ -108,15 +108,17 @@ __device__ __forceinline__ void finish_linear_tile(const LinDev &m, double (&acc
     typedef uint32_t U4 __attribute__((ext_vector_type(4)));
     typedef uint32_t LooseU4 __attribute__((ext_vector_type(4), aligned(4)));
     const auto piece = __builtin_amdgcn_make_buffer_rsrc(dst, 0, n * 4, 0x00027000);
-    for (int i = lane * 4; i < n; i += LANES * 4) {
-        if (i + 4 <= n) {
-            const LooseU4 v = *reinterpret_cast<const LooseU4 *>(out + i);
-            if (m.scores_past) __builtin_amdgcn_raw_buffer_store_b128(U4{v.x, v.y, v.z, v.w}, piece, i * 4, 0, 16 /* sc1 */);
-            else *reinterpret_cast<LooseU4 *>(dst + i) = v;
-        } else {
-            for (int j = i; j < n; ++j) dst[j] = out[j];
+    const auto copy = [&](auto store) {
+        for (int i = lane * 4; i < n; i += LANES * 4) {
+            if (i + 4 <= n) {
+                store(*reinterpret_cast<const LooseU4 *>(out + i), i);
+            } else {
+                for (int j = i; j < n; ++j) dst[j] = out[j];
+            }
         }
-    }
+    };
+    if (m.finish & SCORES_PAST) copy([&](LooseU4 v, int i) { __builtin_amdgcn_raw_buffer_store_b128(U4{v.x, v.y, v.z, v.w}, piece, i * 4, 0, 16 /* sc1 */); });
+    else copy([&](LooseU4 v, int i) { *reinterpret_cast<LooseU4 *>(dst + i) = v; });
 }
 
 // The lane's share of a 64 x 32 chunk, as V-float pieces: piece i is columns [V * (lane % (32 / V)),
@@ -198,9 +200,8 @@ __device__ __forceinline__ void park_chunk(float *xs, const Piece<V> (&pre)[CHUN
     }
 }
 
-// V: floats per global load (4 when rows are 16-byte aligned, i.e. F % 4 == 0; else 2 or 1).  ONCE: a chunk is whole lines,
-// which nothing reads again and the caches need not keep; elsewhere two chunks share a line, and with that policy it came from
-// memory twice (1M x 300, 2 classes 319 us a call, 240 so; 1.5M x 200 287 and 221; 2M x 128, 10 classes the other way 191 and 215).
+// V: floats per global load (4 when rows are 16-byte aligned, i.e. F % 4 == 0; else 2 or 1).  ONCE: the loads are non-temporal
+// (plan_linear).
 template <int KP, int V, bool ONCE>
 __global__ __launch_bounds__(LANES *LWAVES) void linear_kernel(LinDev m, const float *__restrict__ X,
                                                                 int64_t n_rows, float *scores, int32_t *labels)
@@ -423,8 +424,7 @@ hipError_t launch_linear(const LinDev &m, const float *X, int64_t n_rows, float 
     const int64_t n_blocks = (n_rows + LANES * waves - 1) / (LANES * waves);
     if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     LinDev launched = m;
-    launched.scores_past = p.scores_past;
-    launched.labels_past = p.labels_past;
+    launched.finish |= (p.scores_past ? SCORES_PAST : 0) | (p.labels_past ? LABELS_PAST : 0);
     hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(n_blocks)), dim3(LANES * waves), p.lds_bytes, stream, launched, X, n_rows,
                        scores, labels);
     return hipGetLastError();
