@@ -28,7 +28,6 @@ typedef const __attribute__((address_space(4))) double *WeightPtr;
 typedef const double *WeightPtr;  // host pass: the kernel body is only parsed
 #endif
 
-constexpr int LWAVES = 4;
 constexpr int STRIDE = CHUNK + 4;  // row pitch of the LDS tile in floats: 16-byte aligned rows, and the
                                    // 8 lanes of a 128-bit read phase fall into 8 different bank groups
 
@@ -203,14 +202,14 @@ __device__ __forceinline__ void park_chunk(float *xs, const Piece<V> (&pre)[CHUN
 // V: floats per global load (4 when rows are 16-byte aligned, i.e. F % 4 == 0; else 2 or 1).  ONCE: the loads are non-temporal
 // (plan_linear).
 template <int KP, int V, bool ONCE>
-__global__ __launch_bounds__(LANES *LWAVES) void linear_kernel(LinDev m, const float *__restrict__ X,
+__global__ __launch_bounds__(LANES *CHUNK_WAVES) void linear_kernel(LinDev m, const float *__restrict__ X,
                                                                 int64_t n_rows, float *scores, int32_t *labels)
 {
-    __shared__ __align__(16) float tile[LWAVES][LANES * STRIDE];
+    __shared__ __align__(16) float tile[CHUNK_WAVES][LANES * STRIDE];
     const int lane = threadIdx.x & (LANES - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float *xs = tile[wave];
-    const int64_t row0 = (static_cast<int64_t>(blockIdx.x) * LWAVES + wave) * LANES;
+    const int64_t row0 = (static_cast<int64_t>(blockIdx.x) * CHUNK_WAVES + wave) * LANES;
     if (row0 >= n_rows) return;  // wave-uniform
     const int F = m.n_features;
     const int64_t left = n_rows - row0;
@@ -420,7 +419,7 @@ hipError_t launch_linear(const LinDev &m, const float *X, int64_t n_rows, float 
                                      reinterpret_cast<uintptr_t>(labels), m.lds_limit);
     LinearFn fn = pick(p, m.kp);
     if (!fn) return hipErrorInvalidValue;
-    const int waves = p.rows ? ROWS_WAVES : LWAVES;
+    const int waves = p.rows ? ROWS_WAVES : CHUNK_WAVES;
     const int64_t n_blocks = (n_rows + LANES * waves - 1) / (LANES * waves);
     if (n_blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     LinDev launched = m;

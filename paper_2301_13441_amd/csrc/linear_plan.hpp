@@ -9,7 +9,8 @@ namespace linear_impl {
 
 constexpr int LANES = 64;
 constexpr int CHUNK = 32;      // features per pass of the chunked kernel
-constexpr int ROWS_WAVES = 2;  // waves per workgroup of the whole-row kernel
+constexpr int CHUNK_WAVES = 4;  // waves per workgroup of the chunked kernel
+constexpr int ROWS_WAVES = 2;   // of the whole-row kernel
 constexpr int PIECE = LANES * 4;  // floats that one load of the whole-row kernel brings to LDS
 constexpr int PAD = 4;            // floats left free behind a piece in the padded form
 constexpr int STEP = 16;          // features of a step of the padded form
@@ -24,14 +25,37 @@ inline int padded_outputs(int n_outputs)
     return 0;
 }
 
-// The whole-row kernel, or chunks.  Beyond 96 features multiples of 32 go by chunks, whose lines are whole; of the others
-// those of which three workgroups fit a CU (up to 104 features) go by rows, and, with one output, those of which two do (us,
-// chunks with the cache / rows: 100 features, one output 243 / 178, 5 classes 178 / 166; 130, one output 271 / 183; 112
-// features, 5 classes 189 / 198; 150, 12 classes 217 / 279).
-inline bool takes_rows(int n_features, int n_outputs)
+// The whole-row kernel, or chunks.  Up to 96 features always the former; beyond, multiples of 32 go by chunks, whose lines are
+// whole; of the others those of which three row workgroups fit a CU (up to 104 features) and, with one output, those of which
+// two do (150M values, us, chunks / rows: 100 features, one output 243 / 178; 130, one output 271 / 183; 100 features, 2 outputs
+// 132 / 103, 5 outputs 136 / 128; 112 features, 5 classes 189 / 198; 150, 12 classes 217 / 279) may go by rows.  What decides is how
+// the CUs share the workgroups, which own 128 rows and 256 rows:
+// - rows that one round of row workgroups holds: chunks leave CUs with one workgroup and others with two (80,000 x 100, 8 outputs
+//   18.2 / 14.2; 80,000 x 104, 20 outputs 42.5 / 28.6; 16 outputs 26.8 / 18.9; one output, 20,000 x 130 9.7 / 6.4), but for 7 or 8
+//   outputs where every chunk workgroup has a CU to itself (40,000 x 104, 8 outputs 10.6 / 12.6);
+// - a rest behind a round of row workgroups costs as much as the round (120,000 x 104, 2 outputs 13.1 / 18.6, 6 outputs 18.1 / 20.5,
+//   16 outputs, 100 features 28.6 / 31.8; 120,000 x 98, 4 outputs 14.8 / 17.0), until there are many (250,000 x 100, 2 outputs
+//   22.7 / 22.8, 500,000 x 104, 6 outputs 54 / 52); more than 6 outputs stay with chunks (1.44M x 104, 8 outputs 138 / 161, 16 outputs
+//   182 / 229, 20 outputs 284 / 351), unless these load less than 16 bytes at a time (1.53M x 98, 20 outputs 375 / 359);
+// - one output, rows of a multiple of 8 floats, which begin in few LDS banks, from the second row workgroup of a CU on (90,000 x 112
+//   10.6 / 13.4, 140,000 x 152 20.3 / 26.7, 400,000 x 120 41.6 / 45.8, 600,000 x 136 68.4 / 65.7, 1M x 112 82.9 / 80.1).
+constexpr int64_t CUS = 256;
+constexpr int64_t CHUNK_ROUND = CUS * CHUNK_WAVES * LANES;      // rows of a chunk workgroup for every CU
+constexpr int64_t ROWS_ROUND = 3 * CUS * ROWS_WAVES * LANES;    // of three row workgroups
+constexpr int64_t MANY_ROUNDS = int64_t{1} << 18, MANY_ROUNDS_OF_TWO = int64_t{1} << 19;  // rows
+
+inline bool takes_rows(int n_features, int n_outputs, int64_t n_rows)
 {
     if (n_features <= ROWS_MAX_FEATURES) return true;
-    return n_features % CHUNK != 0 && n_features <= (n_outputs == 1 ? ROWS_MAX_OF_TWO : ROWS_MAX_OF_THREE);
+    if (n_features % CHUNK == 0) return false;
+    if (n_outputs == 1 && n_features > ROWS_MAX_OF_THREE)
+        return n_features <= ROWS_MAX_OF_TWO && (n_features % 8 != 0 || n_rows <= CUS * ROWS_WAVES * LANES || n_rows > MANY_ROUNDS_OF_TWO);
+    if (n_features > ROWS_MAX_OF_THREE) return false;
+    const bool loose = n_features % 4 != 0;  // chunks load these rows by halves or single floats
+    if (n_outputs == 1) return true;
+    if (n_rows <= ROWS_ROUND) return n_outputs <= 6 || n_outputs > 8 || n_rows > CHUNK_ROUND;
+    if (n_outputs <= 6) return n_rows > MANY_ROUNDS || (loose && n_outputs <= 3);
+    return loose && n_outputs > 16;
 }
 
 // Rows of a multiple of 16 floats begin in two LDS banks or one and get the padded tile.
@@ -86,7 +110,7 @@ inline LinearPlan plan_linear(int n_features, int n_outputs, int64_t n_rows, uin
     const bool kept = n_outputs > 1 && n_outputs <= FEW_COLUMNS && n_features >= FEW_COLUMNS_FEATURES && n_rows * n_features < FEW_COLUMNS_X;
     p.scores_past = scores && (n_outputs > 1 ? !kept : scores % WRITE_PIECE == 0 && !few_writes);
     p.labels_past = labels && !kept && (labels % WRITE_PIECE == 0 || (n_outputs == 1 && few_writes));
-    if (takes_rows(n_features, n_outputs) && x % 16 == 0) {
+    if (takes_rows(n_features, n_outputs, n_rows) && x % 16 == 0) {
         p.padded = padded_rows(n_features);
         const int64_t lds = static_cast<int64_t>(sizeof(float)) * ROWS_WAVES * rows_tile_floats(n_features, p.padded);
         if (lds <= lds_limit) {

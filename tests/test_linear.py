@@ -131,6 +131,32 @@ def test_chunks_are_kept_in_the_caches_where_they_share_lines_and_outputs_are_fe
             assert s["once"] == (width == 4 and (K > 16 or (F % 32 == 0 and x % 128 == 0)))
 
 
+def test_where_rows_of_more_than_96_features_go_whole():
+    """One round of row workgroups is 98,304 rows where three of them fit a CU; a rest behind it costs another round."""
+    rows = lambda F, K, n: lb.linear_launch_shape(F, K, 1 << 20, n_rows=n)["whole_rows"]
+    for F in (97, 98, 100, 103, 104):
+        loose = F % 4 != 0
+        for n in (1, 1000, 65_536, 65_537, 98_304, 98_305, 200_000, 1 << 18, (1 << 18) + 1, 2_000_000):
+            assert rows(F, 1, n) == 1
+            for K in (2, 3):
+                assert rows(F, K, n) == (loose or n <= 98_304 or n > 1 << 18), (F, K, n)
+            for K in (4, 6):
+                assert rows(F, K, n) == (n <= 98_304 or n > 1 << 18), (F, K, n)
+            for K in (7, 8):
+                assert rows(F, K, n) == (65_536 < n <= 98_304), (F, K, n)
+            for K in (9, 16):
+                assert rows(F, K, n) == (n <= 98_304), (F, K, n)
+            for K in (17, 32):
+                assert rows(F, K, n) == (loose or n <= 98_304), (F, K, n)
+    for F in (105, 108, 112, 120, 130, 136, 144, 152, 155, 156):
+        for n in (1, 32_768, 32_769, 90_000, 1 << 19, (1 << 19) + 1, 4_000_000):
+            assert rows(F, 1, n) == (F % 8 != 0 or n <= 32_768 or n > 1 << 19), (F, n)
+            assert rows(F, 2, n) == 0
+    for K in (1, 2, 10, 32):
+        for n in (1, 90_000, 4_000_000):
+            assert rows(96, K, n) == rows(64, K, n) == 1 and rows(128, K, n) == rows(157, K, n) == rows(160, K, n) == 0
+
+
 # ---------------------------------------------------------------- GPU parity
 def _run(model, X):
     import torch
@@ -197,6 +223,14 @@ def test_tiles_of_rows_with_and_without_padding(F, K, rows):
     output and several, and the narrowest by chunks; partial tiles, whose last floats are copied one by one."""
     m = _rand_model(5 * F + K, F, K, TRANSFORM_SOFTMAX if K > 1 else TRANSFORM_SIGMOID)
     _check(m, np.random.default_rng(F + rows).standard_normal((rows, F)).astype(np.float32))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("F,K,rows", [(100, 2, 98_304), (100, 2, 98_305), (98, 4, 98_369), (104, 8, 65_536), (104, 8, 65_537), (101, 12, 98_311),
+                                      (97, 17, 98_305), (112, 1, 32_768), (112, 1, 32_769), (152, 1, (1 << 19) + 1), (100, 3, (1 << 18) + 1)])
+def test_both_sides_of_the_rows_that_a_round_of_workgroups_holds(F, K, rows):
+    m = _rand_model(F + K, F, K, TRANSFORM_SOFTMAX if K > 1 else TRANSFORM_SIGMOID)
+    _check(m, np.random.default_rng(rows).standard_normal((rows, F), dtype=np.float32))
 
 
 @pytest.mark.gpu
