@@ -90,8 +90,26 @@ constexpr uintptr_t WRITE_PIECE = 64;
 // Elsewhere two chunks share a line, and with that policy it came from memory twice (1M x 300, 2 classes 319 us a call, 240 so;
 // 1.5M x 200 287 and 221; 2M x 128, 10 classes the other way 191 and 215).  More than 16 outputs take longer than that line and
 // do better with it all the same (100M values, with the cache / non-temporal: 17 outputs, 200 features 210 / 191, 112 226 / 197;
-// 20 outputs, 132 225 / 211, 300 203.6 / 202.3, 108 232 / 234; 32 outputs, 200 300 / 270; 16 outputs, 132 133 / 149).
-constexpr int ONCE_OUTPUTS = 16;
+// 20 outputs, 132 225 / 211, 300 203.6 / 202.3, 108 232 / 234; 32 outputs, 200 300 / 270; 16 outputs, 132 133 / 149).  So does a
+// batch whose chunk workgroups have a CU each, where the L1 still holds the line when the next chunk comes for its rest (50,000 x
+// 300, 10 outputs 34.9 / 25.4; 65,536 x 144, one output 12.3 / 9.2; 50,000 x 200, 3 outputs 16.3 / 12.9; 70,000 x 200, one output the
+// other way 16.3 / 20.0), unless X is small enough for the L2s to hold it (10,000 x 300, one output 10.9 / 13.2, 30,000 x 132, 3
+// outputs 8.5 / 9.6; 30,000 x 200, 10 outputs 21.2 / 19.1); and one whose CUs have two, if the outputs take long to sum up (16
+// outputs, 100,000 x 200 42.8 / 36.2, 131,072 x 132 35.9 / 33.0; 12 outputs, 100,000 x 200 34.2 / 31.1; 8 outputs, 100,000 x 112 18.4 /
+// 16.1, 131,072 x 112 20.1 / 19.1, 100,000 x 164 24.1 / 25.2, 70,000 x 300 33.1 / 35.5; 3 outputs, 70,000 x 112 11.6 / 11.7), or even
+// four (16 outputs, 200,000 x 200 73.4 / 66.9, 300 features 103 / 94.5, 132 47 / 51.6; 8 outputs, 200,000 x 200 46.3 / 51.8).
+constexpr int ONCE_OUTPUTS = 16, ONCE_LONG_OUTPUTS = 6, ONCE_LONGER_OUTPUTS = 10, ONCE_LONGEST_OUTPUTS = 12;
+constexpr int ONCE_LONGEST_FEATURES = 160;
+constexpr int64_t ONCE_X = int64_t{1} << 22, ONCE_LONG_X = 7 * (int64_t{1} << 21);  // floats
+
+inline bool reads_once(int n_features, int n_outputs, int64_t n_rows, uintptr_t x)
+{
+    if (n_outputs > ONCE_OUTPUTS || (n_features % CHUNK == 0 && x % 128 == 0)) return true;
+    const int64_t floats = n_rows * n_features;
+    if (n_rows <= CHUNK_ROUND) return floats > ONCE_X;
+    if (n_rows <= 2 * CHUNK_ROUND) return n_outputs > ONCE_LONGER_OUTPUTS || (n_outputs > ONCE_LONG_OUTPUTS && floats <= ONCE_LONG_X);
+    return n_rows <= 4 * CHUNK_ROUND && n_outputs > ONCE_LONGEST_OUTPUTS && n_features > ONCE_LONGEST_FEATURES;
+}
 
 struct LinearPlan {
     int32_t rows = 0;       // 1: the whole-row kernel, 0: chunks
@@ -122,7 +140,7 @@ inline LinearPlan plan_linear(int n_features, int n_outputs, int64_t n_rows, uin
     }
     // chunks: the widest load that every row start and every chunk start is aligned for
     p.width = n_features % 4 == 0 && x % 16 == 0 ? 4 : n_features % 2 == 0 && x % 8 == 0 ? 2 : 1;
-    p.once = p.width == 4 && ((n_features % CHUNK == 0 && x % 128 == 0) || n_outputs > ONCE_OUTPUTS);
+    p.once = p.width == 4 && reads_once(n_features, n_outputs, n_rows, x);
     return p;
 }
 

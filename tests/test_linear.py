@@ -125,10 +125,22 @@ def test_results_of_two_or_three_outputs_of_a_small_batch_of_wide_rows_are_kept_
 def test_chunks_are_kept_in_the_caches_where_they_share_lines_and_outputs_are_few(F):
     for K in (2, 10, 16, 17, 20, 32):
         for x in (0, 4, 8, 16, 64, 128):
-            s = lb.linear_launch_shape(F, K, (1 << 20) + x)
+            s = lb.linear_launch_shape(F, K, (1 << 20) + x, n_rows=300_000)
             width = 4 if F % 4 == 0 and x % 16 == 0 else 2 if F % 2 == 0 and x % 8 == 0 else 1
             assert s["whole_rows"] == 0 and s["load_width"] == width
             assert s["once"] == (width == 4 and (K > 16 or (F % 32 == 0 and x % 128 == 0)))
+
+
+@pytest.mark.parametrize("F", [112, 132, 200, 300])
+def test_chunks_of_a_batch_with_a_cu_for_every_workgroup_are_not_kept_in_the_caches(F):
+    once = lambda K, n, x=0: lb.linear_launch_shape(F, K, (1 << 20) + x, n_rows=n)["once"]
+    few = (1 << 22) // F
+    long = max(65_536, min(131_072, 7 * (1 << 21) // F))
+    longest = 131_072 if F <= 160 else 262_144
+    for K, most in ((2, 65_536), (6, 65_536), (7, long), (10, long), (11, 131_072), (12, 131_072), (13, longest), (16, longest)):
+        assert once(K, 1) == once(K, few) == 0 and once(K, few + 1) == once(K, most) == 1 and once(K, most + 1) == 0
+        assert once(K, most, x=8) == 0  # narrower loads
+    assert once(17, 1) == once(17, 10**6) == 1
 
 
 def test_where_rows_of_more_than_96_features_go_whole():
