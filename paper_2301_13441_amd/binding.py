@@ -79,7 +79,7 @@ EXPORTS = ["forest_load", "forest_free", "forest_info", "forest_out_bytes", "for
 # include/forest_testing.h: host-only views into the model compiler, for its tests
 TESTING_EXPORTS = ["forest_pack", "forest_pack_view", "forest_pack_free", "forest_rank_code",
                    "forest_staged_position", "forest_probe_compare_rate", "forest_launch", "forest_packed_launch",
-                   "forest_packed_launch_no_workspace",
+                   "forest_packed_launch_no_workspace", "forest_ids_go_through",
                    "forest_load_form", "forest_pack_form"]
 
 
@@ -123,6 +123,8 @@ def load_library():
     lib.forest_pack_free.argtypes = [_p]
     lib.forest_rank_code.restype = ctypes.c_int
     lib.forest_rank_code.argtypes = [_i32, ctypes.POINTER(ctypes.c_uint16), ctypes.POINTER(ctypes.c_uint16)]
+    lib.forest_ids_go_through.restype = ctypes.c_int
+    lib.forest_ids_go_through.argtypes = [_i32, ctypes.c_size_t]
     lib.forest_staged_position.restype = ctypes.c_int
     lib.forest_staged_position.argtypes = [_i32, _i32, ctypes.POINTER(_i32)]
     for fn in (lib.forest_launch, lib.forest_packed_launch, lib.forest_packed_launch_no_workspace):
@@ -316,6 +318,14 @@ def forest_packed_launch(forest, n_rows: int, leaves: bool = False, form: str = 
         return _launch(call, h, "forest_packed_launch", n_rows, leaves)
     finally:
         lib.forest_pack_free(h)
+
+
+def forest_ids_go_through(n_trees: int, leaf_out: int) -> bool:
+    """Whether the walk kernels write leaf ids of that many trees to that address past the L2."""
+    got = load_library().forest_ids_go_through(int(n_trees), int(leaf_out))
+    if got < 0:
+        raise ForestError(got, "forest_ids_go_through")
+    return bool(got)
 
 
 def forest_probe_compare_rate(iterations: int, device_word, stream=None) -> int:

@@ -69,6 +69,11 @@ int forest_rank_code(int32_t q, uint16_t *code, uint16_t *entry)
     return RANK_CODES;
 }
 
+int forest_ids_go_through(int32_t n_trees, uintptr_t leaf_out)
+{
+    return n_trees < 1 ? FOREST_EINVAL : ids_go_through(n_trees, leaf_out);
+}
+
 int forest_staged_position(int32_t depth, int32_t pos, int32_t *node)
 {
     if (!node || depth < STAGED_MIN_DEPTH || depth > STAGED_TOP_MAX_DEPTH || pos < 0 || pos >= (1 << depth))

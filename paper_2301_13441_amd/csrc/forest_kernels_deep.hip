@@ -34,7 +34,7 @@ namespace {
 
 // What a kernel leaves behind: the sums of one output column, those of several (trees sorted by
 // column), those of vector leaves, or the leaf ids of every tree (FEW: of few trees, leaves_by_fours in forest_plan.hpp).
-enum { DEEP_COLUMN = 0, DEEP_COLUMNS = 1, DEEP_VECTOR = 2, DEEP_LEAVES = 3, DEEP_FEW_LEAVES = 4 };
+enum { DEEP_COLUMN = 0, DEEP_COLUMNS = 1, DEEP_VECTOR = 2, DEEP_LEAVES = 3, DEEP_LEAVES_THROUGH = 4, DEEP_FEW_LEAVES = 5 };
 
 constexpr uint32_t TOP_BYTES = DEEP_TOP_WORDS * sizeof(WalkNode);     // of a tree
 constexpr uint32_t NODES_BYTES = TOP_BYTES / 2;                        // its nodes, and as much for its first units
@@ -109,7 +109,7 @@ __device__ __forceinline__ void deep_rows(const DevModel m, const float *__restr
                                           int32_t *labels, int32_t *leaf_out)
 {
     constexpr int ROWS = NR * TILE;
-    constexpr bool FEW = MODE == DEEP_FEW_LEAVES, LEAVES = MODE == DEEP_LEAVES || FEW;
+    constexpr bool FEW = MODE == DEEP_FEW_LEAVES, LEAVES = MODE == DEEP_LEAVES || MODE == DEEP_LEAVES_THROUGH || FEW;
     constexpr int W = LEAVES ? 1 : WP;
     constexpr int NT = 2;  // trees whose units are walked together
     static_assert(MODE == DEEP_VECTOR || WP == 1, "scalar leaves");
@@ -286,7 +286,7 @@ __device__ __forceinline__ void deep_rows(const DevModel m, const float *__restr
                     }
                 }
             }
-            const IdStore store{leaf_out + row0 * T, T, !FEW && ids_go_through(T)};
+            const IdStore<MODE == DEEP_LEAVES_THROUGH> store{leaf_out + row0 * T, T};
             if (FEW || T <= 4) {  // straight from the lanes
 #pragma unroll
                 for (int r = 0; r < NR; ++r) {
@@ -368,6 +368,7 @@ KernelFn pick_mode(int groups, int last, int mode, int width)
 {
     switch (mode) {
         case DEEP_FEW_LEAVES: return pick_groups<DEEP_FEW_LEAVES, 1, SHARED>(groups, last);
+        case DEEP_LEAVES_THROUGH: return pick_groups<DEEP_LEAVES_THROUGH, 1, SHARED>(groups, last);
         case DEEP_LEAVES: return pick_groups<DEEP_LEAVES, 1, SHARED>(groups, last);
         case DEEP_COLUMN: return pick_groups<DEEP_COLUMN, 1, SHARED>(groups, last);
         case DEEP_COLUMNS: return pick_groups<DEEP_COLUMNS, 1, SHARED>(groups, last);
@@ -390,7 +391,7 @@ KernelFn pick(int groups, int last, int mode, int width, bool shared)
 
 hipError_t init_deep_kernels(size_t lds_limit)
 {
-    for (int mode : {DEEP_COLUMN, DEEP_COLUMNS, DEEP_VECTOR, DEEP_LEAVES, DEEP_FEW_LEAVES})
+    for (int mode : {DEEP_COLUMN, DEEP_COLUMNS, DEEP_VECTOR, DEEP_LEAVES, DEEP_LEAVES_THROUGH, DEEP_FEW_LEAVES})
         for (int width : {2, 4, 8, 12, 16})
             for (int groups : {1, 2})
                 for (int last = 1; last <= groups; ++last)
@@ -410,7 +411,8 @@ hipError_t launch_deep(const DevModel &m, int groups, const float *X, int64_t n_
                        int32_t *leaf_out, hipStream_t stream)
 {
     const bool shared = deep_shares_cu(m, groups, leaf_out == nullptr);
-    const int mode = leaf_out ? leaves_by_fours(m, groups, n_rows) ? DEEP_FEW_LEAVES : DEEP_LEAVES : m.leaf_width > 1 ? DEEP_VECTOR : m.n_outputs == 1 ? DEEP_COLUMN : DEEP_COLUMNS;
+    int mode = m.leaf_width > 1 ? DEEP_VECTOR : m.n_outputs == 1 ? DEEP_COLUMN : DEEP_COLUMNS;
+    if (leaf_out) mode = leaves_by_fours(m, groups, n_rows) ? DEEP_FEW_LEAVES : ids_go_through(m.n_trees, reinterpret_cast<uintptr_t>(leaf_out)) ? DEEP_LEAVES_THROUGH : DEEP_LEAVES;
     const TailPlan t = ends_in_smaller(m, FOREST_KERNEL_DEEP, groups, n_rows, leaf_out == nullptr) ? choose_tail(groups, n_rows, m.n_splits) : whole(groups, n_rows);
     if (t.full + t.after > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(t.full + t.after), static_cast<unsigned>(m.n_splits));

@@ -106,7 +106,7 @@ __device__ __forceinline__ void walk_trees(uint32_t tree_at, uint32_t xa, const 
 
 // What a kernel leaves behind: the sums of one output column, those of several (trees sorted by
 // column), or the leaf ids of every tree (a kernel of its own, in two forms).
-enum { WALK_COLUMN = 0, WALK_COLUMNS = 1, WALK_LEAVES = 2, WALK_FEW_LEAVES = 3 };
+enum { WALK_COLUMN = 0, WALK_COLUMNS = 1, WALK_LEAVES = 2, WALK_LEAVES_THROUGH = 3, WALK_FEW_LEAVES = 4 };
 
 // The sums of a workgroup's rows, from row0.
 template <int D, int NR, int MODE>
@@ -211,9 +211,10 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
 // (leaves_by_fours, forest_plan.hpp) a wave takes four and stores their ids from its lanes.  Bound: the walk, with 391
 // workgroups for 256 CUs; two shares of the trees, or fewer rows per workgroup, fill the tile more often and took 54.7 and
 // 50.4.
-template <int D, int NR, bool FEW>
+template <int D, int NR, int MODE>
 __device__ __forceinline__ void walk_leaves(const DevModel m, const float *__restrict__ X, int64_t row0, int64_t n_rows, int32_t *leaf_out)
 {
+    constexpr bool FEW = MODE == WALK_FEW_LEAVES;
     constexpr int TREE_BYTES = 8 << D, STEP = walk_stage_trees(D) < 4 ? walk_stage_trees(D) : 4;  // trees copied at a time
     constexpr int STEP_BYTES = TREE_BYTES * STEP, STAGE_BYTES = walk_stage_bytes(D);
     constexpr int PIECES = (STEP_BYTES + 1023) / 1024;
@@ -299,7 +300,7 @@ __device__ __forceinline__ void walk_leaves(const DevModel m, const float *__res
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             if (!FEW && j == n - 1) keep(j);
-        const IdStore store{leaf_out + row0 * T, T, !FEW && ids_go_through(T)};
+        const IdStore<MODE == WALK_LEAVES_THROUGH> store{leaf_out + row0 * T, T};
         if (FEW || T <= 4) {  // straight from the lanes
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
@@ -333,26 +334,26 @@ __device__ __forceinline__ void walk_leaves(const DevModel m, const float *__res
     }
 }
 
-template <int D, int NR, int LAST, bool FEW>
+template <int D, int NR, int LAST, int MODE>
 __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_leaves_kernel(DevModel m, const float *__restrict__ X,
                                                                                  int64_t n_rows, float *, int32_t *,
                                                                                  int32_t *leaf_out)
 {
     if constexpr (NR == LAST) {
-        walk_leaves<D, NR, FEW>(m, X, static_cast<int64_t>(blockIdx.x) * (NR * TILE), n_rows, leaf_out);
+        walk_leaves<D, NR, MODE>(m, X, static_cast<int64_t>(blockIdx.x) * (NR * TILE), n_rows, leaf_out);
     } else {
         bool after;
         const int64_t row0 = first_row(m, NR, LAST, after);
-        if (after) walk_leaves<D, LAST, FEW>(m, X, row0, n_rows, leaf_out);
-        else walk_leaves<D, NR, FEW>(m, X, row0, n_rows, leaf_out);
+        if (after) walk_leaves<D, LAST, MODE>(m, X, row0, n_rows, leaf_out);
+        else walk_leaves<D, NR, MODE>(m, X, row0, n_rows, leaf_out);
     }
 }
 
 template <int D, int NR, int LAST, int MODE>
 KernelFn kernel()
 {
-    if constexpr (MODE == WALK_LEAVES) return forest_walk_leaves_kernel<D, NR, LAST, false>;
-    else if constexpr (MODE == WALK_FEW_LEAVES) return forest_walk_leaves_kernel<D, NR, NR, true>;
+    if constexpr (MODE == WALK_FEW_LEAVES) return forest_walk_leaves_kernel<D, NR, NR, MODE>;
+    else if constexpr (MODE == WALK_LEAVES || MODE == WALK_LEAVES_THROUGH) return forest_walk_leaves_kernel<D, NR, LAST, MODE>;
     else return forest_walk_kernel<D, NR, LAST, MODE>;
 }
 
@@ -361,7 +362,7 @@ template <int D, int MODE>
 KernelFn pick_groups(int groups, int last)
 {
     constexpr int MOST = MODE == WALK_COLUMNS ? 2 : 4;  // walk_max_groups
-    if constexpr (MODE == WALK_LEAVES)
+    if constexpr (MODE == WALK_LEAVES || MODE == WALK_LEAVES_THROUGH)
         if (last == groups && groups > 1) return groups == 2 ? kernel<D, 2, 2, MODE>() : kernel<D, MOST, MOST, MODE>();
     switch (groups) {
         case 1: return kernel<D, 1, 1, MODE>();
@@ -388,6 +389,7 @@ KernelFn pick(int depth, int groups, int last, int mode)
     if (mode == WALK_COLUMN) return pick_depth<WALK_COLUMN>(depth, groups, last);
     if (mode == WALK_COLUMNS) return pick_depth<WALK_COLUMNS>(depth, groups, last);
     if (mode == WALK_LEAVES) return pick_depth<WALK_LEAVES>(depth, groups, last);
+    if (mode == WALK_LEAVES_THROUGH) return pick_depth<WALK_LEAVES_THROUGH>(depth, groups, last);
     return pick_depth<WALK_FEW_LEAVES>(depth, groups, last);
 }
 
@@ -395,7 +397,7 @@ KernelFn pick(int depth, int groups, int last, int mode)
 
 hipError_t init_walk_kernels(size_t lds_limit)
 {
-    for (int mode : {WALK_COLUMN, WALK_COLUMNS, WALK_LEAVES, WALK_FEW_LEAVES})
+    for (int mode : {WALK_COLUMN, WALK_COLUMNS, WALK_LEAVES, WALK_LEAVES_THROUGH, WALK_FEW_LEAVES})
         for (int depth = WALK_MIN_DEPTH; depth <= WALK_MAX_DEPTH; ++depth)
             for (int groups = 1; groups <= walk_max_groups(mode == WALK_COLUMNS ? 2 : 1); groups *= 2)
                 for (int last = 1; last <= groups; last *= 2) {
@@ -413,7 +415,8 @@ hipError_t init_walk_kernels(size_t lds_limit)
 hipError_t launch_walk(const DevModel &m, int groups, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                        int32_t *leaf_out, hipStream_t stream)
 {
-    const int mode = leaf_out ? leaves_by_fours(m, groups, n_rows) ? WALK_FEW_LEAVES : WALK_LEAVES : m.n_outputs == 1 ? WALK_COLUMN : WALK_COLUMNS;
+    int mode = m.n_outputs == 1 ? WALK_COLUMN : WALK_COLUMNS;
+    if (leaf_out) mode = leaves_by_fours(m, groups, n_rows) ? WALK_FEW_LEAVES : ids_go_through(m.n_trees, reinterpret_cast<uintptr_t>(leaf_out)) ? WALK_LEAVES_THROUGH : WALK_LEAVES;
     const TailPlan t = ends_in_smaller(m, FOREST_KERNEL_WALK, groups, n_rows, leaf_out == nullptr) ? choose_tail(groups, n_rows, m.n_splits) : whole(groups, n_rows);
     if (t.full + t.after > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(t.full + t.after), static_cast<unsigned>(m.n_splits));

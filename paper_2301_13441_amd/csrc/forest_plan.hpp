@@ -461,16 +461,15 @@ inline bool takes_point(const DevModel &m, const Workspace *ws, int64_t n_rows, 
     return choose_walk_splits(m, ws, n_rows, sums) < choose_walk_splits(m, &ample, n_rows, sums);
 }
 
-// Whether the leaf ids of T trees are written past the L2, where their lines would wait to be put out by others and go to
-// memory in no order of use.  A row's ids are then pieces of 16 aligned bytes; with other counts pieces share lines and a line
-// goes to memory once for each (us, kept in the L2 / past it: 50 trees, 262,144 rows 36 / 43, 75 trees 48 / 61, 101 59 / 62; 52
-// trees 34.2 / 32.8, 128 55.4 / 52.7, 200 trees, 100,003 rows 39.1 / 36).  The stores count the workgroup's ids in 32 bits.
-#if defined(__HIPCC__)
-__host__ __device__
-#endif
-inline bool ids_go_through(int T)
+// Whether leaf ids are written past the L2, where their lines would wait to be put out by others and go to memory in no order of
+// use.  A row's ids are then pieces of 16 aligned bytes; with other counts of trees, and from an address that is no multiple of
+// 16, pieces share lines and a line goes to memory once for each (us, kept in the L2 / past it: 50 trees, 262,144 rows 36 / 43, 75
+// trees 48 / 61, 101 59 / 62, 128 trees from an address 4 bytes off 59.7 / 64.5; 52 trees, 153,846 rows 22.5 / 20.9, 128 trees, 62,500
+// rows 17.9 / 15.6, 16 trees, 4M rows 330 / 317).  Not 17 to 48 trees, of which a wave has two or three ids at a time, so many writes
+// of four bytes (20 trees, 500,000 rows 49.3 / 53.9).  The stores count the workgroup's ids in 32 bits.
+inline bool ids_go_through(int n_trees, uintptr_t leaf_out)
 {
-    return T % 4 == 0 && T <= 1 << 20;
+    return n_trees % 4 == 0 && n_trees <= 1 << 20 && (n_trees <= 16 || n_trees > 48) && leaf_out % 16 == 0;
 }
 
 // Rows of one launch at most.  HIP takes fewer than 2^32 threads per grid axis, and the walk kernels spend

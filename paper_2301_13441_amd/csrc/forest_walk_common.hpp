@@ -44,9 +44,7 @@ typedef const float *GlobalFloats;
 typedef const int32_t *GlobalInts;
 #endif
 
-struct __attribute__((aligned(4))) Int4 {
-    int32_t v[4];
-};
+typedef uint32_t LooseVec4 __attribute__((ext_vector_type(4), aligned(4)));
 
 // The X tile of a workgroup: rows [row0, row0 + 64 NR) as float32, row group g, feature f and row r of the
 // group at xbase + g * group_stride + f * stride + 4 r.  It is filled in pieces of 16 rows x 16 features,
@@ -108,22 +106,23 @@ __device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t 
 
 // The ids of n trees from `begin` of a row, counted from a workgroup's first: those of four with one store.  The row's place
 // comes from 32-bit factors (from the row of the batch, a 64-bit product, leaf ids of 262,144 rows of 128 x depth 6 took
-// 60.4 us instead of 55.4).  THROUGH: past the L2 (ids_go_through, forest_plan.hpp), but for two or three ids of a wave, which
-// would each go to memory as so many writes of four bytes (20 trees, 500,000 rows: 49.3 -> 53.9 us).
+// 60.4 us instead of 55.4).  THROUGH: past the L2 (ids_go_through, forest_plan.hpp), but for two or three ids of a wave.  A form of
+// the kernels of its own: chosen per store, the other form's descriptor cost every kernel four scalar registers, of which they
+// spill some (20 trees of depth 8, 500,000 rows: 63.9 -> 62.9 us; of depth 6, 100,000 rows: 13.6 -> 13.2).
+template <bool THROUGH>
 struct IdStore {
     int32_t *first;  // of the workgroup's first row, wave-uniform
     int T;
-    bool through;
 
     __device__ __forceinline__ void operator()(int li, int begin, int n, Vec4 id) const
     {
         const uint64_t at = static_cast<uint64_t>(static_cast<uint32_t>(li)) * static_cast<uint32_t>(T) + static_cast<uint32_t>(begin);
         if (n == 4 && begin + 4 <= T) {
-            if (through)
+            if constexpr (THROUGH)
                 __builtin_amdgcn_raw_buffer_store_b128(id, __builtin_amdgcn_make_buffer_rsrc(first, 0, 0x7fffffff, 0x00027000), static_cast<int>(at) * 4, 0, 16 /* sc1 */);
             else
-                *reinterpret_cast<Int4 *>(first + at) = Int4{{static_cast<int32_t>(id[0]), static_cast<int32_t>(id[1]), static_cast<int32_t>(id[2]), static_cast<int32_t>(id[3])}};
-        } else if (through && n == 1) {
+                *reinterpret_cast<LooseVec4 *>(first + at) = id;  // one value: of four, three would be stored by the path below and one alone (101 trees, 100,000 rows 28.8 us, so 26.8)
+        } else if (THROUGH && n == 1) {
             if (begin < T) __hip_atomic_store(first + at, static_cast<int32_t>(id[0]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
 #pragma unroll

@@ -224,6 +224,44 @@ def test_launches_that_end_in_smaller_workgroups(what, rows, groups, last):
         model.close()
 
 
+def test_only_whole_aligned_pieces_of_ids_go_past_the_l2():
+    from paper_2301_13441_amd import binding
+    for at in (1 << 20, (1 << 20) + 16, (1 << 20) + 4, (1 << 20) + 8, (1 << 20) + 12):
+        for trees in (4, 8, 16, 17, 20, 32, 48, 50, 52, 64, 101, 128, 200, 1 << 20, (1 << 20) + 4):
+            whole = trees % 4 == 0 and at % 16 == 0 and trees <= 1 << 20
+            assert binding.forest_ids_go_through(trees, at) == (whole and not 16 < trees <= 48), (trees, at)
+    with pytest.raises(binding.ForestError):
+        binding.forest_ids_go_through(0, 1 << 20)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("depth,trees,rows", [(6, 8, 9001), (6, 20, 5003), (6, 64, 9001), (7, 68, 40_001), (5, 101, 9001), (6, 128, 70_003),
+                                              (9, 12, 9001), (9, 64, 5003), (10, 100, 9001), (9, 128, 40_001)])
+def test_leaf_ids_to_any_address(depth, trees, rows):
+    """The caller's buffer may begin at any id; nothing before or behind it is touched."""
+    import torch
+    from paper_2301_13441_amd import binding
+    rng = np.random.default_rng(depth * trees)
+    f = _forest(depth + trees, trees, depth, 9) if depth < 9 else \
+        wl.random_forest(depth + trees, n_trees=trees, n_features=9, max_depth=depth, stop_prob=0.3, aggregate=wl.AGG_SUM)
+    X = rng.standard_normal((rows, 9)).astype(np.float32)
+    want = oracle.predict(f, X, want_leaves=True, n_threads=8).leaf_node_id
+    model = binding.forest_load_form(f, "walk")
+    try:
+        xd = torch.from_numpy(X).cuda()
+        for off in (0, 1, 2, 3, 4):
+            buf = torch.full((rows * trees + 64,), -7, dtype=torch.int32, device="cuda")
+            out = buf[16 + off:16 + off + rows * trees]
+            assert out.data_ptr() % 16 == 4 * (off % 4)
+            rc = model._lib.forest_predict_leaves(model._h, binding._p(xd.data_ptr()), rows, binding._p(out.data_ptr()),
+                                                  binding._p(torch.cuda.current_stream().cuda_stream))
+            assert rc == 0
+            np.testing.assert_array_equal(out.view(rows, trees).cpu().numpy(), want)
+            assert (buf[:16 + off] == -7).all() and (buf[16 + off + rows * trees:] == -7).all()
+    finally:
+        model.close()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("rows", [9001, 40_001, 70_003])
 @pytest.mark.parametrize("depth,trees", [(4, 12), (6, 20), (6, 68), (3, 76), (8, 96), (5, 128), (7, 204), (9, 12), (10, 36), (9, 68), (10, 128), (9, 133)])
