@@ -186,8 +186,9 @@ typedef struct forest_launch_t {
 int forest_launch(const forest *f, int64_t n_rows, int32_t leaves, forest_launch_t *out);
 int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out);
 
-/* 1 if the walk kernels write leaf ids of that many trees to that address past the L2, 0 if not, FOREST_EINVAL for n_trees < 1. */
-int forest_ids_go_through(int32_t n_trees, uintptr_t leaf_out);
+/* 1 if the walk kernels write leaf ids of that many trees and rows to that address past the L2, 0 if not, FOREST_EINVAL for
+ * counts below 1. */
+int forest_ids_go_through(int32_t n_trees, int64_t n_rows, uintptr_t leaf_out);
 
 /* forest_packed_launch of a call that finds every workspace of its handle taken (forest.h, concurrency). */
 int forest_packed_launch_no_workspace(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out);

@@ -124,7 +124,7 @@ def load_library():
     lib.forest_rank_code.restype = ctypes.c_int
     lib.forest_rank_code.argtypes = [_i32, ctypes.POINTER(ctypes.c_uint16), ctypes.POINTER(ctypes.c_uint16)]
     lib.forest_ids_go_through.restype = ctypes.c_int
-    lib.forest_ids_go_through.argtypes = [_i32, ctypes.c_size_t]
+    lib.forest_ids_go_through.argtypes = [_i32, _i64, ctypes.c_size_t]
     lib.forest_staged_position.restype = ctypes.c_int
     lib.forest_staged_position.argtypes = [_i32, _i32, ctypes.POINTER(_i32)]
     for fn in (lib.forest_launch, lib.forest_packed_launch, lib.forest_packed_launch_no_workspace):
@@ -320,9 +320,9 @@ def forest_packed_launch(forest, n_rows: int, leaves: bool = False, form: str = 
         lib.forest_pack_free(h)
 
 
-def forest_ids_go_through(n_trees: int, leaf_out: int) -> bool:
-    """Whether the walk kernels write leaf ids of that many trees to that address past the L2."""
-    got = load_library().forest_ids_go_through(int(n_trees), int(leaf_out))
+def forest_ids_go_through(n_trees: int, n_rows: int, leaf_out: int) -> bool:
+    """Whether the walk kernels write leaf ids of that many trees and rows to that address past the L2."""
+    got = load_library().forest_ids_go_through(int(n_trees), int(n_rows), int(leaf_out))
     if got < 0:
         raise ForestError(got, "forest_ids_go_through")
     return bool(got)

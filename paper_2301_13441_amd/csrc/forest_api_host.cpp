@@ -69,9 +69,9 @@ int forest_rank_code(int32_t q, uint16_t *code, uint16_t *entry)
     return RANK_CODES;
 }
 
-int forest_ids_go_through(int32_t n_trees, uintptr_t leaf_out)
+int forest_ids_go_through(int32_t n_trees, int64_t n_rows, uintptr_t leaf_out)
 {
-    return n_trees < 1 ? FOREST_EINVAL : ids_go_through(n_trees, leaf_out);
+    return n_trees < 1 || n_rows < 1 ? FOREST_EINVAL : ids_go_through(n_trees, n_rows, leaf_out);
 }
 
 int forest_staged_position(int32_t depth, int32_t pos, int32_t *node)

@@ -416,7 +416,7 @@ hipError_t launch_walk(const DevModel &m, int groups, const float *X, int64_t n_
                        int32_t *leaf_out, hipStream_t stream)
 {
     int mode = m.n_outputs == 1 ? WALK_COLUMN : WALK_COLUMNS;
-    if (leaf_out) mode = leaves_by_fours(m, groups, n_rows) ? WALK_FEW_LEAVES : ids_go_through(m.n_trees, reinterpret_cast<uintptr_t>(leaf_out)) ? WALK_LEAVES_THROUGH : WALK_LEAVES;
+    if (leaf_out) mode = leaves_by_fours(m, groups, n_rows) ? WALK_FEW_LEAVES : ids_go_through(m.n_trees, n_rows, reinterpret_cast<uintptr_t>(leaf_out)) ? WALK_LEAVES_THROUGH : WALK_LEAVES;
     const TailPlan t = ends_in_smaller(m, FOREST_KERNEL_WALK, groups, n_rows, leaf_out == nullptr) ? choose_tail(groups, n_rows, m.n_splits) : whole(groups, n_rows);
     if (t.full + t.after > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(t.full + t.after), static_cast<unsigned>(m.n_splits));

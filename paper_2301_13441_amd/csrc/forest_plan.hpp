@@ -466,10 +466,19 @@ inline bool takes_point(const DevModel &m, const Workspace *ws, int64_t n_rows, 
 // 16, pieces share lines and a line goes to memory once for each (us, kept in the L2 / past it: 50 trees, 262,144 rows 36 / 43, 75
 // trees 48 / 61, 101 59 / 62, 128 trees from an address 4 bytes off 59.7 / 64.5; 52 trees, 153,846 rows 22.5 / 20.9, 128 trees, 62,500
 // rows 17.9 / 15.6, 16 trees, 4M rows 330 / 317).  Not 17 to 48 trees, of which a wave has two or three ids at a time, so many writes
-// of four bytes (20 trees, 500,000 rows 49.3 / 53.9).  The stores count the workgroup's ids in 32 bits.
-inline bool ids_go_through(int n_trees, uintptr_t leaf_out)
+// of four bytes (20 trees, 500,000 rows 49.3 / 53.9).  Up to 64 trees a workgroup writes its rows whole.  Of more it writes 256 bytes
+// of a row after the other: where these do not begin 64-byte pieces, the piece between two goes to memory twice, which few ids hide
+// in the cache before the memory (68 trees, 117,647 rows 21.4 / 19.4; 200 trees, 10,000 rows 8.9 / 7.9, 40,000 rows 20.4 / 18.8) and more
+// do not (68 trees, 800,003 rows 120 / 145; 100 trees, 200,000 rows 43.5 / 44.0, 600,000 141 / 164; 200 trees, 100,003 rows, results
+// written over 37.8 / 37.0, in new places 45.2 / 49.4, 300,000 rows 125 / 131; of a multiple of 16 trees 96 trees, 208,333 rows 39.1 /
+// 39.1, 400 trees, 50,000 rows 38.7 / 37.7).  The stores count the workgroup's ids in 32 bits.
+constexpr int64_t FEW_IDS = int64_t{1} << 23;
+
+inline bool ids_go_through(int n_trees, int64_t n_rows, uintptr_t leaf_out)
 {
-    return n_trees % 4 == 0 && n_trees <= 1 << 20 && (n_trees <= 16 || n_trees > 48) && leaf_out % 16 == 0;
+    if (n_trees % 4 != 0 || n_trees > 1 << 20 || leaf_out % 16 != 0) return false;
+    if (n_trees <= 64) return n_trees <= 16 || n_trees > 48;
+    return (n_trees % 16 == 0 && leaf_out % 64 == 0) || n_rows * n_trees <= FEW_IDS;
 }
 
 // Rows of one launch at most.  HIP takes fewer than 2^32 threads per grid axis, and the walk kernels spend

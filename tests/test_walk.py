@@ -229,9 +229,21 @@ def test_only_whole_aligned_pieces_of_ids_go_past_the_l2():
     for at in (1 << 20, (1 << 20) + 16, (1 << 20) + 4, (1 << 20) + 8, (1 << 20) + 12):
         for trees in (4, 8, 16, 17, 20, 32, 48, 50, 52, 64, 101, 128, 200, 1 << 20, (1 << 20) + 4):
             whole = trees % 4 == 0 and at % 16 == 0 and trees <= 1 << 20
-            assert binding.forest_ids_go_through(trees, at) == (whole and not 16 < trees <= 48), (trees, at)
-    with pytest.raises(binding.ForestError):
-        binding.forest_ids_go_through(0, 1 << 20)
+            assert binding.forest_ids_go_through(trees, 1, at) == (whole and not 16 < trees <= 48), (trees, at)
+    for bad in ((0, 1), (1, 0)):
+        with pytest.raises(binding.ForestError):
+            binding.forest_ids_go_through(*bad, 1 << 20)
+
+
+@pytest.mark.parametrize("trees", [52, 64, 68, 84, 96, 100, 128, 132, 200, 300, 400])
+def test_many_ids_go_past_the_l2_only_where_a_rows_runs_are_whole_pieces(trees):
+    """Of more than 64 trees a row's ids leave in runs of 256 bytes: only of a multiple of 16 trees do they begin 64-byte pieces."""
+    from paper_2301_13441_amd import binding
+    few = (1 << 23) // trees
+    for rows in (1, few, few + 1, 10**6):
+        for at in (1 << 20, (1 << 20) + 16):
+            through = trees <= 64 or rows <= few or (trees % 16 == 0 and at % 64 == 0)
+            assert binding.forest_ids_go_through(trees, rows, at) == through, (rows, at)
 
 
 @pytest.mark.gpu
