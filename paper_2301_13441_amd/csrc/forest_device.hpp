@@ -49,14 +49,14 @@ hipError_t init_rankbank_kernels(size_t lds_limit);
 hipError_t launch_rankbank(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                            int32_t *leaf_out, size_t lds_limit, hipStream_t stream);
 
-// Walk kernels (forest_kernels_walk.hip).
+// Walk kernels (forest_kernels_walk.hip).  t: the workgroups of the rows at hand, of which m.full_workgroups holds the first number.
 hipError_t init_walk_kernels(size_t lds_limit);
-hipError_t launch_walk(const DevModel &m, int groups, const float *X, int64_t n_rows, float *scores, int32_t *labels,
+hipError_t launch_walk(const DevModel &m, int groups, const TailPlan &t, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                        int32_t *leaf_out, hipStream_t stream);
 
 // Deep walk kernels (forest_kernels_deep.hip).
 hipError_t init_deep_kernels(size_t lds_limit);
-hipError_t launch_deep(const DevModel &m, int groups, const float *X, int64_t n_rows, float *scores, int32_t *labels,
+hipError_t launch_deep(const DevModel &m, int groups, const TailPlan &t, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                        int32_t *leaf_out, hipStream_t stream);
 
 // One lane per (row, tree) (forest_kernels_split.hip).

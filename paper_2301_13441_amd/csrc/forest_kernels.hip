@@ -280,13 +280,13 @@ Workspace carve_workspace(const DevModel &m, void *base, size_t bytes, int64_t t
     return ws;
 }
 
-static hipError_t launch_family(const DevModel &m, const LaunchPlan &p, const float *X, int64_t n_rows, float *scores,
+static hipError_t launch_family(const DevModel &m, const LaunchPlan &p, const TailPlan &t, const float *X, int64_t n_rows, float *scores,
                                 int32_t *labels, int32_t *leaf_out, hipStream_t stream)
 {
     switch (p.kernel) {
         case FOREST_KERNEL_POINT: return launch_point(m, X, n_rows, scores, labels, leaf_out, stream);
-        case FOREST_KERNEL_WALK: return launch_walk(m, p.groups, X, n_rows, scores, labels, leaf_out, stream);
-        case FOREST_KERNEL_DEEP: return launch_deep(m, p.groups, X, n_rows, scores, labels, leaf_out, stream);
+        case FOREST_KERNEL_WALK: return launch_walk(m, p.groups, t, X, n_rows, scores, labels, leaf_out, stream);
+        case FOREST_KERNEL_DEEP: return launch_deep(m, p.groups, t, X, n_rows, scores, labels, leaf_out, stream);
         case FOREST_KERNEL_RANK: return launch_rank(m, X, n_rows, scores, labels, leaf_out, stream);
         case FOREST_KERNEL_RANK_BANK: return launch_rankbank(m, X, n_rows, scores, labels, leaf_out, g_lds_limit, stream);
         case FOREST_KERNEL_RANK_LDS: return launch_ranklds(m, X, n_rows, scores, labels, leaf_out, g_lds_limit, stream);
@@ -326,7 +326,9 @@ hipError_t launch_predict(const DevModel &model, const Workspace *ws, bool must_
     }
     for (int64_t r = 0; r < n_rows; r += MAX_LAUNCH_ROWS) {  // batches cut into shares are far smaller than a range
         const int64_t here = n_rows - r < MAX_LAUNCH_ROWS ? n_rows - r : MAX_LAUNCH_ROWS;
-        const hipError_t e = launch_family(m, p, X + r * m.n_features, here, scores ? scores + r * m.n_outputs : nullptr,
+        const TailPlan t = range_workgroups(m, p, here, sums);
+        m.full_workgroups = t.full;
+        const hipError_t e = launch_family(m, p, t, X + r * m.n_features, here, scores ? scores + r * m.n_outputs : nullptr,
                                            labels ? labels + r : nullptr, leaf_out ? leaf_out + r * m.n_trees : nullptr, stream);
         if (e != hipSuccess) return e;
     }

@@ -407,19 +407,16 @@ hipError_t init_deep_kernels(size_t lds_limit)
     return hipSuccess;
 }
 
-hipError_t launch_deep(const DevModel &m, int groups, const float *X, int64_t n_rows, float *scores, int32_t *labels,
+hipError_t launch_deep(const DevModel &m, int groups, const TailPlan &t, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                        int32_t *leaf_out, hipStream_t stream)
 {
     const bool shared = deep_shares_cu(m, groups, leaf_out == nullptr);
     int mode = m.leaf_width > 1 ? DEEP_VECTOR : m.n_outputs == 1 ? DEEP_COLUMN : DEEP_COLUMNS;
     if (leaf_out) mode = leaves_by_fours(m, groups, n_rows) ? DEEP_FEW_LEAVES : ids_go_through(m.n_trees, n_rows, reinterpret_cast<uintptr_t>(leaf_out)) ? DEEP_LEAVES_THROUGH : DEEP_LEAVES;
-    const TailPlan t = ends_in_smaller(m, FOREST_KERNEL_DEEP, groups, n_rows, leaf_out == nullptr) ? choose_tail(groups, n_rows, m.n_splits) : whole(groups, n_rows);
     if (t.full + t.after > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid(static_cast<unsigned>(t.full + t.after), static_cast<unsigned>(m.n_splits));
     const size_t lds = deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, groups, leaf_out == nullptr);
-    DevModel launched = m;
-    launched.full_workgroups = t.full;
-    hipLaunchKernelGGL(pick(groups, t.groups, mode, deep_width(m.leaf_width), shared), grid, dim3(DEEP_WAVES * TILE), lds, stream, launched, X,
+    hipLaunchKernelGGL(pick(groups, t.groups, mode, deep_width(m.leaf_width), shared), grid, dim3(DEEP_WAVES * TILE), lds, stream, m, X,
                        n_rows, scores, labels, leaf_out);
     return hipGetLastError();
 }

@@ -544,6 +544,12 @@ inline LaunchPlan plan_launch(const DevModel &m, const Workspace *ws, int64_t n_
     return p;
 }
 
+// The workgroups of one range of rows, walk kernels.
+inline TailPlan range_workgroups(const DevModel &m, const LaunchPlan &p, int64_t n_rows, bool sums)
+{
+    return ends_in_smaller(m, p.kernel, p.groups, n_rows, sums) ? choose_tail(p.groups, n_rows, p.splits) : whole(p.groups, n_rows);
+}
+
 // The shape of the launches of a plan.
 inline forest_launch_t launch_shape(const DevModel &m, const LaunchPlan &p, int64_t n_rows, bool sums)
 {
@@ -579,12 +585,10 @@ inline forest_launch_t launch_shape(const DevModel &m, const LaunchPlan &p, int6
     const int64_t rows = n_rows < MAX_LAUNCH_ROWS ? n_rows : MAX_LAUNCH_ROWS;
     s.workgroups = (rows + s.rows_per_workgroup - 1) / s.rows_per_workgroup;
     s.last_rows_per_workgroup = s.rows_per_workgroup;
-    if (ends_in_smaller(m, p.kernel, p.groups, rows, sums)) {
-        const TailPlan t = choose_tail(p.groups, rows, p.splits);
-        if (t.after > 0) {
-            s.workgroups = t.full + t.after;
-            s.last_rows_per_workgroup = PLAN_ROWS * t.groups;
-        }
+    if (p.kernel == FOREST_KERNEL_WALK || p.kernel == FOREST_KERNEL_DEEP) {
+        const TailPlan t = range_workgroups(m, p, rows, sums);
+        s.workgroups = t.full + t.after;
+        s.last_rows_per_workgroup = PLAN_ROWS * t.groups;
     }
     return s;
 }
