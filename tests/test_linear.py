@@ -272,6 +272,33 @@ def test_x_that_starts_off_a_16_byte_boundary_and_absent_bias(F):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("F", [105, 112, 128, 130, 156, 160, 200])
+@pytest.mark.parametrize("K", [1, 3, 20])
+def test_chunks_of_x_at_every_alignment(F, K):
+    """Rows that go by chunks wherever X begins, on and off the lines that chunks of 32 features are, and those of one output
+    that go whole from a 16-byte boundary only; full and partial tiles, one of them with all its chunks whole."""
+    import torch
+    rng = np.random.default_rng(F + K)
+    model = _rand_model(F * K, F, K, TRANSFORM_SOFTMAX if K > 1 else TRANSFORM_SIGMOID)
+    m = lb.linear_load(model)
+    try:
+        for rows in (1, 64, 300):
+            X = rng.standard_normal((rows, F)).astype(np.float32)
+            ref = predict_linear(model, X)
+            for off in (0, 1, 2, 4, 8, 16, 32):
+                buf = torch.empty(rows * F + 32, dtype=torch.float32, device="cuda")
+                xd = buf[off:off + rows * F].view(rows, F)
+                xd.copy_(torch.from_numpy(X))
+                assert xd.data_ptr() % 128 == 4 * (off % 32)
+                scores, labels = m.predict(xd)
+                torch.cuda.synchronize()
+                np.testing.assert_array_equal(labels.cpu().numpy(), ref.labels)
+                np.testing.assert_allclose(scores.cpu().numpy(), ref.scores, rtol=RTOL, atol=ATOL)
+    finally:
+        m.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("F", [12, 28, 64, 90, 128, 130])
 @pytest.mark.parametrize("K", [1, 2, 3, 10, 20])
 def test_results_that_start_off_a_16_byte_boundary(F, K):
