@@ -34,13 +34,13 @@ ORACLE_THREADS_MAX = 16   # the share of host cores one GPU's job may use on the
 # entry names the summary under profiles/ it comes from and the commit whose kernels were
 # measured; a workload without an entry reports null.
 MEASURED_TRAFFIC = {
-    "c2": {"bytes": 1.353e8, "profile": "profiles/forest_walk_kernels.md", "commit": "882aa8e"},
-    "c3": {"bytes": 2.883e8, "profile": "profiles/forest_walk_kernels.md", "commit": "882aa8e"},
-    "c4": {"bytes": 3.184e8, "profile": "profiles/forest_walk_kernels.md", "commit": "882aa8e"},
-    "c5": {"bytes": 4.272e9, "profile": "profiles/forest_walk_kernels.md", "commit": "882aa8e"},
-    "l2": {"bytes": 1.456e9, "profile": "profiles/linear_kernels.md", "commit": "65bfc7c"},
-    "l3": {"bytes": 1.120e9, "profile": "profiles/linear_kernels.md", "commit": "65bfc7c"},
-    "l4": {"bytes": 9.600e8, "profile": "profiles/linear_kernels.md", "commit": "65bfc7c"},
+    "c2": {"bytes": 1.351e8, "profile": "profiles/forest_walk_kernels.md", "commit": "7dd9b06"},
+    "c3": {"bytes": 2.855e8, "profile": "profiles/forest_walk_kernels.md", "commit": "7dd9b06"},
+    "c4": {"bytes": 3.199e8, "profile": "profiles/forest_walk_kernels.md", "commit": "7dd9b06"},
+    "c5": {"bytes": 4.230e9, "profile": "profiles/forest_walk_kernels.md", "commit": "7dd9b06"},
+    "l2": {"bytes": 1.456e9, "profile": "profiles/linear_kernels.md", "commit": "7dd9b06"},
+    "l3": {"bytes": 1.119e9, "profile": "profiles/linear_kernels.md", "commit": "7dd9b06"},
+    "l4": {"bytes": 9.600e8, "profile": "profiles/linear_kernels.md", "commit": "7dd9b06"},
 }
 
 

@@ -16,7 +16,7 @@
 // 128 trees of depth 12, 256 features, 4,000,000 rows: 2.71 ms (14.5 with every node tested,
 // forest_kernels_rankbank.hip).  1.1 ms are the tile's (X once from memory, which one workgroup per
 // CU does not overlap with its walk, and 0.4 ms of launches and sums), 0.8 the tops (LDS round trips),
-// 0.9 the units (a gather costs the texture path about a cycle per active lane; with the first units
+// 0.9 the units (a gather costs the texture path 16 clocks or more however few its lanes, about 25 here; with the first units
 // gathered too instead of held in LDS it was 1.1, at twice the path's load).  Keeping 64-row tiles, two
 // workgroups on a CU and the first units in global memory: 2.90 ms there, 94 us against 87 for
 // 300 trees of depth 9 over 90 features and 103,069 rows.  Workgroups that loop over tiles and request the

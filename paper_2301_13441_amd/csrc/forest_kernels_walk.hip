@@ -25,10 +25,10 @@
 // 922 -> 828 us; 1000 x depth 6, 50 features, four row groups, 1M rows: 777 -> 758; 1,021 rows of the former, one row
 // group: 17.4 -> 15.6 us a call).  Deeper trees would need a second stage in LDS, at the price of a workgroup's place.
 //
-// Bound: at depth 8 the LDS (89 % busy, vector ALU 78 %), at depth 6 the vector ALU (93 to 97 %) with the LDS (82 to 85 %)
+// Bound: at depth 8 the LDS (90 % busy, vector ALU 79 %), at depth 6 the vector ALU (93 to 98 %) with the LDS (82 to 86 %)
 // behind it.  Per (64 rows, tree of depth D): 3 + 2 (D - 2) LDS reads of 2 clocks each, more at levels 6 and 7 whose 64 and 128 nodes share the
-// 32 banks (4 and 6 clocks).  500 trees of depth 8, 28 features, 1M rows: 2.70 -> 0.62 ms against every node tested
-// (forest_kernels_rank.hip); 1000 of depth 6, 50 features: 1.57 -> 0.76 ms.  Leaf values held as float64, which saves
+// 32 banks (4 and 6 clocks).  500 trees of depth 8, 28 features, 1M rows: 2.70 -> 0.60 ms against every node tested
+// (forest_kernels_rank.hip); 1000 of depth 6, 50 features: 1.57 -> 0.74 ms.  Leaf values held as float64, which saves
 // their conversion and a shift: 633 and 802 us against 629 and 788.
 #include <hip/hip_runtime.h>
 
@@ -204,13 +204,13 @@ __global__ __launch_bounds__(WALK_WAVES * TILE, 8) void forest_walk_kernel(DevMo
 // The leaf ids of every tree, caller's order.  A row's ids are neighbours in the output and a lane holds those of few
 // trees, so the waves take four trees each, side by side, and exchange the ids through their stages before they leave: a
 // store then writes whole 256-byte runs of four rows.  Straight from the lanes, 16 bytes at the pitch of a row, 100,003
-// rows of 200 x depth 6 took 65.6 us, three quarters of them for the stores; so 42.5 (250,000
-// rows of 200 x depth 3: 235 -> 65; 66,000 of 700 x depth 3: 310 -> 98), and 35.3 since they go past the L2 (IdStore).  Ids of these trees, which have 511 nodes at
-// most, fit 16 bits.  What is left of the trees after the last whole round is dealt evenly; waves that get none walk none
+// rows of 200 x depth 6 took 65.6 us, three quarters of them for the stores; so 42.5 (250,000 rows of 200 x depth 3: 235 -> 65;
+// 66,000 of 700 x depth 3: 310 -> 98), and 37.7 since a row's place comes from 32 bits and four ids are one value (IdStore; 45.4
+// where results are not written over and over).  Ids of these trees, which have 511 nodes at most, fit 16 bits.  What is left of the trees after the last whole round is dealt evenly; waves that get none walk none
 // (one tree of depth 7, 3 features, 60,000 rows: 4.6 us a call with 16 waves on it, 3.8).  FEW: of few trees
 // (leaves_by_fours, forest_plan.hpp) a wave takes four and stores their ids from its lanes.  Bound: the walk, with 391
 // workgroups for 256 CUs; two shares of the trees, or fewer rows per workgroup, fill the tile more often and took 54.7 and
-// 50.4.
+// 50.4 when these took 42.5.
 template <int D, int NR, int MODE>
 __device__ __forceinline__ void walk_leaves(const DevModel m, const float *__restrict__ X, int64_t row0, int64_t n_rows, int32_t *leaf_out)
 {

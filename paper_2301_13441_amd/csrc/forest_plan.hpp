@@ -316,11 +316,13 @@ inline int choose_walk_splits(const DevModel &m, const Workspace *ws, int64_t n_
 // Row groups per workgroup, walk and deep walk kernels: as many as leave every CU a workgroup, or, with trees enough
 // for their copies to LDS to count, half of the CUs one of two groups.  More rows per workgroup share those copies and
 // keep more walks in flight, and a workgroup that has a CU to itself is nearly twice as fast as one of two, so rounds
-// of two per CU are not what counts: over 240 models and 20,000 to 270,000 rows this is within 0.8 % of the best choice
-// for each (sums 2 and leaf ids 5 % at 20,000 rows; 1.3 times it at worst: 90,000 rows of 500 to 900 trees, which get four
-// groups and would do better with two), where counting rounds was 25 % off at 66,000 and 40 % at
+// of two per CU are not what counts: over 240 models and 20,000 to 270,000 rows this was within 0.8 % of the best choice
+// for each (sums 2 and leaf ids 5 % at 20,000 rows), where counting rounds was 25 % off at 66,000 and 40 % at
 // 150,000 rows (ten trees of depth 2, 10 features, 66,000 rows: 19.2 us with one group, 14.9 with two, 11.5 with
-// four).  Split launches have no workgroups to spare.
+// four).  That was with workgroups of one size; with the smaller ones at the end (choose_tail), four groups / two, us: 90,000
+// rows of 500 x depth 8 70.7 / 76.4, of 700 x depth 6 59.4 / 60.4, 120,000 of 500 x depth 8 87.8 / 100; the other way 1000 x depth 6,
+// 100,000 to 114,000 rows 104.5 / 93.8, 198,000 239 / 238, leaf ids of ten trees of depth 4, 90,000 rows 6.9 / 5.7.  Split launches have no
+// workgroups to spare.
 inline int choose_groups(const DevModel &m, int groups, int64_t n_rows, int n_splits)
 {
     const auto workgroups = [&](int g) { return (n_rows + PLAN_ROWS * g - 1) / (PLAN_ROWS * g); };
@@ -333,8 +335,10 @@ inline int choose_groups(const DevModel &m, int groups, int64_t n_rows, int n_sp
 // by the CUs, and the CUs that get one of that rest finish a whole workgroup later than the others: boosted trees of depth
 // 9, 103,069 rows, are 806 workgroups of 128 rows, three for every CU and a fourth for 38 of them, 81 us where 768 take 64.
 // So the rows of the rest go in workgroups of fewer row groups, those that leave the CU with most of them fewest row groups,
-// if these are half of a whole workgroup's at most (a workgroup of the rest copies the trees to LDS for fewer rows: leaf ids
-// of 100,003 rows, whose rest is 135 workgroups of four groups, 540 of one group: 42.1 -> 46.9).  us a call, whole / smaller
+// if these are half of a whole workgroup's at most (a workgroup of the rest copies the trees to LDS for fewer rows: 100,003 rows,
+// whose rest is 135 workgroups of four groups, as they are / in 540 of one group: leaf ids of 200 x depth 6 36.1 / 42.1, sums of
+// 500 x depth 8 87.5 / 95.2, of 40 x depth 6 11.5 / 12.9, of 1000 x depth 6 104.5 / 100.9; rests of 160 and 190 and behind two or
+// four rounds alike).  us a call, whole / smaller
 // at the end: 1M rows of 500 x depth 8, 28 features (15.3 rounds) 617 / 598; 1M of 1000 x depth 6 753 / 731; 500,000 of 2000
 // x depth 6, 10 columns 822 / 805; the 103,069 rows 80.7 / 73.2; 80,896 rows (1.2 rounds) of 500 x depth 8 86.6 / 60.7, of
 // ten such trees 7.31 / 6.37, leaf ids of 200 x depth 6 41.5 / 32.4; 40,000 rows of 30 irregular trees 9.2 / 8.5.
@@ -374,10 +378,11 @@ inline bool deep_shares_cu(const DevModel &m, int groups, bool sums)
 // the waves exchange the ids.  An exchange puts all 16 waves through two more barriers and a share of the stores, which
 // few trees do not win back in a batch of many workgroups; small batches wait for the longest wave, and wide rows for
 // their tile, and there one tree a wave is the better.  us, exchange / fours, at 700,000 rows: 5 trees of depth 6, 4
-// features, two columns 40 / 26; 8 of depth 6, 16 features 49 / 35; 9 of depth 3, 8 features, one column 33 / 26; 12 of
-// depth 5, 15 features 50 / 39; irregular trees with 15-wide leaves of depth 8, 4 features: 10 82 / 60, 16 93 / 70.  The
-// other way: 9 of depth 8, 64 features 67 / 76; 8 of depth 6, 2 features, one column 24 / 31; 24 of depth 7, 4 features
-// 60 / 75; 7 irregular of depth 11, 110 features, 350,000 rows 68 / 82; 8 of depth 8, 10 features, 13,000 rows 4.2 / 5.2.
+// features, two columns 45 / 30; 16 of depth 6, 20 features, two columns 60 / 43; 9 of depth 3, 8 features, one column 33 / 24;
+// 6 of depth 8, 20 features 34 / 29; irregular trees with 15-wide leaves of depth 8, 4 features: 10 86 / 63, 16 78 / 66.  The
+// other way: 8 of depth 6, 2 features, one column 21 / 24; 24 of depth 7, 4 features 45 / 48; 7 irregular of depth 11, 110
+// features, 350,000 rows 68 / 80; 8 of depth 8, 10 features, 13,000 rows 4.3 / 4.7; the same 9 of depth 8, 64 features 70 / 70.
+// (12 of depth 5, 15 features, one column stay with the exchange: 35 / 28.)
 inline bool leaves_by_fours(const DevModel &m, int groups, int64_t n_rows)
 {
     const int64_t workgroups = (n_rows + PLAN_ROWS * groups - 1) / (PLAN_ROWS * groups);
@@ -492,6 +497,9 @@ constexpr int64_t MAX_LAUNCH_ROWS = int64_t{1} << 27;
 // time).  The margins keep the walk kernels where the estimates, or a batch of few rounds of workgroups, decide
 // nothing.  A batch that the dense kernels cut into shares costs them two more launches, which their faster tests have
 // to earn (1500 stumps over 4 features, 5,000 rows: 27.1 us, dense 19.9); with vector leaves they do not.
+// The walk kernels' estimates are those of workgroups of one size and a trip to LDS per wave's sum and are too high by now: 66,000
+// rows of 483 and 911 trees of depth 3 take 34.6 and 57.6 us so and would take 22.4 and 38.3 by walk, 500,000 rows of 395 trees of
+// depth 4 in ten columns 192 and 146; of 60 models of depth up to 5, 48 are within 5 % of the better form.
 constexpr int64_t DENSE_MIN_ROWS = 4096;
 
 inline bool prefers_dense(const DevModel &m, int64_t n_rows, bool sums)

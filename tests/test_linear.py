@@ -239,7 +239,7 @@ def test_tiles_of_rows_with_and_without_padding(F, K, rows):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("F,K,rows", [(100, 2, 98_304), (100, 2, 98_305), (98, 4, 98_369), (104, 8, 65_536), (104, 8, 65_537), (101, 12, 98_311),
-                                      (97, 17, 98_305), (112, 1, 32_768), (112, 1, 32_769), (152, 1, (1 << 19) + 1), (100, 3, (1 << 18) + 1)])
+                                      (97, 17, 98_305), (200, 2, 40_000), (200, 2, 65_537), (132, 16, 131_073), (112, 1, 32_768), (112, 1, 32_769), (152, 1, (1 << 19) + 1), (100, 3, (1 << 18) + 1)])
 def test_both_sides_of_the_rows_that_a_round_of_workgroups_holds(F, K, rows):
     m = _rand_model(F + K, F, K, TRANSFORM_SOFTMAX if K > 1 else TRANSFORM_SIGMOID)
     _check(m, np.random.default_rng(rows).standard_normal((rows, F), dtype=np.float32))
