@@ -80,7 +80,10 @@ constexpr int rows_tile_floats(int n_features, bool padded) { return LANES * n_f
 // two waves share a piece, which past the L2 goes to memory once for each (one output and label, where labels begin behind the
 // scores of an odd number of rows, and results that are not written over and over, us, both past the L2 / labels kept: 20M x 10
 // 198 / 165, 16M x 13 196 / 167, 7.1M x 28 163 / 143, 7.5M x 48 273 / 247; two outputs, 31M x 8 249 / 234).  16 bytes per lane
-// of a tile's several scores do not mind (5.4M x 28, 5 outputs, 4 to 12 bytes off: 119.9, on the boundary 118.9).
+// of a tile's several scores do not mind (5.4M x 28, 5 outputs, 4 to 12 bytes off: 119.9, on the boundary 118.9).  Rows of a few
+// features, which are as many bytes as their results, do not gain from the scores alone where their labels are kept (4,734,629 x
+// 1, both kept / scores past the L2 21.3 / 22.8, x 3 22.7 / 23.5, x 5 25.9 / 26.1, x 6 27.7 / 27.7, x 10 38.8 / 38.0).
+constexpr int TINY_FEATURES = 5;
 constexpr int FEW_COLUMNS = 3, FEW_COLUMNS_FEATURES = 56;
 constexpr int64_t FEW_COLUMNS_X = int64_t{1} << 27;  // floats
 constexpr int FEW_WRITES_FEATURES = 64;
@@ -126,7 +129,8 @@ inline LinearPlan plan_linear(int n_features, int n_outputs, int64_t n_rows, uin
     LinearPlan p;
     const bool few_writes = n_features >= FEW_WRITES_FEATURES;
     const bool kept = n_outputs > 1 && n_outputs <= FEW_COLUMNS && n_features >= FEW_COLUMNS_FEATURES && n_rows * n_features < FEW_COLUMNS_X;
-    p.scores_past = scores && (n_outputs > 1 ? !kept : scores % WRITE_PIECE == 0 && !few_writes);
+    const bool tiny = n_features <= TINY_FEATURES && labels % WRITE_PIECE != 0;
+    p.scores_past = scores && (n_outputs > 1 ? !kept : scores % WRITE_PIECE == 0 && !few_writes && !tiny);
     p.labels_past = labels && !kept && (labels % WRITE_PIECE == 0 || (n_outputs == 1 && few_writes));
     if (takes_rows(n_features, n_outputs, n_rows) && x % 16 == 0) {
         p.padded = padded_rows(n_features);

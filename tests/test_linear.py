@@ -98,6 +98,16 @@ def test_only_whole_pieces_of_one_value_a_row_go_past_the_l2(F, rows):
             assert lb.linear_launch_shape(F, K, 1 << 12, at, 0)["labels_past"] == 0
 
 
+def test_rows_of_a_few_features_keep_both_or_neither_result_in_the_l2():
+    at = 1 << 20
+    for rows in (16, 17, 4_734_624, 4_734_629):
+        for F in (1, 5, 6, 12):
+            s = lb.linear_launch_shape(F, 1, 1 << 12, at, at + 4 * rows)
+            assert (s["scores_past"], s["labels_past"]) == (rows % 16 == 0 or F > 5, rows % 16 == 0)
+        assert lb.linear_launch_shape(1, 1, 1 << 12, at, 0)["scores_past"] == 1
+        assert lb.linear_launch_shape(1, 2, 1 << 12, at, at + 8 * rows)["scores_past"] == 1
+
+
 @pytest.mark.parametrize("rows", [64, 1000, 4_000_000, 4_000_005])
 def test_one_score_of_a_wide_row_stays_out_of_the_way_of_its_label(rows):
     """From 64 features on the score is stored non-temporally with and without a label, and the label past the L2; below,
