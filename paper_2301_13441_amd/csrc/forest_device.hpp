@@ -59,6 +59,8 @@ hipError_t init_deep_kernels(size_t lds_limit);
 hipError_t launch_deep(const DevModel &m, int groups, const TailPlan &t, const float *X, int64_t n_rows, float *scores, int32_t *labels,
                        int32_t *leaf_out, hipStream_t stream);
 
+hipError_t launch_deep_tiles(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels, hipStream_t stream);
+
 // One lane per (row, tree) (forest_kernels_split.hip).
 hipError_t launch_point(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels, int32_t *leaf_out,
                         hipStream_t stream);

@@ -97,6 +97,46 @@ __device__ __forceinline__ void finish_values(const DevModel &m, double *raw, in
     }
 }
 
+// The same for a row whose K sums are in registers.
+template <int K>
+__device__ __forceinline__ void finish_few(const DevModel &m, double (&s)[K], int64_t row, float *scores, int32_t *labels)
+{
+    double best = 0.0;
+    int best_k = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (const double n = ((ColumnTrees)m.col_trees)[k]; m.aggregate == FOREST_AGG_MEAN && n > 0.0) s[k] = s[k] / n;
+        s[k] = static_cast<double>(((ColumnBase)m.base)[k]) + s[k];
+        if (k == 0 || s[k] > best) {
+            best = s[k];
+            best_k = k;
+        }
+    }
+    if (labels) {
+        int lab = best_k;
+        if (K == 1) lab = (m.transform == FOREST_TRANSFORM_SIGMOID) ? (best > 0.0) : (best > 0.5);
+        labels[row] = lab;
+    }
+    if (!scores) return;
+    float *dst = scores + row * K;
+    if (m.transform == FOREST_TRANSFORM_SOFTMAX) {
+        double z = 0.0;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            s[k] = exp(s[k] - best);
+            z += s[k];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(s[k] / z);
+    } else if (m.transform == FOREST_TRANSFORM_SIGMOID) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(1.0 / (1.0 + exp(-s[k])));
+    } else {
+#pragma unroll
+        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(s[k]);
+    }
+}
+
 // Tile row `li` (0 <= li < rows) once its K column sums are in acc[k * rows + li]: the rest of
 // the row (aggregate, label, transform, store) or, in a split launch, the store of the sums.
 __device__ __forceinline__ void finish_summed_row(const DevModel &m, double *acc, int rows, int li, int64_t row,

@@ -286,7 +286,9 @@ static hipError_t launch_family(const DevModel &m, const LaunchPlan &p, const Ta
     switch (p.kernel) {
         case FOREST_KERNEL_POINT: return launch_point(m, X, n_rows, scores, labels, leaf_out, stream);
         case FOREST_KERNEL_WALK: return launch_walk(m, p.groups, t, X, n_rows, scores, labels, leaf_out, stream);
-        case FOREST_KERNEL_DEEP: return launch_deep(m, p.groups, t, X, n_rows, scores, labels, leaf_out, stream);
+        case FOREST_KERNEL_DEEP:
+            if (p.tiles) return launch_deep_tiles(m, X, n_rows, scores, labels, stream);
+            return launch_deep(m, p.groups, t, X, n_rows, scores, labels, leaf_out, stream);
         case FOREST_KERNEL_RANK: return launch_rank(m, X, n_rows, scores, labels, leaf_out, stream);
         case FOREST_KERNEL_RANK_BANK: return launch_rankbank(m, X, n_rows, scores, labels, leaf_out, g_lds_limit, stream);
         case FOREST_KERNEL_RANK_LDS: return launch_ranklds(m, X, n_rows, scores, labels, leaf_out, g_lds_limit, stream);

@@ -13,17 +13,16 @@
 // ([group][feature][row]); every wave walks its own run of trees for all the rows, two trees at a time
 // below their tops.
 //
-// 128 trees of depth 12, 256 features, 4,000,000 rows: 2.71 ms (14.5 with every node tested,
-// forest_kernels_rankbank.hip).  1.1 ms are the tile's (X once from memory, which one workgroup per
-// CU does not overlap with its walk, and 0.4 ms of launches and sums), 0.8 the tops (LDS round trips),
-// 0.9 the units (a gather costs the texture path 16 clocks or more however few its lanes, about 25 here; with the first units
-// gathered too instead of held in LDS it was 1.1, at twice the path's load).  Keeping 64-row tiles, two
-// workgroups on a CU and the first units in global memory: 2.90 ms there, 94 us against 87 for
-// 300 trees of depth 9 over 90 features and 103,069 rows.  Workgroups that loop over tiles and request the
-// next rows before they finish the sums: 3.15 ms.
+// Where a CU holds one workgroup, large batches run a kernel of their own for the sums (forest_deep_tiles_kernel), whose
+// workgroups take tile after tile.  128 trees of depth 12, 256 features, 4,000,000 rows: 2.15 ms (a workgroup per tile 2.71;
+// 14.5 with every node tested, forest_kernels_rankbank.hip).
+//
+// In the kernel with a workgroup per tile: keeping 64-row tiles, two workgroups on a CU and the first units in global memory,
+// 2.90 ms there, 94 us against 87 for 300 trees of depth 9 over 90 features and 103,069 rows.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 #include "forest_device.hpp"
 #include "forest_kernel_common.hpp"
@@ -354,6 +353,227 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, SHARED ? 8 : 4) void forest_deep
     else deep_rows<NR, MODE, WP>(m, X, row0, n_rows, scores, labels, leaf_out);
 }
 
+// The tops of NT trees whose nodes stand NODES_BYTES apart, all row groups: idx = the tree's LDS address | 8 * (leaf slot reached).
+template <int NT, int NR>
+__device__ __forceinline__ void deep_tops(uint32_t stage, const uint32_t (&xa)[NR], const DeepHead (&head)[NT], uint32_t (&idx)[NT][NR])
+{
+    float x1[NT][NR], x2[NT][NR], x3[NT][NR];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            x1[j][r] = lds_read<float>(xa[r] + head[j].w[3]);
+            x2[j][r] = lds_read<float>(xa[r] + head[j].w[5]);
+            x3[j][r] = lds_read<float>(xa[r] + head[j].w[7]);
+        }
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const float t1 = __uint_as_float(head[j].w[2]), t2 = __uint_as_float(head[j].w[4]), t3 = __uint_as_float(head[j].w[6]);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const uint64_t m1 = __ballot(!(x1[j][r] <= t1)), m2 = __ballot(!(x2[j][r] <= t2)), m3 = __ballot(!(x3[j][r] <= t3));
+            const uint64_t second = (m1 & m3) | (~m1 & m2);
+            uint32_t b0, b1;
+            asm("v_cndmask_b32 %0, 0, 8, %1" : "=v"(b0) : "s"(m1));
+            asm("v_cndmask_b32 %0, 0, 16, %1" : "=v"(b1) : "s"(second));
+            idx[j][r] = (stage + j * NODES_BYTES) | b0 | b1;
+        }
+    }
+#pragma unroll
+    for (int l = 2; l < DEEP_TOP; ++l) {
+        Vec2 node[NT][NR];
+        float x[NT][NR];
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) node[j][r] = lds_read<Vec2>(idx[j][r] + (8u << l));
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) x[j][r] = lds_read<float>(xa[r] + node[j][r].y);
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) idx[j][r] = x[j][r] <= __uint_as_float(node[j][r].x) ? idx[j][r] : idx[j][r] | 8u << l;
+    }
+}
+
+// The sums of tile after tile, by workgroups that have a CU to themselves (takes_tiles, forest_plan.hpp): the rows of the next
+// tile are on their way from memory to registers while this one is walked, and the tops of two trees are walked together, in
+// turn with their units in the same stage.
+//
+// What bounds it is the CU's vector memory path, which returns loads in the order they were asked for, whichever wave did.  A tile's
+// rows hold up everybody's units behind them for as long as they take from memory, so they are asked for once a tile, before
+// the sums and the first tops, which need no memory (asked for before every two trees 2.75 ms, once behind the barrier of the sums
+// 2.6), and in whole lines: eight rows' 128 bytes a load; 64 bytes of 16 rows, whose lines the non-temporal policy drops between
+// their halves, take 4.3 us a tile instead of 2.0 (2.31 ms).  Then the units: 33 lines from the L2 per tree and 64 rows, 64 bytes a
+// clock; 24 lanes have a path beyond the top, and what a step reads of a line is often gone before the next.  Gathered into whole
+// waves through LDS the lanes ask for as many lines, in a longer chain: 1.36 ms of units instead of 0.9.  Without X it would take
+// 1.83 ms, without units 1.23, without either 0.89 (LDS 62 % busy).  All the tops of four pairs of trees before their units, so that
+// X waits behind more of them: 2.45 ms instead of 2.31.
+template <int NR, int MODE, int WP>
+__global__ __launch_bounds__(DEEP_WAVES * TILE, 4) void forest_deep_tiles_kernel(DevModel model, const float *__restrict__ X, int64_t n_rows,
+                                                                                float *scores, int32_t *labels, int32_t *)
+{
+    constexpr int ROWS = NR * TILE, W = WP, NT = 2;
+    static_assert(MODE == DEEP_COLUMN ? WP == 1 : MODE == DEEP_VECTOR && WP == 2, "sums that fit the waves' stages");
+    static_assert(DEEP_WAVES * W * ROWS * sizeof(double) <= XBASE, "sums that fit the waves' stages");
+    const int lane = threadIdx.x & (TILE - 1), wave = uniform(threadIdx.x >> 6);
+    const int F = model.n_features, T = model.n_trees;
+    const uint32_t group_stride = static_cast<uint32_t>(F) * 256;
+    const uint32_t stage = static_cast<uint32_t>(wave) * TOP_BYTES;  // of two trees, the nodes or the first units
+    const int t_begin = T * wave / DEEP_WAVES, t_end = T * (wave + 1) / DEEP_WAVES;
+
+    Vec4 nodes[NT], units[NT];  // of the pair that comes next
+    // 16 bytes a lane of what stands `from` bytes behind the tops of trees t and t + 1
+    const auto top_of = [&](int t) { return reinterpret_cast<const char *>(model.deep.top) + static_cast<int64_t>(min(t, T - 1)) * TOP_BYTES; };
+    const auto fetch = [&](Vec4 (&to)[NT], int t, uint32_t from) {
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const char *top = top_of(t + j);
+            uint32_t mine = lane * 16;
+            asm volatile("" : "+s"(top), "+v"(mine));
+            to[j] = *(GlobalVec4)((GlobalBytes)top + from + mine);
+        }
+    };
+    constexpr int STEP = static_cast<int>(CUS) * ROWS;  // from a workgroup's tile to its next one
+    const int n = static_cast<int>(n_rows);
+    TileAhead<NR> ahead;
+    const auto request = [&](int row0) {
+        if (row0 < n) ahead.request(X + static_cast<int64_t>(row0) * F, min(ROWS, n - row0), F, wave, lane);
+    };
+    int row0 = static_cast<int>(blockIdx.x) * ROWS;
+    request(row0);
+    fetch(nodes, t_begin, 0);
+    fetch(units, t_begin, NODES_BYTES);
+    ahead.store(F, XBASE, group_stride, 256, wave, lane);
+    request(row0 + STEP);
+
+    uint32_t xa[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) xa[r] = XBASE + static_cast<uint32_t>(r) * group_stride + lane * 4;
+    double total[W];
+    bool sums_there = false;  // of the tile before, whose rows' threads have them in `total`
+    for (;;) {
+        __syncthreads();
+        if (sums_there && threadIdx.x < ROWS) finish_few<W>(model, total, row0 - STEP + static_cast<int>(threadIdx.x), scores, labels);
+
+        double acc[W][NR];
+#pragma unroll
+        for (int k = 0; k < W; ++k)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) acc[k][r] = 0.0;
+        for (int t = t_begin; t < t_end; t += NT) {
+            const bool two = t + 1 < t_end;
+            uint32_t idx[NT][NR];
+            DeepHead head[NT];
+            uint32_t pieces = stage + lane * 16;
+            asm volatile("" : "+v"(pieces));
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                head[j] = deep_head(top_of(t + j), 0);
+            }
+#pragma unroll
+            for (int j = 0; j < NT; ++j) lds_write<Vec4>(pieces + j * NODES_BYTES, nodes[j]);
+            deep_tops<NT, NR>(stage, xa, head, idx);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) lds_write<Vec4>(pieces + j * NODES_BYTES, units[j]);
+            const int after = t + NT < t_end ? t + NT : t_begin;
+            fetch(nodes, after, 0);
+            fetch(units, after, NODES_BYTES);
+
+            Vec2 what[NT][NR];
+            uint32_t at[NT][NR];
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    what[j][r] = lds_read<Vec2>(idx[j][r]);
+                    at[j][r] = idx[j][r] - (stage + j * NODES_BYTES);
+                }
+            if (!two) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) what[1][r] = Vec2{0, 0};
+            }
+            const char *units_of[NT];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                units_of[j] = reinterpret_cast<const char *>(model.deep.unit) + static_cast<int64_t>(head[j].w[0]) * 8;
+                asm volatile("" : "+s"(units_of[j]));
+            }
+            const auto at_a_node = [&](int j, int r) { return __builtin_isnan(__uint_as_float(what[j][r].y)); };
+            const auto any_at_a_node = [&]() {
+                bool any = false;
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) any |= at_a_node(j, r);
+                return __any(any) != 0;
+            };
+            if (any_at_a_node()) {
+                do {
+                    float x[NT][NR];
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+#pragma unroll
+                        for (int r = 0; r < NR; ++r) {
+                            uint32_t f = __builtin_amdgcn_ubfe(what[j][r].y, 14, 9);
+                            if (WP == 2) f = min(f, static_cast<uint32_t>(F) - 1);
+                            x[j][r] = lds_read<float>(xa[r] + (f << 8));
+                        }
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+#pragma unroll
+                        for (int r = 0; r < NR; ++r) asm volatile("" : "+v"(x[j][r]));
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+#pragma unroll
+                        for (int r = 0; r < NR; ++r)
+                            if (at_a_node(j, r)) {
+                                at[j][r] += ((what[j][r].y & DEEP_MAX_DISTANCE) + (x[j][r] <= __uint_as_float(what[j][r].x) ? 0u : 1u)) << 3;
+                                what[j][r] = *(GlobalUnits)((GlobalBytes)units_of[j] + at[j][r]);
+                            }
+                } while (any_at_a_node());
+            }
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                if (j > 0 && !two) break;
+#pragma unroll
+                for (int r = 0; r < NR; ++r) {
+                    acc[0][r] += static_cast<double>(__uint_as_float(what[j][r].x));
+                    if (W == 2) acc[W - 1][r] += static_cast<double>(__uint_as_float(what[j][r].y));
+                }
+            }
+        }
+        __syncthreads();  // the tile and the stages are free
+        uint32_t sums = lane * 8;  // [DEEP_WAVES][W][ROWS]
+        asm volatile("" : "+v"(sums));
+#pragma unroll
+        for (int k = 0; k < W; ++k)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) lds_write<double>(sums + wave * (W * ROWS * 8) + (k * ROWS + r * TILE) * 8, acc[k][r]);
+        if (row0 + STEP < n) {
+            ahead.store(F, XBASE, group_stride, 256, wave, lane);
+            request(row0 + 2 * STEP);
+        }
+        __syncthreads();
+        if (threadIdx.x < ROWS) {
+            sums = threadIdx.x * 8;
+            asm volatile("" : "+v"(sums));
+#pragma unroll
+            for (int k = 0; k < W; ++k) {
+                total[k] = 0.0;
+#pragma unroll
+                for (int w = 0; w < DEEP_WAVES; ++w) total[k] += lds_read<double>(sums + (w * W + k) * ROWS * 8);
+            }
+        }
+        row0 += STEP;
+        if (row0 >= n) break;
+        sums_there = true;
+    }
+    if (const int row = row0 - STEP + static_cast<int>(threadIdx.x); threadIdx.x < ROWS && row < n) finish_few<W>(model, total, row, scores, labels);
+}
+
 template <int MODE, int WP, bool SHARED>
 KernelFn pick_groups(int groups, int last)
 {
@@ -391,20 +611,32 @@ KernelFn pick(int groups, int last, int mode, int width, bool shared)
 
 hipError_t init_deep_kernels(size_t lds_limit)
 {
+    const auto init = [&](KernelFn kernel) {
+        const void *fn = reinterpret_cast<const void *>(kernel);
+        hipFuncAttributes attr;
+        if (hipError_t e = hipFuncGetAttributes(&attr, fn); e != hipSuccess) return e;
+        if (attr.sharedSizeBytes != 0) return hipErrorInvalidValue;  // the kernels address LDS from 0
+        return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_limit));
+    };
+    for (KernelFn fn : {forest_deep_tiles_kernel<DEEP_TILE_GROUPS, DEEP_COLUMN, 1>, forest_deep_tiles_kernel<DEEP_TILE_GROUPS, DEEP_VECTOR, 2>})
+        if (hipError_t e = init(fn); e != hipSuccess) return e;
     for (int mode : {DEEP_COLUMN, DEEP_COLUMNS, DEEP_VECTOR, DEEP_LEAVES, DEEP_LEAVES_THROUGH, DEEP_FEW_LEAVES})
         for (int width : {2, 4, 8, 12, 16})
             for (int groups : {1, 2})
                 for (int last = 1; last <= groups; ++last)
-                    for (bool shared : {true, false}) {
-                        const void *fn = reinterpret_cast<const void *>(pick(groups, last, mode, width, shared));
-                        hipFuncAttributes attr;
-                        if (hipError_t e = hipFuncGetAttributes(&attr, fn); e != hipSuccess) return e;
-                        if (attr.sharedSizeBytes != 0) return hipErrorInvalidValue;  // the kernels address LDS from 0
-                        if (hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_limit));
-                            e != hipSuccess)
-                            return e;
-                    }
+                    for (bool shared : {true, false})
+                        if (hipError_t e = init(pick(groups, last, mode, width, shared)); e != hipSuccess) return e;
     return hipSuccess;
+}
+
+hipError_t launch_deep_tiles(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels, hipStream_t stream)
+{
+    static_assert(MAX_LAUNCH_ROWS + 2 * CUS * PLAN_ROWS * DEEP_TILE_GROUPS <= 0x7fffffff, "rows count in 32 bits");
+    const KernelFn fn = m.leaf_width > 1 ? forest_deep_tiles_kernel<DEEP_TILE_GROUPS, DEEP_VECTOR, 2> : forest_deep_tiles_kernel<DEEP_TILE_GROUPS, DEEP_COLUMN, 1>;
+    const size_t lds = deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, DEEP_TILE_GROUPS, true);
+    hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(tile_workgroups(n_rows))), dim3(DEEP_WAVES * TILE), lds, stream, m, X, n_rows, scores,
+                       labels, nullptr);
+    return hipGetLastError();
 }
 
 hipError_t launch_deep(const DevModel &m, int groups, const TailPlan &t, const float *X, int64_t n_rows, float *scores, int32_t *labels,

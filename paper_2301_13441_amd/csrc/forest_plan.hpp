@@ -411,6 +411,27 @@ inline bool ends_in_smaller(const DevModel &m, int kernel, int groups, int64_t n
     return kernel == FOREST_KERNEL_DEEP && (deep_shares_cu(m, groups, sums) || n_rows < TAIL_MAX_ROUNDS * CUS * PLAN_ROWS * groups);
 }
 
+// Sums by workgroups that take tile after tile (forest_deep_tiles_kernel), one on a CU with two row groups: where the tile leaves no room for
+// a second workgroup of two groups, whose walk would hide the first one's wait for its rows, and from two tiles a CU on.  us,
+// a workgroup per tile / tile after tile, 128 trees of depth 12, vector leaves: 1M rows, 40 features 432 / 527, 90 features 500 / 580, 128
+// (two workgroups of one group) 620 / 564, 192 679 / 557, 224 689 / 555; of 300 trees of depth 9 582 / 791, 796 / 761, 846 / 768, 900 / 770 for 90,
+// 128, 192 and 224 features; 256 features: 33,000 rows 37.8 / 38.4, 66,000 60.7 / 57.6, 100,000 83.7 / 77.5, 150,000 113.7 / 97.1,
+// 4M 2712 / 2150.
+constexpr int DEEP_TILE_GROUPS = 2;
+
+inline bool takes_tiles(const DevModel &m, int64_t n_rows, int n_splits, bool sums)
+{
+    if (!sums || n_splits > 1 || m.leaf_width > 2 || (m.leaf_width == 1 && m.n_outputs > 1)) return false;
+    if (n_rows < 2 * CUS * PLAN_ROWS * DEEP_TILE_GROUPS) return false;
+    return !deep_shares_cu(m, DEEP_TILE_GROUPS, true) && deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, DEEP_TILE_GROUPS, true) <= CU_LDS_BYTES;
+}
+
+inline int64_t tile_workgroups(int64_t n_rows)
+{
+    const int64_t tiles = (n_rows + PLAN_ROWS * DEEP_TILE_GROUPS - 1) / (PLAN_ROWS * DEEP_TILE_GROUPS);
+    return tiles < CUS ? tiles : CUS;
+}
+
 // One lane per (row, tree): the smallest batches of the walk kernels' models (forest_kernels_split.hip).
 // Up to a million tests the gathers take less than what a walk kernel's workgroups begin and end with.
 // Microseconds a call, this kernel / walk kernels with their reduction, 500 trees of depth 8: 32 rows 7.5 / 9.3,
@@ -519,6 +540,7 @@ struct LaunchPlan {
     int32_t groups = 1;  // walk kernels: row groups of 64 rows per workgroup
     int32_t splits = 1;  // shares the trees are cut into
     bool fits = true;    // false: the dense kernels' split launch does not fit the workspace
+    bool tiles = false;  // deep kernel: workgroups that take tile after tile
 };
 
 // `sums`: scores or labels are asked for, not leaf ids.  A batch the dense kernels' workspace does not hold is
@@ -540,7 +562,8 @@ inline LaunchPlan plan_launch(const DevModel &m, const Workspace *ws, int64_t n_
         // (128 trees of depth 12: 2.9 ms against 14.5 with the register-bank kernel)
         p.kernel = FOREST_KERNEL_DEEP;
         p.splits = choose_walk_splits(m, ws, n_rows, sums);
-        p.groups = choose_groups(m, m.deep.groups, n_rows, p.splits);
+        p.tiles = takes_tiles(m, n_rows, p.splits, sums);
+        p.groups = p.tiles ? DEEP_TILE_GROUPS : choose_groups(m, m.deep.groups, n_rows, p.splits);
     } else if (m.path == PATH_RANK) {
         p.kernel = FOREST_KERNEL_RANK;
     } else if (m.path == PATH_RANK_LDS) {
@@ -552,10 +575,10 @@ inline LaunchPlan plan_launch(const DevModel &m, const Workspace *ws, int64_t n_
     return p;
 }
 
-// The workgroups of one range of rows, walk kernels.
+// The workgroups of one range of rows, walk kernels; of those that take tile after tile, the tiles.
 inline TailPlan range_workgroups(const DevModel &m, const LaunchPlan &p, int64_t n_rows, bool sums)
 {
-    return ends_in_smaller(m, p.kernel, p.groups, n_rows, sums) ? choose_tail(p.groups, n_rows, p.splits) : whole(p.groups, n_rows);
+    return !p.tiles && ends_in_smaller(m, p.kernel, p.groups, n_rows, sums) ? choose_tail(p.groups, n_rows, p.splits) : whole(p.groups, n_rows);
 }
 
 // The shape of the launches of a plan.
@@ -597,6 +620,7 @@ inline forest_launch_t launch_shape(const DevModel &m, const LaunchPlan &p, int6
         const TailPlan t = range_workgroups(m, p, rows, sums);
         s.workgroups = t.full + t.after;
         s.last_rows_per_workgroup = PLAN_ROWS * t.groups;
+        s.tile_after_tile = p.tiles;
     }
     return s;
 }

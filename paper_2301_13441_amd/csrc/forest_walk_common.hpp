@@ -30,6 +30,7 @@ __device__ __forceinline__ void lds_write(uint32_t at, T v)
 typedef float FloatRun4 __attribute__((ext_vector_type(4), aligned(4)));
 #if defined(__HIP_DEVICE_COMPILE__)
 typedef const __attribute__((address_space(1))) FloatRun4 *GlobalRuns;
+typedef const __attribute__((address_space(1))) Vec4 *GlobalVec4;
 typedef const __attribute__((address_space(4))) uint32_t *WalkTop;
 typedef const __attribute__((address_space(4))) int32_t *WalkTable;
 typedef const __attribute__((address_space(1))) char *GlobalBytes;
@@ -37,6 +38,7 @@ typedef const __attribute__((address_space(1))) float *GlobalFloats;
 typedef const __attribute__((address_space(1))) int32_t *GlobalInts;
 #else
 typedef const FloatRun4 *GlobalRuns;
+typedef const Vec4 *GlobalVec4;
 typedef const uint32_t *WalkTop;  // host pass: the kernel body is only parsed
 typedef const int32_t *WalkTable;
 typedef const char *GlobalBytes;
@@ -103,6 +105,78 @@ __device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t 
         }
     }
 }
+
+// Register a's value of a lane whose bit STEP (1, 2 or 4) is set and register b's of lane ^ STEP change places: that bit of the
+// lane and the register's index, a or b, are exchanged.
+template <int STEP>
+__device__ __forceinline__ void exchange_lane_bit(float &a, float &b, bool odd)
+{
+    const int x = __float_as_int(a), y = __float_as_int(b);
+    if constexpr (STEP == 4) {  // rows of 16 lanes shifted by 4, into the odd fours and into the even ones
+        a = __int_as_float(__builtin_amdgcn_update_dpp(x, y, 0x114, 0xf, 0xa, false));
+        b = __int_as_float(__builtin_amdgcn_update_dpp(y, x, 0x104, 0xf, 0x5, false));
+    } else {
+        constexpr int perm = STEP == 1 ? 0xB1 : 0x4E;  // fours of lanes as [1, 0, 3, 2], [2, 3, 0, 1]
+        const int from_b = __builtin_amdgcn_mov_dpp(y, perm, 0xf, 0xf, true), from_a = __builtin_amdgcn_mov_dpp(x, perm, 0xf, 0xf, true);
+        a = __int_as_float(odd ? from_b : x);
+        b = __int_as_float(odd ? y : from_a);
+    }
+}
+
+// The same tile on its way to registers while the one before is walked.  A piece is 64 rows x 32 features: eight loads of
+// eight rows' 128 bytes, one piece a wave at most.  F >= 4.
+template <int NR>
+struct TileAhead {
+    static constexpr int LOADS = 8;
+    FloatRun4 v[LOADS];
+
+    struct Piece {
+        int group, feature;  // row group, first feature
+    };
+    static __device__ __forceinline__ Piece piece(int F, int wave)
+    {
+        const int blocks = (F + 31) >> 5, at = min(wave, blocks * NR - 1);
+        static_assert(NR <= 2, "one comparison");
+        const int group = NR == 1 ? 0 : at >= blocks;
+        return Piece{group, (at - group * blocks) * 32};
+    }
+    // The tile whose first row `tile` points at and which has `rows` rows.
+    __device__ __forceinline__ void request(const float *tile, int rows, int F, int wave, int lane)
+    {
+        const Piece p = piece(F, wave);
+        asm volatile("" : "+v"(lane));
+        const int f = min(p.feature + (lane & 7) * 4, F - 4);
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u) {
+            const int row = min(p.group * TILE + u * 8 + (lane >> 3), rows - 1);
+            v[u] = __builtin_nontemporal_load((GlobalRuns)((GlobalBytes)tile + static_cast<uint32_t>(row * F + f) * 4));
+        }
+    }
+    __device__ __forceinline__ void store(int F, uint32_t xbase, uint32_t group_stride, uint32_t stride, int wave, int lane) const
+    {
+        asm volatile("" : "+v"(lane));
+        const bool odd1 = lane & 1, odd2 = lane & 2;
+        const Piece p = piece(F, wave);
+        // after the exchange a lane has the features of one row, register k four of them from 4 k
+        const uint32_t row = xbase + static_cast<uint32_t>(p.group) * group_stride + static_cast<uint32_t>((lane & 7) * 8 + (lane >> 3)) * 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float x[LOADS];
+#pragma unroll
+            for (int k = 0; k < LOADS; ++k) x[k] = v[k][i];
+#pragma unroll
+            for (int k = 0; k < LOADS; k += 2) exchange_lane_bit<1>(x[k], x[k + 1], odd1);
+#pragma unroll
+            for (int k = 0; k < LOADS; ++k)
+                if (!(k & 2)) exchange_lane_bit<2>(x[k], x[k + 2], odd2);
+#pragma unroll
+            for (int k = 0; k < LOADS / 2; ++k) exchange_lane_bit<4>(x[k], x[k + 4], false);
+#pragma unroll
+            for (int k = 0; k < LOADS; ++k)
+                lds_write<float>(row + (static_cast<uint32_t>(min(p.feature + k * 4, F - 4)) + i) * stride, x[k]);
+        }
+    }
+};
 
 // The ids of n trees from `begin` of a row, counted from a workgroup's first: those of four with one store.  The row's place
 // comes from 32-bit factors (from the row of the batch, a 64-bit product, leaf ids of 262,144 rows of 128 x depth 6 took

@@ -109,6 +109,31 @@ def test_deep_kernels_by_rows_per_lane(features, depth, outputs, width, rows, gr
         _check(f, _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng), leaves=True)
 
 
+def test_deep_sums_go_tile_after_tile_where_a_cu_holds_one_tile():
+    from paper_2301_13441_amd import binding
+    plan = lambda features, rows, outputs=1, width=1, leaves=False: binding.forest_packed_launch(_forest(1, 20, 9, features, outputs, width), rows, leaves, form="walk")
+    for features, rows, outputs, width, leaves, want in (
+            (96, 10**6, 1, 1, False, 0), (97, 65535, 1, 1, False, 0), (97, 65536, 1, 1, False, 1), (256, 65536, 2, 2, False, 1), (257, 10**6, 1, 1, False, 0),
+            (192, 10**6, 2, 1, False, 0), (192, 10**6, 3, 3, False, 0), (192, 10**6, 1, 1, True, 0)):
+        s = plan(features, rows, outputs, width, leaves)
+        assert s["kernel"] == "deep" and s["tile_after_tile"] == want, (features, rows, outputs, width, leaves)
+        if want:
+            assert s["rows_per_workgroup"] == s["last_rows_per_workgroup"] == 128 and s["workgroups"] == -(-rows // 128)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("features", [97, 127, 130, 193, 224, 253, 256])
+@pytest.mark.parametrize("depth,outputs,width", [(9, 1, 1), (12, 2, 2)])
+@pytest.mark.parametrize("trees,rows", [(1, 65536), (17, 65536 + 1), (33, 65536 + 128 + 65), (48, 3 * 32768 - 3)])
+def test_deep_kernels_tile_after_tile(features, depth, outputs, width, trees, rows):
+    """Whole and ragged pieces of 32 features, a last tile of one row and of two row groups, CUs with two and three tiles; waves
+    without trees, with one and with three."""
+    rng = np.random.default_rng(100 * depth + features + trees)
+    f = _forest(9 * depth + features, trees, depth, features, outputs, width, stop=0.3)
+    X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
+    _check(f, X, leaves=False)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("width", [9, 11, 12, 13, 16])
 def test_deep_kernels_with_wide_leaves(width):
