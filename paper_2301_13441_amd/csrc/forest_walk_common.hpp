@@ -48,48 +48,68 @@ typedef const int32_t *GlobalInts;
 
 typedef uint32_t LooseVec4 __attribute__((ext_vector_type(4), aligned(4)));
 
-// The X tile of a workgroup: rows [row0, row0 + 64 NR) as float32, row group g, feature f and row r of the
-// group at xbase + g * group_stride + f * stride + 4 r.  It is filled in pieces of 16 rows x 16 features,
-// four neighbouring features of a row per lane: 64 bytes of a row of X, and LDS writes that fall into
-// 16 banks.  A wave takes a contiguous run of pieces, so that both halves of a 128-byte line are
-// requested by one wave one after the other, with the non-temporal policy: X is read once and should
-// not push the trees out of the L2.  The four features of a lane that would reach beyond the row are the row's
-// last four (written twice, with the same values), and the rows beyond the batch are its last row, so that every
-// load is whole and none waits for another: a lane's features one by one under a mask of their own cost a
-// second round trip to memory, and the addresses as 64-bit products more instructions than the loads (256 features,
-// 4M rows of 128 deep trees: 2.89 -> 2.80 ms a call; 90 features, 103,069 rows of 300: 87.2 -> 84.5 us; 1,021 rows of
-// 2000 x depth 6: 18.15 -> 17.8).  NAN_IS_INF: a NaN is stored as +Inf.
-template <int NR, int P, bool NAN_IS_INF>
-__device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t n_rows, int F, uint32_t xbase, uint32_t group_stride,
-                                          uint32_t stride, int wave, int lane)
+// Bit BIT of the lane and the index of two registers change places: lane l of b with bit BIT clear and lane l ^ 1 << BIT of a.
+template <int BIT>
+__device__ __forceinline__ void exchange_lane_bit(float &a, float &b, int lane)
 {
+    const uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+    if constexpr (BIT < 2) {
+        constexpr int perm = BIT == 0 ? 0xB1 : 0x4E;  // lanes [1, 0, 3, 2] or [2, 3, 0, 1] of every four
+        const uint32_t from_b = __builtin_amdgcn_mov_dpp(static_cast<int>(y), perm, 0xf, 0xf, true);
+        const uint32_t from_a = __builtin_amdgcn_mov_dpp(static_cast<int>(x), perm, 0xf, 0xf, true);
+        a = __uint_as_float(lane >> BIT & 1 ? from_b : x);
+        b = __uint_as_float(lane >> BIT & 1 ? y : from_a);
+    } else {
+        static_assert(BIT == 4 || BIT == 5, "halves and quarters of a wave");
+        const auto r = BIT == 4 ? __builtin_amdgcn_permlane16_swap(x, y, false, false) : __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        a = __uint_as_float(r[0]);
+        b = __uint_as_float(r[1]);
+    }
+}
+
+// How the lanes of a wave take eight rows' 128 bytes in one load: bits 1 to 3 the row, bits 0, 4 and 5 the four of features.  A line goes whole,
+// and the bits that pairs of registers exchange in one instruction are features.
+__device__ __forceinline__ int line_row(int lane) { return (lane >> 1) & 7; }
+__device__ __forceinline__ int line_four(int lane) { return (lane & 1) | (lane >> 3 & 6); }
+
+// The X tile of a workgroup: rows [row0, row0 + 64 NR) as float32, row group g, feature f and row r of the
+// group at xbase + g * group_stride + f * stride + 4 r.  It is filled in pieces of 8 L rows x 32 features, L loads of
+// eight rows' 128 bytes, non-temporally: X is read once and should not push the trees out of the L2.  A line that is asked for in
+// two halves is read twice so, and what waits for it holds up the other loads of the CU, which return in order (16 rows' 64
+// bytes a load and no exchange: 103,069 rows of 300 deep trees, 90 features 72.2 us, so 69.5; 100 trees of depth 6, 64 features,
+// 300,000 rows 44.9 / 41.2, 300 features, 100,000 rows 61.7 / 55.6; but 8 features, 1M rows 93.8 / 98.0, so rows of at most 16
+// features go that way).  The lanes exchange what they loaded until 16 rows are written at a time, for 16 of 32 LDS banks.
+// The four features of a lane that would reach beyond the row are the row's last four (written twice, with the same values), and
+// the rows beyond the batch are its last row, so that every load is whole and none waits for another: a lane's features
+// one by one under a mask of their own cost a second round trip to memory, and the addresses as 64-bit products more
+// instructions than the loads (256 features, 4M rows of 128 deep trees: 2.89 -> 2.80 ms a call).  NAN_IS_INF: a NaN is stored as +Inf.
+template <int NR, int P, bool NAN_IS_INF, bool LINES>
+__device__ __forceinline__ void fill_pieces(const float *X, int64_t row0, int64_t n_rows, int F, uint32_t xbase, uint32_t group_stride,
+                                            uint32_t stride, int wave, int lane)
+{
+    constexpr int L = !LINES ? 1 : NR == 1 ? 2 : 4, LOAD_ROWS = LINES ? 8 : 16, ROWS = LOAD_ROWS * L, FEATURES = LINES ? 32 : 16, G = P / L;  // G pieces on their way at a time
     const char *tile = reinterpret_cast<const char *>(X + row0 * F);
     const int rows = n_rows - row0 < NR * TILE ? static_cast<int>(n_rows - row0) : NR * TILE;
-    const auto value = [](float v) { return NAN_IS_INF ? fminf(v, __builtin_inff()) : v; };
-    if (F < 4) {  // a lane per row
-        for (int g = wave; g < NR; g += WALK_WAVES)
-            for (int f = 0; f < F; ++f) {
-                const int row = min(g * TILE + lane, rows - 1);
-                lds_write<float>(xbase + g * group_stride + f * stride + lane * 4, value(reinterpret_cast<const float *>(tile)[row * F + f]));
-            }
-        return;
-    }
-    const int blocks = (F + 15) >> 4, pieces = blocks * (NR * 4);
+    const int blocks = LINES ? (F + FEATURES - 1) / FEATURES : 1, pieces = blocks * (NR * TILE / ROWS);
     const int begin = pieces * wave / WALK_WAVES, end = pieces * (wave + 1) / WALK_WAVES;
-    const int r = lane & 15, c = (lane >> 4) * 4;
     const uint32_t pitch = static_cast<uint32_t>(F) * 4;
-    int at_rows = begin / blocks, at_block = begin - at_rows * blocks;  // the piece: 16 rows from 16 * at_rows, 16 features from 16 * at_block
-    for (int t = begin; t < end; t += P) {
-        FloatRun4 v[P];
-        uint32_t to[P];
+    // a lane's row and four of features as loaded, and, of register 0, after the exchange
+    const int r = LINES ? line_row(lane) : lane & 15, c = LINES ? line_four(lane) : lane >> 4;
+    const int after_r = LINES ? (lane >> 1) & (ROWS - 1) : r, after_c = !LINES ? c : L == 2 ? (lane & 1) | (lane >> 5) * 4 : lane & 1;
+    int at_rows = begin / blocks, at_block = begin - at_rows * blocks;  // the piece
+    for (int t = begin; t < end; t += G) {
+        FloatRun4 v[G][L];
+        uint32_t to[G];
+        int block[G];
 #pragma unroll
-        for (int u = 0; u < P; ++u) {
-            if (t + u < end) {  // wave-uniform
-                const int f = min(at_block * 16 + c, F - 4), row = at_rows * 16 + r;
-                const uint32_t from = static_cast<uint32_t>(min(row, rows - 1)) * pitch + static_cast<uint32_t>(f) * 4;
-                v[u] = __builtin_nontemporal_load((GlobalRuns)((GlobalBytes)tile + from));
-                to[u] = xbase + static_cast<uint32_t>(at_rows >> 2) * group_stride + static_cast<uint32_t>(f) * stride +
-                        static_cast<uint32_t>(row & 63) * 4;
+        for (int g = 0; g < G; ++g) {
+            if (t + g < end) {  // wave-uniform
+                const int f = min(at_block * FEATURES + c * 4, F - 4), first = at_rows * ROWS;
+#pragma unroll
+                for (int u = 0; u < L; ++u)
+                    v[g][u] = __builtin_nontemporal_load((GlobalRuns)((GlobalBytes)tile + (static_cast<uint32_t>(min(first + u * LOAD_ROWS + r, rows - 1)) * pitch + static_cast<uint32_t>(f) * 4)));
+                to[g] = xbase + static_cast<uint32_t>(first >> 6) * group_stride + static_cast<uint32_t>((first & 63) + after_r) * 4;
+                block[g] = at_block;
                 if (++at_block == blocks) {
                     at_block = 0;
                     ++at_rows;
@@ -97,29 +117,46 @@ __device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t 
             }
         }
 #pragma unroll
-        for (int u = 0; u < P; ++u) {
-            if (t + u < end) {
+        for (int g = 0; g < G; ++g) {
+            if (t + g < end) {
+                uint32_t at[L];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) lds_write<float>(to[u] + i * stride, value(v[u][i]));
+                for (int k = 0; k < L; ++k) at[k] = to[g] + static_cast<uint32_t>(min(block[g] * FEATURES + (after_c + 2 * k) * 4, F - 4)) * stride;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float x[L];
+#pragma unroll
+                    for (int k = 0; k < L; ++k) x[k] = v[g][k][i];
+                    if constexpr (L > 1) exchange_lane_bit<4>(x[0], x[1], lane);
+                    if constexpr (L == 4) {
+                        exchange_lane_bit<4>(x[2], x[3], lane);
+                        exchange_lane_bit<5>(x[0], x[2], lane);
+                        exchange_lane_bit<5>(x[1], x[3], lane);
+                    }
+#pragma unroll
+                    for (int k = 0; k < L; ++k) lds_write<float>(at[k] + i * stride, NAN_IS_INF ? fminf(x[k], __builtin_inff()) : x[k]);
+                }
             }
         }
     }
 }
 
-// Register a's value of a lane whose bit STEP (1, 2 or 4) is set and register b's of lane ^ STEP change places: that bit of the
-// lane and the register's index, a or b, are exchanged.
-template <int STEP>
-__device__ __forceinline__ void exchange_lane_bit(float &a, float &b, bool odd)
+template <int NR, int P, bool NAN_IS_INF>
+__device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t n_rows, int F, uint32_t xbase, uint32_t group_stride,
+                                          uint32_t stride, int wave, int lane)
 {
-    const int x = __float_as_int(a), y = __float_as_int(b);
-    if constexpr (STEP == 4) {  // rows of 16 lanes shifted by 4, into the odd fours and into the even ones
-        a = __int_as_float(__builtin_amdgcn_update_dpp(x, y, 0x114, 0xf, 0xa, false));
-        b = __int_as_float(__builtin_amdgcn_update_dpp(y, x, 0x104, 0xf, 0x5, false));
-    } else {
-        constexpr int perm = STEP == 1 ? 0xB1 : 0x4E;  // fours of lanes as [1, 0, 3, 2], [2, 3, 0, 1]
-        const int from_b = __builtin_amdgcn_mov_dpp(y, perm, 0xf, 0xf, true), from_a = __builtin_amdgcn_mov_dpp(x, perm, 0xf, 0xf, true);
-        a = __int_as_float(odd ? from_b : x);
-        b = __int_as_float(odd ? y : from_a);
+    if (F > 16) {
+        fill_pieces<NR, P, NAN_IS_INF, true>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
+    } else if (F >= 4) {
+        fill_pieces<NR, P, NAN_IS_INF, false>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
+    } else {  // a lane per row
+        const float *tile = X + row0 * F;
+        const int rows = n_rows - row0 < NR * TILE ? static_cast<int>(n_rows - row0) : NR * TILE;
+        for (int g = wave; g < NR; g += WALK_WAVES)
+            for (int f = 0; f < F; ++f) {
+                const float x = tile[min(g * TILE + lane, rows - 1) * F + f];
+                lds_write<float>(xbase + g * group_stride + f * stride + lane * 4, NAN_IS_INF ? fminf(x, __builtin_inff()) : x);
+            }
     }
 }
 
@@ -140,37 +177,39 @@ struct TileAhead {
         const int group = NR == 1 ? 0 : at >= blocks;
         return Piece{group, (at - group * blocks) * 32};
     }
+    // A lane's row and four of features in a load: bits 0, 1 and 4 the four.
+    static __device__ __forceinline__ int row_of(int lane) { return (lane >> 2 & 3) | (lane >> 3 & 4); }
+    static __device__ __forceinline__ int four_of(int lane) { return (lane & 3) | (lane >> 2 & 4); }
     // The tile whose first row `tile` points at and which has `rows` rows.
     __device__ __forceinline__ void request(const float *tile, int rows, int F, int wave, int lane)
     {
         const Piece p = piece(F, wave);
         asm volatile("" : "+v"(lane));
-        const int f = min(p.feature + (lane & 7) * 4, F - 4);
+        const int f = min(p.feature + four_of(lane) * 4, F - 4);
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) {
-            const int row = min(p.group * TILE + u * 8 + (lane >> 3), rows - 1);
+            const int row = min(p.group * TILE + u * 8 + row_of(lane), rows - 1);
             v[u] = __builtin_nontemporal_load((GlobalRuns)((GlobalBytes)tile + static_cast<uint32_t>(row * F + f) * 4));
         }
     }
     __device__ __forceinline__ void store(int F, uint32_t xbase, uint32_t group_stride, uint32_t stride, int wave, int lane) const
     {
         asm volatile("" : "+v"(lane));
-        const bool odd1 = lane & 1, odd2 = lane & 2;
         const Piece p = piece(F, wave);
         // after the exchange a lane has the features of one row, register k four of them from 4 k
-        const uint32_t row = xbase + static_cast<uint32_t>(p.group) * group_stride + static_cast<uint32_t>((lane & 7) * 8 + (lane >> 3)) * 4;
+        const uint32_t row = xbase + static_cast<uint32_t>(p.group) * group_stride + static_cast<uint32_t>(four_of(lane) * 8 + row_of(lane)) * 4;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             float x[LOADS];
 #pragma unroll
             for (int k = 0; k < LOADS; ++k) x[k] = v[k][i];
 #pragma unroll
-            for (int k = 0; k < LOADS; k += 2) exchange_lane_bit<1>(x[k], x[k + 1], odd1);
+            for (int k = 0; k < LOADS; k += 2) exchange_lane_bit<0>(x[k], x[k + 1], lane);
 #pragma unroll
             for (int k = 0; k < LOADS; ++k)
-                if (!(k & 2)) exchange_lane_bit<2>(x[k], x[k + 2], odd2);
+                if (!(k & 2)) exchange_lane_bit<1>(x[k], x[k + 2], lane);
 #pragma unroll
-            for (int k = 0; k < LOADS / 2; ++k) exchange_lane_bit<4>(x[k], x[k + 4], false);
+            for (int k = 0; k < LOADS / 2; ++k) exchange_lane_bit<4>(x[k], x[k + 4], lane);
 #pragma unroll
             for (int k = 0; k < LOADS; ++k)
                 lds_write<float>(row + (static_cast<uint32_t>(min(p.feature + k * 4, F - 4)) + i) * stride, x[k]);

@@ -292,3 +292,27 @@ def test_leaf_ids_past_the_l2(depth, trees, rows):
     finally:
         model.close()
     np.testing.assert_array_equal(got, oracle.predict(f, X, want_leaves=True, n_threads=8).leaf_node_id)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("features", [3, 4, 5, 15, 16, 17, 30, 31, 32, 33, 47, 61, 64])
+@pytest.mark.parametrize("rows,groups", [(12_301, 1), (33_333, 2), (70_003, 4)])
+def test_tiles_of_every_width(features, rows, groups):
+    """Rows that are no multiple of a line or of a load's features, fewer features than a load takes and one more, a ragged
+    last workgroup; walk kernels and the deep one, every size of workgroup."""
+    import torch
+    from paper_2301_13441_amd import binding
+    rng = np.random.default_rng(features)
+    for f in (_forest(features, 40, 6, features), wl.random_forest(features, n_trees=40, n_features=features, max_depth=9, stop_prob=0.25, aggregate=wl.AGG_SUM)):
+        s = binding.forest_packed_launch(f, rows, True, form="walk")
+        assert s["rows_per_workgroup"] == 64 * (groups if s["kernel"] == "walk" else min(groups, 2)) and s["shares"] == 1, s
+        X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
+        ref = oracle.predict(f, X, want_leaves=True, n_threads=8)
+        model = binding.forest_load_form(f, "walk")
+        try:
+            xd = torch.from_numpy(X).cuda()
+            np.testing.assert_array_equal(model.predict_leaves(xd).cpu().numpy(), ref.leaf_node_id)
+            scores, _ = model.predict(xd)
+            np.testing.assert_allclose(scores.cpu().numpy(), ref.scores, rtol=1e-5, atol=1e-6)
+        finally:
+            model.close()
