@@ -34,10 +34,10 @@ ORACLE_THREADS_MAX = 16   # the share of host cores one GPU's job may use on the
 # entry names the summary under profiles/ it comes from and the commit whose kernels were
 # measured; a workload without an entry reports null.
 MEASURED_TRAFFIC = {
-    "c2": {"bytes": 1.351e8, "profile": "profiles/forest_walk_kernels.md", "commit": "7dd9b06"},
-    "c3": {"bytes": 2.855e8, "profile": "profiles/forest_walk_kernels.md", "commit": "7dd9b06"},
-    "c4": {"bytes": 3.199e8, "profile": "profiles/forest_walk_kernels.md", "commit": "7dd9b06"},
-    "c5": {"bytes": 4.230e9, "profile": "profiles/forest_walk_kernels.md", "commit": "7dd9b06"},
+    "c2": {"bytes": 1.326e8, "profile": "profiles/forest_walk_kernels.md", "commit": "1cf39fc"},
+    "c3": {"bytes": 2.287e8, "profile": "profiles/forest_walk_kernels.md", "commit": "1cf39fc"},
+    "c4": {"bytes": 2.907e8, "profile": "profiles/forest_walk_kernels.md", "commit": "1cf39fc"},
+    "c5": {"bytes": 4.164e9, "profile": "profiles/forest_walk_kernels.md", "commit": "1cf39fc"},
     "l2": {"bytes": 1.456e9, "profile": "profiles/linear_kernels.md", "commit": "7dd9b06"},
     "l3": {"bytes": 1.119e9, "profile": "profiles/linear_kernels.md", "commit": "7dd9b06"},
     "l4": {"bytes": 9.600e8, "profile": "profiles/linear_kernels.md", "commit": "7dd9b06"},
