@@ -74,7 +74,10 @@ __device__ __forceinline__ int line_four(int lane) { return (lane & 1) | (lane >
 
 // The X tile of a workgroup: rows [row0, row0 + 64 NR) as float32, row group g, feature f and row r of the
 // group at xbase + g * group_stride + f * stride + 4 r.  It is filled in pieces of 8 L rows x 32 features, L loads of
-// eight rows' 128 bytes, non-temporally: X is read once and should not push the trees out of the L2.  A line that is asked for in
+// eight rows' 128 bytes, non-temporally where rows are whole lines (ONCE): X is read once and should not push the trees out of the
+// L2.  Where F is no multiple of 32 a line lies in two blocks or two rows and is asked for again, so there it should stay: loads
+// that say nothing of it, 90 features, 103,069 rows of 300 deep trees 71.0 us, so 67.5; trees of depth 6, 1M rows, 127 features
+// 312 / 304, 90 features 362 / 358, but 64 features 317 / 320 and 128 features 801 / 806.  A line that is asked for in
 // two halves is read twice so, and what waits for it holds up the other loads of the CU, which return in order (16 rows' 64
 // bytes a load and no exchange: 103,069 rows of 300 deep trees, 90 features 72.2 us, so 69.5; 100 trees of depth 6, 64 features,
 // 300,000 rows 44.9 / 41.2, 300 features, 100,000 rows 61.7 / 55.6; but 8 features, 1M rows 93.8 / 98.0, so rows of at most 16
@@ -83,7 +86,7 @@ __device__ __forceinline__ int line_four(int lane) { return (lane & 1) | (lane >
 // the rows beyond the batch are its last row, so that every load is whole and none waits for another: a lane's features
 // one by one under a mask of their own cost a second round trip to memory, and the addresses as 64-bit products more
 // instructions than the loads (256 features, 4M rows of 128 deep trees: 2.89 -> 2.80 ms a call).  NAN_IS_INF: a NaN is stored as +Inf.
-template <int NR, int P, bool NAN_IS_INF, bool LINES>
+template <int NR, int P, bool NAN_IS_INF, bool LINES, bool ONCE>
 __device__ __forceinline__ void fill_pieces(const float *X, int64_t row0, int64_t n_rows, int F, uint32_t xbase, uint32_t group_stride,
                                             uint32_t stride, int wave, int lane)
 {
@@ -106,8 +109,10 @@ __device__ __forceinline__ void fill_pieces(const float *X, int64_t row0, int64_
             if (t + g < end) {  // wave-uniform
                 const int f = min(at_block * FEATURES + c * 4, F - 4), first = at_rows * ROWS;
 #pragma unroll
-                for (int u = 0; u < L; ++u)
-                    v[g][u] = __builtin_nontemporal_load((GlobalRuns)((GlobalBytes)tile + (static_cast<uint32_t>(min(first + u * LOAD_ROWS + r, rows - 1)) * pitch + static_cast<uint32_t>(f) * 4)));
+                for (int u = 0; u < L; ++u) {
+                    const auto from = (GlobalRuns)((GlobalBytes)tile + (static_cast<uint32_t>(min(first + u * LOAD_ROWS + r, rows - 1)) * pitch + static_cast<uint32_t>(f) * 4));
+                    v[g][u] = ONCE ? __builtin_nontemporal_load(from) : *from;
+                }
                 to[g] = xbase + static_cast<uint32_t>(first >> 6) * group_stride + static_cast<uint32_t>((first & 63) + after_r) * 4;
                 block[g] = at_block;
                 if (++at_block == blocks) {
@@ -145,10 +150,12 @@ template <int NR, int P, bool NAN_IS_INF>
 __device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t n_rows, int F, uint32_t xbase, uint32_t group_stride,
                                           uint32_t stride, int wave, int lane)
 {
-    if (F > 16) {
-        fill_pieces<NR, P, NAN_IS_INF, true>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
+    if (F > 16 && F % 32 != 0) {
+        fill_pieces<NR, P, NAN_IS_INF, true, false>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
+    } else if (F > 16) {
+        fill_pieces<NR, P, NAN_IS_INF, true, true>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
     } else if (F >= 4) {
-        fill_pieces<NR, P, NAN_IS_INF, false>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
+        fill_pieces<NR, P, NAN_IS_INF, false, true>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
     } else {  // a lane per row
         const float *tile = X + row0 * F;
         const int rows = n_rows - row0 < NR * TILE ? static_cast<int>(n_rows - row0) : NR * TILE;
