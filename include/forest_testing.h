@@ -183,7 +183,7 @@ typedef struct forest_launch_t {
     int32_t leaves_by_fours;    /* walk and deep walk kernels, leaf ids: 1 if each wave stores those of its own four trees */
     int32_t last_rows_per_workgroup; /* of the workgroups that the largest range ends with; walk kernels may take smaller ones there */
     int32_t tile_after_tile;    /* deep walk kernels: 1 if the workgroups counted are tiles, which fewer workgroups take one after the other */
-    int32_t reserved;
+    int32_t loading_waves;      /* walk and deep walk kernels: waves of a workgroup that load X; tile after tile those that have a piece of it */
 } forest_launch_t;
 int forest_launch(const forest *f, int64_t n_rows, int32_t leaves, forest_launch_t *out);
 int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out);

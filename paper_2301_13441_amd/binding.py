@@ -66,7 +66,7 @@ class _View(ctypes.Structure):
 class _Launch(ctypes.Structure):
     _fields_ = [("kernel", _i32), ("shares", _i32), ("rows_per_workgroup", _i32), ("threads", _i32), ("launches", _i32),
                 ("lds_bytes", _i32), ("workgroups", _i64), ("leaves_by_fours", _i32),
-                ("last_rows_per_workgroup", _i32), ("tile_after_tile", _i32), ("reserved", _i32)]
+                ("last_rows_per_workgroup", _i32), ("tile_after_tile", _i32), ("loading_waves", _i32)]
 
 
 _KERNELS = ("lds", "reg", "rank", "rank_lds", "rank_bank", "point", "walk", "deep")  # FOREST_KERNEL_*

@@ -426,6 +426,9 @@ inline bool takes_tiles(const DevModel &m, int64_t n_rows, int n_splits, bool su
     return !deep_shares_cu(m, DEEP_TILE_GROUPS, true) && deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, DEEP_TILE_GROUPS, true) <= CU_LDS_BYTES;
 }
 
+// Pieces of 64 rows x 32 features that such a workgroup's tile comes in, one a wave.
+constexpr int ahead_pieces(int n_features, int groups) { return ((n_features + 31) >> 5) * groups; }
+
 inline int64_t tile_workgroups(int64_t n_rows)
 {
     const int64_t tiles = (n_rows + PLAN_ROWS * DEEP_TILE_GROUPS - 1) / (PLAN_ROWS * DEEP_TILE_GROUPS);
@@ -621,6 +624,7 @@ inline forest_launch_t launch_shape(const DevModel &m, const LaunchPlan &p, int6
         s.workgroups = t.full + t.after;
         s.last_rows_per_workgroup = PLAN_ROWS * t.groups;
         s.tile_after_tile = p.tiles;
+        s.loading_waves = p.tiles ? ahead_pieces(m.n_features, DEEP_TILE_GROUPS) : s.threads / PLAN_ROWS;
     }
     return s;
 }

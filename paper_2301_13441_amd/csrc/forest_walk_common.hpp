@@ -168,7 +168,10 @@ __device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t 
 }
 
 // The same tile on its way to registers while the one before is walked.  A piece is 64 rows x 32 features: eight loads of
-// eight rows' 128 bytes, one piece a wave at most.  F >= 4.
+// eight rows' 128 bytes, one piece a wave at most (ahead_pieces, forest_plan.hpp).  Waves beyond the last piece load and store nothing:
+// with the last piece once more for each of them, on the path that bounds the kernel, a tile was asked for up to twice: 128
+// features, 66,000 rows of 20 trees of depth 9 20.5 us (so 16.0), 1M rows 177 (134), of 300 such trees 763 (722), of 128 trees of depth 12
+// 557 (514).  F >= 4.
 template <int NR>
 struct TileAhead {
     static constexpr int LOADS = 8;
@@ -179,10 +182,10 @@ struct TileAhead {
     };
     static __device__ __forceinline__ Piece piece(int F, int wave)
     {
-        const int blocks = (F + 31) >> 5, at = min(wave, blocks * NR - 1);
+        const int blocks = ahead_pieces(F, 1);
         static_assert(NR <= 2, "one comparison");
-        const int group = NR == 1 ? 0 : at >= blocks;
-        return Piece{group, (at - group * blocks) * 32};
+        const int group = NR == 1 ? 0 : wave >= blocks;
+        return Piece{group, (wave - group * blocks) * 32};
     }
     // A lane's row and four of features in a load: bits 0, 1 and 4 the four.
     static __device__ __forceinline__ int row_of(int lane) { return (lane >> 2 & 3) | (lane >> 3 & 4); }
@@ -190,6 +193,7 @@ struct TileAhead {
     // The tile whose first row `tile` points at and which has `rows` rows.
     __device__ __forceinline__ void request(const float *tile, int rows, int F, int wave, int lane)
     {
+        if (wave >= ahead_pieces(F, NR)) return;  // wave-uniform, here and below: the exchanges have all their lanes
         const Piece p = piece(F, wave);
         asm volatile("" : "+v"(lane));
         const int f = min(p.feature + four_of(lane) * 4, F - 4);
@@ -201,6 +205,7 @@ struct TileAhead {
     }
     __device__ __forceinline__ void store(int F, uint32_t xbase, uint32_t group_stride, uint32_t stride, int wave, int lane) const
     {
+        if (wave >= ahead_pieces(F, NR)) return;
         asm volatile("" : "+v"(lane));
         const Piece p = piece(F, wave);
         // after the exchange a lane has the features of one row, register k four of them from 4 k

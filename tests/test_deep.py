@@ -121,6 +121,14 @@ def test_deep_sums_go_tile_after_tile_where_a_cu_holds_one_tile():
             assert s["rows_per_workgroup"] == s["last_rows_per_workgroup"] == 128 and s["workgroups"] == -(-rows // 128)
 
 
+@pytest.mark.parametrize("features,waves", [(97, 8), (128, 8), (129, 10), (160, 10), (161, 12), (200, 14), (225, 16), (256, 16)])
+def test_tiles_ahead_are_loaded_once(features, waves):
+    """A wave per piece of 64 rows x 32 features; no wave asks for another's again."""
+    from paper_2301_13441_amd import binding
+    s = binding.forest_packed_launch(_forest(1, 20, 9, features), 10**6, form="walk")
+    assert s["tile_after_tile"] == 1 and s["loading_waves"] == waves == 2 * -(-features // 32) <= s["threads"] // 64
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("features", [97, 127, 130, 193, 224, 253, 256])
 @pytest.mark.parametrize("depth,outputs,width", [(9, 1, 1), (12, 2, 2)])
