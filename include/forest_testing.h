@@ -192,6 +192,10 @@ int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves,
  * counts below 1. */
 int forest_ids_go_through(int32_t n_trees, int64_t n_rows, uintptr_t leaf_out);
 
+/* 1 if the walk kernels' loads of X from that address leave its lines in the L2, 0 if they are non-temporal or the call takes
+ * other kernels. */
+int forest_keeps_lines(const forest_packed *p, int64_t n_rows, int32_t leaves, uintptr_t x);
+
 /* forest_packed_launch of a call that finds every workspace of its handle taken (forest.h, concurrency). */
 int forest_packed_launch_no_workspace(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out);
 

@@ -1,6 +1,7 @@
 """ctypes binding with the same names as the C ABI (argument marshalling only)."""
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 import sys
@@ -79,7 +80,7 @@ EXPORTS = ["forest_load", "forest_free", "forest_info", "forest_out_bytes", "for
 # include/forest_testing.h: host-only views into the model compiler, for its tests
 TESTING_EXPORTS = ["forest_pack", "forest_pack_view", "forest_pack_free", "forest_rank_code",
                    "forest_staged_position", "forest_probe_compare_rate", "forest_launch", "forest_packed_launch",
-                   "forest_packed_launch_no_workspace", "forest_ids_go_through",
+                   "forest_packed_launch_no_workspace", "forest_ids_go_through", "forest_keeps_lines",
                    "forest_load_form", "forest_pack_form"]
 
 
@@ -125,6 +126,8 @@ def load_library():
     lib.forest_rank_code.argtypes = [_i32, ctypes.POINTER(ctypes.c_uint16), ctypes.POINTER(ctypes.c_uint16)]
     lib.forest_ids_go_through.restype = ctypes.c_int
     lib.forest_ids_go_through.argtypes = [_i32, _i64, ctypes.c_size_t]
+    lib.forest_keeps_lines.restype = ctypes.c_int
+    lib.forest_keeps_lines.argtypes = [_p, _i64, _i32, ctypes.c_size_t]
     lib.forest_staged_position.restype = ctypes.c_int
     lib.forest_staged_position.argtypes = [_i32, _i32, ctypes.POINTER(_i32)]
     for fn in (lib.forest_launch, lib.forest_packed_launch, lib.forest_packed_launch_no_workspace):
@@ -299,6 +302,20 @@ def _launch(call, handle, what, n_rows, leaves) -> dict:
     return {**{name: int(getattr(s, name)) for name, _ in _Launch._fields_}, "kernel": _KERNELS[s.kernel]}
 
 
+@contextlib.contextmanager
+def _packed(forest, form: str):
+    lib = load_library()
+    d, keep = _desc_from(forest)
+    h = _p()
+    rc = lib.forest_pack_form(ctypes.byref(d), _FORMS[form], ctypes.byref(h))
+    if rc != 0:
+        raise ForestError(rc, "forest_pack_form")
+    try:
+        yield h
+    finally:
+        lib.forest_pack_free(h)
+
+
 def forest_launch(f, n_rows: int, leaves: bool = False) -> dict:
     """What a call on the loaded model launches for n_rows rows (include/forest_testing.h)."""
     return _launch(f._lib.forest_launch, f._h, "forest_launch", n_rows, leaves)
@@ -308,16 +325,18 @@ def forest_packed_launch(forest, n_rows: int, leaves: bool = False, form: str = 
     """The same for a model that is only packed (form: as in forest_load_form): no GPU needed.  Without `workspace`: of
     a call that finds every workspace of its handle taken."""
     lib = load_library()
-    d, keep = _desc_from(forest)
-    h = _p()
-    rc = lib.forest_pack_form(ctypes.byref(d), _FORMS[form], ctypes.byref(h))
-    if rc != 0:
-        raise ForestError(rc, "forest_pack_form")
-    try:
-        call = lib.forest_packed_launch if workspace else lib.forest_packed_launch_no_workspace
+    call = lib.forest_packed_launch if workspace else lib.forest_packed_launch_no_workspace
+    with _packed(forest, form) as h:
         return _launch(call, h, "forest_packed_launch", n_rows, leaves)
-    finally:
-        lib.forest_pack_free(h)
+
+
+def forest_keeps_lines(forest, n_rows: int, leaves: bool = False, form: str = "auto", x: int = 0) -> bool:
+    """Whether the walk kernels' loads of X from address `x` leave its lines in the L2."""
+    with _packed(forest, form) as h:
+        got = load_library().forest_keeps_lines(h, n_rows, int(leaves), x)
+    if got < 0:
+        raise ForestError(got, "forest_keeps_lines")
+    return bool(got)
 
 
 def forest_ids_go_through(n_trees: int, n_rows: int, leaf_out: int) -> bool:

@@ -37,15 +37,20 @@ int forest_pack(const forest_desc *desc, forest_packed **out) { return forest_pa
 
 namespace {
 
+LaunchPlan packed_plan(const DevModel &d, int64_t n_rows, int32_t leaves, bool workspace)
+{
+    Workspace ws;
+    ws.rank_tile_words = static_cast<int64_t>(rank_tile_bytes(d.rank_regs, SPLIT_BELOW_BLOCKS) / sizeof(uint32_t));
+    ws.partial_doubles = split_workspace_doubles(d.n_outputs);
+    return plan_launch(d, workspace ? &ws : nullptr, n_rows, !leaves);
+}
+
 int packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves, bool workspace, forest_launch_t *out)
 {
     if (!p || !out || n_rows < 1) return FOREST_EINVAL;
     if (n_rows > FOREST_MAX_ROWS) return FOREST_ELIMIT;
     const DevModel d = describe(p->m);
-    Workspace ws;
-    ws.rank_tile_words = static_cast<int64_t>(rank_tile_bytes(d.rank_regs, SPLIT_BELOW_BLOCKS) / sizeof(uint32_t));
-    ws.partial_doubles = split_workspace_doubles(d.n_outputs);
-    *out = launch_shape(d, plan_launch(d, workspace ? &ws : nullptr, n_rows, !leaves), n_rows, !leaves);
+    *out = launch_shape(d, packed_plan(d, n_rows, leaves, workspace), n_rows, !leaves);
     return FOREST_OK;
 }
 
@@ -59,6 +64,14 @@ int forest_packed_launch(const forest_packed *p, int64_t n_rows, int32_t leaves,
 int forest_packed_launch_no_workspace(const forest_packed *p, int64_t n_rows, int32_t leaves, forest_launch_t *out)
 {
     return packed_launch(p, n_rows, leaves, false, out);
+}
+
+int forest_keeps_lines(const forest_packed *p, int64_t n_rows, int32_t leaves, uintptr_t x)
+{
+    if (!p || n_rows < 1) return FOREST_EINVAL;
+    if (n_rows > FOREST_MAX_ROWS) return FOREST_ELIMIT;
+    const DevModel d = describe(p->m);
+    return keeps_lines(d, packed_plan(d, n_rows, leaves, true), !leaves, x);
 }
 
 int forest_rank_code(int32_t q, uint16_t *code, uint16_t *entry)

@@ -322,6 +322,7 @@ hipError_t launch_predict(const DevModel &model, const Workspace *ws, bool must_
     m.partial = ws ? ws->partial : nullptr;
     m.partial_capacity = ws ? ws->partial_doubles : 0;
     m.rank_tiles = ws ? ws->rank_tiles : nullptr;
+    m.x_tile = m.n_features | (keeps_lines(m, p, sums, reinterpret_cast<uintptr_t>(X)) ? KEEP_X : 0);
     if (m.n_splits > 1 && (p.kernel == FOREST_KERNEL_RANK || p.kernel == FOREST_KERNEL_RANK_LDS)) {
         const hipError_t e = launch_rank_tiles(m, X, n_rows, stream);
         if (e != hipSuccess) return e;

@@ -140,7 +140,7 @@ __device__ __forceinline__ void deep_rows(const DevModel m, const float *__restr
         fetch(place(t_begin));
         head = deep_head(tops, place(t_begin));
     }
-    tile_fill<NR, NR == 2 ? 8 : 4, false>(X, row0, n_rows, F, XBASE, group_stride, 256, wave, lane);
+    tile_fill<NR, NR == 2 ? 8 : 4, false>(X, row0, n_rows, m.x_tile, XBASE, group_stride, 256, wave, lane);
     __syncthreads();
 
     uint32_t xa[NR];
@@ -411,7 +411,7 @@ __device__ __forceinline__ void deep_tops(uint32_t stage, const uint32_t (&xa)[N
 // waves through LDS the lanes ask for as many lines, in a longer chain: 1.36 ms of units instead of 0.9.  Without X it would take
 // 1.83 ms, without units 1.23, without either 0.89 (LDS 62 % busy).  All the tops of four pairs of trees before their units, so that
 // X waits behind more of them: 2.45 ms instead of 2.31.
-template <int NR, int MODE, int WP>
+template <int NR, int MODE, int WP, bool ONCE>
 __global__ __launch_bounds__(DEEP_WAVES * TILE, 4) void forest_deep_tiles_kernel(DevModel model, const float *__restrict__ X, int64_t n_rows,
                                                                                 float *scores, int32_t *labels, int32_t *)
 {
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(DEEP_WAVES * TILE, 4) void forest_deep_tiles_kernel
     };
     constexpr int STEP = static_cast<int>(CUS) * ROWS;  // from a workgroup's tile to its next one
     const int n = static_cast<int>(n_rows);
-    TileAhead<NR> ahead;
+    TileAhead<NR, ONCE> ahead;
     const auto request = [&](int row0) {
         if (row0 < n) ahead.request(X + static_cast<int64_t>(row0) * F, min(ROWS, n - row0), F, wave, lane);
     };
@@ -607,6 +607,15 @@ KernelFn pick(int groups, int last, int mode, int width, bool shared)
     return shared ? pick_mode<true>(groups, last, mode, width) : pick_mode<false>(groups, last, mode, width);
 }
 
+template <bool ONCE>
+KernelFn pick_tiles(int width)
+{
+    if (width > 1) return forest_deep_tiles_kernel<DEEP_TILE_GROUPS, DEEP_VECTOR, 2, ONCE>;
+    return forest_deep_tiles_kernel<DEEP_TILE_GROUPS, DEEP_COLUMN, 1, ONCE>;
+}
+
+KernelFn pick_tiles(int width, bool once) { return once ? pick_tiles<true>(width) : pick_tiles<false>(width); }
+
 }  // namespace
 
 hipError_t init_deep_kernels(size_t lds_limit)
@@ -618,8 +627,9 @@ hipError_t init_deep_kernels(size_t lds_limit)
         if (attr.sharedSizeBytes != 0) return hipErrorInvalidValue;  // the kernels address LDS from 0
         return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_limit));
     };
-    for (KernelFn fn : {forest_deep_tiles_kernel<DEEP_TILE_GROUPS, DEEP_COLUMN, 1>, forest_deep_tiles_kernel<DEEP_TILE_GROUPS, DEEP_VECTOR, 2>})
-        if (hipError_t e = init(fn); e != hipSuccess) return e;
+    for (int width : {1, 2})
+        for (bool once : {false, true})
+            if (hipError_t e = init(pick_tiles(width, once)); e != hipSuccess) return e;
     for (int mode : {DEEP_COLUMN, DEEP_COLUMNS, DEEP_VECTOR, DEEP_LEAVES, DEEP_LEAVES_THROUGH, DEEP_FEW_LEAVES})
         for (int width : {2, 4, 8, 12, 16})
             for (int groups : {1, 2})
@@ -632,7 +642,7 @@ hipError_t init_deep_kernels(size_t lds_limit)
 hipError_t launch_deep_tiles(const DevModel &m, const float *X, int64_t n_rows, float *scores, int32_t *labels, hipStream_t stream)
 {
     static_assert(MAX_LAUNCH_ROWS + 2 * CUS * PLAN_ROWS * DEEP_TILE_GROUPS <= 0x7fffffff, "rows count in 32 bits");
-    const KernelFn fn = m.leaf_width > 1 ? forest_deep_tiles_kernel<DEEP_TILE_GROUPS, DEEP_VECTOR, 2> : forest_deep_tiles_kernel<DEEP_TILE_GROUPS, DEEP_COLUMN, 1>;
+    const KernelFn fn = pick_tiles(m.leaf_width, !(m.x_tile & KEEP_X));
     const size_t lds = deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, DEEP_TILE_GROUPS, true);
     hipLaunchKernelGGL(fn, dim3(static_cast<unsigned>(tile_workgroups(n_rows))), dim3(DEEP_WAVES * TILE), lds, stream, m, X, n_rows, scores,
                        labels, nullptr);

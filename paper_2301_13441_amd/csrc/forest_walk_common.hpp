@@ -74,10 +74,7 @@ __device__ __forceinline__ int line_four(int lane) { return (lane & 1) | (lane >
 
 // The X tile of a workgroup: rows [row0, row0 + 64 NR) as float32, row group g, feature f and row r of the
 // group at xbase + g * group_stride + f * stride + 4 r.  It is filled in pieces of 8 L rows x 32 features, L loads of
-// eight rows' 128 bytes, non-temporally where rows are whole lines (ONCE): X is read once and should not push the trees out of the
-// L2.  Where F is no multiple of 32 a line lies in two blocks or two rows and is asked for again, so there it should stay: loads
-// that say nothing of it, 90 features, 103,069 rows of 300 deep trees 71.0 us, so 67.5; trees of depth 6, 1M rows, 127 features
-// 312 / 304, 90 features 362 / 358, but 64 features 317 / 320 and 128 features 801 / 806.  A line that is asked for in
+// eight rows' 128 bytes, non-temporally (ONCE) or not (keeps_lines, forest_plan.hpp).  A line that is asked for in
 // two halves is read twice so, and what waits for it holds up the other loads of the CU, which return in order (16 rows' 64
 // bytes a load and no exchange: 103,069 rows of 300 deep trees, 90 features 72.2 us, so 69.5; 100 trees of depth 6, 64 features,
 // 300,000 rows 44.9 / 41.2, 300 features, 100,000 rows 61.7 / 55.6; but 8 features, 1M rows 93.8 / 98.0, so rows of at most 16
@@ -147,10 +144,11 @@ __device__ __forceinline__ void fill_pieces(const float *X, int64_t row0, int64_
 }
 
 template <int NR, int P, bool NAN_IS_INF>
-__device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t n_rows, int F, uint32_t xbase, uint32_t group_stride,
+__device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t n_rows, int x_tile, uint32_t xbase, uint32_t group_stride,
                                           uint32_t stride, int wave, int lane)
 {
-    if (F > 16 && F % 32 != 0) {
+    const int F = x_tile & (KEEP_X - 1);
+    if (x_tile & KEEP_X) {  // more than 16 features
         fill_pieces<NR, P, NAN_IS_INF, true, false>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
     } else if (F > 16) {
         fill_pieces<NR, P, NAN_IS_INF, true, true>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
@@ -172,7 +170,7 @@ __device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t 
 // with the last piece once more for each of them, on the path that bounds the kernel, a tile was asked for up to twice: 128
 // features, 66,000 rows of 20 trees of depth 9 20.5 us (so 16.0), 1M rows 177 (134), of 300 such trees 763 (722), of 128 trees of depth 12
 // 557 (514).  F >= 4.
-template <int NR>
+template <int NR, bool ONCE>
 struct TileAhead {
     static constexpr int LOADS = 8;
     FloatRun4 v[LOADS];
@@ -200,7 +198,8 @@ struct TileAhead {
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) {
             const int row = min(p.group * TILE + u * 8 + row_of(lane), rows - 1);
-            v[u] = __builtin_nontemporal_load((GlobalRuns)((GlobalBytes)tile + static_cast<uint32_t>(row * F + f) * 4));
+            const auto from = (GlobalRuns)((GlobalBytes)tile + static_cast<uint32_t>(row * F + f) * 4);
+            v[u] = ONCE ? __builtin_nontemporal_load(from) : *from;
         }
     }
     __device__ __forceinline__ void store(int F, uint32_t xbase, uint32_t group_stride, uint32_t stride, int wave, int lane) const

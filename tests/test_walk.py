@@ -294,6 +294,48 @@ def test_leaf_ids_past_the_l2(depth, trees, rows):
     np.testing.assert_array_equal(got, oracle.predict(f, X, want_leaves=True, n_threads=8).leaf_node_id)
 
 
+def test_lines_of_x_stay_in_the_l2_where_rows_share_them_and_the_trees_keep_their_place():
+    from paper_2301_13441_amd import binding
+    few, many = _forest(1, 40, 6, 16), _forest(2, 500, 8, 16)  # 30 KB and 1.5 MB of tables
+    at = lambda f, features: wl.Forest(**{**f.__dict__, "n_features": features})
+    for features in (32, 64, 96, 224):  # whole lines are asked for once
+        assert not binding.forest_keeps_lines(at(few, features), 10**6)
+        assert all(binding.forest_keeps_lines(at(few, features), 10**6, x=x) for x in (4, 64))
+    for features, rows, keep_few, keep_many in ((16, 10**6, 0, 0), (17, 10**6, 1, 1), (127, 10**6, 1, 1), (200, 10**6, 1, 0), (300, 10**6, 1, 0),
+                                                (500, 10**6, 1, 0), (300, 5000, 1, 1)):  # the last: shares of the trees read a tile several times
+        assert binding.forest_keeps_lines(at(few, features), rows) == keep_few, (features, rows)
+        assert binding.forest_keeps_lines(at(many, features), rows) == keep_many, (features, rows)
+    assert not binding.forest_keeps_lines(few, 1, x=4)  # a lane per (row, tree)
+    for bad in (0, 1 << 62):
+        with pytest.raises(binding.ForestError):
+            binding.forest_keeps_lines(few, bad)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind,trees,depth,features,rows,shift,keep", [
+    ("walk", 500, 8, 201, 33_333, 0, 0), ("walk", 500, 8, 301, 33_333, 0, 0), ("walk", 40, 6, 64, 70_003, 1, 1), ("walk", 40, 6, 128, 33_333, 16, 1),
+    ("walk", 500, 8, 256, 33_333, 3, 0), ("deep", 200, 12, 131, 65_536 + 77, 0, 0), ("deep", 200, 12, 225, 65_536 + 1, 0, 0),
+    ("deep", 20, 9, 160, 65_536 + 1, 1, 1), ("deep", 200, 12, 95, 40_009, 0, 0)])
+def test_tiles_by_how_x_is_loaded(kind, trees, depth, features, rows, shift, keep):
+    """Rows that share lines, by their width or by X's address, loaded either way; tile after tile too."""
+    import torch
+    from paper_2301_13441_amd import binding
+    rng = np.random.default_rng(features)
+    f = _forest(features, trees, depth, features) if kind == "walk" else wl.random_forest(features, n_trees=trees, n_features=features, max_depth=depth, stop_prob=0.05 if trees > 20 else 0.25, aggregate=wl.AGG_SUM)
+    X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
+    flat = torch.zeros(X.size + 32, dtype=torch.float32, device="cuda")
+    xd = flat[shift:shift + X.size].view(rows, features)
+    xd.copy_(torch.from_numpy(X))
+    assert xd.data_ptr() % 128 == 4 * shift
+    assert binding.forest_packed_launch(f, rows)["kernel"] == kind and binding.forest_keeps_lines(f, rows, x=xd.data_ptr()) == keep
+    model = binding.forest_load(f)
+    try:
+        scores, _ = model.predict(xd)
+        np.testing.assert_allclose(scores.cpu().numpy(), oracle.predict(f, X, n_threads=8).scores, rtol=1e-5, atol=1e-6)
+    finally:
+        model.close()
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("features", [3, 4, 5, 15, 16, 17, 30, 31, 32, 33, 47, 61, 64])
 @pytest.mark.parametrize("rows,groups", [(12_301, 1), (33_333, 2), (70_003, 4)])
