@@ -421,16 +421,25 @@ inline bool ends_in_smaller(const DevModel &m, int kernel, int groups, int64_t n
 
 // Sums by workgroups that take tile after tile (forest_deep_tiles_kernel), one on a CU with two row groups: where the tile leaves no room for
 // a second workgroup of two groups, whose walk would hide the first one's wait for its rows, and from two tiles a CU on.  us,
-// a workgroup per tile / tile after tile, 128 trees of depth 12, vector leaves: 1M rows, 40 features 432 / 527, 90 features 500 / 580, 128
-// (two workgroups of one group) 620 / 564, 192 679 / 557, 224 689 / 555; of 300 trees of depth 9 582 / 791, 796 / 761, 846 / 768, 900 / 770 for 90,
-// 128, 192 and 224 features; 256 features: 33,000 rows 37.8 / 38.4, 66,000 60.7 / 57.6, 100,000 83.7 / 77.5, 150,000 113.7 / 97.1,
-// 4M 2712 / 2150.
+// a workgroup per tile / tile after tile, 1M rows of 128 trees of depth 12, vector leaves: 40 features 430 / 499, 90
+// features 475 / 513, 128 (two workgroups of one group) 590 / 515, 192 625 / 531, 224 631 / 549; of 300 trees of depth 9 529 / 706, 558 / 718,
+// 768 / 720, 799 / 741, 831 / 754; 256 features: 33,000 rows 37.8 / 38.4, 66,000 60.7 / 57.6, 100,000 83.7 / 77.5, 150,000 113.7 / 97.1,
+// 4M 2712 / 2150 (the last before whole lines).
+//
+// A batch of whole rounds and few tiles more has a last round that leaves most CUs idle.  Up to 192 features, where the other kernel has two
+// workgroups of 64 rows on a CU, that kernel spreads the rest better, which counts while the rounds are few.  Tile after tile, of a workgroup
+// per 64 rows = 1, 97 to 192 features, in 2.0 to 2.4 rounds / 3.0 to 3.4 / 4.1 to 4.3 / 5.1 to 5.5 / 6.0: 300 trees of depth 9 1.09 / 1.05 / 1.03 /
+// 1.01 / 1.01, 1000 of them 1.08 / 1.05 / 1.04 / 1.03 / 1.02, 300 of depth 12 1.04 / 1.01 / 1.00 / 0.99 / 0.98, 128 of depth 9 1.02 / 0.98 / 0.95 / 0.93 /
+// 0.92, 20 of them 1.04 / 0.98 / 0.95 / 0.91 / 0.89; rounds and a half or more 0.85 to 0.95; 7.0 rounds of 1000 trees 1.00.
 constexpr int DEEP_TILE_GROUPS = 2;
+constexpr int REST_MAX_ROUNDS = 7, REST_MAX_ROUNDS_FEW_TREES = 3, REST_FEW_TREES = 200;
 
 inline bool takes_tiles(const DevModel &m, int64_t n_rows, int n_splits, bool sums)
 {
     if (!sums || n_splits > 1 || m.leaf_width > 2 || (m.leaf_width == 1 && m.n_outputs > 1)) return false;
     if (n_rows < 2 * CUS * PLAN_ROWS * DEEP_TILE_GROUPS) return false;
+    const int64_t tiles = (n_rows + PLAN_ROWS * DEEP_TILE_GROUPS - 1) / (PLAN_ROWS * DEEP_TILE_GROUPS), rest = tiles % CUS;
+    if (rest > 0 && rest <= CUS / 2 && deep_shares_cu(m, 1, true) && tiles / CUS < (m.n_trees < REST_FEW_TREES ? REST_MAX_ROUNDS_FEW_TREES : REST_MAX_ROUNDS)) return false;
     return !deep_shares_cu(m, DEEP_TILE_GROUPS, true) && deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, DEEP_TILE_GROUPS, true) <= CU_LDS_BYTES;
 }
 

@@ -121,6 +121,21 @@ def test_deep_sums_go_tile_after_tile_where_a_cu_holds_one_tile():
             assert s["rows_per_workgroup"] == s["last_rows_per_workgroup"] == 128 and s["workgroups"] == -(-rows // 128)
 
 
+@pytest.mark.parametrize("features", [97, 192, 193, 256])
+def test_rounds_and_few_tiles_more_are_left_to_smaller_workgroups(features):
+    """Where these share a CU, up to 192 features, and the rounds are few."""
+    from paper_2301_13441_amd import binding
+    rounds = 256 * 128
+    for trees, most in ((20, 2), (199, 2), (200, 6)):
+        f = _forest(1, trees, 9, features)
+        for n in (2, 3, 6, 7):
+            spread = features <= 192 and n <= most
+            for rows, want in ((n * rounds, 1), (n * rounds + 1, not spread), (n * rounds + 128 * 128, not spread), (n * rounds + 128 * 128 + 1, 1)):
+                s = binding.forest_packed_launch(f, rows, form="walk")
+                assert s["kernel"] == "deep" and s["tile_after_tile"] == want, (trees, rows)
+                assert want or s["rows_per_workgroup"] == 64
+
+
 @pytest.mark.parametrize("features,waves", [(97, 8), (128, 8), (129, 10), (160, 10), (161, 12), (200, 14), (225, 16), (256, 16)])
 def test_tiles_ahead_are_loaded_once(features, waves):
     """A wave per piece of 64 rows x 32 features; no wave asks for another's again."""
