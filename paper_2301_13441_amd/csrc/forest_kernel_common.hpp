@@ -56,20 +56,21 @@ typedef const double *ColumnTrees;  // host pass: the kernel body is only parsed
 typedef const float *ColumnBase;
 #endif
 
-// Aggregate, label, transform, store for one row whose K summed leaf values are raw[k * stride];
-// raw[] is overwritten: with the aggregated values, or with their exponentials where a softmax is stored.
-__device__ __forceinline__ void finish_values(const DevModel &m, double *raw, int64_t stride, int64_t row,
-                                              float *scores, int32_t *labels)
+// Aggregate, label, transform, store for one row whose summed leaf values are sum(k), a double & each; they are overwritten:
+// with the aggregated values, or with their exponentials where a softmax is stored.  FEW: the number of columns where the sums are
+// in registers, else 0.
+template <int FEW, typename Sum>
+__device__ __forceinline__ void finish_sums(const DevModel &m, const Sum &sum, int64_t row, float *scores, int32_t *labels)
 {
-    const int K = m.n_outputs;
+    const int K = FEW > 0 ? FEW : m.n_outputs;
     double best = 0.0;
     int best_k = 0;
     for (int k = 0; k < K; ++k) {
-        double s = raw[k * stride];
+        double s = sum(k);
         // a column no tree feeds: the mean over no trees adds nothing to the base score
         if (const double n = ((ColumnTrees)m.col_trees)[k]; m.aggregate == FOREST_AGG_MEAN && n > 0.0) s = s / n;
         s = static_cast<double>(((ColumnBase)m.base)[k]) + s;
-        raw[k * stride] = s;
+        sum(k) = s;
         if (k == 0 || s > best) {
             best = s;
             best_k = k;
@@ -85,56 +86,30 @@ __device__ __forceinline__ void finish_values(const DevModel &m, double *raw, in
     if (m.transform == FOREST_TRANSFORM_SOFTMAX) {
         double z = 0.0;
         for (int k = 0; k < K; ++k) {
-            const double e = exp(raw[k * stride] - best);
-            raw[k * stride] = e;
+            const double e = exp(sum(k) - best);
+            sum(k) = e;
             z += e;
         }
-        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(raw[k * stride] / z);
+        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(sum(k) / z);
     } else if (m.transform == FOREST_TRANSFORM_SIGMOID) {
-        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(1.0 / (1.0 + exp(-raw[k * stride])));
+        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(1.0 / (1.0 + exp(-sum(k))));
     } else {
-        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(raw[k * stride]);
+        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(sum(k));
     }
 }
 
-// The same for a row whose K sums are in registers.
+// Of sums raw[k * stride] in memory.
+__device__ __forceinline__ void finish_values(const DevModel &m, double *raw, int64_t stride, int64_t row,
+                                              float *scores, int32_t *labels)
+{
+    finish_sums<0>(m, [=](int k) -> double & { return raw[k * stride]; }, row, scores, labels);
+}
+
+// Of K sums in registers.
 template <int K>
 __device__ __forceinline__ void finish_few(const DevModel &m, double (&s)[K], int64_t row, float *scores, int32_t *labels)
 {
-    double best = 0.0;
-    int best_k = 0;
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        if (const double n = ((ColumnTrees)m.col_trees)[k]; m.aggregate == FOREST_AGG_MEAN && n > 0.0) s[k] = s[k] / n;
-        s[k] = static_cast<double>(((ColumnBase)m.base)[k]) + s[k];
-        if (k == 0 || s[k] > best) {
-            best = s[k];
-            best_k = k;
-        }
-    }
-    if (labels) {
-        int lab = best_k;
-        if (K == 1) lab = (m.transform == FOREST_TRANSFORM_SIGMOID) ? (best > 0.0) : (best > 0.5);
-        labels[row] = lab;
-    }
-    if (!scores) return;
-    float *dst = scores + row * K;
-    if (m.transform == FOREST_TRANSFORM_SOFTMAX) {
-        double z = 0.0;
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            s[k] = exp(s[k] - best);
-            z += s[k];
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(s[k] / z);
-    } else if (m.transform == FOREST_TRANSFORM_SIGMOID) {
-#pragma unroll
-        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(1.0 / (1.0 + exp(-s[k])));
-    } else {
-#pragma unroll
-        for (int k = 0; k < K; ++k) dst[k] = static_cast<float>(s[k]);
-    }
+    finish_sums<K>(m, [&](int k) -> double & { return s[k]; }, row, scores, labels);
 }
 
 // Tile row `li` (0 <= li < rows) once its K column sums are in acc[k * rows + li]: the rest of
