@@ -109,6 +109,14 @@ def test_deep_kernels_by_rows_per_lane(features, depth, outputs, width, rows, gr
         _check(f, _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng), leaves=True)
 
 
+def _tiles(f, rows):
+    """What a test is about: the kernel whose workgroups take tile after tile."""
+    from paper_2301_13441_amd import binding
+    for form in ("auto", "walk"):
+        s = binding.forest_packed_launch(f, rows, form=form)
+        assert s["kernel"] == "deep" and s["tile_after_tile"] == 1, s
+
+
 def test_deep_sums_go_tile_after_tile_where_a_cu_holds_one_tile():
     from paper_2301_13441_amd import binding
     plan = lambda features, rows, outputs=1, width=1, leaves=False: binding.forest_packed_launch(_forest(1, 20, 9, features, outputs, width), rows, leaves, form="walk")
@@ -147,14 +155,32 @@ def test_tiles_ahead_are_loaded_once(features, waves):
 @pytest.mark.gpu
 @pytest.mark.parametrize("features", [97, 127, 130, 193, 224, 253, 256])
 @pytest.mark.parametrize("depth,outputs,width", [(9, 1, 1), (12, 2, 2)])
-@pytest.mark.parametrize("trees,rows", [(1, 65536), (17, 65536 + 1), (33, 65536 + 128 + 65), (48, 3 * 32768 - 3)])
+@pytest.mark.parametrize("trees,rows", [(1, 65536), (17, 3 * 32768 + 1), (33, 3 * 32768 + 128 + 65), (48, 3 * 32768 - 3)])
 def test_deep_kernels_tile_after_tile(features, depth, outputs, width, trees, rows):
-    """Whole and ragged pieces of 32 features, a last tile of one row and of two row groups, CUs with two and three tiles; waves
+    """Whole and ragged pieces of 32 features, a last tile of one row and of two row groups, CUs with two, three and four tiles; waves
     without trees, with one and with three."""
     rng = np.random.default_rng(100 * depth + features + trees)
-    f = _forest(9 * depth + features, trees, depth, features, outputs, width, stop=0.3)
+    f = _forest(9 * depth + features, trees, depth, features, outputs, width, stop=0.3 if trees > 1 else 0.0)
+    assert len(f.feature) > 200  # a tree alone reads features too
+    _tiles(f, rows)
     X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
     _check(f, X, leaves=False)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("aggregate,transform,outputs,output", [
+    (wl.AGG_MEAN, wl.TRANSFORM_NONE, 1, wl.OUT_BOTH), (wl.AGG_MEAN, wl.TRANSFORM_NONE, 2, wl.OUT_BOTH), (wl.AGG_SUM, wl.TRANSFORM_NONE, 1, wl.OUT_LABELS),
+    (wl.AGG_SUM, wl.TRANSFORM_NONE, 2, wl.OUT_SCORES), (wl.AGG_MEAN, wl.TRANSFORM_SIGMOID, 1, wl.OUT_SCORES), (wl.AGG_SUM, wl.TRANSFORM_SIGMOID, 2, wl.OUT_BOTH),
+    (wl.AGG_MEAN, wl.TRANSFORM_SOFTMAX, 2, wl.OUT_LABELS)])
+def test_tile_after_tile_finishes_rows_as_the_model_says(aggregate, transform, outputs, output):
+    """Means and sums, base scores, every transform, scores or labels alone."""
+    rows, features = 65536 + 65, 200
+    rng = np.random.default_rng(outputs)
+    f = wl.random_forest(5 + outputs, n_trees=37, n_features=features, max_depth=10, stop_prob=0.2, n_outputs=outputs, leaf_width=outputs,
+                         aggregate=aggregate, transform=transform, output=output)
+    f = wl.Forest(**{**f.__dict__, "base_score": np.float32([0.25, -0.5][:outputs])})
+    _tiles(f, rows)
+    _check(f, _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng), leaves=False)
 
 
 @pytest.mark.gpu
