@@ -33,12 +33,11 @@ ORACLE_THREADS_MAX = 16   # the share of host cores one GPU's job may use on the
 # scaled by what the same counter reads for a plain copy of known size).  Not taken live: every
 # entry names the summary under profiles/ it comes from and the commit whose kernels were
 # measured; a workload without an entry reports null.
-# "c2" and "c3" were counted before rows that are not whole lines were read with ordinary loads.
 MEASURED_TRAFFIC = {
-    "c2": {"bytes": 1.326e8, "profile": "profiles/forest_walk_kernels.md", "commit": "1cf39fc"},
-    "c3": {"bytes": 2.287e8, "profile": "profiles/forest_walk_kernels.md", "commit": "1cf39fc"},
-    "c4": {"bytes": 2.907e8, "profile": "profiles/forest_walk_kernels.md", "commit": "1cf39fc"},
-    "c5": {"bytes": 4.164e9, "profile": "profiles/forest_walk_kernels.md", "commit": "1cf39fc"},
+    "c2": {"bytes": 1.327e8, "profile": "profiles/forest_walk_kernels.md", "commit": "e207a50"},
+    "c3": {"bytes": 2.110e8, "profile": "profiles/forest_walk_kernels.md", "commit": "e207a50"},
+    "c4": {"bytes": 2.907e8, "profile": "profiles/forest_walk_kernels.md", "commit": "e207a50"},
+    "c5": {"bytes": 4.164e9, "profile": "profiles/forest_walk_kernels.md", "commit": "e207a50"},
     "l2": {"bytes": 1.456e9, "profile": "profiles/linear_kernels.md", "commit": "7dd9b06"},
     "l3": {"bytes": 1.119e9, "profile": "profiles/linear_kernels.md", "commit": "7dd9b06"},
     "l4": {"bytes": 9.600e8, "profile": "profiles/linear_kernels.md", "commit": "7dd9b06"},

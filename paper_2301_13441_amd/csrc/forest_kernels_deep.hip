@@ -405,8 +405,8 @@ __device__ __forceinline__ void deep_tops(uint32_t stage, const uint32_t (&xa)[N
 // What bounds it is the CU's vector memory path, which returns loads in the order they were asked for, whichever wave did.  A tile's
 // rows hold up everybody's units behind them for as long as they take from memory, so they are asked for once a tile, before
 // the sums and the first tops, which need no memory (asked for before every two trees 2.75 ms, once behind the barrier of the sums
-// 2.6), and in whole lines: eight rows' 128 bytes a load; 64 bytes of 16 rows, whose lines the non-temporal policy drops between
-// their halves, take 4.3 us a tile instead of 2.0 (2.31 ms).  Then the units: 33 lines from the L2 per tree and 64 rows, 64 bytes a
+// 2.6), and in whole lines: eight rows' 128 bytes a load; with 64 bytes of 16 rows, whose lines the non-temporal policy drops between
+// their halves, 2.31 ms (a tile on an otherwise idle chip 4.3 us instead of 2.0, with all CUs at it 5.4 instead of 4.7).  Then the units: 33 lines from the L2 per tree and 64 rows, 64 bytes a
 // clock; 24 lanes have a path beyond the top, and what a step reads of a line is often gone before the next.  Gathered into whole
 // waves through LDS the lanes ask for as many lines, in a longer chain: 1.36 ms of units instead of 0.9.  Without X it would take
 // 1.83 ms, without units 1.23, without either 0.89 (LDS 62 % busy).  All the tops of four pairs of trees before their units, so that

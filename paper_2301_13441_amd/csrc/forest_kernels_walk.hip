@@ -28,7 +28,7 @@
 // Bound: at depth 8 the LDS (90 % busy, vector ALU 79 %), at depth 6 the vector ALU (93 to 98 %) with the LDS (82 to 86 %)
 // behind it.  Per (64 rows, tree of depth D): 3 + 2 (D - 2) LDS reads of 2 clocks each, more at levels 6 and 7 whose 64 and 128 nodes share the
 // 32 banks (4 and 6 clocks).  500 trees of depth 8, 28 features, 1M rows: 2.70 -> 0.60 ms against every node tested
-// (forest_kernels_rank.hip); 1000 of depth 6, 50 features: 1.57 -> 0.74 ms.  Leaf values held as float64, which saves
+// (forest_kernels_rank.hip); 1000 of depth 6, 50 features: 1.57 -> 0.71 ms.  Leaf values held as float64, which saves
 // their conversion and a shift: 633 and 802 us against 629 and 788.
 #include <hip/hip_runtime.h>
 

@@ -407,9 +407,10 @@ inline bool leaves_by_fours(const DevModel &m, int groups, int64_t n_rows)
 }
 
 // Whether a launch may end in smaller workgroups.  Not leaf ids by fours, whose few trees are walked in less time than a
-// workgroup takes to begin and end.  Where a CU holds one workgroup of the deep kernel, the form with both sizes walks 1.3 %
-// slower (4M rows of 128 x depth 12, 256 features, 122 rounds of the CUs: 2811 / 2853 us whole / smaller at the end; 20 rounds
-// 491 / 490, 5 140 / 135, one 47.0 / 39.7).
+// workgroup takes to begin and end.  Where a CU holds one workgroup of the deep kernel (leaf ids, several columns, wider leaves; what does
+// not go tile after tile), the form with both sizes walks up to 1.3 % slower, which long launches do not win back: whole / smaller at the
+// end, us, 224 features, leaf ids of 300 trees of depth 9 in 1.2 rounds of the CUs 80.9 / 74.8, 10.2 484 / 481, 19.1 870 / 871, 30.2 1332 / 1344;
+// of 128 trees of depth 12 21.1 rounds 560 / 557, 40.1 1026 / 1034; three columns of 300 trees 1.2 58.9 / 52.4, 21.1 629 / 623, 50.1 1435 / 1432.
 constexpr int64_t TAIL_MAX_ROUNDS = 20;
 
 inline bool ends_in_smaller(const DevModel &m, int kernel, int groups, int64_t n_rows, bool sums)
