@@ -432,7 +432,13 @@ inline bool ends_in_smaller(const DevModel &m, int kernel, int groups, int64_t n
 // per 64 rows = 1, 97 to 192 features, in 2.0 to 2.4 rounds / 3.0 to 3.4 / 4.1 to 4.3 / 5.1 to 5.5 / 6.0: 300 trees of depth 9 1.09 / 1.05 / 1.03 /
 // 1.01 / 1.01, 1000 of them 1.08 / 1.05 / 1.04 / 1.03 / 1.02, 300 of depth 12 1.04 / 1.01 / 1.00 / 0.99 / 0.98, 128 of depth 9 1.02 / 0.98 / 0.95 / 0.93 /
 // 0.92, 20 of them 1.04 / 0.98 / 0.95 / 0.91 / 0.89; rounds and a half or more 0.85 to 0.95; 7.0 rounds of 1000 trees 1.00.
+//
+// Waves with one tree each or none have no second tree whose top would fill the first one's waits, and the two workgroups of 64 rows have twice as
+// many of them on a CU; only many tiles pay for that.  Tile after tile, of a workgroup per 64 rows = 1, 100 / 130 / 160 / 192 features: 8 trees of depth
+// 13, 99,000 rows 1.16 / 1.25 / 1.16 / 1.18, 300,000 1.06 / 1.13 / 1.06 / 1.07, 1M 1.00 / 1.06 / 0.98 / 0.97; 16 of them 1.11 / 1.21 / 1.14 / 1.16, 0.99 / 1.04 /
+// 0.93 / 0.96, 0.91 / 0.95 / 0.80 / 0.80; 24 of them 1.03 / 1.10 / 1.02 / 1.03, 0.93 / 0.99 / 0.91 / 0.91; 200 features, 8 trees 1.00, 0.93, 0.90.
 constexpr int DEEP_TILE_GROUPS = 2;
+constexpr int SINGLE_TREES_MIN_ROUNDS = 16;
 constexpr int REST_MAX_ROUNDS = 7, REST_MAX_ROUNDS_FEW_TREES = 3, REST_FEW_TREES = 200;
 
 inline bool takes_tiles(const DevModel &m, int64_t n_rows, int n_splits, bool sums)
@@ -440,6 +446,7 @@ inline bool takes_tiles(const DevModel &m, int64_t n_rows, int n_splits, bool su
     if (!sums || n_splits > 1 || m.leaf_width > 2 || (m.leaf_width == 1 && m.n_outputs > 1)) return false;
     if (n_rows < 2 * CUS * PLAN_ROWS * DEEP_TILE_GROUPS) return false;
     const int64_t tiles = (n_rows + PLAN_ROWS * DEEP_TILE_GROUPS - 1) / (PLAN_ROWS * DEEP_TILE_GROUPS), rest = tiles % CUS;
+    if (m.n_trees <= DEEP_WAVES && deep_shares_cu(m, 1, true) && tiles < SINGLE_TREES_MIN_ROUNDS * CUS) return false;
     if (rest > 0 && rest <= CUS / 2 && deep_shares_cu(m, 1, true) && tiles / CUS < (m.n_trees < REST_FEW_TREES ? REST_MAX_ROUNDS_FEW_TREES : REST_MAX_ROUNDS)) return false;
     return !deep_shares_cu(m, DEEP_TILE_GROUPS, true) && deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, DEEP_TILE_GROUPS, true) <= CU_LDS_BYTES;
 }

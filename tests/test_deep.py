@@ -144,6 +144,16 @@ def test_rounds_and_few_tiles_more_are_left_to_smaller_workgroups(features):
                 assert want or s["rows_per_workgroup"] == 64
 
 
+@pytest.mark.parametrize("features,trees", [(97, 1), (97, 16), (192, 16), (192, 17), (193, 16)])
+def test_waves_with_one_tree_go_tile_after_tile_only_over_many(features, trees):
+    """Where two smaller workgroups, with twice as many such waves, share a CU."""
+    from paper_2301_13441_amd import binding
+    f = _forest(1, trees, 9, features, stop=0.2 if trees > 1 else 0.0)
+    for tiles, many in ((3 * 256, False), (16 * 256 - 1, False), (16 * 256, True)):
+        s = binding.forest_packed_launch(f, 128 * tiles, form="walk")
+        assert s["kernel"] == "deep" and s["tile_after_tile"] == (many or trees > 16 or features > 192), (tiles, s)
+
+
 @pytest.mark.parametrize("features,waves", [(97, 8), (128, 8), (129, 10), (160, 10), (161, 12), (200, 14), (225, 16), (256, 16)])
 def test_tiles_ahead_are_loaded_once(features, waves):
     """A wave per piece of 64 rows x 32 features; no wave asks for another's again."""
@@ -158,11 +168,12 @@ def test_tiles_ahead_are_loaded_once(features, waves):
 @pytest.mark.parametrize("trees,rows", [(1, 65536), (17, 3 * 32768 + 1), (33, 3 * 32768 + 128 + 65), (48, 3 * 32768 - 3)])
 def test_deep_kernels_tile_after_tile(features, depth, outputs, width, trees, rows):
     """Whole and ragged pieces of 32 features, a last tile of one row and of two row groups, CUs with two, three and four tiles; waves
-    without trees, with one and with three."""
+    without trees, with one and with three.  A tree alone takes smaller workgroups up to 192 features."""
     rng = np.random.default_rng(100 * depth + features + trees)
     f = _forest(9 * depth + features, trees, depth, features, outputs, width, stop=0.3 if trees > 1 else 0.0)
     assert len(f.feature) > 200  # a tree alone reads features too
-    _tiles(f, rows)
+    if trees > 1 or features > 192:
+        _tiles(f, rows)
     X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
     _check(f, X, leaves=False)
 

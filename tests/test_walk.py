@@ -314,8 +314,8 @@ def test_lines_of_x_stay_in_the_l2_where_rows_share_them_and_the_trees_keep_thei
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind,trees,depth,features,rows,shift,keep", [
     ("walk", 500, 8, 201, 33_333, 0, 0), ("walk", 500, 8, 301, 33_333, 0, 0), ("walk", 40, 6, 64, 70_003, 1, 1), ("walk", 40, 6, 128, 33_333, 16, 1),
-    ("walk", 500, 8, 256, 33_333, 3, 0), ("deep", 200, 12, 131, 65_536 + 77, 0, 0), ("deep", 200, 12, 225, 65_536 + 1, 0, 0),
-    ("deep", 20, 9, 160, 65_536 + 1, 1, 1), ("deep", 200, 12, 95, 40_009, 0, 0)])
+    ("walk", 500, 8, 256, 33_333, 3, 0), ("deep", 200, 12, 131, 3 * 32_768, 0, 0), ("deep", 200, 12, 225, 65_536 + 1, 0, 0),
+    ("deep", 20, 9, 160, 3 * 32_768 - 3, 1, 1), ("deep", 200, 12, 95, 40_009, 0, 0)])
 def test_tiles_by_how_x_is_loaded(kind, trees, depth, features, rows, shift, keep):
     """Rows that share lines, by their width or by X's address, loaded either way; tile after tile too."""
     import torch
@@ -327,7 +327,8 @@ def test_tiles_by_how_x_is_loaded(kind, trees, depth, features, rows, shift, kee
     xd = flat[shift:shift + X.size].view(rows, features)
     xd.copy_(torch.from_numpy(X))
     assert xd.data_ptr() % 128 == 4 * shift
-    assert binding.forest_packed_launch(f, rows)["kernel"] == kind and binding.forest_keeps_lines(f, rows, x=xd.data_ptr()) == keep
+    s = binding.forest_packed_launch(f, rows)
+    assert s["kernel"] == kind and s["tile_after_tile"] == (kind == "deep" and features > 96) and binding.forest_keeps_lines(f, rows, x=xd.data_ptr()) == keep
     model = binding.forest_load(f)
     try:
         scores, _ = model.predict(xd)
