@@ -606,17 +606,18 @@ inline LaunchPlan plan_launch(const DevModel &m, const Workspace *ws, int64_t n_
 // Whether a tile of X is read with loads that leave its lines in the L2, or non-temporally: X is read once and should not push
 // the trees out.  Where rows are no whole lines a line lies in two blocks of 32 features or two rows and is asked for again, and a
 // second fetch holds up what waits behind it; but the lines that stay cost the trees their place.  So they stay where both about fit an
-// XCD's L2 (the trees counted for more where a workgroup reads them for one row group), or where several shares of the trees read the
-// tile.  Over 1,872 calls of 12 models with 30 KB to 4 MB of tables, 17 to 500 features and 5,000 to 1M rows, fresh X and X that the
-// memory-side cache holds, the lines kept always take 0.7 % more than the better of both and 12 % at worst, never 2.1 and 21, by this rule
+// XCD's L2 (the trees three times where a CU walks them for one row group at a time), where the trees are few whatever X does to them
+// (33 x depth 7, 285 features 184 / 216 us, 480,000 rows), or where several shares of the trees read the tile.  Over 3,012 calls of 29 models with 30 KB to 4 MB of tables, 17 to 530 features and 5,000 to 1M rows, fresh X and X that the
+// memory-side cache holds, the lines kept always take 1.7 % more than the better of both and 17 % at worst, never 1.6 and 22, by this rule
 // 0.3.  Kept / non-temporal, 1M rows: 128 trees of depth 12, 3-wide leaves (4.2 MB), 200 features 1224 / 1095 us; 600 irregular
-// trees of depth 10 (4.1 MB), 90 features 1319 / 1268; 500 x depth 8 (1.5 MB), 300 features 1877 / 1722, 127 features 0.98; 300
+// trees of depth 10 (4.1 MB), 90 features 1319 / 1268; 500 x depth 8 (1.5 MB), 300 features 1877 / 1722, 127 features 0.98; 500 x
+// depth 7 (0.8 MB), 260 features 1.05, 400 features 1.14; 200 x depth 6 (150 KB), 400 features 0.99; 300
 // irregular trees of depth 9 (1.4 MB), three columns, 200 features 1.06; the same, one column, 90 features, 103,069 rows 0.99, X
 // in the memory-side cache 67.5 / 70.6; 40 x depth 6, 100 features 0.91; in two shares and more 300 x depth 6, five columns, 200
 // features, 10,007 rows 0.93.  Where it errs: 500 features, 1000 x depth 3 1.05; leaf ids of more trees than features, 300,000 rows of
 // 200 x depth 6 over 127 features 1.09, 100,003 rows 1.00, 0.93 where X is in the cache.
-constexpr int64_t KEEP_L2_BYTES = 4608 << 10;
-constexpr int KEEP_MIN_FEATURES = 17, XCD_CUS = 32;  // rows of at most 16 features go by 64 bytes of 16 rows
+constexpr int64_t KEEP_L2_BYTES = 4608 << 10, KEEP_FEW_TREES_BYTES = 128 << 10;
+constexpr int KEEP_MIN_FEATURES = 17, XCD_CUS = 32;
 
 inline bool keeps_lines(const DevModel &m, const LaunchPlan &p, bool sums, uintptr_t X)
 {
@@ -627,10 +628,11 @@ inline bool keeps_lines(const DevModel &m, const LaunchPlan &p, bool sums, uintp
     const int64_t T = m.n_trees, node = sizeof(WalkNode), id = sizeof(int32_t), value = sizeof(float);
     const int64_t tables = walk ? (T * (node + value)) << m.walk.depth
                                 : T * static_cast<int64_t>(DEEP_STAGE_BYTES) + m.deep.units * (node + (sums ? 0 : id)) + (sums ? m.deep.values * value : 0);
+    if (tables <= KEEP_FEW_TREES_BYTES) return true;
     const size_t lds = walk ? walk_lds_bytes(m.walk.depth, m.n_features, m.n_outputs, m.walk.groups)
                             : deep_lds_bytes(m.n_features, m.n_outputs, m.leaf_width, p.groups, sums);
     const int64_t rows = static_cast<int64_t>(XCD_CUS) * (2 * lds <= CU_LDS_BYTES ? 2 : 1) * PLAN_ROWS * p.groups;  // of an XCD's workgroups
-    return tables + (p.groups == 1 ? tables / 2 : 0) + rows * m.n_features * value <= KEEP_L2_BYTES;
+    return tables * (rows == XCD_CUS * PLAN_ROWS ? 3 : 1) + rows * m.n_features * value <= KEEP_L2_BYTES;
 }
 
 // The workgroups of one range of rows, walk kernels; of those that take tile after tile, the tiles.

@@ -306,6 +306,9 @@ def test_lines_of_x_stay_in_the_l2_where_rows_share_them_and_the_trees_keep_thei
         assert binding.forest_keeps_lines(at(few, features), rows) == keep_few, (features, rows)
         assert binding.forest_keeps_lines(at(many, features), rows) == keep_many, (features, rows)
     assert not binding.forest_keeps_lines(few, 1, x=4)  # a lane per (row, tree)
+    some = _forest(3, 500, 7, 16)  # 0.8 MB: too many where a CU has one row group
+    assert [binding.forest_keeps_lines(at(some, features), 10**6) for features in (100, 129, 200, 300)] == [1, 1, 1, 0]
+    assert binding.forest_keeps_lines(_forest(4, 33, 7, 285), 10**6)  # few trees beside 4.5 MB of X
     for bad in (0, 1 << 62):
         with pytest.raises(binding.ForestError):
             binding.forest_keeps_lines(few, bad)
@@ -313,7 +316,7 @@ def test_lines_of_x_stay_in_the_l2_where_rows_share_them_and_the_trees_keep_thei
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("kind,trees,depth,features,rows,shift,keep", [
-    ("walk", 500, 8, 201, 33_333, 0, 0), ("walk", 500, 8, 301, 33_333, 0, 0), ("walk", 40, 6, 64, 70_003, 1, 1), ("walk", 40, 6, 128, 33_333, 16, 1),
+    ("walk", 500, 8, 201, 33_333, 0, 0), ("walk", 1600, 8, 31, 33_333, 0, 0), ("walk", 1600, 8, 31, 9_001, 0, 1), ("walk", 500, 8, 301, 33_333, 0, 0), ("walk", 40, 6, 64, 70_003, 1, 1), ("walk", 40, 6, 128, 33_333, 16, 1),
     ("walk", 500, 8, 256, 33_333, 3, 0), ("deep", 200, 12, 131, 3 * 32_768, 0, 0), ("deep", 200, 12, 225, 65_536 + 1, 0, 0),
     ("deep", 20, 9, 160, 3 * 32_768 - 3, 1, 1), ("deep", 200, 12, 95, 40_009, 0, 0)])
 def test_tiles_by_how_x_is_loaded(kind, trees, depth, features, rows, shift, keep):
@@ -335,6 +338,27 @@ def test_tiles_by_how_x_is_loaded(kind, trees, depth, features, rows, shift, kee
         np.testing.assert_allclose(scores.cpu().numpy(), oracle.predict(f, X, n_threads=8).scores, rtol=1e-5, atol=1e-6)
     finally:
         model.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("features", [16, 17, 31, 32, 33])
+@pytest.mark.parametrize("outputs", [1, 2])
+def test_narrow_tiles_of_few_trees(features, outputs):
+    """Leaf ids by fours, whose narrow rows are loaded another way than those of more trees; four row groups and two."""
+    import torch
+    from paper_2301_13441_amd import binding
+    rows = 70_003
+    rng = np.random.default_rng(features)
+    f = _forest(features, 7, 6, features, outputs)
+    s = binding.forest_packed_launch(f, rows, True, form="walk")
+    assert s["kernel"] == "walk" and s["leaves_by_fours"] == 1 and s["rows_per_workgroup"] == (256 if outputs == 1 else 128), s
+    X = _special_rows(rng.standard_normal((rows, features)).astype(np.float32), f, rng)
+    model = binding.forest_load_form(f, "walk")
+    try:
+        got = model.predict_leaves(torch.from_numpy(X).cuda()).cpu().numpy()
+    finally:
+        model.close()
+    np.testing.assert_array_equal(got, oracle.predict(f, X, want_leaves=True, n_threads=8).leaf_node_id)
 
 
 @pytest.mark.gpu
