@@ -140,7 +140,7 @@ __device__ __forceinline__ void deep_rows(const DevModel m, const float *__restr
         fetch(place(t_begin));
         head = deep_head(tops, place(t_begin));
     }
-    tile_fill<NR, NR == 2 ? 8 : 4, false>(X, row0, n_rows, m.x_tile, XBASE, group_stride, 256, wave, lane);
+    tile_fill<NR, NR == 2 ? 8 : 4, false>(X, row0, n_rows, m.x_tile, 17, XBASE, group_stride, 256, wave, lane);
     __syncthreads();
 
     uint32_t xa[NR];

@@ -135,7 +135,7 @@ __device__ __forceinline__ void walk_rows(const DevModel m, const float *__restr
         for (int i = 0; i < PIECES; ++i) ahead[i] = *reinterpret_cast<const Vec4 *>(image + at + i * 1024);
     };
     if (s_begin < s_end) fetch(s_begin);
-    tile_fill<NR, NR == 4 ? 8 : 4, true>(X, row0, n_rows, m.x_tile, xbase, 256, stride, wave, lane);
+    tile_fill<NR, NR == 4 ? 8 : 4, true>(X, row0, n_rows, m.x_tile, 17, xbase, 256, stride, wave, lane);
     __syncthreads();
 
     const uint32_t xa = xbase + lane * 4;
@@ -242,7 +242,7 @@ __device__ __forceinline__ void walk_leaves(const DevModel m, const float *__res
     };
     int k = FEW ? 0 : static_cast<int>(blockIdx.y);
     if (k < rounds && (!FEW || first_tree(k) < T)) fetch(first_tree(k));
-    tile_fill<NR, NR == 4 ? 8 : 4, true>(X, row0, n_rows, m.x_tile, xbase, 256, stride, wave, lane);
+    tile_fill<NR, NR == 4 ? 8 : 4, true>(X, row0, n_rows, m.x_tile, FEW && NR <= 2 ? 33 : 17, xbase, 256, stride, wave, lane);
     __syncthreads();
 
     const uint32_t xa = xbase + lane * 4;

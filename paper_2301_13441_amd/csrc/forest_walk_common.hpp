@@ -77,20 +77,22 @@ __device__ __forceinline__ int line_four(int lane) { return (lane & 1) | (lane >
 // eight rows' 128 bytes, non-temporally (ONCE) or not (keeps_lines, forest_plan.hpp).  A line that is asked for in
 // two halves is read twice so, and what waits for it holds up the other loads of the CU, which return in order (16 rows' 64
 // bytes a load and no exchange: 103,069 rows of 300 deep trees, 90 features 72.2 us, so 69.5; 100 trees of depth 6, 64 features,
-// 300,000 rows 44.9 / 41.2, 300 features, 100,000 rows 61.7 / 55.6; but 8 features, 1M rows 93.8 / 98.0, so rows of at most 16
-// features go that way).  The lanes exchange what they loaded until 16 rows are written at a time, for 16 of 32 LDS banks.
+// 300,000 rows 44.9 / 41.2, 300 features, 100,000 rows 61.7 / 55.6).  But of narrow rows lines make few pieces, which
+// few waves load and exchange while the others wait: 8 features, 1M rows 93.8 / 98.0.  So rows of fewer than lines_from features go by 64
+// bytes of 16 rows: of 17, and of 33 for leaf ids of few trees, which are little but the fill, in workgroups of one and two row groups (2 trees of
+// depth 8, two columns, 25 features, 800,000 rows 29.8 / 42.0 us; 12 of depth 5, 32 features, 300,000 rows 17.3 / 20.7).  The lanes exchange what they loaded until 16 rows are written at a time, for 16 of 32 LDS banks.
 // The four features of a lane that would reach beyond the row are the row's last four (written twice, with the same values), and
 // the rows beyond the batch are its last row, so that every load is whole and none waits for another: a lane's features
 // one by one under a mask of their own cost a second round trip to memory, and the addresses as 64-bit products more
 // instructions than the loads (256 features, 4M rows of 128 deep trees: 2.89 -> 2.80 ms a call).  NAN_IS_INF: a NaN is stored as +Inf.
-template <int NR, int P, bool NAN_IS_INF, bool LINES, bool ONCE>
+template <int NR, int P, bool NAN_IS_INF, bool LINES, bool ONCE, bool ONE_BLOCK = false>
 __device__ __forceinline__ void fill_pieces(const float *X, int64_t row0, int64_t n_rows, int F, uint32_t xbase, uint32_t group_stride,
                                             uint32_t stride, int wave, int lane)
 {
     constexpr int L = !LINES ? 1 : NR == 1 ? 2 : 4, LOAD_ROWS = LINES ? 8 : 16, ROWS = LOAD_ROWS * L, FEATURES = LINES ? 32 : 16, G = P / L;  // G pieces on their way at a time
     const char *tile = reinterpret_cast<const char *>(X + row0 * F);
     const int rows = n_rows - row0 < NR * TILE ? static_cast<int>(n_rows - row0) : NR * TILE;
-    const int blocks = LINES ? (F + FEATURES - 1) / FEATURES : 1, pieces = blocks * (NR * TILE / ROWS);
+    const int blocks = ONE_BLOCK ? 1 : (F + FEATURES - 1) / FEATURES, pieces = blocks * (NR * TILE / ROWS);
     const int begin = pieces * wave / WALK_WAVES, end = pieces * (wave + 1) / WALK_WAVES;
     const uint32_t pitch = static_cast<uint32_t>(F) * 4;
     // a lane's row and four of features as loaded, and, of register 0, after the exchange
@@ -144,16 +146,17 @@ __device__ __forceinline__ void fill_pieces(const float *X, int64_t row0, int64_
 }
 
 template <int NR, int P, bool NAN_IS_INF>
-__device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t n_rows, int x_tile, uint32_t xbase, uint32_t group_stride,
+__device__ __forceinline__ void tile_fill(const float *X, int64_t row0, int64_t n_rows, int x_tile, int lines_from, uint32_t xbase, uint32_t group_stride,
                                           uint32_t stride, int wave, int lane)
 {
     const int F = x_tile & (KEEP_X - 1);
-    if (x_tile & KEEP_X) {  // more than 16 features
-        fill_pieces<NR, P, NAN_IS_INF, true, false>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
+    if (F >= lines_from) {
+        if (x_tile & KEEP_X) fill_pieces<NR, P, NAN_IS_INF, true, false>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
+        else fill_pieces<NR, P, NAN_IS_INF, true, true>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
     } else if (F > 16) {
-        fill_pieces<NR, P, NAN_IS_INF, true, true>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
-    } else if (F >= 4) {
         fill_pieces<NR, P, NAN_IS_INF, false, true>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
+    } else if (F >= 4) {
+        fill_pieces<NR, P, NAN_IS_INF, false, true, true>(X, row0, n_rows, F, xbase, group_stride, stride, wave, lane);
     } else {  // a lane per row
         const float *tile = X + row0 * F;
         const int rows = n_rows - row0 < NR * TILE ? static_cast<int>(n_rows - row0) : NR * TILE;
